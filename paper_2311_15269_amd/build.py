@@ -10,8 +10,8 @@ import tempfile
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libtessel_hip.so")
-SOURCES = ["tessel_kernels.hip", "tessel_wide.hip", "tessel_api.cpp"]
-HEADERS = ["tessel_device.h", os.path.join("..", "..", "include", "tessel.h")]
+SOURCES = ["tessel_kernels.hip", "tessel_wide.hip", "tessel_graph.hip", "tessel_api.cpp"]
+HEADERS = ["tessel_device.h", "tessel_common.h", os.path.join("..", "..", "include", "tessel.h")]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
@@ -78,9 +78,9 @@ def _word_aligned(reg, block, upto, depth=0, unknown=True):
 
 
 def misaligned_scalar_loads(asm):
-    """Scalar loads of the device code whose address is not visibly a multiple of four: a register offset, or a base
-    computed in its basic block from anything but indices shifted left by two or more or multiplied by a multiple of
-    four.  The scalar memory path drops the low two bits of the base, so `base + i` with a byte index i, to which the
+    """Scalar loads of the device code whose address is not visibly a multiple of four: a register offset that its basic
+    block does not show to be one (an index shifted left by two or more), or a base computed in its basic block from
+    anything but indices shifted left by two or more or multiplied by a multiple of four.  The scalar memory path drops the low two bits of the base, so `base + i` with a byte index i, to which the
     compiler once added `3 i` as the offset of a load of word i, reads the wrong word.  (Seen in a variant of the
     completion kernel that read its per-type tables from global memory; the kernels keep such tables in LDS.)
     Returns the offending lines."""
@@ -94,7 +94,8 @@ def misaligned_scalar_loads(asm):
         m = re.search(r"\bs_(?:buffer_)?load_\w+\s+\S+,\s+s\[(\d+):\d+\],\s*(\S+)", line)
         if not m:
             continue
-        if re.match(r"s\d+", m.group(2)):                       # register offset
+        off = re.match(r"s(\d+)", m.group(2))
+        if off and not _word_aligned(int(off.group(1)), lines[start:n], n - start, unknown=False):    # register offset
             bad.append("%d: %s" % (n + 1, line.strip()))
             continue
         if not _word_aligned(int(m.group(1)), lines[start:n], n - start):

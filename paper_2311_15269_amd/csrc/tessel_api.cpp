@@ -25,6 +25,7 @@ namespace tessel { size_t block_rec_bytes(int blocks); }
 struct tessel_problem {
     uint64_t id = 0;                    // never reused: names the handle as the owner of a workspace
     KParams kp;
+    GraphTab graph;                     // tables of the graph kernel (graph.ok)
     std::vector<int32_t> t, m;
     std::vector<uint32_t> mask;
     std::vector<int32_t> dep_src, dep_dst;
@@ -147,6 +148,152 @@ static bool gen_leads(const tessel_problem &p, int K, int NR, std::vector<int8_t
         }
     }
     return true;
+}
+
+// Tables of the graph kernel (GraphTab).  Leaves ok = 0 where the problem is outside what they hold: more than kGraphOut
+// consumers or the fields of a type's word producers of one type, a type without any dependency, more than kGraphTp types
+// on several devices, memory prefixes beyond 16 bits, an LDS need beyond 64 KB.
+static void graph_tables(const tessel_problem &p, GraphTab &gt)
+{
+    memset(&gt, 0, sizeof gt);
+    const KParams &kp = p.kp;
+    const int D = kp.D, K = kp.K, NR = kp.NR;
+    if (!kp.dag) return;
+    int most = 0;
+    for (int d = 0; d < D; d++) most = std::max(most, kp.ntd[d]);
+    gt.np = most <= 2 ? 1 : most <= 4 ? 2 : 3;
+    // distinct dependencies, by consumer and by producer
+    std::vector<std::vector<int>> in(K), outs(K);
+    for (size_t e = 0; e < p.dep_src.size(); e++) {
+        const int a = p.dep_src[e], b = p.dep_dst[e];
+        if (std::find(in[b].begin(), in[b].end(), a) == in[b].end()) { in[b].push_back(a); outs[a].push_back(b); }
+    }
+    for (int i = 0; i < K; i++) {
+        if (in[i].empty() && outs[i].empty()) return;
+        gt.maxout = std::max(gt.maxout, (int)outs[i].size());
+        gt.maxin = std::max(gt.maxin, (int)in[i].size());
+    }
+    if (gt.maxout > kGraphOut || gt.maxin > kGraphIn) return;
+    gt.chain = gt.maxout <= 1 && gt.maxin <= 1;
+    // the word of a type: next micro-batch (up to 2 N_R - 1) on top, fields with a guard bit below
+    int bits = 1;
+    while ((1 << bits) <= 2 * NR - 1) bits++;
+    const int f = bits + 1, fields = (32 - bits) / f;
+    if (1 + gt.maxin > fields) return;
+    gt.mushift = 32 - bits;
+    for (int s = 0; s < fields; s++) { gt.add |= ((1u << bits) - 1u) << (f * s); gt.guard |= 1u << (f * s + bits); }
+    long span_max = 0;
+    for (int d = 0; d < D; d++) {
+        long span = 0;
+        for (int i = 0; i < K; i++) if (p.mask[i] >> d & 1u) span += std::labs((long)p.m[i]) * (2 * NR - 1);
+        span_max = std::max(span_max, span);
+    }
+    if (span_max > 30000 || (int64_t)kp.UB * 64 >= (int64_t)1 << 31) return;
+    // the dependencies for the sampled leads, consumers before producers
+    for (int k = 0; k < K; k++) {
+        const int i = kp.rtopo[k], from = gt.nlead;
+        for (int e = 0; e < kp.ndeps; e++)
+            if (kp.dsrc[e] == i)
+                gt.lead_edge[gt.nlead++] = (uint32_t)i | (uint32_t)kp.ddst[e] << 8 | (uint32_t)e << 16 | (uint32_t)(kp.dcross[e] != 0) << 24;
+        if (gt.nlead > from) { gt.lead_edge[from] |= 1u << 25; gt.lead_edge[gt.nlead - 1] |= 1u << 26; }
+    }
+    for (int b = 0; b < K; b++)
+        for (size_t s = 0; s < in[b].size(); s++)
+            gt.edge[gt.nedge++] = (uint32_t)in[b][s] | (uint32_t)b << 8 | (uint32_t)(f * (1 + (int)s)) << 16;
+    // LDS: code tables, sweep tables, tables of types on several devices, slot rows, then build and sweep state in one place
+    const int code_row = 32 << gt.np, ncode = (2 + 2 * gt.maxout) * code_row;
+    const uint32_t row = kWave * 4;
+    uint32_t at = (uint32_t)ncode * 4;
+    const int pairs = gt.chain && !kp.tp ? 0 : (gt.maxin + 1) / 2;
+    gt.sw = at; at += (uint32_t)(2 + pairs) * kMaxKW * 4;
+    gt.init = at; at += kMaxKW * 4;
+    for (int i = 0; i < K; i++) {
+        uint32_t w = (uint32_t)NR;
+        for (int s = (int)in[i].size(); s < fields - 1; s++) w |= 1u << (f * (1 + s));
+        gt.tab[gt.init / 4 + i] = w;
+    }
+    gt.dev = at; at += 32 * 4;
+    for (int d = 0; d < D; d++) gt.tab[gt.dev / 4 + d] = (uint32_t)kp.ntd[d];
+    std::vector<int> tp_no(K, -1);
+    if (kp.tp) {
+        for (int i = 0; i < K; i++) if (p.mask[i] & (p.mask[i] - 1)) tp_no[i] = gt.ntp++;
+        if (gt.ntp > kGraphTp) return;
+        gt.tpm = at; at += kMaxKW * 4;
+        gt.tpi = at; at += (kMaxKW + kGraphTp) * 4;
+        gt.tps = at; at += (uint32_t)gt.ntp * 32 * 4;
+        gt.smask = at; at += 32 * 4;
+    }
+    gt.ntab = (int)(at / 4);
+    at = (at + row - 1) / row * row;
+    gt.slot_rows = at; at += 4 * row;
+    const uint32_t base = at;
+    gt.rec = at; at += (uint32_t)D * (gt.np + 2) * row;
+    gt.wrow = at; at += (uint32_t)K * row;
+    gt.trash = at; at += row;
+    const uint32_t build_end = at;
+    at = base;
+    gt.state = at; at += (uint32_t)kp.nslots * row;
+    gt.prev = at; at += (uint32_t)D * row;
+    gt.strash = at; at += row;
+    gt.leads = at; at += (uint32_t)((kp.ntok + 3) / 4) * row;
+    gt.lds_bytes = std::max(build_end, at);
+    if (gt.lds_bytes > 64 * 1024 - row) return;             // (16-bit LDS addresses, eight-bit row numbers)
+    gt.meta = 3 + (kp.ntok + 3) / 4;
+    gt.nwords = ((kp.total + 1) / 2 + 3) / 4 * 4;
+    auto type_at = [&](int d, int y) -> int { return (int)((y < 4 ? kp.type_of[d] >> (8 * y) : kp.type_of_hi[d] >> (8 * (y - 4))) & 0xFFu); };
+    auto symbol_on = [&](int g, int d) -> int { for (int y = 0; y < kp.ntd[d]; y++) if (type_at(d, y) == g) return y; return 0; };
+    auto lowest = [&](int g) -> int { return __builtin_ctz(p.mask[g]); };
+    for (int d = 0; d < D; d++)
+        for (int y = 0; y < kp.ntd[d]; y++) {
+            const int g = type_at(d, y), c = (d << gt.np) + y;
+            gt.tab[c] = ((uint32_t)p.m[g] << 16) | (((gt.wrow + (uint32_t)g * row) / row) << 8) | (tp_no[g] >= 0 ? 64u : 0u) | (uint32_t)g;
+            uint32_t dec = (1u << gt.mushift) - 1u;
+            for (size_t s = 0; s < in[g].size(); s++) dec -= 1u << (f * (1 + (int)s));
+            gt.tab[code_row + c] = dec;
+            for (int k = 0; k < gt.maxout; k++) {
+                uint32_t c0, c1 = 0;
+                if (k < (int)outs[g].size()) {
+                    const int h = outs[g][k], dh = lowest(h);
+                    const int slot = (int)(std::find(in[h].begin(), in[h].end(), g) - in[h].begin());
+                    c0 = (gt.rec + (uint32_t)(dh * (gt.np + 2) + gt.np + 1) * row) << 16 | ((gt.wrow + (uint32_t)h * row) / row) << 8 |
+                         (uint32_t)dh << 3 | (uint32_t)symbol_on(h, dh);
+                    c1 = 1u << (f * (1 + slot));
+                } else
+                    c0 = (gt.rec + (uint32_t)(d * (gt.np + 2) + gt.np + 1) * row) << 16 | (gt.trash / row) << 8 | (uint32_t)d << 3;
+                gt.tab[(2 + 2 * k) * code_row + c] = c0;
+                gt.tab[(3 + 2 * k) * code_row + c] = c1;
+            }
+        }
+    // rings: a type of a shared stretch reads and writes the stretch's; a type with no producer reads its own, where its
+    // micro-batch has not been written; a type nobody consumes writes nothing (chains: the stretch's ring, read by nobody then)
+    std::vector<uint32_t> ring(K, 0);
+    auto ring_address = [&](int g) -> uint32_t { return gt.state + (uint32_t)kp.tokbase[g] * row; };
+    for (int g = 0; g < K; g++) {
+        const bool own = kp.tokbase[g] != kNoRing;
+        uint32_t to = own ? ring_address(g) : gt.strash;
+        if (gt.chain && !own) to = ring_address(in[g][0]);
+        gt.tab[gt.sw / 4 + g] = (uint32_t)p.t[g] | (own ? 1u << 31 : 0u);
+        gt.tab[gt.sw / 4 + kMaxKW + g] = (gt.state + (uint32_t)lowest(g) * row) | to << 16;
+        for (int k = 0; k < pairs; k++) {
+            auto from = [&](int s) -> uint32_t { return in[g].empty() ? to : ring_address(s < (int)in[g].size() ? in[g][s] : in[g][0]); };
+            gt.tab[gt.sw / 4 + (2 + k) * kMaxKW + g] = from(2 * k) | from(2 * k + 1) << 16;
+        }
+    }
+    if (kp.tp)
+        for (int g = 0; g < K; g++) {
+            if (tp_no[g] < 0) {
+                gt.tab[gt.smask / 4 + lowest(g)] |= 1u << symbol_on(g, lowest(g));
+                continue;
+            }
+            const uint32_t info = (uint32_t)(6 * tp_no[g]) | (uint32_t)lowest(g) << 8 | (uint32_t)__builtin_popcount(p.mask[g]) << 16;
+            gt.tab[gt.tpm / 4 + g] = p.mask[g];
+            gt.tab[gt.tpi / 4 + g] = info;
+            gt.tab[gt.tpi / 4 + kMaxKW + tp_no[g]] = info;
+            for (int d = 0; d < D; d++) if (p.mask[g] >> d & 1u) gt.tab[gt.tps / 4 + tp_no[g] * 32 + d] = (uint32_t)symbol_on(g, d);
+        }
+    gt.first_tries = std::min(kGraphTries, kp.dag_tries);
+    gt.retry_tries = 4 * kp.dag_tries;
+    gt.ok = 1;
 }
 
 extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_problem **out)
@@ -488,6 +635,11 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
     p->result.period = INT_MAX;
     { const char *fg = getenv("TESSEL_FORCE_GENERAL"); p->force_general = fg && fg[0] == '1'; }
     if (p->force_general) kp.fast_ok = 0;
+    // (TESSEL_FAR_MODE chooses between placements of the general kernel's state: it takes the problem then)
+    p->graph.ok = 0;
+    if (!p->force_general && !getenv("TESSEL_FAR_MODE")) graph_tables(*p, p->graph);
+    kp.graph_ok = p->graph.ok; kp.graph_np = p->graph.np; kp.graph_lds = p->graph.lds_bytes;
+    kp.graph_slot_words = (uint32_t)(p->graph.meta + p->graph.nwords);
     *out = p;
     return TESSEL_OK;
 }
@@ -570,6 +722,10 @@ static int bind_workspace(tessel_problem *p, void *ws, size_t bytes, hipStream_t
     }
     hipError_t pe = hipMemcpyAsync((char *)ws + kWsParamsOff, &p->kp, sizeof(KParams), hipMemcpyHostToDevice, st);
     if (pe != hipSuccess) return hip_fail(p, (int)pe);
+    if (p->kp.graph_ok) {
+        pe = hipMemcpyAsync((char *)ws + kWsGraphOff, &p->graph, sizeof(GraphTab), hipMemcpyHostToDevice, st);
+        if (pe != hipSuccess) return hip_fail(p, (int)pe);
+    }
     int e = launch_reset(ws, st);
     if (e) return hip_fail(p, e);
     p->ws = ws; p->ws_ready = true; p->have_detail = false; p->max_blocks = max_blocks;

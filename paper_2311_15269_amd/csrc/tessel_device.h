@@ -140,6 +140,10 @@ struct KParams {
                                  // lower half for a single type (which never writes below its lead)
     uint8_t  dsrc[kMaxDeps], ddst[kMaxDeps], dcross[kMaxDeps];   // the dependencies in the caller's order
     uint64_t predmask_of[kMaxDW][kMaxLTW]; // producers of local symbol y of device d
+    int32_t  graph_ok;           // the graph kernel takes the problem
+    int32_t  graph_np;           // GraphTab::np
+    uint32_t graph_lds;          // GraphTab::lds_bytes
+    uint32_t graph_slot_words;   // words of one candidate's slot: GraphTab::meta + nwords
     int32_t  many;               // some device holds more than kMaxLT block types (3-bit symbols; sampled spaces only)
     const int8_t   *leadtab;     // CANONICAL: [nlead][K] in device memory
     const uint64_t *wtab;        // CANONICAL: arrangements by remaining counts, base NR+1 digits
@@ -220,7 +224,9 @@ constexpr size_t kWsListOff = kWsTablesOff + kWsTablesMax;     // candidates def
 constexpr uint32_t kWsListCap = 1u << 20;
 constexpr size_t kWsCompParamsOff = kWsListOff + (size_t)kWsListCap * 8;   // CompParams
 constexpr size_t kWsCompMatrixOff = kWsCompParamsOff + 1024;              // CompMatrix
-constexpr size_t kWsBlockRecOff = kWsCompMatrixOff + 3072;
+constexpr size_t kWsGraphOff = kWsCompMatrixOff + 3072;                   // GraphTab of the bound problem
+constexpr size_t kWsGraphMax = 24576;
+constexpr size_t kWsBlockRecOff = kWsGraphOff + kWsGraphMax;
 constexpr int kDeferBlocks = 64;                                // grid of the deferred pass
 constexpr int kFirstPassTries = 2;                              // sweeps before a candidate queues for the longer search
 constexpr uint64_t kMaxPerLaunch = 1ull << 26;                  // candidates per pass of the kernels
@@ -239,8 +245,57 @@ static_assert(sizeof(CompParams) <= 1024 && sizeof(CompMatrix) <= 3072, "complet
 static_assert(sizeof(KParams) <= kWsTablesOff - kWsParamsOff, "parameter block must fit its workspace slot");
 static_assert(sizeof(DevDetail) <= kWsParamsOff - kWsDetailOff, "detail record must fit its workspace slot");
 
+// ------------------------------------------------------------------ the graph kernel (tessel_graph.hip)
+// Problems the fast kernel does not take (graphs with fan-in or fan-out, more than 8 devices, 32 types, 4 types on a
+// device or windows of 8 micro-batches): tables made by the host once per handle, uploaded with the parameter block.
+constexpr int kGraphOut = 4;          // consumers of a type the kernel's tables hold
+constexpr int kGraphIn = 4;           // ... producers (fewer for long windows: the fields of a type's word)
+constexpr int kGraphTp = 10;          // ... block types on several devices (6 bits each of a 64-bit word)
+constexpr int kGraphSlots = 192;      // programs of one wave between build and sweeps: 64 being built, fewer than 64 waiting
+                                      // for their first sweeps and fewer than 64 for the longer search
+constexpr int kGraphTries = 2;        // window sweeps every candidate gets
+constexpr int kGraphTabWords = (2 + 2 * kGraphOut) * 256 + kMaxKW * 4 + kMaxKW * 3 + kGraphTp * 33 + 64;
+struct GraphTab {
+    int32_t ok;                  // the kernel takes the problem
+    int32_t np;                  // bits of a device's symbols: 1 (up to two types a device), 2 (four), 3 (eight)
+    int32_t maxout, maxin;       // most consumers and producers of a type
+    int32_t chain;               // no type has more than one of either
+    int32_t nedge, nlead, ntp, first_tries, retry_tries;
+    int32_t mushift;             // a type's word: next micro-batch from this bit on; below it fields with a guard bit each:
+                                 // occurrences left, then per producer the micro-batches waiting (1 where there is none)
+    uint32_t add, guard;         // (word + add) & guard == guard: no field is zero, the type may run
+    int32_t nwords;              // program words: two entries each, rounded up to four words
+    int32_t meta;                // words per slot before the program: index (2), peak, leads of the rings' first types
+    uint32_t lds_bytes;
+    // LDS byte addresses
+    uint32_t slot_rows;          // one row to hand slots to lanes, three rows of slot states
+    uint32_t rec, wrow, trash;   // build: device records, one row per type, a row that stays zero
+    uint32_t state, prev, strash, leads;   // sweeps: device times and rings (numbered as KParams::nslots counts them), device
+                                 // times at the last boundary, a row for stores nobody reads, leads of the rings' first types
+    uint32_t sw;                 // sweep tables by type, kMaxKW words each: t | has a ring << 31, device row | own ring << 16,
+                                 // rings of the producers (16 bits each)
+    uint32_t dev, init;          // by device the number of its block types; by type its word for lead 0 and nothing waiting
+    uint32_t tpm, tpi, tps, smask;   // blocks on several devices: by type the device mask (0: one device) and 6 * number |
+                                 // lowest device << 8 | devices << 16; symbol by number and device; by device the symbols of types
+                                 // that sit on it alone
+    uint32_t lead_edge[kMaxDeps];// the dependencies, consumers' types first: src | dst << 8 | number << 16 | joins different device
+                                 // sets << 24 | first of its source << 25 | last of it << 26
+    uint32_t edge[kMaxDeps];     // distinct dependencies: src | dst << 8 | shift of the field in dst's word << 16
+    int32_t ntab;
+    uint32_t tab[kGraphTabWords];// the LDS up to slot_rows: by code (device << np | symbol, rows of 32 << np words) memory delta
+                                 // << 16 | LDS row of the type's word << 8 | on several devices << 6 | type; what placing a block
+                                 // adds to that word; then per consumer k: address of the record's last word << 16 | LDS row of its
+                                 // word << 8 | device << 3 | symbol, and the increment of its word; then the sweep tables
+};
+
+static_assert(sizeof(GraphTab) <= kWsGraphMax, "graph tables must fit their workspace slot");
+
 struct LaunchShape { int blocks, threads; size_t lds_bytes; };
 
+// tessel_graph.hip
+const void *graph_kernel(const KParams &kp);
+int launch_graph(const KParams &kp, uint64_t first, uint64_t count, int blocks, void *recs, int32_t *code, int32_t *peak, void *ws,
+                 uint32_t *slots, void *stream);
 // kernels.hip
 // max_blocks: 0, or the most workgroups the workspace has queues for
 LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks);

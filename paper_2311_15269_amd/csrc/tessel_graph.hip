@@ -1,0 +1,706 @@
+// The graph kernel (gfx950): scores repetend candidates of the problems the fast kernel does not take -- any acyclic
+// micro-batch graph, up to 32 devices, 64 block types, eight types on a device, windows of 16 micro-batches -- one
+// candidate per lane, with the same build as the fast kernel made independent of the number of devices and types.
+//
+// Two 32-bit masks by device are all that a lane keeps in registers between two blocks: HD = devices whose head may run,
+// RD = devices with any type that may run.  Everything indexed by a device or a type sits in LDS, [row][lane]:
+//   device record   the order as np bit planes, the entries not yet placed, and one word: symbols that may run (8 bits),
+//                   head of the list (one-hot, 8 bits), memory now (signed, 16 bits)
+//   type word       next micro-batch, and fields with a guard bit each: occurrences left, and per producer the micro-batches
+//                   waiting at the input.  One addition places a block; the type may run iff no field is zero, which
+//                   one addition and one compare of the guard bits tell
+// One block is placed per step and lane (any order of heads that may run gives the same per-device orders): lowest
+// device of HD, else (repair) of RD; there the earliest entry whose type may run.  Three dependent rounds of LDS reads:
+// the record; the tables of the (device, symbol); words and records these name.
+//
+// Bound by the latency of those rounds at the few waves per CU that the LDS holds (a record is np + 2 rows of 256
+// bytes per device, a word one row per type).  Kernel times against the general kernel, which looks at every device's
+// head in turn and keeps counters for 64 types in registers: 200,003 candidates of a pipeline on 16 devices, 256 blocks
+// a window, 34.6 -> 0.655 ms; 100,003 of one on 12 devices, 288 blocks, 10.0 -> 0.265 ms; 300,007 with six types on each
+// of four devices, 96 blocks, 6.9 -> 0.302 ms; 2^22 of a graph of 6 types on three devices, 24 blocks, 3.48 -> 1.465 ms.
+//
+// The program (block type and micro-batch, 16 bits a block) goes to global memory, [word][slot], a slot per candidate;
+// sweeps read it back four words ahead.  A wave owns kGraphSlots slots: candidates that survive the build keep theirs
+// until 64 wait, are swept on full waves, and the few whose boundary values have not settled wait again for a longer
+// search.  What is open after that goes to the general kernel's list.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include <limits.h>
+
+#include "tessel_common.h"
+
+namespace tessel {
+
+constexpr uint32_t kRow = kWave * 4u;            // one LDS row: a word per lane
+constexpr uint32_t kProgRow = kGraphSlots;       // words of one program word over all slots of a wave
+
+__device__ __forceinline__ void lds_add(uint32_t a, uint32_t v)
+{
+    __hip_atomic_fetch_add((lds_word *)(uintptr_t)a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// a device's order while it is decoded: bit p of plane k = bit k of the symbol at position p
+template <int NP>
+struct Planes {
+    uint32_t p0, p1, p2;
+    __device__ __forceinline__ void clear() { p0 = p1 = p2 = 0; }
+    __device__ __forceinline__ void put(uint32_t y, uint32_t pos)
+    {
+        p0 |= (y & 1u) << pos;
+        if (NP > 1) p1 |= ((y >> 1) & 1u) << pos;
+        if (NP > 2) p2 |= (y >> 2) << pos;
+    }
+};
+
+// blocks of device d in the sampled spaces: a draw picks among the blocks left, types in ascending order
+template <int NP>
+__device__ __forceinline__ void sampled_order(uint32_t ka, uint32_t kb, int d, uint32_t ntd, uint32_t NR, Planes<NP> &o)
+{
+    const uint32_t n = ntd * NR;
+    o.clear();
+    // cumulative counts of the blocks left by type: one (shifted by 16) for two types; else bytes 0x80 - t, so that adding
+    // the replicated digit leaves "digit >= t" in bit 7 of every byte (t, digit <= 32)
+    uint32_t c = NR << 16, ta = 0, tb = 0, tc = 0;
+    if (NP > 1) {
+        auto cum = [&](uint32_t k) -> uint32_t { return min(k, ntd) * NR; };
+        ta = 0x808080u - (cum(1) | (cum(2) << 8) | (cum(3) << 16));
+        if (NP > 2) { tb = 0x808080u - (cum(4) | (cum(5) << 8) | (cum(6) << 16)); tc = 0x80u - cum(7); }
+    }
+    auto pick = [&](uint32_t draw, uint32_t left, uint32_t pos) {
+        if (NP == 1) {
+            const uint32_t prod = __umul24(draw, left);
+            const uint32_t y = prod >= c ? 1u : 0u;
+            c -= y ? 0u : 0x10000u;
+            o.p0 |= y << pos;
+            return;
+        }
+        const uint32_t digit = (uint32_t)(((uint64_t)draw * (uint64_t)((left << 16) & 0xFFFFFFu)) >> 32);   // 24-bit high multiply
+        const uint32_t ga = mad24(digit, 0x010101u, ta) & 0x808080u;
+        ta += (ga >> 7) ^ 0x010101u;                    // a threshold above the digit loses one block
+        uint32_t y = (uint32_t)__builtin_popcount(ga);
+        if (NP > 2) {
+            const uint32_t gb = mad24(digit, 0x010101u, tb) & 0x808080u;
+            tb += (gb >> 7) ^ 0x010101u;
+            const uint32_t gc = (tc + digit) & 0x80u;
+            tc += (gc >> 7) ^ 1u;
+            y += (uint32_t)__builtin_popcount(gb) + (gc >> 7);
+        }
+        o.put(y, pos);
+    };
+    for (uint32_t pos = 0; pos < n; pos += 2) {
+        const uint32_t word = stream_word(ka, kb, (kDrawOrdBase + 32u * (uint32_t)d + pos) >> 1);
+        pick(word & 0xFFFFu, n - pos, pos);
+        if (pos + 1 < n) pick(word >> 16, n - pos - 1u, pos + 1u);
+    }
+}
+
+template <int NP, bool REPAIR, bool TP>
+__global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__restrict__ Pp, const GraphTab *__restrict__ Gp, uint64_t first,
+                                                           uint64_t count, BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
+                                                           int32_t *__restrict__ peak_out, uint64_t *__restrict__ out_list,
+                                                           uint32_t *__restrict__ out_count, uint32_t out_cap,
+                                                           uint32_t *__restrict__ overflow, uint32_t *slots_all)
+{
+    extern __shared__ uint32_t lds[];
+    // all LDS addresses below are offsets from 0: nothing else of the kernel lies in front of this array
+    if (lds_address(lds) != 0u) { if (threadIdx.x == 0) *overflow = 0x100u; return; }
+    const KParams &P = *Pp;
+    const GraphTab &G = *Gp;
+    const int lane = threadIdx.x;
+    const uint32_t lane4 = (uint32_t)lane * 4u;
+    for (int w = lane; w < G.ntab; w += kWave) lds[w] = G.tab[w];
+    const uint32_t sel_row = G.slot_rows, st_row = G.slot_rows + kRow;
+#pragma unroll
+    for (int j = 0; j < 3; j++) lds_store(st_row + (uint32_t)j * kRow + lane4, 0u);
+    __syncthreads();
+
+    constexpr uint32_t kCodeRow = (32u << NP) * 4u;              // bytes of one code table
+    constexpr uint32_t RS = (NP + 2) * kRow;                     // bytes of one device record
+    const int D = P.D, K = P.K, M = P.M, total = P.total, space = P.space, nwords = G.nwords;
+    const uint32_t NR = (uint32_t)P.NR, ADD = G.add, GUARD = G.guard, mushift = (uint32_t)G.mushift;
+    const uint32_t rec0 = G.rec + lane4, wrow0 = G.wrow + lane4;
+    const int maxout = G.maxout, ntp = TP ? G.ntp : 0;
+    uint32_t *slots = slots_all + (size_t)blockIdx.x * (size_t)(G.meta + nwords) * kProgRow;
+    uint32_t *progs = slots + (size_t)G.meta * kProgRow;
+    const bool drop_mem = REPAIR && peak_out == nullptr;         // a rejected candidate's peak is that of the whole window
+
+    int best = INT_MAX;
+    uint64_t best_idx = 0;
+    uint32_t cnt[kNumStatus];
+#pragma unroll
+    for (int s = 0; s < kNumStatus; s++) cnt[s] = 0;
+    uint32_t nev = 0, nretry = 0;
+
+    auto rank_in = [&](uint64_t m) -> uint32_t {
+        return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    };
+    // (table words with a uniform index come from the LDS copy too)
+    auto uniform_word = [&](uint32_t a) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_load(a)); };
+    auto types_on = [&](int d) -> uint32_t { return uniform_word(G.dev + (uint32_t)d * 4u); };
+    auto ready = [&](uint32_t w) -> bool { return ((w + ADD) & GUARD) == GUARD; };
+    // The first 64 slots in state `cls`, one per lane (fewer: the other lanes get some slot of the wave); how many there
+    // are.  `take` false: only counts.
+    auto slots_in = [&](uint32_t cls, bool take, uint32_t &mine) -> uint32_t {
+        uint32_t n = 0;
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+            const bool in = lds_load(st_row + (uint32_t)j * kRow + lane4) == cls;
+            const uint64_t m = __ballot(in);
+            if (take && in) {
+                const uint32_t r = n + rank_in(m);
+                if (r < (uint32_t)kWave) lds_store(sel_row + r * 4u, (uint32_t)(j * kWave + lane));
+            }
+            n += (uint32_t)__builtin_popcountll(m);
+        }
+        if (take) { __syncthreads(); mine = lds_load(sel_row + lane4); __syncthreads(); }
+        return n;
+    };
+
+    // ---------------------------------------------------------------- build: 64 new candidates
+    auto build = [&](uint64_t idx, bool valid) {
+        uint32_t slot = 0;
+        lds_store(sel_row + lane4, (uint32_t)lane);
+        __syncthreads();
+        slots_in(0u, true, slot);                                // (always 64 or more free: see kGraphSlots)
+        uint32_t *prog = progs + slot;
+        int status = kOk;
+        uint32_t ka = 0, kb = 0;
+        uint64_t rest = idx;
+        const bool sampled = space == kSampledStrict || space == kSampledRepair;
+        if (sampled) ka = stream_keys(P.seed, idx, kb);
+        lds_store(G.trash + lane4, 0u);
+        // ---- leads, by type
+        for (int g = 0; g < K; g++) {
+            uint32_t lead = 0;
+            if (sampled && P.has_fixed) lead = P.fixed[g];
+            lds_store(wrow0 + (uint32_t)g * kRow, uniform_word(G.init + (uint32_t)g * 4u) + (lead << mushift));
+        }
+        if (sampled && !P.has_fixed) {
+            // consumers before producers: a type's lead is the largest (consumer's lead + step) over its dependencies
+            uint32_t lead = 0, before = ~0u, before_lead = 0, at = ~0u, word = 0;
+            for (int k = 0; k < G.nlead; k++) {
+                const uint32_t E = (uint32_t)__builtin_amdgcn_readfirstlane((int)G.lead_edge[k]);
+                const uint32_t src = E & 255u, dst = (E >> 8) & 255u, e = (E >> 16) & 255u;
+                if (E >> 25 & 1u) lead = 0;
+                const uint32_t ld = dst == before ? before_lead : lds_load(wrow0 + dst * kRow) >> mushift;
+                uint32_t step = 0;
+                if (E >> 24 & 1u) {
+                    const uint32_t wi = (kDrawLeadBase + e) >> 1;
+                    if (wi != at) { word = stream_word(ka, kb, wi); at = wi; }
+                    const uint32_t u = (e & 1u) ? word >> 16 : word & 0xFFFFu;
+                    step = u < P.step_q16 ? 1u : 0u;
+                }
+                lead = max(lead, ld + step);
+                if (E >> 26 & 1u) {
+                    lead = min(NR - 1u, lead);
+                    lds_store(wrow0 + src * kRow, uniform_word(G.init + src * 4u) + (lead << mushift));
+                    before = src; before_lead = lead;
+                }
+            }
+        }
+        // ---- orders, by device
+        bool dup = false, tpm = false;
+        for (int d = 0; d < D; d++) {
+            const uint32_t ntd = types_on(d), n = ntd * NR;
+            Planes<NP> o;
+            if (sampled) sampled_order<NP>(ka, kb, d, ntd, NR, o);
+            else if (space == kCanonical) {
+                o.clear();
+                const uint32_t B = NR + 1;
+                uint64_t r = rest % P.cdev[d];
+                rest /= P.cdev[d];
+                uint32_t c0 = ntd > 0 ? NR : 0u, c1 = ntd > 1 ? NR : 0u, c2 = ntd > 2 ? NR : 0u, c3 = ntd > 3 ? NR : 0u;
+                for (uint32_t pos = 0; pos < n; pos++) {
+                    bool chosen = false;
+                    uint32_t y = 0;
+                    auto look = [&](uint32_t &c, uint32_t sym) {
+                        if (chosen || c == 0) return;
+                        c--;
+                        const uint64_t w = P.wtab[((c0 * B + c1) * B + c2) * B + c3];
+                        if (r < w) { y = sym; chosen = true; } else { r -= w; c++; }
+                    };
+                    look(c0, 0u); look(c1, 1u);
+                    if (NP > 1) { look(c2, 2u); look(c3, 3u); }
+                    o.put(y, pos);
+                }
+            } else {
+                o.clear();
+                uint32_t r = (uint32_t)(rest % P.cdev[d]);
+                rest /= P.cdev[d];
+                uint64_t list = P.init_list[d];
+                uint32_t firstlab = 0xFFFFFFFFu, seen = 0;
+                for (uint32_t pos = 0; pos < n; pos++) {
+                    const uint32_t f = P.fact[n - 1 - pos];
+                    const uint32_t digit = r / f;
+                    r -= digit * f;
+                    const uint32_t code = (uint32_t)(list >> (5u * digit)) & 31u;
+                    const uint64_t low = list & ((1ull << (5u * digit)) - 1ull);
+                    list = low | (((list >> (5u * digit)) >> 5) << (5u * digit));
+                    const uint32_t y = code >> 3, lab = code & 7u;
+                    o.put(y, pos);
+                    const uint32_t fl = byte_of(firstlab, y), sc = byte_of(seen, y);
+                    if (fl == 0xFFu) firstlab = (firstlab & ~(0xFFu << (8u * y))) | (lab << (8u * y));
+                    else {
+                        uint32_t want = fl + sc;                 // labels continue cyclically (Property 1)
+                        if (want >= NR) want -= NR;
+                        if (lab != want) dup = true;
+                    }
+                    seen += 1u << (8u * y);
+                }
+                for (uint32_t y = 0; y < ntd; y++) {
+                    const uint32_t g = uniform_word((((uint32_t)d << NP) + y) * 4u) & 63u;
+                    const uint32_t fl = byte_of(firstlab, y), a = wrow0 + g * kRow;
+                    if ((uint32_t)__builtin_ctz(P.mask_type[g]) == (uint32_t)d) lds_store(a, uniform_word(G.init + (uint32_t)g * 4u) + (fl << mushift));
+                    else if (lds_load(a) >> mushift != fl) tpm = true;
+                }
+            }
+            const uint32_t ra = rec0 + (uint32_t)d * RS;
+            lds_store(ra, o.p0);
+            if (NP > 1) lds_store(ra + kRow, o.p1);
+            if (NP > 2) lds_store(ra + 2 * kRow, o.p2);
+            const uint32_t alive = n >= 32u ? 0xFFFFFFFFu : (1u << n) - 1u;
+            const uint32_t y0 = (o.p0 & 1u) | (NP > 1 ? (o.p1 & 1u) << 1 : 0u) | (NP > 2 ? (o.p2 & 1u) << 2 : 0u);
+            lds_store(ra + NP * kRow, alive);
+            lds_store(ra + (NP + 1) * kRow, n ? 1u << (8u + y0) : 0u);
+        }
+        if (space == kCanonical) {
+            const int8_t *row = P.leadtab + rest * (uint64_t)K;
+            for (int g = 0; g < K; g++) lds_store(wrow0 + (uint32_t)g * kRow, uniform_word(G.init + (uint32_t)g * 4u) + ((uint32_t)row[g] << mushift));
+        }
+        // ---- micro-batches waiting at every input: what the last window's producer is ahead of its consumer
+        bool prop2 = false;
+        for (int k = 0; k < G.nedge; k++) {
+            const uint32_t E = (uint32_t)__builtin_amdgcn_readfirstlane((int)G.edge[k]);
+            const uint32_t a = wrow0 + (E & 255u) * kRow, b = wrow0 + ((E >> 8) & 255u) * kRow;
+            const uint32_t ls = lds_load(a) >> mushift, ld = lds_load(b) >> mushift;
+            if (ls < ld) prop2 = true;
+            else lds_add(b, (ls - ld) << (E >> 16));
+        }
+        if (space == kFactorial) status = dup ? kDup : tpm ? kTpMismatch : prop2 ? kProp2 : kOk;
+        // ---- what may run, memory at the window entry (type i has handled micro-batches 0 .. lead - 1), heads
+        uint32_t RD = 0, HD = 0;
+        uint64_t hcnt = 0;                                       // TP: devices a type heads, six bits a type
+        uint32_t rtp = 0;                                        // TP: such types that may run
+        for (int d = 0; d < D; d++) {
+            const uint32_t ra = rec0 + (uint32_t)d * RS + (NP + 1) * kRow;
+            uint32_t runs = 0;
+            int mem = 0;
+            const uint32_t head = lds_load(ra);
+            const int ntd = (int)types_on(d);
+            for (int y = 0; y < ntd; y++) {
+                const uint32_t T0 = uniform_word((((uint32_t)d << NP) + (uint32_t)y) * 4u);
+                const uint32_t w = lds_load((T0 & 0xFF00u) + lane4);
+                const bool ok = ready(w);
+                runs |= (ok ? 1u : 0u) << y;
+                mem += ((int)T0 >> 16) * (int)(w >> mushift);
+                if (TP && (T0 & 64u)) {
+                    const uint32_t inf = uniform_word(G.tpi + (T0 & 63u) * 4u);
+                    if (head >> (8 + y) & 1u) hcnt += 1ull << (inf & 63u);
+                    rtp |= ok ? 1u << ((inf & 63u) / 6u) : 0u;
+                }
+            }
+            const uint32_t smask = TP ? uniform_word(G.smask + (uint32_t)d * 4u) : 0xFFu;
+            lds_store(ra, runs | head | ((uint32_t)mem << 16));
+            RD |= (runs ? 1u : 0u) << d;
+            HD |= (runs & (head >> 8) & smask ? 1u : 0u) << d;
+        }
+        // ---- blocks in an executable sequence
+        bool building = REPAIR || (valid && status == kOk);
+        int worst = INT_MIN;
+        const uint32_t dlast = (uint32_t)D - 1u;
+        // the head of a device list changed: TP types it left or reached
+        auto head_moved = [&](uint32_t code0, uint32_t from, uint32_t to) {
+            if (from == to) return;
+            if (from) {
+                const uint32_t T = lds_load((code0 | (uint32_t)__builtin_ctz(from)) << 2);
+                if (T & 64u) hcnt -= 1ull << (lds_load(G.tpi + (T & 63u) * 4u) & 63u);
+            }
+            if (to) {
+                const uint32_t T = lds_load((code0 | (uint32_t)__builtin_ctz(to)) << 2);
+                if (T & 64u) hcnt += 1ull << (lds_load(G.tpi + (T & 63u) * 4u) & 63u);
+            }
+        };
+        auto step = [&]() -> uint32_t {
+            uint32_t hd = HD;
+            if (TP)
+                for (int i = 0; i < ntp; i++) {
+                    // a type on several devices is a head that may run when it heads all of them; placed from its lowest
+                    const uint32_t inf = uniform_word(G.tpi + (kMaxKW + (uint32_t)i) * 4u);
+                    const bool full = ((uint32_t)(hcnt >> (6 * i)) & 63u) == inf >> 16;
+                    hd |= full && (rtp >> i & 1u) ? 1u << ((inf >> 8) & 31u) : 0u;
+                }
+            const uint32_t sel = hd ? hd : (REPAIR ? RD : 0u);
+            if (!REPAIR && building && sel == 0) { status = kDeadlock; building = false; }
+            const uint32_t d = REPAIR ? min(low_bit(sel) & 31u, dlast) : building ? low_bit(sel) & 31u : 0u;
+            const uint32_t ra = d * RS + rec0;
+            const uint32_t p0 = lds_load(ra), p1 = NP > 1 ? lds_load(ra + kRow) : 0u, p2 = NP > 2 ? lds_load(ra + 2 * kRow) : 0u;
+            const uint32_t alive = lds_load(ra + NP * kRow), rhm = lds_load(ra + (NP + 1) * kRow);
+            // earliest entry whose type may run: a multiplexer keyed by the planes.  (A device picked for its head: the head.)
+            auto runs = [&](int y) -> uint32_t { return (uint32_t)__builtin_amdgcn_sbfe((int)rhm, y, 1); };
+            uint32_t gate;
+            if (NP == 1) gate = bfi(p0, runs(1), runs(0));
+            else {
+                gate = bfi(p1, bfi(p0, runs(3), runs(2)), bfi(p0, runs(1), runs(0)));
+                if (NP > 2) gate = bfi(p2, bfi(p1, bfi(p0, runs(7), runs(6)), bfi(p0, runs(5), runs(4))), gate);
+            }
+            const uint32_t p = low_bit(alive & gate);
+            auto symbol = [&](uint32_t pos) -> uint32_t {
+                uint32_t y = __builtin_amdgcn_ubfe(p0, pos, 1);
+                if (NP > 1) y |= __builtin_amdgcn_ubfe(p1, pos, 1) << 1;
+                if (NP > 2) y |= __builtin_amdgcn_ubfe(p2, pos, 1) << 2;
+                return y;
+            };
+            const uint32_t y = symbol(p), code0 = d << NP, ca = (code0 | y) << 2;
+            uint32_t T0 = lds_load(ca), T1 = lds_load(ca + kCodeRow), C0 = lds_load(ca + 2 * kCodeRow), C1 = lds_load(ca + 3 * kCodeRow);
+            TESSEL_PIN(T0); TESSEL_PIN(T1); TESSEL_PIN(C0); TESSEL_PIN(C1);
+            const uint32_t wa = (T0 & 0xFF00u) + lane4;
+            uint32_t cwa = (C0 & 0xFF00u) + lane4, cra = (C0 >> 16) + lane4;
+            uint32_t w = lds_load(wa), wc = lds_load(cwa), rc = lds_load(cra);
+            TESSEL_PIN(w); TESSEL_PIN(wc); TESSEL_PIN(rc);
+            const uint32_t alive2 = alive & ~(1u << p);
+            const uint32_t head2 = alive2 ? 1u << (8u + symbol(low_bit(alive2))) : 0u;
+            const uint32_t w2 = w + T1;
+            const bool again = ready(w2);
+            const uint32_t onec = 1u << y;
+            uint32_t rhm2 = ((rhm + (T0 & 0xFFFF0000u)) & 0xFFFF0000u) | (rhm & 0xFFu & ~onec) | (again ? onec : 0u) | head2;
+            uint32_t entry = 0;
+            if (REPAIR || building) {
+                worst = max(worst, (int)rhm2 >> 16);
+                lds_store(ra + NP * kRow, alive2);
+                lds_store(wa, w2);
+                lds_store(ra + (NP + 1) * kRow, rhm2);
+                const uint32_t smask = TP ? lds_load(G.smask + (d << 2)) : 0xFFu;
+                const uint32_t oned = 1u << d;
+                RD = rhm2 & 0xFFu ? RD | oned : RD & ~oned;
+                HD = rhm2 & (rhm2 >> 8) & smask ? HD | oned : HD & ~oned;
+                if (TP) {
+                    head_moved(code0, rhm >> 8 & 0xFFu, head2 >> 8);
+                    if (T0 & 64u) {
+                        // the block's earliest entry on its other devices
+                        const uint32_t g = T0 & 63u, inf = lds_load(G.tpi + g * 4u), i = (inf & 63u) / 6u;
+                        rtp = again ? rtp | 1u << i : rtp & ~(1u << i);
+                        for (uint32_t others = lds_load(G.tpm + g * 4u) & ~oned; others; others &= others - 1u) {
+                            const uint32_t dd = (uint32_t)__builtin_ctz(others), rq = dd * RS + rec0;
+                            const uint32_t q0 = lds_load(rq), q1 = NP > 1 ? lds_load(rq + kRow) : 0u, q2 = NP > 2 ? lds_load(rq + 2 * kRow) : 0u;
+                            const uint32_t qa = lds_load(rq + NP * kRow), qr = lds_load(rq + (NP + 1) * kRow);
+                            const uint32_t ys = lds_load(G.tps + (i * 32u + dd) * 4u);
+                            uint32_t same = qa & (ys & 1u ? q0 : ~q0);
+                            if (NP > 1) same &= ys & 2u ? q1 : ~q1;
+                            if (NP > 2) same &= ys & 4u ? q2 : ~q2;
+                            const uint32_t left = qa & ~(same & (0u - same));
+                            const uint32_t ph = low_bit(left);
+                            uint32_t yh = __builtin_amdgcn_ubfe(q0, ph, 1);
+                            if (NP > 1) yh |= __builtin_amdgcn_ubfe(q1, ph, 1) << 1;
+                            if (NP > 2) yh |= __builtin_amdgcn_ubfe(q2, ph, 1) << 2;
+                            const uint32_t hq = left ? 1u << (8u + yh) : 0u;
+                            const uint32_t r2 = ((qr + (T0 & 0xFFFF0000u)) & 0xFFFF0000u) | (qr & 0xFFu & ~(1u << ys)) | (again ? 1u << ys : 0u) | hq;
+                            worst = max(worst, (int)r2 >> 16);
+                            lds_store(rq + NP * kRow, left);
+                            lds_store(rq + (NP + 1) * kRow, r2);
+                            const uint32_t ob = 1u << dd, sm = lds_load(G.smask + (dd << 2));
+                            RD = r2 & 0xFFu ? RD | ob : RD & ~ob;
+                            HD = r2 & (r2 >> 8) & sm ? HD | ob : HD & ~ob;
+                            head_moved(dd << NP, qr >> 8 & 0xFFu, hq >> 8);
+                        }
+                    }
+                }
+                entry = (T0 & 63u) | (w >> mushift) << 6;
+                // the consumers: one more micro-batch waits.  (No consumer: the row that
+                // stays zero, increment 0, and the block's own record.)
+                for (int k = 0;;) {
+                    const uint32_t wc2 = wc + C1;
+                    const bool runs_now = ready(wc2);
+                    const uint32_t dc = (C0 >> 3) & 31u, bit = 1u << (C0 & 7u);
+                    lds_store(cwa, wc2);
+                    if (TP) {
+                        const uint32_t cg = ((C0 & 0xFF00u) - G.wrow) / kRow;        // (the zero row lies behind the types')
+                        const uint32_t cm = cg < (uint32_t)K ? lds_load(G.tpm + cg * 4u) : 0u;
+                        if (runs_now) {
+                            if (cm) {
+                                const uint32_t i = (lds_load(G.tpi + cg * 4u) & 63u) / 6u;
+                                rtp |= 1u << i;
+                                RD |= cm;
+                                for (uint32_t rest_d = cm; rest_d; rest_d &= rest_d - 1u) {
+                                    const uint32_t dd = (uint32_t)__builtin_ctz(rest_d), rq = dd * RS + rec0 + (NP + 1) * kRow;
+                                    lds_store(rq, lds_load(rq) | 1u << lds_load(G.tps + (i * 32u + dd) * 4u));
+                                }
+                            } else {
+                                const uint32_t now = lds_load(cra) | bit;
+                                lds_store(cra, now);
+                                RD |= 1u << dc;
+                                HD |= now & (now >> 8) & lds_load(G.smask + (dc << 2)) ? 1u << dc : 0u;
+                            }
+                        }
+                    } else {
+                        uint32_t now = k == 0 ? (dc == d ? rhm2 : rc) : lds_load(cra);
+                        now |= runs_now ? bit : 0u;
+                        lds_store(cra, now);
+                        RD |= (now & 0xFFu ? 1u : 0u) << dc;
+                        HD |= (now & (now >> 8) & 0xFFu ? 1u : 0u) << dc;
+                    }
+                    if (++k >= maxout) break;
+                    C0 = lds_load(ca + (2u + 2u * (uint32_t)k) * kCodeRow); C1 = lds_load(ca + (3u + 2u * (uint32_t)k) * kCodeRow);
+                    cwa = (C0 & 0xFF00u) + lane4; cra = (C0 >> 16) + lane4;
+                    wc = lds_load(cwa);
+                }
+            }
+            return entry;
+        };
+        const int full = total / 2;
+        bool whole = true;
+        for (int wi = 0; wi < full; wi++) {
+            const uint32_t e0 = step(), e1 = step();
+            prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
+            if ((wi & 7) == 7) {
+                const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
+                if (__ballot(going) == 0) { whole = false; break; }
+            }
+        }
+        if (whole && (total & 1)) prog[(size_t)full * kProgRow] = step();
+        // ---- verdict
+        int peak = worst;
+        if (status == kOk) {
+            for (int d = 0; d < D; d++) if (types_on(d) == 0) peak = max(peak, 0);      // a device without blocks holds nothing
+            if (peak > M) status = kMem;
+        }
+        const bool rejected = valid && status != kOk, ok = valid && status == kOk;
+        nev += (uint32_t)__builtin_popcountll(__ballot(rejected));
+#pragma unroll
+        for (int s = 1; s < kNumStatus; s++) cnt[s] += (uint32_t)__builtin_popcountll(__ballot(rejected && status == s));
+        if (rejected) {
+            if (code_out) code_out[idx - first] = -status;
+            if (peak_out) peak_out[idx - first] = status == kMem ? peak : 0;
+        }
+        if (ok) {
+            uint32_t *meta = slots + slot;
+            meta[0] = (uint32_t)idx; meta[kProgRow] = (uint32_t)(idx >> 32); meta[2 * kProgRow] = (uint32_t)peak;
+            // (all N_R occurrences are placed: next micro-batch - N_R is the lead)
+            for (int r = 0; r < P.ntok; r += 4) {
+                uint32_t pack = 0;
+                for (int q = 0; q < 4 && r + q < P.ntok; q++)
+                    pack |= ((lds_load(wrow0 + (uint32_t)P.ring_head[r + q] * kRow) >> mushift) - NR) << (8 * q);
+                meta[(size_t)(3 + r / 4) * kProgRow] = pack;
+            }
+            lds_store(st_row + slot * 4u, 1u);
+        }
+    };
+
+    // ---------------------------------------------------------------- window sweeps of up to 64 candidates in state `cls`
+    // Times, rings and boundary as in the general kernel; eigenvector test after every sweep.
+    auto sweep = [&](uint32_t cls, bool more_to_come) {
+        uint32_t slot = 0;
+        lds_store(sel_row + lane4, (uint32_t)lane);
+        __syncthreads();
+        const uint32_t n = slots_in(cls, true, slot);
+        const bool have = (uint32_t)lane < n;
+        const uint32_t *meta = slots + slot, *prog = progs + slot;
+        __threadfence_block();                                   // the wave's other lanes wrote these words
+        const uint64_t idx = have ? (uint64_t)meta[0] | ((uint64_t)meta[kProgRow] << 32) : first;
+        const int pk = (int)meta[2 * kProgRow];
+        const uint32_t st0 = G.state + lane4;
+        for (int r = 0; r < P.ntok; r += 4) lds_store(G.leads + (uint32_t)(r / 4) * kRow + lane4, have ? meta[(size_t)(3 + r / 4) * kProgRow] : 0u);
+        for (int s = 0; s < P.nslots; s++) lds_store(st0 + (uint32_t)s * kRow, 0u);
+        for (int d = 0; d < D; d++) lds_store(G.prev + (uint32_t)d * kRow + lane4, 0u);
+        const bool chain = G.chain != 0;
+        const int maxin = G.maxin;
+        auto block = [&](uint32_t e, uint32_t A, uint32_t B) {
+            const uint32_t mu8 = (e >> 6) << 8, da = (B & 0xFFFFu) + lane4;
+            if (!TP && chain) {
+                const uint32_t ta = (B >> 16) + mu8 + lane4;
+                const uint32_t en = max(lds_load(da), lds_load(ta)) + (A & 0xFFFFFFu);
+                lds_store(da, en);
+                lds_store(ta, en);
+                return;
+            }
+            const uint32_t g4 = (e & 63u) << 2;
+            uint32_t s = 0;
+            const uint32_t mask = TP ? lds_load(G.tpm + g4) : 0u;
+            s = lds_load(da);
+            for (uint32_t rest = mask; rest; rest &= rest - 1u) s = max(s, lds_load(st0 + (uint32_t)__builtin_ctz(rest) * kRow));
+            for (int k = 0; k < maxin; k += 2) {
+                const uint32_t pr = lds_load(G.sw + (2u + (uint32_t)k / 2u) * (kMaxKW * 4u) + g4);
+                s = max(s, max(lds_load((pr & 0xFFFFu) + mu8 + lane4), lds_load((pr >> 16) + mu8 + lane4)));
+            }
+            const uint32_t en = s + (A & 0xFFFFFFu);
+            lds_store(da, en);
+            for (uint32_t rest = mask; rest; rest &= rest - 1u) lds_store(st0 + (uint32_t)__builtin_ctz(rest) * kRow, en);
+            lds_store((B >> 16) + (mu8 & (uint32_t)((int)A >> 31)) + lane4, en);
+        };
+        uint32_t T = 0;
+        bool done = !have;
+        const int tries = cls == 1u ? G.first_tries : G.retry_tries;
+        const bool settle = cls != 1u && D + P.ntok * (int)NR <= 128;        // (one bit per value)
+        uint32_t top_before = 0;
+        uint64_t was_lo = 0, was_hi = 0;
+        for (int j = 0;; j++) {
+            const uint32_t open = (uint32_t)__builtin_popcountll(__ballot(!done));
+            if (open == 0) break;
+            // The first pass goes on while many lanes are open; a few stragglers wait until 64 of them fill a wave.  (One
+            // more sweep here costs the wave one sweep; a straggler costs a restart of three or more sweeps of 64 lanes.)
+            if (cls == 1u ? j >= tries && (tries == 0 || j >= 8 || (open <= 20u && more_to_come)) : j >= tries) break;
+            // four program words (eight blocks) at a time, the next four on their way
+            uint32_t cur[4], nxt[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) cur[q] = prog[(size_t)q * kProgRow];
+            for (int wi = 0; wi < nwords; wi += 4) {
+                const int ahead = wi + 4 < nwords ? wi + 4 : wi;
+#pragma unroll
+                for (int q = 0; q < 4; q++) nxt[q] = prog[(size_t)(ahead + q) * kProgRow];
+                uint32_t e[8], A[8], B[8];
+                const int left = total - 2 * wi;                 // blocks from here on
+#pragma unroll
+                for (int q = 0; q < 8; q++) {
+                    // (a word past the last block was never written, and a lane without a candidate has stale ones: type and
+                    // micro-batch stay inside the tables and the rings, or are not used)
+                    e[q] = q & 1 ? cur[q / 2] >> 16 : cur[q / 2] & 0xFFFFu;
+                    if (!have) e[q] = 0;
+                    const uint32_t g4 = (e[q] & 63u) << 2;
+                    A[q] = lds_load(G.sw + g4);
+                    B[q] = lds_load(G.sw + kMaxKW * 4u + g4);
+                }
+#pragma unroll
+                for (int q = 0; q < 8; q++) if (q < left) block(e[q], A[q], B[q]);
+#pragma unroll
+                for (int q = 0; q < 4; q++) cur[q] = nxt[q];
+            }
+            // Window boundary: micro-batches mu >= N_R are mu - N_R of the next window.  Every value that crosses it and
+            // means anything (devices with blocks, ring entries below the lead of the ring's first type) grew by the same
+            // amount: an eigenvector, and the amount is the period.  In the longer search also: the largest growth D was
+            // that of the boundary before, and every value that grew by D then grew by D now.  No cycle ratio exceeds the
+            // largest growth; and a value that grew by D got its time from one that grew by D the time before (that
+            // one's growth bounds its own from above), which is again one of these, so following them closes a cycle
+            // of ratio D.  (Forward-only pipelines need this: devices before the slowest keep a smaller growth for ever.)
+            bool same = true, seen = false;
+            uint32_t delta = 0;
+            auto grew = [&](uint32_t by, bool on) {
+                if (on) { if (!seen) { delta = by; seen = true; } else if (by != delta) same = false; }
+            };
+            auto in_flight = [&](int r) -> uint32_t {
+                return (lds_load(G.leads + (uint32_t)(r / 4) * kRow + lane4) >> (8 * (r & 3))) & 255u;
+            };
+            uint32_t top = 0;
+            if (settle) {
+                for (int d = 0; d < D; d++)
+                    if (types_on(d) > 0) top = max(top, lds_load(st0 + (uint32_t)d * kRow) - lds_load(G.prev + (uint32_t)d * kRow + lane4));
+                for (int r = 0; r < P.ntok; r++) {
+                    const uint32_t base = st0 + (uint32_t)P.ring_base[r] * kRow, kept = st0 + (uint32_t)P.ring_kept[r] * kRow, lg = in_flight(r);
+                    for (uint32_t m = 0; m < NR; m++) {
+                        const uint32_t by = lds_load(base + (m + NR) * kRow) - lds_load(kept + m * kRow);
+                        top = max(top, m < lg ? by : 0u);
+                    }
+                }
+            }
+            bool held = j > 0 && top == top_before;
+            uint64_t now_lo = 0, now_hi = 0;
+            uint32_t v = 0;                                      // number of the value (uniform)
+            auto keeps = [&](uint32_t by, bool on) {
+                if (!settle) return;
+                const uint64_t was = (v < 64u ? was_lo : was_hi) >> (v & 63u) & 1u, is = on && by == top ? 1u : 0u;
+                if (was && !is) held = false;
+                if (v < 64u) now_lo |= is << v; else now_hi |= is << (v & 63u);
+                v++;
+            };
+            for (int d = 0; d < D; d++) {
+                const uint32_t x = lds_load(st0 + (uint32_t)d * kRow), pa = G.prev + (uint32_t)d * kRow + lane4, by = x - lds_load(pa);
+                lds_store(pa, x);
+                if (types_on(d) > 0) { grew(by, true); keeps(by, true); }
+            }
+            for (int r = 0; r < P.ntok; r++) {
+                const uint32_t base = st0 + (uint32_t)P.ring_base[r] * kRow, kept = st0 + (uint32_t)P.ring_kept[r] * kRow, lg = in_flight(r);
+                for (uint32_t m = 0; m < NR; m++) {
+                    const uint32_t x = lds_load(base + (m + NR) * kRow), by = x - lds_load(kept + m * kRow);
+                    grew(by, m < lg);
+                    keeps(by, m < lg);
+                    const uint32_t keep = m < lg ? x : 0u;
+                    lds_store(base + m * kRow, keep);
+                    lds_store(kept + m * kRow, keep);
+                    lds_store(base + (m + NR) * kRow, 0u);
+                }
+            }
+            if (settle) {
+                if (!done && held) { T = top; done = true; }
+                top_before = top; was_lo = now_lo; was_hi = now_hi;
+            }
+            if (!done && same && seen) { T = delta; done = true; }
+        }
+        const bool scored = have && done, left_open = have && !done;
+        const uint32_t ns = (uint32_t)__builtin_popcountll(__ballot(scored));
+        nev += ns;
+        cnt[kOk] += ns;
+        if (scored) {
+            if (key_less((int)T, idx, best, best_idx)) { best = (int)T; best_idx = idx; }
+            if (code_out) code_out[idx - first] = (int)T;
+            if (peak_out) peak_out[idx - first] = pk;
+        }
+        if (left_open && cls != 1u) {
+            const uint32_t at = atomicAdd(out_count, 1u);
+            if (at < out_cap) out_list[at] = idx; else *overflow = 1u;
+        }
+        if (cls == 1u) nretry += (uint32_t)__builtin_popcountll(__ballot(left_open));
+        if (have) lds_store(st_row + slot * 4u, left_open && cls == 1u ? 2u : 0u);
+        __syncthreads();
+    };
+
+    const uint64_t stride = (uint64_t)gridDim.x * kWave;
+    const uint64_t rounds = (count + stride - 1) / stride;          // the same trip count for every lane of the grid
+    for (uint64_t r = 0;;) {
+        uint32_t unused;
+        const uint32_t n1 = slots_in(1u, false, unused), n2 = slots_in(2u, false, unused);
+        // (a wave whose share has ended early does no more rounds)
+        const bool fresh = r < rounds && r * stride + (uint64_t)blockIdx.x * kWave < count;
+        if (n2 >= (uint32_t)kWave || (!fresh && n1 == 0 && n2 > 0)) sweep(2u, true);
+        else if (n1 >= (uint32_t)kWave || (!fresh && n1 > 0)) sweep(1u, fresh || n1 > (uint32_t)kWave || n2 > 0);
+        else if (fresh) {
+            const uint64_t kk = r++ * stride + (uint64_t)blockIdx.x * kWave + lane;
+            const bool valid = kk < count;
+            build(valid ? first + kk : first, valid);
+            __syncthreads();
+        } else break;
+    }
+    if (!recs) return;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        int op = __shfl_xor(best, off);
+        uint32_t ilo = __shfl_xor((uint32_t)best_idx, off), ihi = __shfl_xor((uint32_t)(best_idx >> 32), off);
+        uint64_t oi = ((uint64_t)ihi << 32) | ilo;
+        if (key_less(op, oi, best, best_idx)) { best = op; best_idx = oi; }
+    }
+    if (lane == 0) {
+        BlockRec rr;
+        // (window sweeps and blocks placed are reported for the fast kernel only)
+        rr.period = best; rr.n_retried = nretry; rr.index = best_idx; rr.n_evaluated = nev; rr.n_sweeps = 0; rr.n_blocks = 0; rr.pad = 0;
+#pragma unroll
+        for (int s = 0; s < kNumStatus; s++) rr.n_status[s] = cnt[s];
+        recs[blockIdx.x] = rr;
+    }
+}
+
+// ------------------------------------------------------------------ launcher
+typedef void (*graph_fn)(const KParams *, const GraphTab *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, uint64_t *, uint32_t *,
+                         uint32_t, uint32_t *, uint32_t *);
+
+template <bool REPAIR, bool TP>
+static graph_fn pick_np(int np)
+{
+    return np == 1 ? eval_graph_kernel<1, REPAIR, TP> : np == 2 ? eval_graph_kernel<2, REPAIR, TP> : eval_graph_kernel<3, REPAIR, TP>;
+}
+
+static graph_fn pick_graph(const KParams &kp)
+{
+    if (kp.space == kSampledRepair) return kp.tp ? pick_np<true, true>(kp.graph_np) : pick_np<true, false>(kp.graph_np);
+    return kp.tp ? pick_np<false, true>(kp.graph_np) : pick_np<false, false>(kp.graph_np);
+}
+
+const void *graph_kernel(const KParams &kp) { return (const void *)pick_graph(kp); }
+
+int launch_graph(const KParams &kp, uint64_t first, uint64_t count, int blocks, void *recs, int32_t *code, int32_t *peak, void *ws,
+                 uint32_t *slots, void *stream)
+{
+    DevResult *res = (DevResult *)((char *)ws + kWsResultOff);
+    hipLaunchKernelGGL(pick_graph(kp), dim3(blocks), dim3(kWave), kp.graph_lds, (hipStream_t)stream, (const KParams *)((char *)ws + kWsParamsOff),
+                       (const GraphTab *)((char *)ws + kWsGraphOff), first, count, (BlockRec *)recs, code, peak,
+                       (uint64_t *)((char *)ws + kWsListOff), &res->defer_count, kWsListCap, &res->overflow, slots);
+    return (int)hipGetLastError();
+}
+
+}  // namespace tessel

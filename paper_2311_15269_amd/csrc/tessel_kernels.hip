@@ -11,7 +11,8 @@
 //            flight at the window boundary); its growth rate is the maximum cycle ratio
 //   argmin   (period, index) lexicographic, lane -> wave -> block record -> grid merge
 //
-// Two kernels compute the same thing:
+// Three kernels compute the same thing, the third in tessel_graph.hip (what the fast kernel does not take, within its
+// tables):
 //   eval_kernel       general: multi-device blocks, cyclic device scan, 16-bit program in LDS,
 //                     Karp's formula over V+1 sweeps; also decodes the best candidate
 //   eval_fast_kernel  single-device blocks: bit-mask build, program words in VGPRs, eigenvector
@@ -26,23 +27,9 @@
 #include <algorithm>
 
 #include "tessel_device.h"
+#include "tessel_common.h"
 
 namespace tessel {
-
-
-struct BlockRec {
-    int32_t  period;
-    uint32_t n_retried;          // candidates whose first sweeps found no eigenvector (they got more in the same launch)
-    uint64_t index;
-    uint32_t n_status[kNumStatus];
-    uint32_t n_evaluated;
-    uint32_t n_sweeps;           // window sweeps spent on period computations
-    uint32_t n_blocks;           // blocks placed by the build (fast kernel)
-    uint32_t pad;
-};
-
-constexpr uint32_t kDrawLeadBase = 0u;
-constexpr uint32_t kDrawOrdBase = 128u;
 
 // ------------------------------------------------------------------ 4-bit counters per type
 // next micro-batch index of every block type: lead + occurrences placed, 4 bits each
@@ -96,8 +83,6 @@ struct MuWide {
     __device__ __forceinline__ void inc(uint32_t g) { add(g, 1ull << ((g & 7u) * 8u)); }
     static constexpr int kTypeBits = 6;          // of a program entry
 };
-
-__device__ __forceinline__ uint32_t byte_of(uint32_t packed, uint32_t y) { return (packed >> (8u * y)) & 0xFFu; }
 
 // entry y of eight: a select tree, so that the table comes through scalar loads
 template <class T>
@@ -838,11 +823,6 @@ __device__ __forceinline__ int evaluate_dag(const KParams &P, const DagTables &T
     return kOk;
 }
 
-__device__ __forceinline__ bool key_less(int pa, uint64_t ia, int pb, uint64_t ib)
-{
-    return pa < pb || (pa == pb && ia < ib);
-}
-
 // ==================================================================== fast path
 // Single-device blocks only.  Block types are addressed by their code c = device*4 + symbol, so
 // that bit c of a 32-bit mask means "type c": R = types whose next occurrence may be placed now
@@ -919,29 +899,6 @@ struct FastConst {
     uint32_t tpg[kMaxD];
 };
 
-__device__ __forceinline__ uint32_t bfi(uint32_t sel, uint32_t a, uint32_t b) { return (sel & a) | (~sel & b); }
-
-// position of the lowest set bit; all ones for 0, which "& 28", shift counts and bit-field offsets (all of them use the
-// low five bits) read as 31: no guard bit has to be set first
-__device__ __forceinline__ uint32_t low_bit(uint32_t x)
-{
-    uint32_t r;
-    asm("v_ffbl_b32 %0, %1" : "=v"(r) : "v"(x));
-    return r;
-}
-
-// a * b + c for a, b below 2^24, low 32 bits: the full-rate 24-bit multiply-add (b uniform)
-__device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c)
-{
-    uint32_t r;
-    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
-    return r;
-}
-
-// keeps a value in a VGPR at this point, so that the loads above it are issued together instead of
-// being sunk into later branches
-#define TESSEL_PIN(x) asm volatile("" : "+v"(x))
-
 // One block of the window: s = max(device free, previous block of the micro-batch); both become s + t.  The
 // micro-batch it handles is the device's counter of its type in `cnt`, the counter word as it was before the
 // caller's atomic incremented it (the caller may have the next node's atomic in flight already).
@@ -974,17 +931,6 @@ __device__ __forceinline__ void sweep_node_group(const FastLds &L, const uint4 t
     for (int dd = 0; dd < DM; dd++)
         if (dd < D && ((G >> (4 * dd)) & 15u)) L.dfree[dd * kWave + lane] = en;
     *tk = en;
-}
-
-// LDS accesses by byte address: address arithmetic stays integer arithmetic, and a constant added to an
-// address goes into the instruction's offset field.
-typedef __attribute__((address_space(3))) uint32_t lds_word;
-__device__ __forceinline__ uint32_t lds_address(const void *p) { return (uint32_t)(uintptr_t)(const lds_word *)p; }
-__device__ __forceinline__ uint32_t lds_load(uint32_t a) { return *(const lds_word *)(uintptr_t)a; }
-__device__ __forceinline__ void lds_store(uint32_t a, uint32_t v) { *(lds_word *)(uintptr_t)a = v; }
-__device__ __forceinline__ uint32_t lds_fetch_add(uint32_t a, uint32_t v)
-{
-    return __hip_atomic_fetch_add((lds_word *)(uintptr_t)a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // a lane's device record: four words at a stride of 64 words (two two-address accesses)
@@ -1184,17 +1130,6 @@ __device__ __forceinline__ uint32_t even_bits(uint64_t x)
     x = (x | (x >> 8)) & 0x0000FFFF0000FFFFull;
     x = (x | (x >> 16)) & 0x00000000FFFFFFFFull;
     return (uint32_t)x;
-}
-
-// even bits of a 32-bit word, compacted (bit 2p -> bit p)
-__device__ __forceinline__ uint32_t even_bits32(uint32_t x)
-{
-    x &= 0x55555555u;
-    x = (x | (x >> 1)) & 0x33333333u;
-    x = (x | (x >> 2)) & 0x0F0F0F0Fu;
-    x = (x | (x >> 4)) & 0x00FF00FFu;
-    x = (x | (x >> 8)) & 0x0000FFFFu;
-    return x;
 }
 
 // MODE: 0 exhaustive spaces, 1 sampled without repair, 2 sampled with repair.
@@ -2082,16 +2017,16 @@ LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks)
     LaunchShape s;
     s.threads = kWave;
     fast_fn ff = pick_fast(kp);
-    s.lds_bytes = ff ? fast_lds_bytes(kp) : general_lds_bytes(kp);
+    s.lds_bytes = ff ? fast_lds_bytes(kp) : kp.graph_ok ? kp.graph_lds : general_lds_bytes(kp);
     // resident workgroups per CU as the runtime computes them from LDS and registers
     int per_cu = 0;
-    const void *fn = ff ? (const void *)ff : (const void *)pick_kernel(kp);
+    const void *fn = ff ? (const void *)ff : kp.graph_ok ? graph_kernel(kp) : (const void *)pick_kernel(kp);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, s.lds_bytes) != hipSuccess || per_cu < 1) {
         (void)hipGetLastError();
         per_cu = (int)((160 * 1024) / ((s.lds_bytes + 511) / 512 * 512));
     }
     if (per_cu > 16) per_cu = 16;
-    if (far_mode(kp) == 2 && per_cu > 4) per_cu = 4;                 // (keeps the state regions of a launch small)
+    if (!kp.graph_ok && far_mode(kp) == 2 && per_cu > 4) per_cu = 4;                 // (keeps the state regions of a launch small)
     if (const char *env = getenv("TESSEL_BLOCKS_PER_CU")) {        // tuning knob: fewer resident workgroups per CU
         int want = atoi(env);
         if (want >= 1 && want < per_cu) per_cu = want;
@@ -2133,17 +2068,26 @@ static size_t ring_offset(int blocks, int num_cus)
     return (kWsBlockRecOff + (eval > comp ? eval : comp) + 256 + 255) & ~(size_t)255;
 }
 
+// what a workgroup of the scoring kernel owns behind the records: queues of the fast kernel, slots of the graph kernel, or
+// state and program of the general one
+static size_t block_bytes(const KParams &kp)
+{
+    return pick_fast(kp) ? (size_t)3 * ring_words(kp) * 4 : kp.graph_ok ? (size_t)kp.graph_slot_words * kGraphSlots * 4 : far_bytes(kp);
+}
+
 size_t eval_workspace_bytes(const KParams &kp, int num_cus, int max_blocks)
 {
     const LaunchShape s = eval_launch_shape(kp, num_cus, max_blocks);
-    return ring_offset(s.blocks, num_cus) + (pick_fast(kp) ? (size_t)s.blocks * 3 * ring_words(kp) * 4 : (size_t)s.blocks * far_bytes(kp));
+    // (behind the slots of the graph kernel what the general kernel needs for the candidates left to it)
+    return ring_offset(s.blocks, num_cus) + (size_t)s.blocks * block_bytes(kp) + (kp.graph_ok ? (size_t)kDeferBlocks * far_bytes(kp) : 0);
 }
 
 // where the state regions of the general kernel's workgroups start (wide problems whose state does not fit the LDS)
 static uint32_t *far_base(const KParams &kp, void *ws, int num_cus, int max_blocks)
 {
     if (!far_mode(kp)) return nullptr;
-    return (uint32_t *)((char *)ws + ring_offset(eval_launch_shape(kp, num_cus, max_blocks).blocks, num_cus));
+    const int blocks = eval_launch_shape(kp, num_cus, max_blocks).blocks;
+    return (uint32_t *)((char *)ws + ring_offset(blocks, num_cus) + (kp.graph_ok ? (size_t)blocks * block_bytes(kp) : 0));
 }
 
 static int launch_general(const KParams &kp, const KParams *kp_dev, uint64_t first, uint64_t count, int blocks, BlockRec *recs,
@@ -2176,6 +2120,15 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
     const int blocks = need < (uint64_t)s.blocks ? (int)need : s.blocks;
     if (blocks < 1) return 0;
     fast_fn ff = general ? nullptr : pick_fast(kp);
+    if (!ff && kp.graph_ok && !general) {
+        // (every problem its tables hold: on 24 blocks of three devices 2.4 times the general kernel's rate, on 96 to 288
+        // blocks 23 to 53 times)
+        int rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, (uint32_t *)((char *)ws + ring_offset(s.blocks, num_cus)), st);
+        if (rc) return -rc;
+        rc = launch_general(kp, kp_dev, first, count, kDeferBlocks, recs ? recs + blocks : nullptr, code, peak, nullptr, list,
+                            &res->defer_count, far_base(kp, ws, num_cus, max_blocks), st);
+        return rc ? -rc : blocks + kDeferBlocks;
+    }
     if (!ff) {
         int rc = launch_general(kp, kp_dev, first, count, blocks, recs, code, peak, nullptr, nullptr, nullptr,
                                 far_base(kp, ws, num_cus, max_blocks), st);
@@ -2277,8 +2230,8 @@ int scratch_workspace(void **ptr, size_t *bytes)
 // the largest grid of the scoring kernels whose records and queues fit `bytes`; 0: not even one workgroup
 int eval_blocks_that_fit(const KParams &kp, int num_cus, size_t bytes)
 {
-    const size_t per_block = sizeof(BlockRec) + (pick_fast(kp) ? (size_t)3 * ring_words(kp) * 4 : far_bytes(kp));
-    const size_t fixed = ring_offset(0, num_cus) + 512;
+    const size_t per_block = sizeof(BlockRec) + block_bytes(kp);
+    const size_t fixed = ring_offset(0, num_cus) + 512 + (kp.graph_ok ? (size_t)kDeferBlocks * far_bytes(kp) : 0);
     if (bytes < fixed + per_block) return 0;
     int blocks = (int)std::min<size_t>((bytes - fixed) / per_block, (size_t)num_cus * 16);
     while (blocks > 0 && eval_workspace_bytes(kp, num_cus, blocks) > bytes) blocks--;

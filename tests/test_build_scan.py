@@ -18,6 +18,13 @@ def test_a_register_offset_is_reported():
     assert len(misaligned_scalar_loads("\ts_load_dword s2, s[4:5], s7\n")) == 1
 
 
+def test_a_register_offset_that_is_a_shifted_index_passes():
+    assert misaligned_scalar_loads("\ts_lshl_b32 s7, s3, 2\n\ts_load_dword s2, s[4:5], s7 offset:0x74\n") == []
+    assert len(misaligned_scalar_loads("\ts_lshl_b32 s7, s3, 1\n\ts_load_dword s2, s[4:5], s7 offset:0x74\n")) == 1
+    assert len(misaligned_scalar_loads("\ts_lshl_b32 s7, s3, 2\n\ts_add_u32 s4, s4, s9\n\ts_mul_i32 s9, s1, 3\n"
+                                       "\ts_add_u32 s4, s8, s9\n\ts_load_dword s2, s[4:5], s7\n")) == 1
+
+
 def test_word_indices_and_whole_pointers_pass():
     asm = """
 .LBB0_1:
