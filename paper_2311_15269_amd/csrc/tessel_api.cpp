@@ -39,9 +39,7 @@ struct tessel_problem {
     bool ws_ready = false;
     hipStream_t stream = nullptr;
     int last_hip = 0;
-    bool have_detail = false;
     bool force_general = false;         // TESSEL_FORCE_GENERAL=1: score with the general kernel only
-    uint64_t detail_index = 0;
     DevDetail detail;
     DevResult result;
     // index ranges scored since the last reset (adjacent ones merged), and whether launches are cut into the
@@ -728,7 +726,7 @@ static int bind_workspace(tessel_problem *p, void *ws, size_t bytes, hipStream_t
     }
     int e = launch_reset(ws, st);
     if (e) return hip_fail(p, e);
-    p->ws = ws; p->ws_ready = true; p->have_detail = false; p->max_blocks = max_blocks;
+    p->ws = ws; p->ws_ready = true; p->max_blocks = max_blocks;
     p->comp_ready = false;              // the completion parameters lived in the workspace bound before
     p->ranges.clear();
     p->best_dirty = true;
@@ -747,7 +745,6 @@ extern "C" int tessel_eval_candidates(tessel_problem *p, uint64_t first, uint64_
     rc = bind_workspace(p, workspace_dev, workspace_bytes, st);
     if (rc) return rc;
     p->stream = st;
-    p->have_detail = false;
     if (count == 0) return TESSEL_OK;
     p->best_dirty = true;
     if (!p->ranges.empty() && p->ranges.back().first + p->ranges.back().second == first) p->ranges.back().second += count;
@@ -776,7 +773,6 @@ extern "C" int tessel_eval_candidates_noalloc(tessel_problem *p, uint64_t first,
     rc = bind_workspace(p, ws, bytes, st, blocks);
     if (rc) return rc;
     p->stream = st;
-    p->have_detail = false;
     if (count == 0) return TESSEL_OK;
     p->best_dirty = true;
     if (!p->ranges.empty() && p->ranges.back().first + p->ranges.back().second == first) p->ranges.back().second += count;
@@ -813,7 +809,6 @@ extern "C" int tessel_alu_probe(int blocks, int rounds, uint32_t *out_dev, size_
 extern "C" int tessel_reset(tessel_problem *p)
 {
     if (!p) return TESSEL_E_INVALID_ARG;
-    p->have_detail = false;
     p->result.period = INT_MAX;
     p->ranges.clear();
     p->best_dirty = true;
@@ -822,14 +817,33 @@ extern "C" int tessel_reset(tessel_problem *p)
     return e ? hip_fail(p, e) : TESSEL_OK;
 }
 
+// One launch and one copy: the candidate of the running best is decoded on the device from the record there, and record
+// and decoded candidate, which lie in a row, come back together.
+static int read_back(tessel_problem *p)
+{
+    int le = launch_detail(p->ws, p->stream);
+    if (le) return hip_fail(p, le);
+    struct { unsigned char bytes[kWsDetailOff]; DevDetail detail; } both;
+    static_assert(offsetof(decltype(both), detail) == kWsDetailOff && kWsResultOff == 0, "result and detail are copied in one piece");
+    hipError_t e = hipMemcpyAsync(&both, p->ws, sizeof both, hipMemcpyDeviceToHost, p->stream);
+    if (e != hipSuccess) return hip_fail(p, (int)e);
+    e = hipStreamSynchronize(p->stream);
+    if (e != hipSuccess) return hip_fail(p, (int)e);
+    memcpy(&p->result, both.bytes, sizeof(DevResult));
+    p->detail = both.detail;
+    return TESSEL_OK;
+}
+
 static int fetch_best(tessel_problem *p)
 {
     if (!p->ws || !p->ws_ready) { memset(&p->result, 0, sizeof p->result); p->result.period = INT_MAX; return TESSEL_OK; }
     if (!owns_workspace(p)) return TESSEL_E_WORKSPACE;       // another handle has bound the buffer since: the running best is gone
-    hipError_t e = hipStreamSynchronize(p->stream);
-    if (e != hipSuccess) return hip_fail(p, (int)e);
-    e = hipMemcpy(&p->result, (char *)p->ws + kWsResultOff, sizeof(DevResult), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(p, (int)e);
+    if (!p->best_dirty) {                                    // nothing scored since the best was read back
+        hipError_t e = hipStreamSynchronize(p->stream);
+        return e != hipSuccess ? hip_fail(p, (int)e) : TESSEL_OK;
+    }
+    int rc = read_back(p);
+    if (rc) return rc;
     if (p->result.overflow && !p->safe_pieces) {
         // some launch left more candidates unfinished than its list holds, so the running best is incomplete:
         // score every range again, from now on in pieces small enough for the lists
@@ -840,22 +854,10 @@ static int fetch_best(tessel_problem *p)
             le = launch_eval(p->kp, r.first, r.second, p->ws, p->num_cus, p->max_blocks, p->stream, kSafePerLaunch);
             if (le) return hip_fail(p, le);
         }
-        e = hipStreamSynchronize(p->stream);
-        if (e != hipSuccess) return hip_fail(p, (int)e);
-        e = hipMemcpy(&p->result, (char *)p->ws + kWsResultOff, sizeof(DevResult), hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return hip_fail(p, (int)e);
+        rc = read_back(p);
+        if (rc) return rc;
     }
-    if (p->result.period == INT_MAX) { p->have_detail = false; return TESSEL_OK; }
-    if (p->have_detail && p->detail_index == p->result.index) { p->best_dirty = false; return TESSEL_OK; }
-    // decode and re-score the best candidate on the GPU for its peaks and orders
-    int le = launch_detail(p->kp, p->result.index, p->ws, p->num_cus, p->max_blocks, p->stream);
-    if (le) return hip_fail(p, le);
-    e = hipStreamSynchronize(p->stream);
-    if (e != hipSuccess) return hip_fail(p, (int)e);
-    e = hipMemcpy(&p->detail, (char *)p->ws + kWsDetailOff, sizeof(DevDetail), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(p, (int)e);
-    p->have_detail = true; p->detail_index = p->result.index;
-    p->best_dirty = false;
+    if (p->result.period != INT_MAX) p->best_dirty = false;
     return TESSEL_OK;
 }
 

@@ -168,7 +168,8 @@ struct DevResult {
 
 // Decoded best candidate, written by the detail kernel.
 struct DevDetail {
-    int32_t status, period;
+    int32_t status, period;      // status -1: nothing decoded since the search began
+    uint64_t index;
     int32_t peak[kMaxDW];
     int32_t leads[kMaxKW];
     int32_t order_len[kMaxDW];
@@ -296,6 +297,8 @@ struct LaunchShape { int blocks, threads; size_t lds_bytes; };
 const void *graph_kernel(const KParams &kp);
 int launch_graph(const KParams &kp, uint64_t first, uint64_t count, int blocks, void *recs, int32_t *code, int32_t *peak, void *ws,
                  uint32_t *slots, void *stream);
+// tessel_detail.hip: decodes the candidate of the running best (if there is one) into the workspace's DevDetail
+int launch_detail(void *ws, void *stream);
 // kernels.hip
 // max_blocks: 0, or the most workgroups the workspace has queues for
 LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks);
@@ -307,7 +310,6 @@ int launch_score(const KParams &kp, uint64_t first, uint64_t count, int32_t *cod
 constexpr size_t kScratchBytes = (size_t)24 << 20;
 int scratch_workspace(void **ptr, size_t *bytes);
 int eval_blocks_that_fit(const KParams &kp, int num_cus, size_t bytes);
-int launch_detail(const KParams &kp, uint64_t index, void *ws, int num_cus, int max_blocks, void *stream);
 int launch_reset(void *ws, void *stream);
 // completion search: S = state words per lane; returns 0 or a HIP error (negative: LDS need exceeds the device's)
 size_t completion_lds_bytes(const CompParams &cp, const CompMatrix &cm);

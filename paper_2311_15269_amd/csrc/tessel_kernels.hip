@@ -14,7 +14,7 @@
 // Three kernels compute the same thing, the third in tessel_graph.hip (what the fast kernel does not take, within its
 // tables):
 //   eval_kernel       general: multi-device blocks, cyclic device scan, 16-bit program in LDS,
-//                     Karp's formula over V+1 sweeps; also decodes the best candidate
+//                     Karp's formula over V+1 sweeps
 //   eval_fast_kernel  single-device blocks: bit-mask build, program words in VGPRs, eigenvector
 //                     test after every sweep; what it cannot finish goes to the general kernel
 //
@@ -415,7 +415,7 @@ __device__ __forceinline__ int decode_candidate(const KParams &P, uint64_t idx, 
 // ------------------------------------------------------------------ one candidate (general path)
 template <int DM, int VM>
 __device__ __forceinline__ int evaluate(const KParams &P, uint64_t idx, uint16_t *prog, uint32_t *state, const int32_t *t_tab,
-                        const uint32_t *mask_tab, int &period, int (&peak)[DM], DevDetail *detail)
+                        const uint32_t *mask_tab, int &period, int (&peak)[DM])
 {
     uint64_t rem[DM];
     int remlen[DM];
@@ -426,11 +426,6 @@ __device__ __forceinline__ int evaluate(const KParams &P, uint64_t idx, uint16_t
     {
         int st = decode_candidate<DM>(P, idx, rem, remlen, mu);
         if (st != kOk) return st;
-    }
-
-    if (detail) {
-        for (int g = 0; g < P.K; g++) detail->leads[g] = (int)mu.get((uint32_t)g);
-        for (int d = 0; d < kMaxDW; d++) detail->order_len[d] = 0;
     }
 
     // ---------------- memory at the window entry: blocks that ran before it (type i has
@@ -474,7 +469,6 @@ __device__ __forceinline__ int evaluate(const KParams &P, uint64_t idx, uint16_t
             remlen[dd]--;
             memcur[dd] += m;
             peak[dd] = max(peak[dd], memcur[dd]);
-            if (detail) detail->orders[dd][detail->order_len[dd]++] = (int)g;
         }
     };
 
@@ -689,7 +683,7 @@ __device__ __forceinline__ int least_period_dag(const KParams &P, const DagTable
 __device__ __forceinline__ uint32_t even_bits(uint64_t x);
 template <int DM, class CNT>
 __device__ __forceinline__ int evaluate_dag(const KParams &P, const DagTables &Tb, uint64_t idx, uint16_t *prog, uint32_t *state,
-                                            int &period, int (&peak)[DM], DevDetail *detail)
+                                            int &period, int (&peak)[DM])
 {
     uint32_t p0[DM], p1[DM], p2[DM], alive[DM];
     CNT mu;
@@ -708,10 +702,6 @@ __device__ __forceinline__ int evaluate_dag(const KParams &P, const DagTables &T
         }
     }
     const CNT lead = mu;
-    if (detail) {
-        for (int g = 0; g < P.K; g++) detail->leads[g] = (int)mu.get((uint32_t)g);
-        for (int d = 0; d < kMaxDW; d++) detail->order_len[d] = 0;
-    }
     auto type_at = [&](int d, uint32_t y) -> uint32_t { return y < 4u ? byte_of(P.type_of[d], y) : byte_of(P.type_of_hi[d], y - 4u); };
     int memcur[DM];
 #pragma unroll
@@ -759,7 +749,6 @@ __device__ __forceinline__ int evaluate_dag(const KParams &P, const DagTables &T
             alive[dd] &= ~(1u << pos);
             memcur[dd] += m;
             peak[dd] = max(peak[dd], memcur[dd]);
-            if (detail) detail->orders[dd][detail->order_len[dd]++] = (int)g;
         }
     };
     bool deadlock = false;
@@ -1743,8 +1732,7 @@ __host__ __device__ inline size_t far_words(const KParams &P, int where)
 template <int DM, int VM>
 __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__ Pp, uint64_t first, uint64_t count,
                                                      BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
-                                                     int32_t *__restrict__ peak_out, DevDetail *__restrict__ detail,
-                                                     const uint64_t *__restrict__ list, const uint32_t *__restrict__ list_count,
+                                                     int32_t *__restrict__ peak_out, const uint64_t *__restrict__ list, const uint32_t *__restrict__ list_count,
                                                      uint32_t *far, int where)
 {
     const KParams &P = *Pp;
@@ -1788,9 +1776,9 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
         const uint64_t k = idx - first;
         int period, peak[DM];
         int status;
-        if constexpr (wide) status = evaluate_dag<DM, MuWide>(P, Tb, idx, prog, state, period, peak, detail);
-        else status = P.dag ? evaluate_dag<DM, Mu>(P, Tb, idx, prog, state, period, peak, detail)
-                            : evaluate<DM, VM>(P, idx, prog, state, t_tab, mask_tab, period, peak, detail);
+        if constexpr (wide) status = evaluate_dag<DM, MuWide>(P, Tb, idx, prog, state, period, peak);
+        else status = P.dag ? evaluate_dag<DM, Mu>(P, Tb, idx, prog, state, period, peak)
+                            : evaluate<DM, VM>(P, idx, prog, state, t_tab, mask_tab, period, peak);
         nev++;
 #pragma unroll
         for (int s = 0; s < kNumStatus; s++) cnt[s] += status == s;
@@ -1803,12 +1791,6 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
         }
         if (code_out) code_out[k] = status == kOk ? period : -status;
         if (peak_out) peak_out[k] = pk;
-        if (detail) {
-            detail->status = status; detail->period = period;
-            for (int d = 0; d < kMaxDW; d++) detail->peak[d] = 0;
-#pragma unroll
-            for (int d = 0; d < DM; d++) if (d < P.D) detail->peak[d] = peak[d];
-        }
     }
     if (!recs) return;
     // wave argmin over the total order (period, index); sums of the counters
@@ -1834,7 +1816,7 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
 // The two instantiations for problems beyond the fast kernel's limits (16 and 32 devices) take as long to compile as
 // everything else in this file: tessel_wide.hip includes this file up to here and holds them, so that the two halves
 // build side by side.
-#define TESSEL_EVAL_KERNEL_ARGS const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, DevDetail *, const uint64_t *, const uint32_t *, uint32_t *, int
+#define TESSEL_EVAL_KERNEL_ARGS const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *, uint32_t *, int
 #ifdef TESSEL_WIDE_INSTANTIATIONS
 template __global__ void eval_kernel<16, 1>(TESSEL_EVAL_KERNEL_ARGS);
 template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
@@ -1842,55 +1824,60 @@ template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
 extern template __global__ void eval_kernel<16, 1>(TESSEL_EVAL_KERNEL_ARGS);
 extern template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
 
-// merges the block records of one launch into the running best (one wave)
-__global__ __launch_bounds__(kWave) void merge_kernel(const BlockRec *recs, int nrecs, DevResult *res)
+// Merges the block records of one launch into the running best: one workgroup, a record per thread and round, waves
+// first.  Bound by the latency of the record loads: 4,160 records took one wave 14.6 us (65 dependent rounds), eight
+// waves take 9 to 10.
+constexpr int kMergeThreads = 512;
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__restrict__ recs, int nrecs, DevResult *__restrict__ res)
 {
-    const int lane = threadIdx.x;
-    int best = INT_MAX;
-    uint64_t best_idx = 0, nev = 0, nsw = 0, nbl = 0, cnt[kNumStatus];
-    uint32_t nre = 0;
+    struct Sum { int best; uint32_t nre; uint64_t best_idx, nev, nsw, nbl, cnt[kNumStatus]; };
+    __shared__ Sum part[kMergeThreads / kWave];
+    Sum a;
+    a.best = INT_MAX; a.nre = 0; a.best_idx = 0; a.nev = a.nsw = a.nbl = 0;
 #pragma unroll
-    for (int s = 0; s < kNumStatus; s++) cnt[s] = 0;
-    for (int k = lane; k < nrecs; k += kWave) {
-        BlockRec r = recs[k];
-        nre += r.n_retried;
-        if (key_less(r.period, r.index, best, best_idx)) { best = r.period; best_idx = r.index; }
-        nev += r.n_evaluated;
-        nsw += r.n_sweeps;
-        nbl += r.n_blocks;
+    for (int s = 0; s < kNumStatus; s++) a.cnt[s] = 0;
+    for (int k = threadIdx.x; k < nrecs; k += kMergeThreads) {
+        const BlockRec r = recs[k];
+        if (key_less(r.period, r.index, a.best, a.best_idx)) { a.best = r.period; a.best_idx = r.index; }
+        a.nre += r.n_retried;
+        a.nev += r.n_evaluated;
+        a.nsw += r.n_sweeps;
+        a.nbl += r.n_blocks;
 #pragma unroll
-        for (int s = 0; s < kNumStatus; s++) cnt[s] += r.n_status[s];
+        for (int s = 0; s < kNumStatus; s++) a.cnt[s] += r.n_status[s];
     }
+    auto from = [](uint64_t v, int off) -> uint64_t {
+        const uint32_t lo = __shfl_xor((uint32_t)v, off), hi = __shfl_xor((uint32_t)(v >> 32), off);
+        return ((uint64_t)hi << 32) | lo;
+    };
+    auto fold = [&](int width) {
+        for (int off = width / 2; off >= 1; off >>= 1) {
+            const int op = __shfl_xor(a.best, off);
+            const uint64_t oi = from(a.best_idx, off);
+            if (key_less(op, oi, a.best, a.best_idx)) { a.best = op; a.best_idx = oi; }
+            a.nre += __shfl_xor(a.nre, off);
+            a.nev += from(a.nev, off); a.nsw += from(a.nsw, off); a.nbl += from(a.nbl, off);
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        int op = __shfl_xor(best, off);
-        uint32_t ilo = __shfl_xor((uint32_t)best_idx, off), ihi = __shfl_xor((uint32_t)(best_idx >> 32), off);
-        uint64_t oi = ((uint64_t)ihi << 32) | ilo;
-        if (key_less(op, oi, best, best_idx)) { best = op; best_idx = oi; }
-        uint32_t lo = __shfl_xor((uint32_t)nev, off), hi = __shfl_xor((uint32_t)(nev >> 32), off);
-        nev += ((uint64_t)hi << 32) | lo;
-        uint32_t slo = __shfl_xor((uint32_t)nsw, off), shi = __shfl_xor((uint32_t)(nsw >> 32), off);
-        nsw += ((uint64_t)shi << 32) | slo;
-        uint32_t blo = __shfl_xor((uint32_t)nbl, off), bhi = __shfl_xor((uint32_t)(nbl >> 32), off);
-        nbl += ((uint64_t)bhi << 32) | blo;
-        nre += __shfl_xor(nre, off);
-#pragma unroll
-        for (int s = 0; s < kNumStatus; s++) {
-            uint32_t l2 = __shfl_xor((uint32_t)cnt[s], off), h2 = __shfl_xor((uint32_t)(cnt[s] >> 32), off);
-            cnt[s] += ((uint64_t)h2 << 32) | l2;
+            for (int s = 0; s < kNumStatus; s++) a.cnt[s] += from(a.cnt[s], off);
         }
-    }
-    if (lane == 0) {
-        if (key_less(best, best_idx, res->period, res->index)) { res->period = best; res->index = best_idx; }
+    };
+    fold(kWave);
+    if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = a;
+    __syncthreads();
+    if (threadIdx.x >= kWave) return;
+    a = part[threadIdx.x & (kMergeThreads / kWave - 1)];
+    fold(kMergeThreads / kWave);
+    if (threadIdx.x == 0) {
+        if (key_less(a.best, a.best_idx, res->period, res->index)) { res->period = a.best; res->index = a.best_idx; }
         // the pass over the list of deferred candidates has run (stream order)
-        res->n_retried += nre;
+        res->n_retried += a.nre;
         res->n_deferred += min(res->defer_count, kWsListCap);
         res->defer_count = 0;
-        res->n_evaluated += nev;
-        res->n_sweeps += nsw;
-        res->n_blocks += nbl;
+        res->n_evaluated += a.nev;
+        res->n_sweeps += a.nsw;
+        res->n_blocks += a.nbl;
 #pragma unroll
-        for (int s = 0; s < kNumStatus; s++) res->n_status[s] += cnt[s];
+        for (int s = 0; s < kNumStatus; s++) res->n_status[s] += a.cnt[s];
     }
 }
 
@@ -1900,9 +1887,10 @@ __global__ void clear_defer_kernel(DevResult *res)
     if (threadIdx.x == 0 && blockIdx.x == 0) res->defer_count = 0;
 }
 
-__global__ void reset_kernel(DevResult *res)
+__global__ void reset_kernel(DevResult *res, DevDetail *detail)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
+        detail->status = -1;                     // no candidate decoded yet
         res->period = INT_MAX; res->pad = 0; res->index = ~0ull; res->n_evaluated = 0; res->n_sweeps = 0; res->n_blocks = 0;
         res->n_retried = 0; res->n_deferred = 0; res->overflow = 0; res->defer_count = 0;
         for (int s = 0; s < kNumStatus; s++) res->n_status[s] = 0;
@@ -1910,8 +1898,8 @@ __global__ void reset_kernel(DevResult *res)
 }
 
 // ------------------------------------------------------------------ launchers
-typedef void (*eval_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, DevDetail *, const uint64_t *,
-                        const uint32_t *, uint32_t *, int);
+typedef void (*eval_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *,
+                        uint32_t *, int);
 typedef void (*fast_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, int, int, uint64_t *, uint32_t *,
                         uint32_t, uint32_t *, uint32_t *, uint32_t, int);
 
@@ -2091,7 +2079,7 @@ static uint32_t *far_base(const KParams &kp, void *ws, int num_cus, int max_bloc
 }
 
 static int launch_general(const KParams &kp, const KParams *kp_dev, uint64_t first, uint64_t count, int blocks, BlockRec *recs,
-                          int32_t *code, int32_t *peak, DevDetail *detail, const uint64_t *list, const uint32_t *list_count,
+                          int32_t *code, int32_t *peak, const uint64_t *list, const uint32_t *list_count,
                           uint32_t *far, hipStream_t st)
 {
     const int where = far_mode(kp);
@@ -2102,7 +2090,7 @@ static int launch_general(const KParams &kp, const KParams *kp_dev, uint64_t fir
         hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, detail, list, list_count, far, where);
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, list, list_count, far, where);
     return (int)hipGetLastError();
 }
 
@@ -2125,12 +2113,12 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
         // blocks 23 to 53 times)
         int rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, (uint32_t *)((char *)ws + ring_offset(s.blocks, num_cus)), st);
         if (rc) return -rc;
-        rc = launch_general(kp, kp_dev, first, count, kDeferBlocks, recs ? recs + blocks : nullptr, code, peak, nullptr, list,
+        rc = launch_general(kp, kp_dev, first, count, kDeferBlocks, recs ? recs + blocks : nullptr, code, peak, list,
                             &res->defer_count, far_base(kp, ws, num_cus, max_blocks), st);
         return rc ? -rc : blocks + kDeferBlocks;
     }
     if (!ff) {
-        int rc = launch_general(kp, kp_dev, first, count, blocks, recs, code, peak, nullptr, nullptr, nullptr,
+        int rc = launch_general(kp, kp_dev, first, count, blocks, recs, code, peak, nullptr, nullptr,
                                 far_base(kp, ws, num_cus, max_blocks), st);
         return rc ? -rc : blocks;
     }
@@ -2140,7 +2128,7 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
                        list, &res->defer_count, kWsListCap, &res->overflow, ring, ring_words(kp), stage_words(kp));
     int rc = (int)hipGetLastError();
     if (rc) return -rc;
-    rc = launch_general(kp, kp_dev, first, count, kDeferBlocks, recs ? recs + blocks : nullptr, code, peak, nullptr, list,
+    rc = launch_general(kp, kp_dev, first, count, kDeferBlocks, recs ? recs + blocks : nullptr, code, peak, list,
                         &res->defer_count, nullptr, st);
     return rc ? -rc : blocks + kDeferBlocks;
 }
@@ -2156,7 +2144,7 @@ int launch_eval(const KParams &kp, uint64_t first, uint64_t count, void *ws, int
         int n = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, recs, nullptr, nullptr, false, st);
         if (n < 0) return -n;
         if (n > 0) {
-            hipLaunchKernelGGL(merge_kernel, dim3(1), dim3(kWave), 0, st, recs, n, res);
+            hipLaunchKernelGGL(merge_kernel, dim3(1), dim3(kMergeThreads), 0, st, recs, n, res);
             int rc = (int)hipGetLastError();
             if (rc) return rc;
         }
@@ -2184,17 +2172,10 @@ int launch_score(const KParams &kp, uint64_t first, uint64_t count, int32_t *cod
     return 0;
 }
 
-int launch_detail(const KParams &kp, uint64_t index, void *ws, int num_cus, int max_blocks, void *stream)
-{
-    int rc = launch_general(kp, (const KParams *)((char *)ws + kWsParamsOff), index, 1, 1, nullptr, nullptr, nullptr,
-                            (DevDetail *)((char *)ws + kWsDetailOff), nullptr, nullptr, far_base(kp, ws, num_cus, max_blocks),
-                            (hipStream_t)stream);
-    return rc;
-}
-
 int launch_reset(void *ws, void *stream)
 {
-    hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, (DevResult *)((char *)ws + kWsResultOff));
+    hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, (DevResult *)((char *)ws + kWsResultOff),
+                       (DevDetail *)((char *)ws + kWsDetailOff));
     return (int)hipGetLastError();
 }
 
