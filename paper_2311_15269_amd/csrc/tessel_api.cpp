@@ -525,6 +525,9 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
             if (multi || multi_next) kp.slow_mask |= grp;
         }
         kp.fast_tp = kp.tp;
+        kp.tp_all = kp.tp;
+        for (int i = 0; i < K; i++)
+            if ((desc->dev_mask[i] & (desc->dev_mask[i] - 1)) && desc->dev_mask[i] != (D < 32 ? (1u << D) - 1u : ~0u)) kp.tp_all = 0;
         // the memory prefix of a device is kept in 8 bits: entry (lead <= N_R-1 each) plus N_R occurrences
         for (int d = 0; d < D; d++) {
             long span = 0;

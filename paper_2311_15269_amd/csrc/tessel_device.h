@@ -118,6 +118,7 @@ struct KParams {
     // blocks on several devices in the fast kernel: such a type has one code on every device it occupies
     int32_t  fast_tp;            // the problem has such blocks (the TP variants of the fast kernel take it)
     int32_t  ntp;                // number of such types
+    int32_t  tp_all;             // each of them sits on every device
     uint32_t tp_group[kMaxD];    // their codes, one mask per type
     uint32_t slow_mask;          // codes of types that sit on several devices or whose consumer does
     uint32_t grp_code[kMaxK];    // by code: all codes of the same type
@@ -218,6 +219,7 @@ struct CompRec { int32_t makespan; int32_t pad; uint64_t ordinal; };
 constexpr size_t kWsResultOff = 0;
 constexpr size_t kWsCompletionOff = 192;       // DevCompletion
 constexpr size_t kWsDetailOff = 256;
+constexpr size_t kWsLeftOff = 7936;            // by program word, how many of the candidates one wave in 16 built first were alive after it
 constexpr size_t kWsParamsOff = 8192;          // KParams of the bound problem
 constexpr size_t kWsTablesOff = 16384;         // lead table, arrangement table
 constexpr size_t kWsTablesMax = 1 << 20;
@@ -244,7 +246,7 @@ static_assert(sizeof(CompParams) <= 1024, "completion parameters must fit their 
 static_assert(sizeof(DevResult) <= kWsCompletionOff && kWsCompletionOff + sizeof(DevCompletion) <= kWsDetailOff, "result records overlap");
 static_assert(sizeof(CompParams) <= 1024 && sizeof(CompMatrix) <= 3072, "completion parameters must fit their workspace slots");
 static_assert(sizeof(KParams) <= kWsTablesOff - kWsParamsOff, "parameter block must fit its workspace slot");
-static_assert(sizeof(DevDetail) <= kWsParamsOff - kWsDetailOff, "detail record must fit its workspace slot");
+static_assert(sizeof(DevDetail) <= kWsLeftOff - kWsDetailOff && kWsLeftOff + kWave * 4 <= kWsParamsOff, "detail record must fit its workspace slot");
 
 // ------------------------------------------------------------------ the graph kernel (tessel_graph.hip)
 // Problems the fast kernel does not take (graphs with fan-in or fan-out, more than 8 devices, 32 types, 4 types on a

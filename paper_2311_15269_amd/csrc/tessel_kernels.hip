@@ -840,7 +840,7 @@ struct FastProgram {
 constexpr int kFastTableWords = 16 * kMaxK;      // uniform tables at the start of the fast kernel's LDS
 constexpr int kSweepTabWord = 12 * kMaxK;        // ... of which the sweeps' three tables by code; a multiple of 64 words, so
                                                  // that one two-address LDS read fetches a code's first and third word
-constexpr int kTpTableWords = 5 * kMaxK;         // the TP variants' own tables behind them
+constexpr int kTpTableWords = 5 * kMaxK + kMaxD; // the TP variants' own tables behind them
 // Everything a lane reads by a run-time index lies word by word: word w of entry i at w * 64 + i words, so that
 // lanes with different entries hit different banks, a lane's words of one entry come with two-address reads
 // (stride 64 words), and an LDS atomic on one word of the records meets no bank twice.
@@ -851,7 +851,7 @@ struct FastLds {
     uint32_t *ch_tab;     // [32]  by code, right behind sw_tab: LDS address of the first token of the code's chain (lane 0)
     uint32_t *in_tab;     // [32]  by code, behind ch_tab: 1 << s | s, s = 16 + 4 * symbol: counter increment and field position
     uint4 *tt_tab;        // [32]  by code, for the sweeps of the TP variants: x: t, y: byte offset of the first token slot of the code's
-                          //       chain, z: byte offset of its device's words, w: bit offset of its micro-batch counter
+                          //       chain, z: byte offset of its device's words, w: bit offset of its micro-batch counter, bit 31: on several devices
     uint32_t *type_tab;   // [4][64], code in the low half of every 64: what placing one block of the type does:
                           //   word 0: added to the last word of its device record: memory delta << 16, one waiting
                           //      micro-batch of the type less, one more for its consumer if that sits on the same device
@@ -865,6 +865,8 @@ struct FastLds {
     uint32_t *vtab;       // [32]  KParams::vtab
     uint32_t *cum_tab, *predbit_tab;   // [32] each: KParams::cum_code, pred_bit
     uint32_t *grp_tab;    // [32]  TP variants: KParams::grp_code
+    uint32_t *tpg_tab;    // [8]   TP variants: KParams::tp_group (read in every build step with a uniform index; an array in
+                          //       registers indexed at run time went to scratch memory)
     uint32_t rec;         // build: LDS address of the records [DM][4][64]: word 0: low plane, 1: high plane,
                           //        2: not-yet-placed mask, 3: micro-batches waiting at the input of the 4 types
                           //        (4 bits each) | memory now (signed) << 16
@@ -883,9 +885,8 @@ struct FastConst {
     int ntd[DM];
     uint32_t mpack[DM];
     // blocks on several devices (TP variants of the kernel only)
-    int ntp;
+    int ntp, tp_all;
     uint32_t slow;
-    uint32_t tpg[kMaxD];
 };
 
 // One block of the window: s = max(device free, previous block of the micro-batch); both become s + t.  The
@@ -909,7 +910,7 @@ __device__ __forceinline__ void sweep_node(const FastLds &L, const uint4 tt, uin
 template <int DM>
 __device__ __forceinline__ void sweep_node_group(const FastLds &L, const uint4 tt, uint32_t cnt, uint32_t lane, uint32_t G, int D)
 {
-    const uint32_t mu = __builtin_amdgcn_ubfe(cnt, tt.w, 4);
+    const uint32_t mu = __builtin_amdgcn_ubfe(cnt, tt.w & 31u, 4);
     uint32_t *tk = (uint32_t *)((char *)L.dfree + (tt.y + lane * 4u + (mu << 8)));
     uint32_t s = *tk;
 #pragma unroll
@@ -1018,13 +1019,42 @@ __device__ __forceinline__ void sweep_fast(const FastConst<DM> &C, const FastLds
     // its counters would leave the token ring
     if (!active) return;
     const uint32_t lane4 = (uint32_t)lane * 4u;
-    if (TP) {
+    if (TP && C.tp_all) {
+        // Every block on several devices sits on all of them: it waits for the latest end so far (one register) and
+        // leaves a floor under all device times (another), instead of a visit to every device.  (36 blocks on 8 devices, all
+        // of 2^24 candidates feasible: 25.8 -> 8.4 ms for the launch, with the tables of the build out of scratch memory.)
+        uint32_t latest = 0, floor_all = 0;
+#pragma unroll
+        for (int d = 0; d < DM; d++) if (d < C.D) latest = max(latest, L.dfree[d * kWave + lane]);
+        const int nwords = (C.total + 5) / 6;
+        for (int wi = 0; wi < nwords; wi++) {
+            uint32_t w = prog.get(wi);
+            const int nj = min(6, C.total - 6 * wi);
+#pragma unroll 1
+            for (int j = 0; j < nj; j++, w >>= 5) {
+                const uint4 tt = L.tt_tab[w & 31u];
+                uint32_t *fr = (uint32_t *)((char *)L.dfree + (tt.z + lane4)), *cp = fr + DM * kWave;
+                const uint32_t cnt = *cp;
+                *cp = cnt + (1u << (tt.w & 31u));
+                const uint32_t mu = __builtin_amdgcn_ubfe(cnt, tt.w & 31u, 4);
+                uint32_t *tk = (uint32_t *)((char *)L.dfree + (tt.y + lane4 + (mu << 8)));
+                const bool all = (int)tt.w < 0;
+                const uint32_t en = max(*tk, all ? latest : max(*fr, floor_all)) + tt.x;
+                *fr = en;
+                *tk = en;
+                latest = max(latest, en);
+                floor_all = all ? en : floor_all;
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < DM; d++) if (d < C.D) L.dfree[d * kWave + lane] = max(L.dfree[d * kWave + lane], floor_all);
+    } else if (TP) {
         for (int k = 0; k < C.total; k++) {
             const uint32_t code = (prog.get(k / 6) >> (5 * (k % 6))) & 31u;
             const uint4 tt = L.tt_tab[code];
             uint32_t *cp = (uint32_t *)((char *)L.dfree + (tt.z + lane4)) + DM * kWave;
             const uint32_t cnt = *cp;
-            *cp = cnt + (1u << tt.w);
+            *cp = cnt + (1u << (tt.w & 31u));
             sweep_node_group<DM>(L, tt, cnt, (uint32_t)lane, L.grp_tab[code], C.D);
         }
     } else {
@@ -1276,7 +1306,7 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
 // Places the blocks of program words [w_from, w_to) (six blocks a word).  `live`: the lane holds a candidate.
 template <int DM, int MODE, bool TP>
 __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM> &C, const FastLds &L, int lane, bool live,
-                                            int w_from, int w_to, FastProgram &prog, BuildState &S)
+                                            int w_from, int w_to, FastProgram &prog, BuildState &S, uint32_t *left_after)
 {
     // With repair every candidate has an executable order (the blocks not yet placed form a DAG, so some type
     // is always runnable): no lane ever stops building, not even one without a candidate of the range (it scores
@@ -1296,7 +1326,10 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
         for (int j = 0; j < nj; j++) {
             uint32_t hm = R & HM;
             if (TP)
-                for (int k = 0; k < C.ntp; k++) hm = (hm & C.tpg[k]) == C.tpg[k] ? hm : hm & ~C.tpg[k];
+                for (int k = 0; k < C.ntp; k++) {
+                    const uint32_t G = L.tpg_tab[k];
+                    hm = (hm & G) == G ? hm : hm & ~G;
+                }
             const uint32_t sel = hm ? hm : (repair ? R : 0u);
             if (!repair && building && sel == 0) { status = kDeadlock; building = false; }
             const uint32_t b = low_bit(sel);
@@ -1395,13 +1428,22 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
         return acc;
     };
     // the program is two register vectors: one loop for each, so that a store never has to choose between them
+    // (`left_after`: how many candidates are still alive goes into the launch's histogram)
+    auto note = [&](int wi) {
+        if (TP && MODE != 0 && left_after && wi + 1 < w_to) {
+            const uint32_t alive = (uint32_t)__builtin_popcountll(__ballot(repair ? worst <= C.M : building));
+            if (lane == 0) __hip_atomic_fetch_add(left_after + wi + 1, alive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
     for (int wi = w_from; wi < min(w_to, 32); wi++) {
         if (!repair && __ballot(building) == 0) break;
         prog.a[wi] = word(wi);
+        note(wi);
     }
     for (int wi = max(w_from, 32); wi < w_to; wi++) {
         if (!repair && __ballot(building) == 0) break;
         prog.b[wi - 32] = word(wi);
+        note(wi);
     }
     S.R = R; S.HM = HM; S.X = X; S.worst = worst; S.status = status;
 }
@@ -1420,13 +1462,15 @@ __device__ __forceinline__ int build_end(const FastConst<DM> &C, const BuildStat
     return worst > C.M ? kMem : kOk;
 }
 
+// (Waves per SIMD: what the registers of the variant allow without spills in the loops; the TP variants with four waves
+// and 24 boundary values, or 8 devices, spilled up to 600 registers.)
 template <int DM, int VM, int MODE, bool TP = false>
-__global__ __launch_bounds__(kWave, MODE ? 4 : 3) void eval_fast_kernel(const KParams *__restrict__ Pp, uint64_t first, uint64_t count,
+__global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3) void eval_fast_kernel(const KParams *__restrict__ Pp, uint64_t first, uint64_t count,
                                                           BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
                                                           int32_t *__restrict__ peak_out, int tries, int retry_tries,
                                                           uint64_t *__restrict__ out_list, uint32_t *__restrict__ out_count,
                                                           uint32_t out_cap, uint32_t *__restrict__ overflow, uint32_t *ring_base,
-                                                          uint32_t ring_words, int stage_words)
+                                                          uint32_t ring_words, int stage_words, int adapt, uint32_t *left_after)
 {
     extern __shared__ uint32_t lds[];
     // the sweeps address their tables by LDS byte address from 0: the kernel has no other LDS in front of this array
@@ -1441,6 +1485,7 @@ __global__ __launch_bounds__(kWave, MODE ? 4 : 3) void eval_fast_kernel(const KP
     L.predbit_tab = lds + 7 * kMaxK;
     L.tt_tab = (uint4 *)(lds + kFastTableWords);              // 128 words, TP variants only
     L.grp_tab = lds + kFastTableWords + 4 * kMaxK;            // TP variants only
+    L.tpg_tab = lds + kFastTableWords + 5 * kMaxK;            // TP variants only
     L.sw_tab = lds + kSweepTabWord;
     L.ch_tab = lds + kSweepTabWord + kMaxK;
     L.in_tab = lds + kSweepTabWord + 2 * kMaxK;
@@ -1456,7 +1501,8 @@ __global__ __launch_bounds__(kWave, MODE ? 4 : 3) void eval_fast_kernel(const KP
     if (lane < kMaxK) {
         const uint32_t inf = P.info_loc[lane];
         if (TP) L.tt_tab[lane] = make_uint4((uint32_t)P.t_loc[lane], ((((inf >> 12) & 63u) - (uint32_t)P.D + 2u * DM) << 8),
-                                    ((uint32_t)lane >> 2) * (kWave * 4u), 16u + 4u * ((uint32_t)lane & 3u));
+                                    ((uint32_t)lane >> 2) * (kWave * 4u),
+                                    (16u + 4u * ((uint32_t)lane & 3u)) | ((P.grp_code[lane] & (P.grp_code[lane] - 1u)) ? 0x80000000u : 0u));
         {
             const uint32_t su = inf & 63u, dev = (uint32_t)lane >> 2, y = (uint32_t)lane & 3u;
             const int32_t m = (int32_t)(inf << 6) >> 24;
@@ -1485,6 +1531,7 @@ __global__ __launch_bounds__(kWave, MODE ? 4 : 3) void eval_fast_kernel(const KP
         }
         L.chain_tab[lane] = P.chain_tab[lane];
         L.vtab[lane] = lane < 24 ? P.vtab[lane] : 0u;
+        if (TP && lane < kMaxD) L.tpg_tab[lane] = P.tp_group[lane];
         if (TP) L.grp_tab[lane] = P.grp_code[lane] ? P.grp_code[lane] : 1u << lane;
         L.cum_tab[lane] = P.cum_code[lane]; L.predbit_tab[lane] = P.pred_bit[lane];
     }
@@ -1495,9 +1542,7 @@ __global__ __launch_bounds__(kWave, MODE ? 4 : 3) void eval_fast_kernel(const KP
     C.step_q16 = P.step_q16; C.seed = P.seed;
 #pragma unroll
     for (int d = 0; d < DM; d++) { C.ntd[d] = P.ntd[d]; C.mpack[d] = P.mpack[d]; }
-    C.ntp = TP ? P.ntp : 0; C.slow = TP ? P.slow_mask : 0u;
-#pragma unroll
-    for (int k = 0; k < kMaxD; k++) C.tpg[k] = TP ? P.tp_group[k] : 0u;
+    C.ntp = TP ? P.ntp : 0; C.slow = TP ? P.slow_mask : 0u; C.tp_all = TP ? P.tp_all : 0;
 
     int best = INT_MAX;
     uint64_t best_idx = 0;
@@ -1523,9 +1568,24 @@ __global__ __launch_bounds__(kWave, MODE ? 4 : 3) void eval_fast_kernel(const KP
     uint32_t *ring1 = ring_base + (size_t)blockIdx.x * 3u * ring_words, *ring2 = ring1 + ring_words, *ring3 = ring2 + ring_words;
     uint32_t head1 = 0, count1 = 0, head2 = 0, count2 = 0, head3 = 0, count3 = 0, nretry = 0, nblocks = 0;           // wave-uniform
     const int nwords = C.nwords;
-    const bool split = stage_words < nwords;                         // tiny windows: A builds all of it
-    const int wordsA = split ? stage_words : nwords;
-    const int chunksA = (wordsA + 3) / 4, chunksAll = (nwords + 3) / 4;
+    // Program words of phase A: `stage_words`, or, in the variants for blocks on several devices where the waves have many
+    // rounds of candidates to come (`adapt`), what the launch's first candidates ask for: the first two rounds are built in
+    // one go; one wave in 16 adds to a histogram after how many words its candidates were out, and then every wave takes
+    // the number of words that costs the fewest lane words: 64 w in phase A, and for the candidates alive then the rest of the words
+    // and the way through the queue.  How early candidates leave depends on cap, times and leads, not on sizes: with a block
+    // on all of four devices and 7 words a window the best number is 1 (0.36 of the time of building in one go), 2
+    // (0.50) or 7 (2 words: 1.00 to 1.04) by the cap alone.  (A wave that goes by its own 64 candidates is off by as much as
+    // the best number gains, and the launch ends with the slowest wave.  In the other variants the best number is near the one by
+    // size, and the histogram's code costs them registers: 5 to 7 % of the time on 256 blocks.)
+    int wordsA, chunksA;
+    bool split;
+    auto set_stage = [&](int w) {
+        split = w < nwords;                                          // else A builds all of the window
+        wordsA = split ? w : nwords;
+        chunksA = (wordsA + 3) / 4;
+    };
+    set_stage(stage_words);
+    const int chunksAll = (nwords + 3) / 4;
     const bool drop_mem = MODE == 2 && peak_out == nullptr;          // a rejected candidate's peak is that of the whole window
     // every phase has a program of its own (words it does not write stay undefined and are never read), so that no
     // program lives on from one phase to the next
@@ -1640,13 +1700,15 @@ __global__ __launch_bounds__(kWave, MODE ? 4 : 3) void eval_fast_kernel(const KP
             }
         head1 = (head1 + n) & (kRingSlots - 1u);
         count1 -= n;
-        build_words<DM, MODE, TP>(P, C, L, lane, have, wordsA, nwords, prog, S);
+        build_words<DM, MODE, TP>(P, C, L, lane, have, wordsA, nwords, prog, S, nullptr);
         nblocks += n * (uint32_t)(C.total - min(C.total, 6 * wordsA));
         finish_build(have, idx, prog);
     };
 
     const uint64_t stride = (uint64_t)gridDim.x * kWave;
     const uint64_t rounds = (count + stride - 1) / stride;          // the same trip count for every lane of the grid
+    const bool adapting = TP && MODE != 0 && adapt && (MODE == 1 || drop_mem) && rounds >= 12;        // (exhaustive spaces: the decode is most of it, and waves stop early as one)
+    if (adapting) set_stage(nwords);
     // phase A on the next 64 candidates of the wave's share
     auto build_new = [&](uint64_t r) {
         const uint64_t kk = r * stride + (uint64_t)blockIdx.x * kWave + lane;
@@ -1656,9 +1718,31 @@ __global__ __launch_bounds__(kWave, MODE ? 4 : 3) void eval_fast_kernel(const KP
         build_begin<DM, MODE, TP>(P, C, idx, L, lane, lead_code, S);
         FastProgram prog;
         __builtin_amdgcn_s_setprio(1);
-        build_words<DM, MODE, TP>(P, C, L, lane, valid, 0, wordsA, prog, S);
+        const bool watch = adapting && r < 2;
+        const bool report = watch && r == 0 && (blockIdx.x & 15u) == 0;
+        build_words<DM, MODE, TP>(P, C, L, lane, valid, 0, wordsA, prog, S, report ? left_after : nullptr);
         nblocks += (uint32_t)__builtin_popcountll(__ballot(valid)) * (uint32_t)min(C.total, 6 * wordsA);
-        if (!split) { finish_build(valid, idx, prog); return; }
+        if (!split) {
+            finish_build(valid, idx, prog);
+            if (!(TP && MODE != 0) || !watch) return;
+            if (r == 0) {
+                if (report && lane == 0) __hip_atomic_fetch_add(left_after, (uint32_t)kWave, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return;
+            }
+            // (the way through the queue in words, times eight: push and pop of masks, records and program)
+            constexpr uint32_t way = 4 + DM;
+            const uint32_t alive = lane < nwords ? __hip_atomic_load(left_after + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+            const uint32_t all = (uint32_t)__builtin_amdgcn_readfirstlane((int)alive), n8 = 8u * (uint32_t)nwords, w8 = 8u * (uint32_t)lane;
+            // lane w: the cost of w words; lane 0: of building in one go.  (At most 2^14 candidates times 43 words times 8: the
+            // number fits above six bits of w.)
+            uint32_t cost = lane == 0 ? all * n8 : lane < nwords ? all * w8 + alive * (n8 - w8 + way) : 0x3FFFFFFu;
+            cost = (cost << 6) | (uint32_t)lane;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) cost = min(cost, (uint32_t)__shfl_xor(cost, off));
+            const int w = (int)(cost & 63u);
+            set_stage(all == 0 ? stage_words : w == 0 ? nwords : w);
+            return;
+        }
         const bool over = drop_mem && S.status == kOk && S.worst > C.M;
         reject(valid && (S.status != kOk || over), idx, over ? (int)kMem : S.status, 0);
         const bool ok = valid && S.status == kOk && !over;
@@ -1828,8 +1912,11 @@ extern template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
 // first.  Bound by the latency of the record loads: 4,160 records took one wave 14.6 us (65 dependent rounds), eight
 // waves take 9 to 10.
 constexpr int kMergeThreads = 512;
-__global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__restrict__ recs, int nrecs, DevResult *__restrict__ res)
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__restrict__ recs, int nrecs, DevResult *__restrict__ res,
+                                                                 uint32_t *__restrict__ left_after)
 {
+    if (threadIdx.x < kWave) left_after[threadIdx.x] = 0;        // for the next launch
+
     struct Sum { int best; uint32_t nre; uint64_t best_idx, nev, nsw, nbl, cnt[kNumStatus]; };
     __shared__ Sum part[kMergeThreads / kWave];
     Sum a;
@@ -1881,16 +1968,18 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__
     }
 }
 
-// only the counter of the deferred list (after a per-candidate scoring call)
-__global__ void clear_defer_kernel(DevResult *res)
+// only the counter of the deferred list and the histogram (after a per-candidate scoring call; one wave)
+__global__ void clear_defer_kernel(DevResult *res, uint32_t *left_after)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) res->defer_count = 0;
+    left_after[threadIdx.x] = 0;
+    if (threadIdx.x == 0) res->defer_count = 0;
 }
 
-__global__ void reset_kernel(DevResult *res, DevDetail *detail)
+__global__ void reset_kernel(DevResult *res, DevDetail *detail, uint32_t *left_after)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         detail->status = -1;                     // no candidate decoded yet
+        for (int w = 0; w < kWave; w++) left_after[w] = 0;
         res->period = INT_MAX; res->pad = 0; res->index = ~0ull; res->n_evaluated = 0; res->n_sweeps = 0; res->n_blocks = 0;
         res->n_retried = 0; res->n_deferred = 0; res->overflow = 0; res->defer_count = 0;
         for (int s = 0; s < kNumStatus; s++) res->n_status[s] = 0;
@@ -1901,7 +1990,7 @@ __global__ void reset_kernel(DevResult *res, DevDetail *detail)
 typedef void (*eval_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *,
                         uint32_t *, int);
 typedef void (*fast_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, int, int, uint64_t *, uint32_t *,
-                        uint32_t, uint32_t *, uint32_t *, uint32_t, int);
+                        uint32_t, uint32_t *, uint32_t *, uint32_t, int, int, uint32_t *);
 
 // problems too wide for the fast kernel and the chain path (their state stays in LDS where 64 KB hold it)
 static bool wide_problem(const KParams &kp) { return kp.D > kMaxD || kp.K > kMaxK || kp.many || kp.NR > kMaxNR; }
@@ -1926,7 +2015,9 @@ static fast_fn pick_fast(const KParams &kp)
     if (kp.fast_tp) {
         // blocks on several devices
         if (kp.space == kSampledRepair)
-            return kp.D <= 2 ? eval_fast_kernel<2, 24, 2, true> : kp.D <= 4 ? eval_fast_kernel<4, 24, 2, true> : eval_fast_kernel<8, 24, 2, true>;
+            return kp.D <= 2 ? (V <= 10 ? eval_fast_kernel<2, 10, 2, true> : eval_fast_kernel<2, 24, 2, true>)
+                 : kp.D <= 4 ? (V <= 8 ? eval_fast_kernel<4, 8, 2, true> : eval_fast_kernel<4, 24, 2, true>)
+                             : (V <= 16 ? eval_fast_kernel<8, 16, 2, true> : eval_fast_kernel<8, 24, 2, true>);
         if (kp.space == kSampledStrict)
             return kp.D <= 2 ? eval_fast_kernel<2, 24, 1, true> : kp.D <= 4 ? eval_fast_kernel<4, 24, 1, true> : eval_fast_kernel<8, 24, 1, true>;
         return kp.D <= 2 ? eval_fast_kernel<2, 24, 0, true> : kp.D <= 4 ? eval_fast_kernel<4, 24, 0, true> : eval_fast_kernel<8, 24, 0, true>;
@@ -2025,18 +2116,22 @@ LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks)
     return s;
 }
 
-// program words the fast kernel builds before the candidates that are still alive queue for the rest (most
-// candidates that exceed the memory cap do so within the first blocks of the window): about two sevenths of the
-// window, a multiple of four words; windows of fewer than ten words are built in one go
-static int stage_words(const KParams &kp)
+// Program words the fast kernel builds before the candidates that are still alive queue for the rest (most candidates
+// that exceed the memory cap do so within the first blocks of the window).  Windows of ten words and more: 3 of 11, 6 of 22, 9 of
+// 32, 12 of 43, between the best numbers under tight and under wide caps (against two sevenths rounded up to four: 0.96 to
+// 1.00 of the time; smaller windows lose 5 to 10 % by a queue where most candidates fit, and gain as much where few do).
+// Blocks on several devices: two words, whose steps are the dearest; with `adapt` the waves of a long launch find the number
+// themselves (the kernel says how).
+static int stage_words(const KParams &kp, int &adapt)
 {
     const int nwords = (kp.total + 5) / 6;
+    adapt = 1;
     if (const char *env = getenv("TESSEL_STAGE_WORDS")) {           // tuning knob
         const int want = atoi(env);
-        if (want >= 0 && want <= nwords) return want;
+        if (want >= 0 && want <= nwords) { adapt = 0; return want; }
     }
-    // (measured on windows of 256 blocks: 12 of 43 words; the queues move program words four at a time)
-    return nwords >= 10 ? (nwords * 2 / 7 + 3) / 4 * 4 : nwords;
+    if (kp.fast_tp) return nwords > 2 ? 2 : nwords;
+    return nwords >= 10 ? 3 + (nwords - 10) * 9 / 33 : nwords;
 }
 
 // the rings of the fast kernel's waves lie behind the block records, two per wave; words of one ring
@@ -2124,8 +2219,10 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
     }
     const size_t lds = fast_lds_bytes(kp);
     uint32_t *ring = (uint32_t *)((char *)ws + ring_offset(s.blocks, num_cus));
+    int adapt = 0;
+    const int stage = stage_words(kp, adapt);
     hipLaunchKernelGGL(ff, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, kp.eigen_tries, kp.retry_tries,
-                       list, &res->defer_count, kWsListCap, &res->overflow, ring, ring_words(kp), stage_words(kp));
+                       list, &res->defer_count, kWsListCap, &res->overflow, ring, ring_words(kp), stage, adapt, (uint32_t *)((char *)ws + kWsLeftOff));
     int rc = (int)hipGetLastError();
     if (rc) return -rc;
     rc = launch_general(kp, kp_dev, first, count, kDeferBlocks, recs ? recs + blocks : nullptr, code, peak, list,
@@ -2144,7 +2241,8 @@ int launch_eval(const KParams &kp, uint64_t first, uint64_t count, void *ws, int
         int n = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, recs, nullptr, nullptr, false, st);
         if (n < 0) return -n;
         if (n > 0) {
-            hipLaunchKernelGGL(merge_kernel, dim3(1), dim3(kMergeThreads), 0, st, recs, n, res);
+            hipLaunchKernelGGL(merge_kernel, dim3(1), dim3(kMergeThreads), 0, st, recs, n, res,
+                               (uint32_t *)((char *)ws + kWsLeftOff));
             int rc = (int)hipGetLastError();
             if (rc) return rc;
         }
@@ -2164,7 +2262,7 @@ int launch_score(const KParams &kp, uint64_t first, uint64_t count, int32_t *cod
         const uint64_t piece = count - done < max_piece ? count - done : max_piece;
         int n = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, nullptr, code + done, peak ? peak + done : nullptr, general, st);
         if (n < 0) return -n;
-        hipLaunchKernelGGL(clear_defer_kernel, dim3(1), dim3(1), 0, st, res);
+        hipLaunchKernelGGL(clear_defer_kernel, dim3(1), dim3(kWave), 0, st, res, (uint32_t *)((char *)ws + kWsLeftOff));
         int rc = (int)hipGetLastError();
         if (rc) return rc;
         done += piece;
@@ -2175,7 +2273,7 @@ int launch_score(const KParams &kp, uint64_t first, uint64_t count, int32_t *cod
 int launch_reset(void *ws, void *stream)
 {
     hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, (DevResult *)((char *)ws + kWsResultOff),
-                       (DevDetail *)((char *)ws + kWsDetailOff));
+                       (DevDetail *)((char *)ws + kWsDetailOff), (uint32_t *)((char *)ws + kWsLeftOff));
     return (int)hipGetLastError();
 }
 

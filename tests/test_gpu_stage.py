@@ -1,0 +1,47 @@
+"""The fast kernel's first build phase on problems with blocks on several devices, whose length long launches find from
+their own first candidates: the same best candidate and counts as with every length forced, and as the oracle on the
+start of the range; blocks on all devices and on some of them."""
+import pytest
+
+from tests.test_gpu_dag import _compare
+from tests.test_gpu_wide import shared_block
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU: the HIP path has no CPU fallback")
+    from paper_2311_15269_amd import binding
+    binding.load_library()
+    return binding
+
+
+def on_some(D, nr, cap):
+    """the block around the pipeline on the first two devices only"""
+    prob = shared_block(D, nr, cap)
+    return dict(prob, dev_mask=[3] + prob["dev_mask"][1:-1] + [3], name="some-%d" % D)
+
+
+# tight and wide caps; strict: deadlocks instead of the cap
+SHAPES = [shared_block(2, 2, 4), shared_block(2, 4, 11), shared_block(4, 4, 6), shared_block(4, 2, 100), shared_block(7, 4, 9),
+          shared_block(8, 2, 4), shared_block(3, 2, 9, space="sampled_strict"), on_some(4, 3, 8), on_some(8, 2, 100)]
+
+
+@pytest.mark.parametrize("prob", SHAPES, ids=["%s-nr%d-cap%d-%s" % (p["name"], p["NR"], p["M"], p["space"]) for p in SHAPES])
+def test_lengths_of_the_first_phase(gpu, monkeypatch, prob):
+    _compare(gpu, prob, 1 << 30, 1500)
+    n, words = 3500000, (prob["K"] * prob["NR"] + 5) // 6      # enough rounds for the waves to choose
+
+    def best():
+        g = gpu.Problem(prob)
+        g.eval_candidates(7, n)
+        r = g.best()
+        return {k: r[k] for k in ("period", "index", "peak", "n_evaluated", "n_feasible", "n_reject")}
+    want = best()
+    assert want["n_evaluated"] == n
+    for length in sorted({1, 2, words // 2, words} - {0}):
+        monkeypatch.setenv("TESSEL_STAGE_WORDS", str(length))
+        assert best() == want
