@@ -31,6 +31,10 @@ struct tessel_problem {
     std::vector<int32_t> dep_src, dep_dst;
     std::vector<int8_t> leadtab;        // CANONICAL
     std::vector<uint64_t> wtab;         // CANONICAL
+    std::vector<uint64_t> orders;       // CANONICAL with small tables: KParams::orders, leadrows
+    std::vector<uint32_t> leadrows;
+    std::vector<char> tables;           // the four in a row, each from a multiple of 256 bytes on, as the workspace gets them
+    size_t table_at[4] = {0, 0, 0, 0};
     uint64_t nlead = 0;
     uint64_t count = 0;
     int num_cus = 0;
@@ -292,6 +296,46 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
     gt.first_tries = std::min(kGraphTries, kp.dag_tries);
     gt.retry_tries = 4 * kp.dag_tries;
     gt.ok = 1;
+}
+
+// The fast kernel's tables by rank for the CANONICAL space (KParams::ranked), where neither has more than kRankedMax
+// entries: every order of a device, in rank order (lexicographic), and for every lead vector what the build makes of it.
+static void ranked_tables(tessel_problem &p)
+{
+    KParams &kp = p.kp;
+    kp.ranked = 0;
+    if (!kp.fast_ok || p.nlead > kRankedMax) return;
+    for (int d = 0; d < kp.D; d++) if (kp.cdev[d] > kRankedMax) return;
+    for (int n = 0; n <= kMaxLT; n++) {
+        bool used = false;
+        for (int d = 0; d < kp.D; d++) used = used || kp.ntd[d] == n;
+        kp.order_at[n] = (uint32_t)p.orders.size();
+        if (!used) continue;
+        std::vector<int> seq;
+        for (int y = 0; y < n; y++) seq.insert(seq.end(), (size_t)kp.NR, y);
+        do {
+            uint32_t lo = 0, hi = 0;
+            for (size_t pos = 0; pos < seq.size(); pos++) { lo |= (uint32_t)(seq[pos] & 1) << pos; hi |= (uint32_t)(seq[pos] >> 1) << pos; }
+            p.orders.push_back((uint64_t)lo | ((uint64_t)hi << 32));
+        } while (std::next_permutation(seq.begin(), seq.end()));
+    }
+    for (int d = 0; d < kp.D; d++) kp.recip[d] = kp.cdev[d] > 1 ? (uint32_t)(((uint64_t)1 << 32) / kp.cdev[d]) : 0u;
+    p.leadrows.assign((size_t)p.nlead * kLeadRow, 0);
+    for (uint64_t v = 0; v < p.nlead; v++) {
+        const int8_t *lead = p.leadtab.data() + v * (uint64_t)kp.K;
+        uint32_t *row = p.leadrows.data() + v * kLeadRow;
+        for (int w = 4; w < 8; w++) row[w] = 0xFFFFFFFFu;            // 15: a chain's first block never waits
+        auto put = [&](uint32_t *words, int c, uint32_t x) { words[c / 8] = (words[c / 8] & ~(15u << (4 * (c % 8)))) | (x << (4 * (c % 8))); };
+        for (int d = 0; d < kp.D; d++)
+            for (int y = 0; y < kp.ntd[d]; y++) {
+                const int c = 4 * d + y, g = (int)((kp.type_of[d] >> (8 * y)) & 0xFFu), a = kp.pred[g];
+                put(row, c, (uint32_t)lead[g]);
+                const uint32_t wait = a < 0 ? 15u : (uint32_t)(lead[a] - lead[g]);
+                put(row + 4, c, wait);
+                if (wait) row[8] |= 1u << c;
+            }
+    }
+    kp.ranked = 1;
 }
 
 extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_problem **out)
@@ -641,6 +685,16 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
     if (!p->force_general && !getenv("TESSEL_FAR_MODE")) graph_tables(*p, p->graph);
     kp.graph_ok = p->graph.ok; kp.graph_np = p->graph.np; kp.graph_lds = p->graph.lds_bytes;
     kp.graph_slot_words = (uint32_t)(p->graph.meta + p->graph.nwords);
+    if (desc->space == TESSEL_SPACE_CANONICAL) {
+        ranked_tables(*p);
+        const std::pair<const void *, size_t> tabs[] = {{p->leadtab.data(), p->leadtab.size()}, {p->wtab.data(), p->wtab.size() * 8},
+                                                        {p->orders.data(), p->orders.size() * 8}, {p->leadrows.data(), p->leadrows.size() * 4}};
+        for (int k = 0; k < 4; k++) {
+            p->table_at[k] = p->tables.size();
+            p->tables.resize((p->tables.size() + tabs[k].second + 255) & ~(size_t)255);
+            if (tabs[k].second) memcpy(p->tables.data() + p->table_at[k], tabs[k].first, tabs[k].second);
+        }
+    }
     *out = p;
     return TESSEL_OK;
 }
@@ -711,15 +765,14 @@ static int bind_workspace(tessel_problem *p, void *ws, size_t bytes, hipStream_t
     if (bytes < eval_workspace_bytes(p->kp, p->num_cus, max_blocks)) return TESSEL_E_WORKSPACE;
     if (p->ws == ws && owns_workspace(p)) return TESSEL_OK;
     char *base = (char *)ws + kWsTablesOff;
-    size_t lead_bytes = (p->leadtab.size() + 255) & ~(size_t)255, w_bytes = p->wtab.size() * sizeof(uint64_t);
-    if (lead_bytes + w_bytes > kWsTablesMax) return TESSEL_E_TOOBIG;
-    if (!p->leadtab.empty()) {
-        hipError_t e = hipMemcpyAsync(base, p->leadtab.data(), p->leadtab.size(), hipMemcpyHostToDevice, st);
+    if (!p->tables.empty()) {
+        if (p->tables.size() > kWsTablesMax) return TESSEL_E_TOOBIG;
+        hipError_t e = hipMemcpyAsync(base, p->tables.data(), p->tables.size(), hipMemcpyHostToDevice, st);
         if (e != hipSuccess) return hip_fail(p, (int)e);
-        e = hipMemcpyAsync(base + lead_bytes, p->wtab.data(), w_bytes, hipMemcpyHostToDevice, st);
-        if (e != hipSuccess) return hip_fail(p, (int)e);
-        p->kp.leadtab = (const int8_t *)base;
-        p->kp.wtab = (const uint64_t *)(base + lead_bytes);
+        p->kp.leadtab = (const int8_t *)(base + p->table_at[0]);
+        p->kp.wtab = (const uint64_t *)(base + p->table_at[1]);
+        p->kp.orders = (const uint64_t *)(base + p->table_at[2]);
+        p->kp.leadrows = (const uint32_t *)(base + p->table_at[3]);
     }
     hipError_t pe = hipMemcpyAsync((char *)ws + kWsParamsOff, &p->kp, sizeof(KParams), hipMemcpyHostToDevice, st);
     if (pe != hipSuccess) return hip_fail(p, (int)pe);

@@ -55,6 +55,8 @@ constexpr int kMaxK = 32;        // block types of the problems the fast kernel 
 constexpr int kMaxKW = 64;       // ... of any problem: more than kMaxK go the general kernel's path for graphs
 constexpr int kMaxPos = kMaxLT * kMaxNR;   // blocks per device and window (32)
 constexpr int kMaxDeps = 128;     // dependencies of a micro-batch whose graph is not a set of chains
+constexpr int kLeadRow = 12;      // words of one row of KParams::leadrows
+constexpr uint32_t kRankedMax = 4096;   // most entries of one of the two tables
 constexpr uint32_t kNoRing = 0xFFFFu;   // no ring of end times (KParams::tokbase)
 constexpr int kNumStatus = 6;
 constexpr int kWave = 64;
@@ -148,6 +150,14 @@ struct KParams {
     int32_t  many;               // some device holds more than kMaxLT block types (3-bit symbols; sampled spaces only)
     const int8_t   *leadtab;     // CANONICAL: [nlead][K] in device memory
     const uint64_t *wtab;        // CANONICAL: arrangements by remaining counts, base NR+1 digits
+    // CANONICAL on the fast kernel, where the tables are small (ranked = 1): the order of a device by its rank, and what a
+    // lead vector means to the build by the vector's rank
+    int32_t  ranked;
+    uint32_t order_at[kMaxLT + 1];   // by number of block types on the device: its first entry in `orders`
+    uint32_t recip[kMaxD];       // floor(2^32 / arrangements of device d), 0 where there is one
+    const uint64_t *orders;      // low plane | high plane << 32, in rank order
+    const uint32_t *leadrows;    // kLeadRow words a vector: leads by code (4 bits each, 4 words), micro-batches waiting (4), types that
+                                 // may run (1), three unused
 };
 
 // Running best + counters of one search; lives at the start of the caller's workspace.

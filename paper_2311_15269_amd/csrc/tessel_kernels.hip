@@ -1165,8 +1165,8 @@ struct BuildState {
 };
 
 template <int DM, int MODE, bool TP>
-__device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM> &C, uint64_t idx, const FastLds &L, int lane,
-                                            Mu &lead_code, BuildState &S)
+__device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM> &C, uint64_t idx, uint64_t last_idx, const FastLds &L,
+                                            int lane, Mu &lead_code, BuildState &S)
 {
     uint32_t plo[DM], phi[DM];       // order planes per device
     int nlen[DM];
@@ -1175,6 +1175,7 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
     constexpr bool sampled = MODE != 0;    // kSampledStrict / kSampledRepair; else the exhaustive spaces
     Mu leads_type;                   // by type id (exhaustive spaces, fixed leads)
     leads_type.lo = 0; leads_type.hi = 0;
+    const uint32_t *row = nullptr;
     uint32_t ka = 0, kb = 0;
     if (sampled) {
         const uint64_t z = mix64(C.seed + 0x9E3779B97F4A7C15ULL * (idx + 1));
@@ -1214,6 +1215,31 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
         }
         if (C.has_fixed)
             for (int g = 0; g < C.K; g++) leads_type.set((uint32_t)g, P.fixed[g]);
+    } else if (P.ranked) {
+        // Ranks by mixed-radix digits of the index, orders and leads from tables by rank.  (Unranking symbol by symbol, up to
+        // four 64-bit counts from memory per position, and 64-bit divisions were most of the time of a space whose
+        // candidates mostly deadlock in their first blocks: 2^26 candidates of 32 blocks on 4 devices 6.8 -> CANMS ms.)
+        uint64_t rest = idx;
+#pragma unroll
+        for (int d = 0; d < DM; d++) {
+            plo[d] = phi[d] = 0; nlen[d] = 0;
+            if (d >= C.D) continue;
+            nlen[d] = C.ntd[d] * (int)NR;
+            const uint32_t n = (uint32_t)P.cdev[d], inv = P.recip[d];
+            uint32_t rank = 0;
+            if (inv != 0) {                                       // (one arrangement: nothing to take off the index)
+                if ((last_idx >> 32) == 0) {
+                    // the quotient of the reciprocal rounded down is the true one or one less
+                    uint32_t x = (uint32_t)rest, q = __umulhi(x, inv);
+                    rank = x - q * n;
+                    if (rank >= n) { rank -= n; q++; }
+                    rest = q;
+                } else { rank = (uint32_t)(rest % n); rest /= n; }
+            }
+            const uint64_t o = P.orders[P.order_at[C.ntd[d]] + rank];
+            plo[d] = (uint32_t)o; phi[d] = (uint32_t)(o >> 32);
+        }
+        row = P.leadrows + rest * (uint64_t)kLeadRow;
     } else {
         uint64_t ord[DM];
         status = decode_candidate<DM>(P, idx, ord, nlen, leads_type);
@@ -1259,6 +1285,11 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
             if (d < 4) { mu.lo |= (uint64_t)mud << (16 * d); Q.lo = (Q.lo & ~(0xFFFFull << (16 * d))) | ((uint64_t)qd << (16 * d)); }
             else { mu.hi |= (uint64_t)mud << (16 * (d - 4)); Q.hi = (Q.hi & ~(0xFFFFull << (16 * (d - 4)))) | ((uint64_t)qd << (16 * (d - 4))); }
         }
+    } else if (!sampled && P.ranked) {
+        const uint4 a = ((const uint4 *)row)[0], b = ((const uint4 *)row)[1];
+        mu.lo = (uint64_t)a.x | ((uint64_t)a.y << 32); mu.hi = (uint64_t)a.z | ((uint64_t)a.w << 32);
+        Q.lo = (uint64_t)b.x | ((uint64_t)b.y << 32); Q.hi = (uint64_t)b.z | ((uint64_t)b.w << 32);
+        R = row[8];
     } else {
         for (int k = 0; k < C.K; k++) {
             const uint32_t ct = L.chain_tab[k];
@@ -1715,7 +1746,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
         const bool valid = kk < count;
         const uint64_t idx = valid ? first + kk : first;
         __builtin_amdgcn_s_setprio(0);
-        build_begin<DM, MODE, TP>(P, C, idx, L, lane, lead_code, S);
+        build_begin<DM, MODE, TP>(P, C, idx, first + count - 1, L, lane, lead_code, S);
         FastProgram prog;
         __builtin_amdgcn_s_setprio(1);
         const bool watch = adapting && r < 2;
