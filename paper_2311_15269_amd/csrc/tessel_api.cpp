@@ -683,7 +683,7 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
     // (TESSEL_FAR_MODE chooses between placements of the general kernel's state: it takes the problem then)
     p->graph.ok = 0;
     if (!p->force_general && !getenv("TESSEL_FAR_MODE")) graph_tables(*p, p->graph);
-    kp.graph_ok = p->graph.ok; kp.graph_np = p->graph.np; kp.graph_lds = p->graph.lds_bytes;
+    kp.graph_ok = p->graph.ok; kp.graph_np = p->graph.np; kp.graph_chain = p->graph.chain; kp.graph_lds = p->graph.lds_bytes;
     kp.graph_slot_words = (uint32_t)(p->graph.meta + p->graph.nwords);
     if (desc->space == TESSEL_SPACE_CANONICAL) {
         ranked_tables(*p);

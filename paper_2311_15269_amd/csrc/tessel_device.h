@@ -144,7 +144,7 @@ struct KParams {
     uint8_t  dsrc[kMaxDeps], ddst[kMaxDeps], dcross[kMaxDeps];   // the dependencies in the caller's order
     uint64_t predmask_of[kMaxDW][kMaxLTW]; // producers of local symbol y of device d
     int32_t  graph_ok;           // the graph kernel takes the problem
-    int32_t  graph_np;           // GraphTab::np
+    int32_t  graph_np, graph_chain;      // GraphTab::np, chain
     uint32_t graph_lds;          // GraphTab::lds_bytes
     uint32_t graph_slot_words;   // words of one candidate's slot: GraphTab::meta + nwords
     int32_t  many;               // some device holds more than kMaxLT block types (3-bit symbols; sampled spaces only)

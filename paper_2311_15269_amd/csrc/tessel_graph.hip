@@ -16,8 +16,8 @@
 // Bound by the latency of those rounds at the few waves per CU that the LDS holds (a record is np + 2 rows of 256
 // bytes per device, a word one row per type).  Kernel times against the general kernel, which looks at every device's
 // head in turn and keeps counters for 64 types in registers: 200,003 candidates of a pipeline on 16 devices, 256 blocks
-// a window, 34.6 -> 0.655 ms; 100,003 of one on 12 devices, 288 blocks, 10.0 -> 0.265 ms; 300,007 with six types on each
-// of four devices, 96 blocks, 6.9 -> 0.302 ms; 2^22 of a graph of 6 types on three devices, 24 blocks, 3.48 -> 1.465 ms.
+// a window, 34.6 -> 0.485 ms; 100,003 of one on 12 devices, 288 blocks, 10.0 -> 0.248 ms; 300,007 with six types on each
+// of four devices, 96 blocks, 6.9 -> 0.257 ms; 2^22 of a graph of 6 types on three devices, 24 blocks, 3.48 -> 1.32 ms.
 //
 // The program (block type and micro-batch, 16 bits a block) goes to global memory, [word][slot], a slot per candidate;
 // sweeps read it back four words ahead.  A wave owns kGraphSlots slots: candidates that survive the build keep theirs
@@ -94,7 +94,8 @@ __device__ __forceinline__ void sampled_order(uint32_t ka, uint32_t kb, int d, u
     }
 }
 
-template <int NP, bool REPAIR, bool TP>
+// KIND: 0 every type has at most one producer and one consumer, 1 any graph, 2 some block sits on several devices
+template <int NP, bool REPAIR, int KIND>
 __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__restrict__ Pp, const GraphTab *__restrict__ Gp, uint64_t first,
                                                            uint64_t count, BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
                                                            int32_t *__restrict__ peak_out, uint64_t *__restrict__ out_list,
@@ -114,12 +115,13 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
     for (int j = 0; j < 3; j++) lds_store(st_row + (uint32_t)j * kRow + lane4, 0u);
     __syncthreads();
 
+    constexpr bool TP = KIND == 2, CHAIN = KIND == 0;
     constexpr uint32_t kCodeRow = (32u << NP) * 4u;              // bytes of one code table
     constexpr uint32_t RS = (NP + 2) * kRow;                     // bytes of one device record
     const int D = P.D, K = P.K, M = P.M, total = P.total, space = P.space, nwords = G.nwords;
     const uint32_t NR = (uint32_t)P.NR, ADD = G.add, GUARD = G.guard, mushift = (uint32_t)G.mushift;
     const uint32_t rec0 = G.rec + lane4, wrow0 = G.wrow + lane4;
-    const int maxout = G.maxout, ntp = TP ? G.ntp : 0;
+    const int maxout = CHAIN ? 1 : G.maxout, ntp = TP ? G.ntp : 0;
     uint32_t *slots = slots_all + (size_t)blockIdx.x * (size_t)(G.meta + nwords) * kProgRow;
     uint32_t *progs = slots + (size_t)G.meta * kProgRow;
     const bool drop_mem = REPAIR && peak_out == nullptr;         // a rejected candidate's peak is that of the whole window
@@ -352,13 +354,19 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             };
             const uint32_t y = symbol(p), code0 = d << NP, ca = (code0 | y) << 2;
             uint32_t T0 = lds_load(ca), T1 = lds_load(ca + kCodeRow), C0 = lds_load(ca + 2 * kCodeRow), C1 = lds_load(ca + 3 * kCodeRow);
-            TESSEL_PIN(T0); TESSEL_PIN(T1); TESSEL_PIN(C0); TESSEL_PIN(C1);
+            uint32_t E0 = 0, E1 = 0;
+            if (KIND == 1 && maxout > 1) { E0 = lds_load(ca + 4 * kCodeRow); E1 = lds_load(ca + 5 * kCodeRow); }
+            // (worked out while the table words are on their way)
+            const uint32_t alive2 = alive & ~(1u << p);
+            uint32_t head2 = 256u << symbol(low_bit(alive2));
+            TESSEL_PIN(head2);
+            head2 = alive2 ? head2 : 0u;
             const uint32_t wa = (T0 & 0xFF00u) + lane4;
             uint32_t cwa = (C0 & 0xFF00u) + lane4, cra = (C0 >> 16) + lane4;
             uint32_t w = lds_load(wa), wc = lds_load(cwa), rc = lds_load(cra);
-            TESSEL_PIN(w); TESSEL_PIN(wc); TESSEL_PIN(rc);
-            const uint32_t alive2 = alive & ~(1u << p);
-            const uint32_t head2 = alive2 ? 1u << (8u + symbol(low_bit(alive2))) : 0u;
+            // (a second consumer in the same rounds; what the first changes on its device is passed on in registers)
+            uint32_t wd = 0, rd = 0;
+            if (KIND == 1 && maxout > 1) { wd = lds_load((E0 & 0xFF00u) + lane4); rd = lds_load((E0 >> 16) + lane4); }
             const uint32_t w2 = w + T1;
             const bool again = ready(w2);
             const uint32_t onec = 1u << y;
@@ -407,6 +415,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                 entry = (T0 & 63u) | (w >> mushift) << 6;
                 // the consumers: one more micro-batch waits.  (No consumer: the row that
                 // stays zero, increment 0, and the block's own record.)
+                uint32_t dc_before = 0, now_before = 0;
                 for (int k = 0;;) {
                     const uint32_t wc2 = wc + C1;
                     const bool runs_now = ready(wc2);
@@ -432,13 +441,19 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                             }
                         }
                     } else {
-                        uint32_t now = k == 0 ? (dc == d ? rhm2 : rc) : lds_load(cra);
+                        uint32_t now = k == 0 ? (dc == d ? rhm2 : rc) : k == 1 ? (dc == dc_before ? now_before : dc == d ? rhm2 : rc) : lds_load(cra);
                         now |= runs_now ? bit : 0u;
                         lds_store(cra, now);
                         RD |= (now & 0xFFu ? 1u : 0u) << dc;
                         HD |= (now & (now >> 8) & 0xFFu ? 1u : 0u) << dc;
+                        dc_before = dc; now_before = now;
                     }
-                    if (++k >= maxout) break;
+                    if (CHAIN || ++k >= maxout) break;
+                    if (KIND == 1 && k == 1) {
+                        C0 = E0; C1 = E1; wc = wd; rc = rd;
+                        cwa = (C0 & 0xFF00u) + lane4; cra = (C0 >> 16) + lane4;
+                        continue;
+                    }
                     C0 = lds_load(ca + (2u + 2u * (uint32_t)k) * kCodeRow); C1 = lds_load(ca + (3u + 2u * (uint32_t)k) * kCodeRow);
                     cwa = (C0 & 0xFF00u) + lane4; cra = (C0 >> 16) + lane4;
                     wc = lds_load(cwa);
@@ -501,11 +516,10 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         for (int r = 0; r < P.ntok; r += 4) lds_store(G.leads + (uint32_t)(r / 4) * kRow + lane4, have ? meta[(size_t)(3 + r / 4) * kProgRow] : 0u);
         for (int s = 0; s < P.nslots; s++) lds_store(st0 + (uint32_t)s * kRow, 0u);
         for (int d = 0; d < D; d++) lds_store(G.prev + (uint32_t)d * kRow + lane4, 0u);
-        const bool chain = G.chain != 0;
         const int maxin = G.maxin;
-        auto block = [&](uint32_t e, uint32_t A, uint32_t B) {
+        auto block = [&](uint32_t e, uint32_t A, uint32_t B, uint32_t pr) {
             const uint32_t mu8 = (e >> 6) << 8, da = (B & 0xFFFFu) + lane4;
-            if (!TP && chain) {
+            if (CHAIN) {
                 const uint32_t ta = (B >> 16) + mu8 + lane4;
                 const uint32_t en = max(lds_load(da), lds_load(ta)) + (A & 0xFFFFFFu);
                 lds_store(da, en);
@@ -517,9 +531,10 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             const uint32_t mask = TP ? lds_load(G.tpm + g4) : 0u;
             s = lds_load(da);
             for (uint32_t rest = mask; rest; rest &= rest - 1u) s = max(s, lds_load(st0 + (uint32_t)__builtin_ctz(rest) * kRow));
-            for (int k = 0; k < maxin; k += 2) {
-                const uint32_t pr = lds_load(G.sw + (2u + (uint32_t)k / 2u) * (kMaxKW * 4u) + g4);
+            for (int k = 0;;) {
                 s = max(s, max(lds_load((pr & 0xFFFFu) + mu8 + lane4), lds_load((pr >> 16) + mu8 + lane4)));
+                if ((k += 2) >= maxin) break;
+                pr = lds_load(G.sw + (2u + (uint32_t)k / 2u) * (kMaxKW * 4u) + g4);
             }
             const uint32_t en = s + (A & 0xFFFFFFu);
             lds_store(da, en);
@@ -546,7 +561,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                 const int ahead = wi + 4 < nwords ? wi + 4 : wi;
 #pragma unroll
                 for (int q = 0; q < 4; q++) nxt[q] = prog[(size_t)(ahead + q) * kProgRow];
-                uint32_t e[8], A[8], B[8];
+                uint32_t e[8], A[8], B[8], pr[8];
                 const int left = total - 2 * wi;                 // blocks from here on
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
@@ -557,9 +572,10 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                     const uint32_t g4 = (e[q] & 63u) << 2;
                     A[q] = lds_load(G.sw + g4);
                     B[q] = lds_load(G.sw + kMaxKW * 4u + g4);
+                    pr[q] = !CHAIN ? lds_load(G.sw + 2u * (kMaxKW * 4u) + g4) : 0u;
                 }
 #pragma unroll
-                for (int q = 0; q < 8; q++) if (q < left) block(e[q], A[q], B[q]);
+                for (int q = 0; q < 8; q++) if (q < left) block(e[q], A[q], B[q], pr[q]);
 #pragma unroll
                 for (int q = 0; q < 4; q++) cur[q] = nxt[q];
             }
@@ -648,7 +664,16 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         const uint32_t n1 = slots_in(1u, false, unused), n2 = slots_in(2u, false, unused);
         // (a wave whose share has ended early does no more rounds)
         const bool fresh = r < rounds && r * stride + (uint64_t)blockIdx.x * kWave < count;
-        if (n2 >= (uint32_t)kWave || (!fresh && n1 == 0 && n2 > 0)) sweep(2u, true);
+        if (!fresh && n1 > 0 && n1 + n2 <= (uint32_t)kWave) {
+            // the last candidates of the share, stragglers among them: one longer search for all
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                const uint32_t a = st_row + (uint32_t)j * kRow + lane4;
+                if (lds_load(a) == 1u) lds_store(a, 2u);
+            }
+            __syncthreads();
+            sweep(2u, true);
+        } else if (n2 >= (uint32_t)kWave || (!fresh && n1 == 0 && n2 > 0)) sweep(2u, true);
         else if (n1 >= (uint32_t)kWave || (!fresh && n1 > 0)) sweep(1u, fresh || n1 > (uint32_t)kWave || n2 > 0);
         else if (fresh) {
             const uint64_t kk = r++ * stride + (uint64_t)blockIdx.x * kWave + lane;
@@ -679,16 +704,18 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
 typedef void (*graph_fn)(const KParams *, const GraphTab *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, uint64_t *, uint32_t *,
                          uint32_t, uint32_t *, uint32_t *);
 
-template <bool REPAIR, bool TP>
+template <bool REPAIR, int KIND>
 static graph_fn pick_np(int np)
 {
-    return np == 1 ? eval_graph_kernel<1, REPAIR, TP> : np == 2 ? eval_graph_kernel<2, REPAIR, TP> : eval_graph_kernel<3, REPAIR, TP>;
+    return np == 1 ? eval_graph_kernel<1, REPAIR, KIND> : np == 2 ? eval_graph_kernel<2, REPAIR, KIND> : eval_graph_kernel<3, REPAIR, KIND>;
 }
 
 static graph_fn pick_graph(const KParams &kp)
 {
-    if (kp.space == kSampledRepair) return kp.tp ? pick_np<true, true>(kp.graph_np) : pick_np<true, false>(kp.graph_np);
-    return kp.tp ? pick_np<false, true>(kp.graph_np) : pick_np<false, false>(kp.graph_np);
+    const int kind = kp.tp ? 2 : kp.graph_chain ? 0 : 1;
+    if (kp.space == kSampledRepair)
+        return kind == 0 ? pick_np<true, 0>(kp.graph_np) : kind == 1 ? pick_np<true, 1>(kp.graph_np) : pick_np<true, 2>(kp.graph_np);
+    return kind == 0 ? pick_np<false, 0>(kp.graph_np) : kind == 1 ? pick_np<false, 1>(kp.graph_np) : pick_np<false, 2>(kp.graph_np);
 }
 
 const void *graph_kernel(const KParams &kp) { return (const void *)pick_graph(kp); }
