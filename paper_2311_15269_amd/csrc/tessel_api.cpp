@@ -203,18 +203,20 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
         for (size_t s = 0; s < in[b].size(); s++)
             gt.edge[gt.nedge++] = (uint32_t)in[b][s] | (uint32_t)b << 8 | (uint32_t)(f * (1 + (int)s)) << 16;
     // LDS: code tables, sweep tables, tables of types on several devices, slot rows, then build and sweep state in one place
-    const int code_row = 32 << gt.np, ncode = (2 + 2 * gt.maxout) * code_row;
+    const int cw = 2 + 2 * gt.maxout;                       // words of a code
     const uint32_t row = kWave * 4;
-    uint32_t at = (uint32_t)ncode * 4;
+    gt.code_bytes = (uint32_t)cw * 4;
+    uint32_t at = ((uint32_t)D << gt.np) * gt.code_bytes;
     const int pairs = gt.chain && !kp.tp ? 0 : (gt.maxin + 1) / 2;
-    gt.sw = at; at += (uint32_t)(2 + pairs) * kMaxKW * 4;
-    gt.init = at; at += kMaxKW * 4;
+    gt.sw = at; at += (uint32_t)K * 8;
+    gt.swp = at; at += (uint32_t)(pairs * K) * 4;
+    gt.init = at; at += (uint32_t)K * 4;
     for (int i = 0; i < K; i++) {
         uint32_t w = (uint32_t)NR;
         for (int s = (int)in[i].size(); s < fields - 1; s++) w |= 1u << (f * (1 + s));
         gt.tab[gt.init / 4 + i] = w;
     }
-    gt.dev = at; at += 32 * 4;
+    gt.dev = at; at += (uint32_t)D * 4;
     for (int d = 0; d < D; d++) gt.tab[gt.dev / 4 + d] = (uint32_t)kp.ntd[d];
     std::vector<int> tp_no(K, -1);
     if (kp.tp) {
@@ -227,7 +229,7 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
     }
     gt.ntab = (int)(at / 4);
     at = (at + row - 1) / row * row;
-    gt.slot_rows = at; at += 4 * row;
+    gt.slot_rows = at; at += row;
     const uint32_t base = at;
     gt.rec = at; at += (uint32_t)D * (gt.np + 2) * row;
     gt.wrow = at; at += (uint32_t)K * row;
@@ -247,11 +249,11 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
     auto lowest = [&](int g) -> int { return __builtin_ctz(p.mask[g]); };
     for (int d = 0; d < D; d++)
         for (int y = 0; y < kp.ntd[d]; y++) {
-            const int g = type_at(d, y), c = (d << gt.np) + y;
+            const int g = type_at(d, y), c = ((d << gt.np) + y) * cw;
             gt.tab[c] = ((uint32_t)p.m[g] << 16) | (((gt.wrow + (uint32_t)g * row) / row) << 8) | (tp_no[g] >= 0 ? 64u : 0u) | (uint32_t)g;
             uint32_t dec = (1u << gt.mushift) - 1u;
             for (size_t s = 0; s < in[g].size(); s++) dec -= 1u << (f * (1 + (int)s));
-            gt.tab[code_row + c] = dec;
+            gt.tab[c + 1] = dec;
             for (int k = 0; k < gt.maxout; k++) {
                 uint32_t c0, c1 = 0;
                 if (k < (int)outs[g].size()) {
@@ -262,8 +264,8 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
                     c1 = 1u << (f * (1 + slot));
                 } else
                     c0 = (gt.rec + (uint32_t)(d * (gt.np + 2) + gt.np + 1) * row) << 16 | (gt.trash / row) << 8 | (uint32_t)d << 3;
-                gt.tab[(2 + 2 * k) * code_row + c] = c0;
-                gt.tab[(3 + 2 * k) * code_row + c] = c1;
+                gt.tab[c + 2 + 2 * k] = c0;
+                gt.tab[c + 3 + 2 * k] = c1;
             }
         }
     // rings: a type of a shared stretch reads and writes the stretch's; a type with no producer reads its own, where its
@@ -274,11 +276,11 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
         const bool own = kp.tokbase[g] != kNoRing;
         uint32_t to = own ? ring_address(g) : gt.strash;
         if (gt.chain && !own) to = ring_address(in[g][0]);
-        gt.tab[gt.sw / 4 + g] = (uint32_t)p.t[g] | (own ? 1u << 31 : 0u);
-        gt.tab[gt.sw / 4 + kMaxKW + g] = (gt.state + (uint32_t)lowest(g) * row) | to << 16;
+        gt.tab[gt.sw / 4 + 2 * g] = (uint32_t)p.t[g] | (own ? 1u << 31 : 0u);
+        gt.tab[gt.sw / 4 + 2 * g + 1] = (gt.state + (uint32_t)lowest(g) * row) | to << 16;
         for (int k = 0; k < pairs; k++) {
             auto from = [&](int s) -> uint32_t { return in[g].empty() ? to : ring_address(s < (int)in[g].size() ? in[g][s] : in[g][0]); };
-            gt.tab[gt.sw / 4 + (2 + k) * kMaxKW + g] = from(2 * k) | from(2 * k + 1) << 16;
+            gt.tab[gt.swp / 4 + k * K + g] = from(2 * k) | from(2 * k + 1) << 16;
         }
     }
     if (kp.tp)

@@ -281,12 +281,13 @@ struct GraphTab {
     int32_t meta;                // words per slot before the program: index (2), peak, leads of the rings' first types
     uint32_t lds_bytes;
     // LDS byte addresses
-    uint32_t slot_rows;          // one row to hand slots to lanes, three rows of slot states
+    uint32_t slot_rows;          // one row: 64 bytes to hand slots to lanes, 192 bytes of slot states
     uint32_t rec, wrow, trash;   // build: device records, one row per type, a row that stays zero
     uint32_t state, prev, strash, leads;   // sweeps: device times and rings (numbered as KParams::nslots counts them), device
                                  // times at the last boundary, a row for stores nobody reads, leads of the rings' first types
-    uint32_t sw;                 // sweep tables by type, kMaxKW words each: t | has a ring << 31, device row | own ring << 16,
-                                 // rings of the producers (16 bits each)
+    uint32_t code_bytes;         // table bytes of one code
+    uint32_t sw, swp;            // sweep tables by type: two words, t | has a ring << 31 and device row | own ring << 16; then for
+                                 // every two producers a word per type, their rings (16 bits each)
     uint32_t dev, init;          // by device the number of its block types; by type its word for lead 0 and nothing waiting
     uint32_t tpm, tpi, tps, smask;   // blocks on several devices: by type the device mask (0: one device) and 6 * number |
                                  // lowest device << 8 | devices << 16; symbol by number and device; by device the symbols of types
@@ -295,10 +296,10 @@ struct GraphTab {
                                  // sets << 24 | first of its source << 25 | last of it << 26
     uint32_t edge[kMaxDeps];     // distinct dependencies: src | dst << 8 | shift of the field in dst's word << 16
     int32_t ntab;
-    uint32_t tab[kGraphTabWords];// the LDS up to slot_rows: by code (device << np | symbol, rows of 32 << np words) memory delta
-                                 // << 16 | LDS row of the type's word << 8 | on several devices << 6 | type; what placing a block
-                                 // adds to that word; then per consumer k: address of the record's last word << 16 | LDS row of its
-                                 // word << 8 | device << 3 | symbol, and the increment of its word; then the sweep tables
+    uint32_t tab[kGraphTabWords];// the LDS up to slot_rows: by code (device << np | symbol) memory delta << 16 | LDS row of the type's
+                                 // word << 8 | on several devices << 6 | type; what placing a block adds to that word; then per
+                                 // consumer address of the record's last word << 16 | LDS row of its word << 8 | device << 3 |
+                                 // symbol, and the increment of its word; then the other tables
 };
 
 static_assert(sizeof(GraphTab) <= kWsGraphMax, "graph tables must fit their workspace slot");

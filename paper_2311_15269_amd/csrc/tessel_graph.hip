@@ -16,8 +16,10 @@
 // Bound by the latency of those rounds at the few waves per CU that the LDS holds (a record is np + 2 rows of 256
 // bytes per device, a word one row per type).  Kernel times against the general kernel, which looks at every device's
 // head in turn and keeps counters for 64 types in registers: 200,003 candidates of a pipeline on 16 devices, 256 blocks
-// a window, 34.6 -> 0.485 ms; 100,003 of one on 12 devices, 288 blocks, 10.0 -> 0.248 ms; 300,007 with six types on each
-// of four devices, 96 blocks, 6.9 -> 0.257 ms; 2^22 of a graph of 6 types on three devices, 24 blocks, 3.48 -> 1.32 ms.
+// a window, 34.6 -> 0.441 ms; 100,003 of one on 12 devices, 288 blocks, 10.0 -> 0.250 ms; 300,007 with six types on each
+// of four devices, 96 blocks, 6.9 -> 0.203 ms; 2^22 of a graph of 6 types on three devices, 24 blocks, 3.48 -> 0.774 ms.
+// LDS decides how many waves hide each other's rounds, so tables are as large as the problem, not its limits, and slot
+// states are bytes: 13.0 -> 9.7 KB a wave took the last of these from 1.32 ms.
 //
 // The program (block type and micro-batch, 16 bits a block) goes to global memory, [word][slot], a slot per candidate;
 // sweeps read it back four words ahead.  A wave owns kGraphSlots slots: candidates that survive the build keep theirs
@@ -38,6 +40,18 @@ __device__ __forceinline__ void lds_add(uint32_t a, uint32_t v)
 {
     __hip_atomic_fetch_add((lds_word *)(uintptr_t)a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+
+// two words in a row, eight-byte aligned
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) u32x2 lds_pair;
+__device__ __forceinline__ void lds_load2(uint32_t a, uint32_t &x, uint32_t &y)
+{
+    const u32x2 v = *(const lds_pair *)(uintptr_t)a;
+    x = v.x; y = v.y;
+}
+typedef __attribute__((address_space(3))) uint8_t lds_byte;
+__device__ __forceinline__ uint32_t lds_load8(uint32_t a) { return *(const lds_byte *)(uintptr_t)a; }
+__device__ __forceinline__ void lds_store8(uint32_t a, uint32_t v) { *(lds_byte *)(uintptr_t)a = (uint8_t)v; }
 
 // a device's order while it is decoded: bit p of plane k = bit k of the symbol at position p
 template <int NP>
@@ -110,13 +124,13 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
     const int lane = threadIdx.x;
     const uint32_t lane4 = (uint32_t)lane * 4u;
     for (int w = lane; w < G.ntab; w += kWave) lds[w] = G.tab[w];
-    const uint32_t sel_row = G.slot_rows, st_row = G.slot_rows + kRow;
+    const uint32_t sel_row = G.slot_rows, st_row = G.slot_rows + kWave;      // a byte per lane, a byte per slot
 #pragma unroll
-    for (int j = 0; j < 3; j++) lds_store(st_row + (uint32_t)j * kRow + lane4, 0u);
+    for (int j = 0; j < 3; j++) lds_store8(st_row + (uint32_t)(j * kWave + lane), 0u);
     __syncthreads();
 
     constexpr bool TP = KIND == 2, CHAIN = KIND == 0;
-    constexpr uint32_t kCodeRow = (32u << NP) * 4u;              // bytes of one code table
+    const uint32_t cw4 = CHAIN ? 16u : G.code_bytes;             // bytes of one code's table words
     constexpr uint32_t RS = (NP + 2) * kRow;                     // bytes of one device record
     const int D = P.D, K = P.K, M = P.M, total = P.total, space = P.space, nwords = G.nwords;
     const uint32_t NR = (uint32_t)P.NR, ADD = G.add, GUARD = G.guard, mushift = (uint32_t)G.mushift;
@@ -146,22 +160,22 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         uint32_t n = 0;
 #pragma unroll
         for (int j = 0; j < 3; j++) {
-            const bool in = lds_load(st_row + (uint32_t)j * kRow + lane4) == cls;
+            const bool in = lds_load8(st_row + (uint32_t)(j * kWave + lane)) == cls;
             const uint64_t m = __ballot(in);
             if (take && in) {
                 const uint32_t r = n + rank_in(m);
-                if (r < (uint32_t)kWave) lds_store(sel_row + r * 4u, (uint32_t)(j * kWave + lane));
+                if (r < (uint32_t)kWave) lds_store8(sel_row + r, (uint32_t)(j * kWave + lane));
             }
             n += (uint32_t)__builtin_popcountll(m);
         }
-        if (take) { __syncthreads(); mine = lds_load(sel_row + lane4); __syncthreads(); }
+        if (take) { __syncthreads(); mine = lds_load8(sel_row + (uint32_t)lane); __syncthreads(); }
         return n;
     };
 
     // ---------------------------------------------------------------- build: 64 new candidates
     auto build = [&](uint64_t idx, bool valid) {
         uint32_t slot = 0;
-        lds_store(sel_row + lane4, (uint32_t)lane);
+        lds_store8(sel_row + (uint32_t)lane, (uint32_t)lane);
         __syncthreads();
         slots_in(0u, true, slot);                                // (always 64 or more free: see kGraphSlots)
         uint32_t *prog = progs + slot;
@@ -250,7 +264,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                     seen += 1u << (8u * y);
                 }
                 for (uint32_t y = 0; y < ntd; y++) {
-                    const uint32_t g = uniform_word((((uint32_t)d << NP) + y) * 4u) & 63u;
+                    const uint32_t g = uniform_word((((uint32_t)d << NP) + y) * cw4) & 63u;
                     const uint32_t fl = byte_of(firstlab, y), a = wrow0 + g * kRow;
                     if ((uint32_t)__builtin_ctz(P.mask_type[g]) == (uint32_t)d) lds_store(a, uniform_word(G.init + (uint32_t)g * 4u) + (fl << mushift));
                     else if (lds_load(a) >> mushift != fl) tpm = true;
@@ -290,7 +304,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             const uint32_t head = lds_load(ra);
             const int ntd = (int)types_on(d);
             for (int y = 0; y < ntd; y++) {
-                const uint32_t T0 = uniform_word((((uint32_t)d << NP) + (uint32_t)y) * 4u);
+                const uint32_t T0 = uniform_word((((uint32_t)d << NP) + (uint32_t)y) * cw4);
                 const uint32_t w = lds_load((T0 & 0xFF00u) + lane4);
                 const bool ok = ready(w);
                 runs |= (ok ? 1u : 0u) << y;
@@ -314,11 +328,11 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         auto head_moved = [&](uint32_t code0, uint32_t from, uint32_t to) {
             if (from == to) return;
             if (from) {
-                const uint32_t T = lds_load((code0 | (uint32_t)__builtin_ctz(from)) << 2);
+                const uint32_t T = lds_load((code0 | (uint32_t)__builtin_ctz(from)) * cw4);
                 if (T & 64u) hcnt -= 1ull << (lds_load(G.tpi + (T & 63u) * 4u) & 63u);
             }
             if (to) {
-                const uint32_t T = lds_load((code0 | (uint32_t)__builtin_ctz(to)) << 2);
+                const uint32_t T = lds_load((code0 | (uint32_t)__builtin_ctz(to)) * cw4);
                 if (T & 64u) hcnt += 1ull << (lds_load(G.tpi + (T & 63u) * 4u) & 63u);
             }
         };
@@ -352,10 +366,11 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                 if (NP > 2) y |= __builtin_amdgcn_ubfe(p2, pos, 1) << 2;
                 return y;
             };
-            const uint32_t y = symbol(p), code0 = d << NP, ca = (code0 | y) << 2;
-            uint32_t T0 = lds_load(ca), T1 = lds_load(ca + kCodeRow), C0 = lds_load(ca + 2 * kCodeRow), C1 = lds_load(ca + 3 * kCodeRow);
+            const uint32_t y = symbol(p), code0 = d << NP, ca = CHAIN ? (code0 | y) << 4 : __umul24(code0 | y, cw4);
+            uint32_t T0, T1, C0, C1;
+            lds_load2(ca, T0, T1); lds_load2(ca + 8u, C0, C1);
             uint32_t E0 = 0, E1 = 0;
-            if (KIND == 1 && maxout > 1) { E0 = lds_load(ca + 4 * kCodeRow); E1 = lds_load(ca + 5 * kCodeRow); }
+            if (KIND == 1 && maxout > 1) lds_load2(ca + 16u, E0, E1);
             // (worked out while the table words are on their way)
             const uint32_t alive2 = alive & ~(1u << p);
             uint32_t head2 = 256u << symbol(low_bit(alive2));
@@ -454,7 +469,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                         cwa = (C0 & 0xFF00u) + lane4; cra = (C0 >> 16) + lane4;
                         continue;
                     }
-                    C0 = lds_load(ca + (2u + 2u * (uint32_t)k) * kCodeRow); C1 = lds_load(ca + (3u + 2u * (uint32_t)k) * kCodeRow);
+                    lds_load2(ca + 8u + 8u * (uint32_t)k, C0, C1);
                     cwa = (C0 & 0xFF00u) + lane4; cra = (C0 >> 16) + lane4;
                     wc = lds_load(cwa);
                 }
@@ -496,7 +511,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                     pack |= ((lds_load(wrow0 + (uint32_t)P.ring_head[r + q] * kRow) >> mushift) - NR) << (8 * q);
                 meta[(size_t)(3 + r / 4) * kProgRow] = pack;
             }
-            lds_store(st_row + slot * 4u, 1u);
+            lds_store8(st_row + slot, 1u);
         }
     };
 
@@ -504,7 +519,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
     // Times, rings and boundary as in the general kernel; eigenvector test after every sweep.
     auto sweep = [&](uint32_t cls, bool more_to_come) {
         uint32_t slot = 0;
-        lds_store(sel_row + lane4, (uint32_t)lane);
+        lds_store8(sel_row + (uint32_t)lane, (uint32_t)lane);
         __syncthreads();
         const uint32_t n = slots_in(cls, true, slot);
         const bool have = (uint32_t)lane < n;
@@ -534,7 +549,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             for (int k = 0;;) {
                 s = max(s, max(lds_load((pr & 0xFFFFu) + mu8 + lane4), lds_load((pr >> 16) + mu8 + lane4)));
                 if ((k += 2) >= maxin) break;
-                pr = lds_load(G.sw + (2u + (uint32_t)k / 2u) * (kMaxKW * 4u) + g4);
+                pr = lds_load(G.swp + (uint32_t)k / 2u * (uint32_t)K * 4u + g4);
             }
             const uint32_t en = s + (A & 0xFFFFFFu);
             lds_store(da, en);
@@ -570,9 +585,8 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                     e[q] = q & 1 ? cur[q / 2] >> 16 : cur[q / 2] & 0xFFFFu;
                     if (!have) e[q] = 0;
                     const uint32_t g4 = (e[q] & 63u) << 2;
-                    A[q] = lds_load(G.sw + g4);
-                    B[q] = lds_load(G.sw + kMaxKW * 4u + g4);
-                    pr[q] = !CHAIN ? lds_load(G.sw + 2u * (kMaxKW * 4u) + g4) : 0u;
+                    lds_load2(G.sw + 2u * g4, A[q], B[q]);
+                    pr[q] = !CHAIN ? lds_load(G.swp + g4) : 0u;
                 }
 #pragma unroll
                 for (int q = 0; q < 8; q++) if (q < left) block(e[q], A[q], B[q], pr[q]);
@@ -653,7 +667,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             if (at < out_cap) out_list[at] = idx; else *overflow = 1u;
         }
         if (cls == 1u) nretry += (uint32_t)__builtin_popcountll(__ballot(left_open));
-        if (have) lds_store(st_row + slot * 4u, left_open && cls == 1u ? 2u : 0u);
+        if (have) lds_store8(st_row + slot, left_open && cls == 1u ? 2u : 0u);
         __syncthreads();
     };
 
@@ -668,8 +682,8 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             // the last candidates of the share, stragglers among them: one longer search for all
 #pragma unroll
             for (int j = 0; j < 3; j++) {
-                const uint32_t a = st_row + (uint32_t)j * kRow + lane4;
-                if (lds_load(a) == 1u) lds_store(a, 2u);
+                const uint32_t a = st_row + (uint32_t)(j * kWave + lane);
+                if (lds_load8(a) == 1u) lds_store8(a, 2u);
             }
             __syncthreads();
             sweep(2u, true);
