@@ -30,8 +30,8 @@ extern "C" {
 
 /* ---- limits of this implementation -------------------------------------------------- */
 #define TESSEL_MAX_DEVICES        32   /* simulated devices D (more than 8, or more than 32
-                                          block types: scored by the general kernel alone;
-                                          no searched completion)                            */
+                                          block types: scored by the graph kernel or the
+                                          general one; no searched completion)                            */
 #define TESSEL_MAX_TYPES_PER_DEV  8    /* block types that occupy one device (more than 4:
                                           sampled spaces only; as for more than 8 devices);
                                           at most 32 blocks per device and window             */
@@ -102,7 +102,7 @@ typedef struct {
     const uint32_t *dev_mask;   /* [K] bit d set <=> the block occupies device d (d_B)          */
     int32_t  num_deps;          /* dependencies inside one micro-batch, B_src -> B_dst: any acyclic graph;
                                    disjoint chains score fastest, other graphs (at most 128 dependencies)
-                                   on a slower general path                                       */
+                                   on slower paths                                       */
     const int32_t  *dep_src;    /* [num_deps]                                                   */
     const int32_t  *dep_dst;    /* [num_deps]                                                   */
     int32_t  space;             /* TESSEL_SPACE_*                                               */
@@ -126,11 +126,12 @@ typedef struct {
     uint64_t n_feasible;
     uint64_t n_reject[TESSEL_NUM_STATUS];     /* indexed by TESSEL_STATUS_*; [0] unused        */
     uint64_t n_window_sweeps;                 /* sweeps of the window spent on period computations
-                                                 (0 when the general kernel did the scoring)    */
+                                                 (0 when the graph or the general kernel did the
+                                                 scoring)                                        */
     uint64_t n_blocks_placed;                 /* blocks the builds placed in executable order: a candidate that
                                                  is over the cap early is not built to the end by
                                                  tessel_eval_candidates (exact in the REPAIR space, an upper
-                                                 bound elsewhere; 0 when the general kernel did the scoring) */
+                                                 bound elsewhere; 0 when another kernel did the scoring) */
 } tessel_result;
 
 /* A complete schedule of N micro-batches: warm-up, R copies of the best window, cool-down
@@ -158,7 +159,8 @@ int  tessel_candidate_count(const tessel_problem *p, uint64_t *count);
 
 /* Bytes of device workspace tessel_eval_candidates / tessel_score_candidates need: the running best, the list of
  * candidates left to the general kernel (8 MiB) and, for problems the fast kernel takes, three queues per resident
- * wave between the phases of the kernel (3 x 27 KB per wave for 256 blocks a window; a few hundred MB in all).  Sized for the current
+ * wave between the phases of the kernel (3 x 27 KB per wave for 256 blocks a window; a few hundred MB in all), for those the
+ * graph kernel takes 192 programs per resident wave (about 100 KB for 256 blocks).  Sized for the current
  * device (for 512 compute units where there is none to ask); a workspace too small for the device a call runs on is
  * refused there with TESSEL_E_WORKSPACE. */
 int  tessel_workspace_bytes(const tessel_problem *p, size_t *bytes);

@@ -2153,7 +2153,8 @@ LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks)
 // 1.00 of the time; smaller windows lose 5 to 10 % by a queue where most candidates fit, and gain as much where few do).
 // Blocks on several devices: two words, whose steps are the dearest; with `adapt` the waves of a long launch find the number
 // themselves (the kernel says how).
-static int stage_words(const KParams &kp, int &adapt)
+// With repair, when every candidate's peak is wanted, none leaves early: all of the window, no queue.
+static int stage_words(const KParams &kp, bool peaks, int &adapt)
 {
     const int nwords = (kp.total + 5) / 6;
     adapt = 1;
@@ -2161,6 +2162,7 @@ static int stage_words(const KParams &kp, int &adapt)
         const int want = atoi(env);
         if (want >= 0 && want <= nwords) { adapt = 0; return want; }
     }
+    if (peaks && kp.space == kSampledRepair) { adapt = 0; return nwords; }
     if (kp.fast_tp) return nwords > 2 ? 2 : nwords;
     return nwords >= 10 ? 3 + (nwords - 10) * 9 / 33 : nwords;
 }
@@ -2251,7 +2253,7 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
     const size_t lds = fast_lds_bytes(kp);
     uint32_t *ring = (uint32_t *)((char *)ws + ring_offset(s.blocks, num_cus));
     int adapt = 0;
-    const int stage = stage_words(kp, adapt);
+    const int stage = stage_words(kp, peak != nullptr, adapt);
     hipLaunchKernelGGL(ff, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, kp.eigen_tries, kp.retry_tries,
                        list, &res->defer_count, kWsListCap, &res->overflow, ring, ring_words(kp), stage, adapt, (uint32_t *)((char *)ws + kWsLeftOff));
     int rc = (int)hipGetLastError();
