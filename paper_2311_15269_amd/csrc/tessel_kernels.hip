@@ -1218,7 +1218,7 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
     } else if (P.ranked) {
         // Ranks by mixed-radix digits of the index, orders and leads from tables by rank.  (Unranking symbol by symbol, up to
         // four 64-bit counts from memory per position, and 64-bit divisions were most of the time of a space whose
-        // candidates mostly deadlock in their first blocks: 2^26 candidates of 32 blocks on 4 devices 6.8 -> 2.5 ms.)
+        // candidates mostly deadlock in their first blocks: 2^26 candidates of 32 blocks on 4 devices 6.8 -> CANMS ms.)
         uint64_t rest = idx;
 #pragma unroll
         for (int d = 0; d < DM; d++) {
@@ -2406,6 +2406,8 @@ __global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__res
         }
         ptab[lane] = pw; aff[lane] = af; redo[lane] = rd;
     }
+    // some type has several consumers, or more than three other types on its device (wave-uniform)
+    const bool crowded = __ballot(lane < K && (__builtin_popcount(redo[lane]) > 2 || __builtin_popcount(aff[lane]) > 3)) != 0;
     __syncthreads();
     uint32_t *ckey = lds + kCompParamWords + (nstate + 1) / 2 * kWave + lane;      // [type][lane], behind the 16-bit state
     // ... and behind the keys what the replay of the R windows needs.  Either their (max, +) matrix: kMatIn slot
@@ -2471,26 +2473,13 @@ __global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__res
             };
             if (single_dev) {
                 // ---- every type on one device: one straight-line step per scheduled block
-                // The smallest key of every device stays in registers: a scheduled block changes the keys on its own device,
-                // which the step has at hand anyway, and its consumer's, which on another device can only bring that device's
-                // smallest key down (a consumer not offered before is offered now; one offered before keeps its key).  The pick is
-                // the least of eight instead of a read of every type's key from LDS (2^20 candidates of 64 micro-batches on 8
-                // devices, 32 types: 2.38 -> 2.30 ms).
-                uint32_t least[kMaxD];
-#pragma unroll
-                for (int j = 0; j < kMaxD; j++) least[j] = 0xFFFFFFFFu;
-                for (int i = 0; i < K; i++) {
-                    const uint32_t key = offer_key(i), dev = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ptab[i] >> 22 & 7u));
-                    ckey[i * kWave] = key;
-#pragma unroll
-                    for (int j = 0; j < kMaxD; j++) least[j] = min(least[j], dev == (uint32_t)j ? key : 0xFFFFFFFFu);
-                }
+                for (int i = 0; i < K; i++) ckey[i * kWave] = offer_key(i);
                 for (;;) {
                     const bool busy = live && !fail && left > 0;
                     if (__ballot(busy) == 0) break;
                     uint32_t bestp = 0xFFFFFFFFu;
-#pragma unroll
-                    for (int j = 0; j < kMaxD; j++) bestp = min(bestp, least[j]);
+#pragma unroll 8
+                    for (int i = 0; i < K; i++) bestp = min(bestp, ckey[i * kWave]);
                     const bool placed = busy && bestp < 0x80000000u;
                     fail = fail | (busy && !placed);              // blocks left, none eligible: no schedule
                     // A lane that places nothing goes through the step with type 0 and writes nothing.  The step is
@@ -2571,15 +2560,23 @@ __global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__res
                     ckey[(h0 ? a0 : K) * kWave] = k0;
                     ckey[(h1 ? a1 : K) * kWave] = k1;
                     ckey[(h2 ? a2 : K) * kWave] = k2;
-                    {
-                        const uint32_t none = 0xFFFFFFFFu;
-                        const bool here = has_c && dc == d;
-                        uint32_t own = min(min(key_b, here ? key_c : none), min(min(h0 ? k0 : none, h1 ? k1 : none), h2 ? k2 : none));
-                        const int at_own = placed ? d : kMaxD, at_next = has_c && !here ? dc : kMaxD;
-#pragma unroll
-                        for (int j = 0; j < kMaxD; j++) {
-                            const uint32_t l = at_own == j ? own : least[j];
-                            least[j] = min(l, at_next == j ? key_c : none);
+                    if (crowded) {
+                        // a type with several consumers, or more than four types on a device: the rest one by one
+                        uint32_t todo = placed ? rd & (rd - 1u) : 0u;
+                        while (__ballot(todo != 0u) != 0) {
+                            if (todo != 0u) {
+                                const int i = __builtin_ctz(todo);
+                                todo &= todo - 1u;
+                                ckey[i * kWave] = offer_key(i);
+                            }
+                        }
+                        todo = placed ? af2 & (af2 - 1u) : 0u;
+                        while (__ballot(todo != 0u) != 0) {
+                            if (todo != 0u) {
+                                const int i = __builtin_ctz(todo);
+                                todo &= todo - 1u;
+                                ckey[i * kWave] = moved(ckey[i * kWave], ptab[i], TESSEL_ST(oNext + i));
+                            }
                         }
                     }
                 }
