@@ -296,7 +296,8 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
             for (int d = 0; d < D; d++) if (p.mask[g] >> d & 1u) gt.tab[gt.tps / 4 + tp_no[g] * 32 + d] = (uint32_t)symbol_on(g, d);
         }
     gt.first_tries = std::min(kGraphTries, kp.dag_tries);
-    gt.retry_tries = 4 * kp.dag_tries;
+    // (every period seen settled within eight sweeps or never; a wave waits for its slowest lane)
+    gt.retry_tries = kp.dag_tries + kp.dag_tries / 2;
     gt.ok = 1;
 }
 

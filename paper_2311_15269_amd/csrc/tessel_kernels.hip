@@ -590,16 +590,18 @@ __device__ __forceinline__ void sweep_window_dag(const KParams &P, const DagTabl
 // ring's stretch overwrite the entries themselves); device times against `prevfree`.
 template <int DM, class CNT>
 __device__ __forceinline__ bool boundary_dag(const KParams &P, const DagTables &Tb, uint32_t *state, const CNT &lead, uint32_t (&prevfree)[DM],
-                                             uint32_t shift, bool first, uint32_t &want, uint32_t &top)
+                                             uint32_t shift, bool first, uint32_t &want, uint32_t &top, uint32_t &most)
 {
     bool same = true, have = !first;
     top = 0;
+    most = 0;                                    // the largest growth (of a first kind of call)
 #pragma unroll
     for (int d = 0; d < DM; d++) {
         if (d >= P.D) continue;
         const uint32_t x = state[d * kWave], y = x > shift ? x - shift : 0u;
         if (P.ntd[d] > 0) {
             const uint32_t dv = y - prevfree[d];
+            most = max(most, dv);
             if (!have) { want = dv; have = true; } else if (dv != want) same = false;
         }
         prevfree[d] = y; state[d * kWave] = y;
@@ -613,6 +615,7 @@ __device__ __forceinline__ bool boundary_dag(const KParams &P, const DagTables &
             const uint32_t y = x > shift ? x - shift : 0u;
             if ((uint32_t)m < lg) {
                 const uint32_t dv = y - old;
+                most = max(most, dv);
                 if (!have) { want = dv; have = true; } else if (dv != want) same = false;
                 top = max(top, y);
             }
@@ -641,22 +644,23 @@ __device__ __forceinline__ int least_period_dag(const KParams &P, const DagTable
     };
     reset();
     bool done = false;
-    uint32_t T = 0;
+    uint32_t T = 0, bound = (uint32_t)P.UB;
     for (int j = 0; j < P.dag_tries; j++) {
         if (__ballot(!done) == 0) break;
         sweep_window_dag<CNT::kTypeBits>(P, Tb, prog, state);
-        uint32_t delta = 0, top;
-        const bool eig = boundary_dag<DM>(P, Tb, state, lead, prevfree, 0u, true, delta, top);
+        uint32_t delta = 0, top, most;
+        const bool eig = boundary_dag<DM>(P, Tb, state, lead, prevfree, 0u, true, delta, top, most);
+        // no cycle ratio exceeds the largest growth of one sweep, whatever the values before it
+        bound = min(bound, most);
         if (!done && eig) { T = delta; done = true; }
     }
     if (__ballot(!done) == 0) return (int)T;
-    // bisection, the same number of steps in every lane; lanes that have their period keep a fixed interval
+    // bisection between the lower bound and the least growth seen (a growth of the last sweeps is within a unit or two of
+    // the ratio, so one to three steps instead of the seven or eight from the serial time), until every lane has its period
     int crossing = P.D;
     for (int r = 0; r < P.ntok; r++) crossing += (int)lead.get((uint32_t)P.ring_head[r]);
-    uint32_t lo = done ? T : (uint32_t)P.LB, hi = done ? T : (uint32_t)P.UB;
-    int steps = 0;
-    for (uint32_t span = (uint32_t)(P.UB - P.LB); span; span >>= 1) steps++;
-    for (int it = 0; it < steps; it++) {
+    uint32_t lo = done ? T : (uint32_t)P.LB, hi = done ? T : max(bound, (uint32_t)P.LB);
+    while (__ballot(lo < hi) != 0) {
         const uint32_t mid = lo + (hi - lo) / 2u;
         const bool open = lo < hi;
         reset();
@@ -665,8 +669,8 @@ __device__ __forceinline__ int least_period_dag(const KParams &P, const DagTable
         for (int w = 0; w < kMaxKW * kMaxNRW + kMaxDW + 2; w++) {
             if (__ballot(!decided) == 0) break;
             sweep_window_dag<CNT::kTypeBits>(P, Tb, prog, state);
-            uint32_t zero = 0, top;
-            const bool rest = boundary_dag<DM>(P, Tb, state, lead, prevfree, mid, false, zero, top);
+            uint32_t zero = 0, top, most;
+            const bool rest = boundary_dag<DM>(P, Tb, state, lead, prevfree, mid, false, zero, top, most);
             if (!decided) {
                 if (rest) { decided = true; feasible = true; }
                 else if (top > (uint32_t)P.UB || w > crossing + 1) { decided = true; feasible = false; }
@@ -1218,7 +1222,7 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
     } else if (P.ranked) {
         // Ranks by mixed-radix digits of the index, orders and leads from tables by rank.  (Unranking symbol by symbol, up to
         // four 64-bit counts from memory per position, and 64-bit divisions were most of the time of a space whose
-        // candidates mostly deadlock in their first blocks: 2^26 candidates of 32 blocks on 4 devices 6.8 -> CANMS ms.)
+        // candidates mostly deadlock in their first blocks: 2^26 candidates of 32 blocks on 4 devices 6.8 -> 2.5 ms.)
         uint64_t rest = idx;
 #pragma unroll
         for (int d = 0; d < DM; d++) {
@@ -2153,7 +2157,8 @@ LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks)
 // 1.00 of the time; smaller windows lose 5 to 10 % by a queue where most candidates fit, and gain as much where few do).
 // Blocks on several devices: two words, whose steps are the dearest; with `adapt` the waves of a long launch find the number
 // themselves (the kernel says how).
-// With repair, when every candidate's peak is wanted, none leaves early: all of the window, no queue.
+// With repair, when every candidate's peak is wanted, none leaves early: all of the window, no queue (256 blocks on 8
+// devices 0.97 of the time; on up to 4 devices, whose queue moves half the words, 1.02, and they keep it).
 static int stage_words(const KParams &kp, bool peaks, int &adapt)
 {
     const int nwords = (kp.total + 5) / 6;
@@ -2162,7 +2167,7 @@ static int stage_words(const KParams &kp, bool peaks, int &adapt)
         const int want = atoi(env);
         if (want >= 0 && want <= nwords) { adapt = 0; return want; }
     }
-    if (peaks && kp.space == kSampledRepair) { adapt = 0; return nwords; }
+    if (peaks && kp.space == kSampledRepair && (kp.fast_tp || kp.D > 4 || nwords < 10)) { adapt = 0; return nwords; }
     if (kp.fast_tp) return nwords > 2 ? 2 : nwords;
     return nwords >= 10 ? 3 + (nwords - 10) * 9 / 33 : nwords;
 }
@@ -2236,7 +2241,10 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
     const int blocks = need < (uint64_t)s.blocks ? (int)need : s.blocks;
     if (blocks < 1) return 0;
     fast_fn ff = general ? nullptr : pick_fast(kp);
-    if (!ff && kp.graph_ok && !general) {
+    // (a few candidates of a few blocks: one launch instead of the graph kernel's and the list's; 8 candidates of 6 blocks
+    // 37.6 against 41.1 us a call)
+    const bool tiny = !wide_problem(kp) && kp.total <= 12 && count <= 4096;
+    if (!ff && kp.graph_ok && !general && !tiny) {
         // (every problem its tables hold: on 24 blocks of three devices 4.5 times the general kernel's rate, on 96 to 288
         // blocks 34 to 78 times)
         int rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, (uint32_t *)((char *)ws + ring_offset(s.blocks, num_cus)), st);
