@@ -876,10 +876,22 @@ extern "C" int tessel_reset(tessel_problem *p)
     return e ? hip_fail(p, e) : TESSEL_OK;
 }
 
-// One launch and one copy: the candidate of the running best is decoded on the device from the record there, and record
-// and decoded candidate, which lie in a row, come back together.
+// The running best as it is on the device, into p->result and p->detail.  The record is read on every call: scoring
+// launches that the caller captured in a graph change it when they are replayed, without a call of this library.
+// Where nothing has been scored through this handle since the last reading, the record alone comes back, and the candidate
+// decoded then stands if the record still names it.  Else one launch and one copy: the candidate is decoded on
+// the device from the record there, and record and decoded candidate, which lie in a row, come back together.
 static int read_back(tessel_problem *p)
 {
+    if (!p->best_dirty) {
+        DevResult now;
+        hipError_t e = hipMemcpyAsync(&now, (char *)p->ws + kWsResultOff, sizeof now, hipMemcpyDeviceToHost, p->stream);
+        if (e != hipSuccess) return hip_fail(p, (int)e);
+        e = hipStreamSynchronize(p->stream);
+        if (e != hipSuccess) return hip_fail(p, (int)e);
+        if (now.period == p->result.period && now.index == p->result.index) { p->result = now; return TESSEL_OK; }
+        p->best_dirty = true;
+    }
     int le = launch_detail(p->ws, p->stream);
     if (le) return hip_fail(p, le);
     struct { unsigned char bytes[kWsDetailOff]; DevDetail detail; } both;
@@ -897,16 +909,13 @@ static int fetch_best(tessel_problem *p)
 {
     if (!p->ws || !p->ws_ready) { memset(&p->result, 0, sizeof p->result); p->result.period = INT_MAX; return TESSEL_OK; }
     if (!owns_workspace(p)) return TESSEL_E_WORKSPACE;       // another handle has bound the buffer since: the running best is gone
-    if (!p->best_dirty) {                                    // nothing scored since the best was read back
-        hipError_t e = hipStreamSynchronize(p->stream);
-        return e != hipSuccess ? hip_fail(p, (int)e) : TESSEL_OK;
-    }
     int rc = read_back(p);
     if (rc) return rc;
     if (p->result.overflow && !p->safe_pieces) {
         // some launch left more candidates unfinished than its list holds, so the running best is incomplete:
         // score every range again, from now on in pieces small enough for the lists
         p->safe_pieces = true;
+        p->best_dirty = true;
         int le = launch_reset(p->ws, p->stream);
         if (le) return hip_fail(p, le);
         for (const auto &r : p->ranges) {
