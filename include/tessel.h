@@ -201,7 +201,8 @@ int  tessel_score_candidates(tessel_problem *p, uint64_t first, uint64_t count,
  * candidates to the general kernel than its list holds (2^20 of a range of up to 2^26: possible only
  * when most periods need more than the fast kernel's ten sweeps), every range scored since the last
  * reset is scored again here in smaller pieces before the result is returned.  WORKSPACE: the buffer
- * was bound to another handle in the meantime. */
+ * was bound to another handle in the meantime.  HIP: also when the period is not the least one of the decoded candidate's
+ * orders (never expected; worked out on the host, apart from the kernels). */
 int  tessel_best(tessel_problem *p, tessel_result *out);
 
 /* Decoded form of the best candidate as the GPU decoded it: leads[K], order_len[D] and

@@ -46,6 +46,8 @@ struct tessel_problem {
     bool force_general = false;         // TESSEL_FORCE_GENERAL=1: score with the general kernel only
     DevDetail detail;
     DevResult result;
+    std::vector<int32_t> starts;        // least start times of the decoded candidate, by type * N_R + occurrence
+    bool period_right = false;          // ... and whether the record's period is its least one
     // index ranges scored since the last reset (adjacent ones merged), and whether launches are cut into the
     // small pieces in which no list of unfinished candidates can overflow
     std::vector<std::pair<uint64_t, uint64_t>> ranges;
@@ -876,6 +878,121 @@ extern "C" int tessel_reset(tessel_problem *p)
     return e ? hip_fail(p, e) : TESSEL_OK;
 }
 
+// ---- host post-processing of the single best candidate ---------------------------------
+namespace {
+
+// Difference constraints of the repeated window for the decoded candidate (Eq. 1 [1] and [3] with the window-to-window
+// lags): block v starts at least w after block u, of the window `lag` before.  By u, the blocks in an executable
+// sequence of one window, so that one pass over `edges` carries a start time through all of it.
+struct Edge { int u, v, w, lag; };
+struct Window {
+    int blocks = 0, most = 0;           // most: no least start time is later (every path visits a block at most once)
+    std::vector<Edge> edges;
+    std::vector<int> from;              // edges of block u: from[u] .. from[u + 1] - 1
+};
+
+// sorts the blocks so that every edge `along` selects goes forward; false: these edges have a cycle
+template <class Along>
+bool in_sequence(const Window &w, Along along, std::vector<int> &sequence)
+{
+    std::vector<int> waits(w.blocks, 0);
+    for (const Edge &e : w.edges) if (along(e)) waits[e.v]++;
+    sequence.clear();
+    for (int u = 0; u < w.blocks; u++) if (waits[u] == 0) sequence.push_back(u);
+    for (size_t k = 0; k < sequence.size(); k++)
+        for (int e = w.from[sequence[k]]; e < w.from[sequence[k] + 1]; e++)
+            if (along(w.edges[e]) && --waits[w.edges[e].v] == 0) sequence.push_back(w.edges[e].v);
+    return (int)sequence.size() == w.blocks;
+}
+
+void sort_edges(Window &w, const std::vector<int> &rank)
+{
+    std::vector<Edge> by(w.edges.size());
+    w.from.assign(w.blocks + 1, 0);
+    for (const Edge &e : w.edges) w.from[rank[e.u] + 1]++;
+    for (int u = 0; u < w.blocks; u++) w.from[u + 1] += w.from[u];
+    std::vector<int> next(w.from.begin(), w.from.end() - 1);
+    for (const Edge &e : w.edges) by[next[rank[e.u]]++] = Edge{rank[e.u], rank[e.v], e.w, e.lag};
+    w.edges.swap(by);
+}
+
+// `rank`: number of block type * N_R + occurrence in the window; false: the device orders cannot be executed
+bool make_window(const tessel_problem *p, const DevDetail &c, Window &w, std::vector<int> &rank)
+{
+    const int NR = p->kp.NR, K = p->kp.K, D = p->kp.D;
+    w.blocks = K * NR; w.most = p->kp.UB;
+    for (size_t e = 0; e < p->dep_src.size(); e++) {
+        int i = p->dep_src[e], j = p->dep_dst[e], delta = c.leads[i] - c.leads[j];
+        for (int q = 0; q < NR; q++) {
+            int qp = q - delta;
+            w.edges.push_back(qp >= 0 ? Edge{i * NR + qp, j * NR + q, p->t[i], 0} : Edge{i * NR + qp + NR, j * NR + q, p->t[i], 1});
+        }
+    }
+    for (int d = 0; d < D; d++) {
+        std::vector<int> occ(K, 0), nodes;
+        for (int k = 0; k < c.order_len[d]; k++) { int g = c.orders[d][k]; nodes.push_back(g * NR + occ[g]++); }
+        for (size_t k = 0; k + 1 < nodes.size(); k++) w.edges.push_back(Edge{nodes[k], nodes[k + 1], p->t[nodes[k] / NR], 0});
+        if (!nodes.empty()) w.edges.push_back(Edge{nodes.back(), nodes.front(), p->t[nodes.back() / NR], 1});
+    }
+    rank.resize(w.blocks);
+    std::vector<int> sequence;
+    for (int u = 0; u < w.blocks; u++) rank[u] = u;
+    sort_edges(w, rank);
+    if (!in_sequence(w, [](const Edge &e) { return e.lag == 0; }, sequence)) return false;
+    for (int k = 0; k < w.blocks; k++) rank[sequence[k]] = k;
+    sort_edges(w, rank);
+    return true;
+}
+
+// the least non-negative start times at period T; false: there are none, some cycle takes longer than T per window
+bool least_starts(const Window &w, int T, std::vector<int> &s)
+{
+    std::vector<int> by(w.blocks, -1), mark(w.blocks);
+    s.assign(w.blocks, 0);
+    for (int pass = 0; pass <= w.blocks; pass++) {
+        bool changed = false;
+        for (const Edge &e : w.edges) {
+            const int v = s[e.u] + e.w - e.lag * T;
+            if (v <= s[e.v]) continue;
+            if (v > w.most) return false;
+            s[e.v] = v; by[e.v] = e.u; changed = true;
+        }
+        if (!changed) return true;
+        // a block that owes its start time to itself: that cycle goes on for ever
+        std::fill(mark.begin(), mark.end(), -1);
+        for (int u = 0; u < w.blocks; u++) {
+            int v = u;
+            while (v >= 0 && mark[v] < 0) { mark[v] = u; v = by[v]; }
+            if (v >= 0 && mark[v] == u) return false;
+        }
+    }
+    return false;
+}
+
+// Whether T is the least period, worked out without the kernels' sweeps: there are start times at T, and either some cycle of
+// constraints is tight under them, so that it takes T per window exactly (times are positive: such a cycle
+// crosses a window boundary), or there are no start times at T - 1 (a ratio that is no whole number, rounded up).
+bool is_least_period(const Window &w, int T, std::vector<int> &s)
+{
+    if (!least_starts(w, T, s)) return false;
+    std::vector<int> other;
+    if (!in_sequence(w, [&](const Edge &e) { return s[e.u] + e.w - e.lag * T == s[e.v]; }, other)) return true;
+    return !least_starts(w, T - 1, other);
+}
+
+// p->starts and p->period_right of the running best just read
+void check_period(tessel_problem *p)
+{
+    Window w;
+    std::vector<int> rank, s;
+    p->starts.assign((size_t)p->kp.K * p->kp.NR, 0);
+    p->period_right = p->detail.status == kOk && make_window(p, p->detail, w, rank) && is_least_period(w, p->result.period, s);
+    if (p->period_right)
+        for (size_t k = 0; k < p->starts.size(); k++) p->starts[k] = s[rank[k]];
+}
+
+}  // namespace
+
 // The running best as it is on the device, into p->result and p->detail.  The record is read on every call: scoring
 // launches that the caller captured in a graph change it when they are replayed, without a call of this library.
 // Where nothing has been scored through this handle since the last reading, the record alone comes back, and the candidate
@@ -902,6 +1019,7 @@ static int read_back(tessel_problem *p)
     if (e != hipSuccess) return hip_fail(p, (int)e);
     memcpy(&p->result, both.bytes, sizeof(DevResult));
     p->detail = both.detail;
+    if (p->result.period != INT_MAX) check_period(p);
     return TESSEL_OK;
 }
 
@@ -947,47 +1065,9 @@ extern "C" int tessel_best(tessel_problem *p, tessel_result *out)
     out->index = p->result.index;
     out->peak_max = INT_MIN;
     for (int d = 0; d < p->kp.D; d++) { out->peak_mem[d] = p->detail.peak[d]; out->peak_max = std::max(out->peak_max, p->detail.peak[d]); }
-    if (p->detail.status != kOk || p->detail.period != p->result.period) return TESSEL_E_HIP;   // kernels disagree: never expected
+    if (!p->period_right) return TESSEL_E_HIP;               // the decoded candidate has another period: never expected
     return TESSEL_OK;
 }
-
-// ---- host post-processing of the single best candidate ---------------------------------
-namespace {
-
-struct Edge { int u, v, w, lag; };
-
-// Difference constraints of the repeated window for the decoded candidate (Eq. 1 [1] and [3]
-// with the window-to-window lags), then the least non-negative start times at period T.
-std::vector<int> least_starts(const tessel_problem *p, const DevDetail &c, int T)
-{
-    const int NR = p->kp.NR, K = p->kp.K, D = p->kp.D;
-    std::vector<Edge> edges;
-    for (size_t e = 0; e < p->dep_src.size(); e++) {
-        int i = p->dep_src[e], j = p->dep_dst[e], delta = c.leads[i] - c.leads[j];
-        for (int q = 0; q < NR; q++) {
-            int qp = q - delta;
-            edges.push_back(qp >= 0 ? Edge{i * NR + qp, j * NR + q, p->t[i], 0} : Edge{i * NR + qp + NR, j * NR + q, p->t[i], 1});
-        }
-    }
-    for (int d = 0; d < D; d++) {
-        std::vector<int> occ(K, 0), nodes;
-        for (int k = 0; k < c.order_len[d]; k++) { int g = c.orders[d][k]; nodes.push_back(g * NR + occ[g]++); }
-        for (size_t k = 0; k + 1 < nodes.size(); k++) edges.push_back(Edge{nodes[k], nodes[k + 1], p->t[nodes[k] / NR], 0});
-        if (!nodes.empty()) edges.push_back(Edge{nodes.back(), nodes.front(), p->t[nodes.back() / NR], 1});
-    }
-    std::vector<int> s(K * NR, 0);
-    for (int pass = 0; pass <= K * NR; pass++) {
-        bool changed = false;
-        for (const Edge &e : edges) {
-            int v = s[e.u] + e.w - e.lag * T;
-            if (v > s[e.v]) { s[e.v] = v; changed = true; }
-        }
-        if (!changed) break;
-    }
-    return s;
-}
-
-}  // namespace
 
 extern "C" int tessel_best_candidate(tessel_problem *p, int32_t *leads, int32_t *order_len, int32_t *orders, int32_t *starts)
 {
@@ -1000,8 +1080,8 @@ extern "C" int tessel_best_candidate(tessel_problem *p, int32_t *leads, int32_t 
     if (order_len) for (int d = 0; d < p->kp.D; d++) order_len[d] = c.order_len[d];
     if (orders) for (int d = 0; d < p->kp.D; d++) for (int k = 0; k < kMaxPos; k++) orders[d * kMaxPos + k] = k < c.order_len[d] ? c.orders[d][k] : -1;
     if (starts) {
-        std::vector<int> s = least_starts(p, c, c.period);
-        for (size_t k = 0; k < s.size(); k++) starts[k] = s[k];
+        if (!p->period_right) return TESSEL_E_HIP;           // no start times at that period: never expected
+        std::copy(p->starts.begin(), p->starts.end(), starts);
     }
     return TESSEL_OK;
 }
@@ -1098,7 +1178,7 @@ static int complete_with(tessel_problem *p, tessel_schedule *out, uint64_t ordin
     rc = greedy_phase(false);
     if (rc) return rc;
     out->makespan = *std::max_element(finish.begin(), finish.end());
-    out->period = c.period;
+    out->period = p->result.period;
     out->num_windows = R;
     return TESSEL_OK;
 }

@@ -7,7 +7,7 @@
 // Bound by the chain of dependent instructions of a round.  One lane that walked the whole candidate and swept its
 // window again took 0.93 ms for 256 blocks on 8 devices and 2.9 ms on 16, longer than scoring 10^5 candidates; this
 // wave with counters in LDS 0.26 and 0.155 ms, with counters in registers 0.149 and 0.119 ms.
-// The period is the one the scoring kernel found.
+// The period in the record is checked against the decoded orders by the host (check_period in tessel_api.cpp).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <limits.h>
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kWave) void detail_kernel(const KParams *__restrict
     if (status == kOk && __ballot(here && peak > P.M) != 0) status = kMem;
     if (lane < kMaxDW) { out->peak[lane] = here ? peak : 0; out->order_len[lane] = len; }
     if (lane < K) out->leads[lane] = (int)lead[lane];
-    if (lane == 0) { out->status = status; out->period = res->period; out->index = idx; }
+    if (lane == 0) { out->status = status; out->index = idx; }
 }
 
 int launch_detail(void *ws, void *stream)

@@ -179,7 +179,7 @@ struct DevResult {
 
 // Decoded best candidate, written by the detail kernel.
 struct DevDetail {
-    int32_t status, period;      // status -1: nothing decoded since the search began
+    int32_t status, pad;         // status -1: nothing decoded since the search began
     uint64_t index;
     int32_t peak[kMaxDW];
     int32_t leads[kMaxKW];
