@@ -240,7 +240,7 @@ constexpr size_t kWsCompMatrixOff = kWsCompParamsOff + 1024;              // Com
 constexpr size_t kWsGraphOff = kWsCompMatrixOff + 3072;                   // GraphTab of the bound problem
 constexpr size_t kWsGraphMax = 24576;
 constexpr size_t kWsBlockRecOff = kWsGraphOff + kWsGraphMax;
-constexpr int kDeferBlocks = 64;                                // grid of the deferred pass
+constexpr int kDeferBlocks = 64;                                // grid of the general kernel behind the fast one
 constexpr int kFirstPassTries = 2;                              // sweeps before a candidate queues for the longer search
 constexpr uint64_t kMaxPerLaunch = 1ull << 26;                  // candidates per pass of the kernels
 constexpr uint64_t kSafePerLaunch = 1ull << 20;                 // ... at which no list can overflow (<= both list capacities)
@@ -304,7 +304,7 @@ struct GraphTab {
 
 static_assert(sizeof(GraphTab) <= kWsGraphMax, "graph tables must fit their workspace slot");
 
-struct LaunchShape { int blocks, threads; size_t lds_bytes; };
+struct LaunchShape { int blocks, list_blocks, threads; size_t lds_bytes; };   // list_blocks: of the general kernel over the list
 
 // tessel_graph.hip
 const void *graph_kernel(const KParams &kp);

@@ -664,7 +664,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         }
         if (left_open && cls != 1u) {
             const uint32_t at = atomicAdd(out_count, 1u);
-            if (at < out_cap) out_list[at] = idx; else *overflow = 1u;
+            if (at < out_cap) out_list[at] = idx;                // (more than that: the general kernel scores the whole range)
         }
         if (cls == 1u) nretry += (uint32_t)__builtin_popcountll(__ballot(left_open));
         if (have) lds_store8(st_row + slot, left_open && cls == 1u ? 2u : 0u);

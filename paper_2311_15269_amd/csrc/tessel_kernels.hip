@@ -1852,13 +1852,19 @@ template <int DM, int VM>
 __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__ Pp, uint64_t first, uint64_t count,
                                                      BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
                                                      int32_t *__restrict__ peak_out, const uint64_t *__restrict__ list, const uint32_t *__restrict__ list_count,
-                                                     uint32_t *far, int where)
+                                                     bool whole, uint32_t *far, int where)
 {
     const KParams &P = *Pp;
     extern __shared__ uint32_t lds[];
     constexpr bool wide = DM > kMaxD;
-    // with a list: score the listed candidates (all inside [first, first + count)) instead of the range
-    if (list) count = min(*list_count, kWsListCap);
+    // with a list: score the listed candidates (all inside [first, first + count)) instead of the range; `whole`: the range
+    // after all where the list was too short for them.  (A workgroup without a candidate leaves no record.)
+    if (list) {
+        const uint32_t listed = *list_count;
+        if (whole && listed > kWsListCap) list = nullptr;
+        else count = min(listed, kWsListCap);
+        if ((uint64_t)blockIdx.x * kWave >= count) return;
+    }
     constexpr int KT = wide ? kMaxKW : kMaxK;             // entries of a table by type
     int32_t *t_tab = (int32_t *)lds;
     uint32_t *mask_tab = lds + KT;
@@ -1935,7 +1941,7 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
 // The two instantiations for problems beyond the fast kernel's limits (16 and 32 devices) take as long to compile as
 // everything else in this file: tessel_wide.hip includes this file up to here and holds them, so that the two halves
 // build side by side.
-#define TESSEL_EVAL_KERNEL_ARGS const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *, uint32_t *, int
+#define TESSEL_EVAL_KERNEL_ARGS const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *, bool, uint32_t *, int
 #ifdef TESSEL_WIDE_INSTANTIATIONS
 template __global__ void eval_kernel<16, 1>(TESSEL_EVAL_KERNEL_ARGS);
 template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
@@ -1947,10 +1953,17 @@ extern template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
 // first.  Bound by the latency of the record loads: 4,160 records took one wave 14.6 us (65 dependent rounds), eight
 // waves take 9 to 10.
 constexpr int kMergeThreads = 512;
-__global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__restrict__ recs, int nrecs, DevResult *__restrict__ res,
-                                                                 uint32_t *__restrict__ left_after)
+// `from_range` records of the kernel over the range, then those of the kernel over the list: one for every 64 candidates on
+// it, `from_list` at most.  `whole`: where the list was too short, the second kernel scored the range, and its
+// `from_list` records are all there is.
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__restrict__ recs, int from_range, int from_list, bool whole,
+                                                                 DevResult *__restrict__ res, uint32_t *__restrict__ left_after)
 {
     if (threadIdx.x < kWave) left_after[threadIdx.x] = 0;        // for the next launch
+    const uint32_t listed = res->defer_count;
+    const bool again = whole && listed > kWsListCap;
+    const int start = again ? from_range : 0;
+    const int nrecs = from_range + min(from_list, (int)((min(listed, kWsListCap) + kWave - 1) / kWave));
 
     struct Sum { int best; uint32_t nre; uint64_t best_idx, nev, nsw, nbl, cnt[kNumStatus]; };
     __shared__ Sum part[kMergeThreads / kWave];
@@ -1958,7 +1971,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__
     a.best = INT_MAX; a.nre = 0; a.best_idx = 0; a.nev = a.nsw = a.nbl = 0;
 #pragma unroll
     for (int s = 0; s < kNumStatus; s++) a.cnt[s] = 0;
-    for (int k = threadIdx.x; k < nrecs; k += kMergeThreads) {
+    for (int k = start + threadIdx.x; k < nrecs; k += kMergeThreads) {
         const BlockRec r = recs[k];
         if (key_less(r.period, r.index, a.best, a.best_idx)) { a.best = r.period; a.best_idx = r.index; }
         a.nre += r.n_retried;
@@ -2023,7 +2036,7 @@ __global__ void reset_kernel(DevResult *res, DevDetail *detail, uint32_t *left_a
 
 // ------------------------------------------------------------------ launchers
 typedef void (*eval_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *,
-                        uint32_t *, int);
+                        bool, uint32_t *, int);
 typedef void (*fast_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, int, int, uint64_t *, uint32_t *,
                         uint32_t, uint32_t *, uint32_t *, uint32_t, int, int, uint32_t *);
 
@@ -2126,28 +2139,57 @@ static size_t fast_lds_bytes(const KParams &kp)
            (share ? 0 : (size_t)(fast_dm(kp) * 2 + ntok) * kWave * 4);
 }
 
-LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks)
+// resident workgroups per CU as the runtime computes them from LDS and registers, 16 at most
+static int blocks_per_cu(const void *fn, size_t lds_bytes)
 {
-    LaunchShape s;
-    s.threads = kWave;
-    fast_fn ff = pick_fast(kp);
-    s.lds_bytes = ff ? fast_lds_bytes(kp) : kp.graph_ok ? kp.graph_lds : general_lds_bytes(kp);
-    // resident workgroups per CU as the runtime computes them from LDS and registers
     int per_cu = 0;
-    const void *fn = ff ? (const void *)ff : kp.graph_ok ? graph_kernel(kp) : (const void *)pick_kernel(kp);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, s.lds_bytes) != hipSuccess || per_cu < 1) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, lds_bytes) != hipSuccess || per_cu < 1) {
         (void)hipGetLastError();
-        per_cu = (int)((160 * 1024) / ((s.lds_bytes + 511) / 512 * 512));
+        per_cu = (int)((160 * 1024) / ((lds_bytes + 511) / 512 * 512));
     }
     if (per_cu > 16) per_cu = 16;
-    if (!kp.graph_ok && far_mode(kp) == 2 && per_cu > 4) per_cu = 4;                 // (keeps the state regions of a launch small)
     if (const char *env = getenv("TESSEL_BLOCKS_PER_CU")) {        // tuning knob: fewer resident workgroups per CU
         int want = atoi(env);
         if (want >= 1 && want < per_cu) per_cu = want;
     }
-    if (per_cu < 1) per_cu = 1;
-    s.blocks = num_cus * per_cu;
-    if (max_blocks > 0 && s.blocks > max_blocks) s.blocks = max_blocks;      // a workspace with room for fewer queues
+    return per_cu < 1 ? 1 : per_cu;
+}
+
+static int general_blocks_per_cu(const KParams &kp)
+{
+    const int per_cu = blocks_per_cu((const void *)pick_kernel(kp), general_lds_bytes(kp));
+    return far_mode(kp) == 2 && per_cu > 4 ? 4 : per_cu;             // (keeps the state regions of a launch small)
+}
+
+static size_t ring_offset(int records, int num_cus);
+
+// Behind the graph kernel the general one gets the grid that it has where it scores a problem alone: there are problems
+// whose periods the graph kernel's sweeps hardly ever settle (cycles whose time is no multiple of the windows they cross; 32
+// chains of two blocks round a ring of 32 devices: none in 2^18), and on 64 workgroups these took 571 ms where the general kernel
+// alone takes 45.  Workgroups beyond the list end at once.
+LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks)
+{
+    LaunchShape s;
+    s.threads = kWave;
+    s.list_blocks = kDeferBlocks;
+    if (fast_fn ff = pick_fast(kp)) {
+        s.lds_bytes = fast_lds_bytes(kp);
+        s.blocks = num_cus * blocks_per_cu((const void *)ff, s.lds_bytes);
+    } else if (kp.graph_ok) {
+        s.lds_bytes = kp.graph_lds;
+        s.blocks = num_cus * blocks_per_cu(graph_kernel(kp), s.lds_bytes);
+        s.list_blocks = num_cus * general_blocks_per_cu(kp);
+    } else {
+        s.lds_bytes = general_lds_bytes(kp);
+        s.blocks = num_cus * general_blocks_per_cu(kp);
+    }
+    if (max_blocks > 0) {                                            // the library's own buffer: room for fewer
+        if (s.blocks > max_blocks) s.blocks = max_blocks;
+        if (kp.graph_ok && far_bytes(kp) > 0) {
+            const size_t fit = (kScratchBytes - ring_offset(s.blocks + s.list_blocks, num_cus)) / far_bytes(kp);
+            if ((size_t)s.list_blocks > fit) s.list_blocks = (int)fit;
+        }
+    }
     return s;
 }
 
@@ -2181,13 +2223,14 @@ static uint32_t ring_words(const KParams &kp)
     return (uint32_t)(program > stage ? program : stage) * kRingSlots;
 }
 
-// behind the records of one launch: one per workgroup of the scoring kernels, or one (smaller) per workgroup of the
+// behind the records of one launch (one per workgroup of the scoring kernels), or one (smaller) per workgroup of the
 // completion search, whose grid is 16 workgroups per compute unit at most
-static size_t ring_offset(int blocks, int num_cus)
+static size_t ring_offset(int records, int num_cus)
 {
-    const size_t eval = (size_t)(blocks + kDeferBlocks) * sizeof(BlockRec), comp = (size_t)num_cus * 16 * sizeof(CompRec);
+    const size_t eval = (size_t)records * sizeof(BlockRec), comp = (size_t)num_cus * 16 * sizeof(CompRec);
     return (kWsBlockRecOff + (eval > comp ? eval : comp) + 256 + 255) & ~(size_t)255;
 }
+static size_t ring_offset(const LaunchShape &s, int num_cus) { return ring_offset(s.blocks + s.list_blocks, num_cus); }
 
 // what a workgroup of the scoring kernel owns behind the records: queues of the fast kernel, slots of the graph kernel, or
 // state and program of the general one
@@ -2199,20 +2242,13 @@ static size_t block_bytes(const KParams &kp)
 size_t eval_workspace_bytes(const KParams &kp, int num_cus, int max_blocks)
 {
     const LaunchShape s = eval_launch_shape(kp, num_cus, max_blocks);
-    // (behind the slots of the graph kernel what the general kernel needs for the candidates left to it)
-    return ring_offset(s.blocks, num_cus) + (size_t)s.blocks * block_bytes(kp) + (kp.graph_ok ? (size_t)kDeferBlocks * far_bytes(kp) : 0);
-}
-
-// where the state regions of the general kernel's workgroups start (wide problems whose state does not fit the LDS)
-static uint32_t *far_base(const KParams &kp, void *ws, int num_cus, int max_blocks)
-{
-    if (!far_mode(kp)) return nullptr;
-    const int blocks = eval_launch_shape(kp, num_cus, max_blocks).blocks;
-    return (uint32_t *)((char *)ws + ring_offset(blocks, num_cus) + (kp.graph_ok ? (size_t)blocks * block_bytes(kp) : 0));
+    // (state and program of the general kernel's workgroups lie where the graph kernel's slots lay: it runs afterwards)
+    const size_t own = (size_t)s.blocks * block_bytes(kp), list = kp.graph_ok ? (size_t)s.list_blocks * far_bytes(kp) : 0;
+    return ring_offset(s, num_cus) + (own > list ? own : list);
 }
 
 static int launch_general(const KParams &kp, const KParams *kp_dev, uint64_t first, uint64_t count, int blocks, BlockRec *recs,
-                          int32_t *code, int32_t *peak, const uint64_t *list, const uint32_t *list_count,
+                          int32_t *code, int32_t *peak, const uint64_t *list, const uint32_t *list_count, bool whole,
                           uint32_t *far, hipStream_t st)
 {
     const int where = far_mode(kp);
@@ -2223,23 +2259,29 @@ static int launch_general(const KParams &kp, const KParams *kp_dev, uint64_t fir
         hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, list, list_count, far, where);
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, list, list_count, whole, far, where);
     return (int)hipGetLastError();
 }
 
+// block records of one pass, as merge_kernel takes them
+struct Records { int from_range = 0, from_list = 0; bool whole = false; };
+
 // Scores [first, first+count).  Where the problem allows it: the fast kernel (a short eigenvector search, a longer one
-// for the candidates that did not converge), then the general kernel over what it could not finish (next to nothing).  Otherwise the general kernel alone.  Returns the number of block records written (recs may be
-// null: per-candidate outputs only) or a negative HIP error.
+// for the candidates that did not converge) or the graph kernel, then the general kernel over what these could not finish (next
+// to nothing in most problems).  Otherwise the general kernel alone.  `recs` may be null: per-candidate outputs only.
+// Returns 0 or a HIP error.
 static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *ws, int num_cus, int max_blocks, BlockRec *recs,
-                       int32_t *code, int32_t *peak, bool general, hipStream_t st)
+                       int32_t *code, int32_t *peak, bool general, hipStream_t st, Records &made)
 {
     const KParams *kp_dev = (const KParams *)((char *)ws + kWsParamsOff);
     DevResult *res = (DevResult *)((char *)ws + kWsResultOff);
     uint64_t *list = (uint64_t *)((char *)ws + kWsListOff);
-    LaunchShape s = eval_launch_shape(kp, num_cus, max_blocks);
-    uint64_t need = (count + kWave - 1) / kWave;
+    const LaunchShape s = eval_launch_shape(kp, num_cus, max_blocks);
+    const uint64_t need = (count + kWave - 1) / kWave;
     const int blocks = need < (uint64_t)s.blocks ? (int)need : s.blocks;
+    const int list_blocks = need < (uint64_t)s.list_blocks ? (int)need : s.list_blocks;
     if (blocks < 1) return 0;
+    uint32_t *behind = (uint32_t *)((char *)ws + ring_offset(s, num_cus));      // queues, slots, or the general kernel's state
     fast_fn ff = general ? nullptr : pick_fast(kp);
     // (a few candidates of a few blocks: one launch instead of the graph kernel's and the list's; 8 candidates of 6 blocks
     // 37.6 against 41.1 us a call)
@@ -2247,28 +2289,24 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
     if (!ff && kp.graph_ok && !general && !tiny) {
         // (every problem its tables hold: on 24 blocks of three devices 4.5 times the general kernel's rate, on 96 to 288
         // blocks 34 to 78 times)
-        int rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, (uint32_t *)((char *)ws + ring_offset(s.blocks, num_cus)), st);
-        if (rc) return -rc;
-        rc = launch_general(kp, kp_dev, first, count, kDeferBlocks, recs ? recs + blocks : nullptr, code, peak, list,
-                            &res->defer_count, far_base(kp, ws, num_cus, max_blocks), st);
-        return rc ? -rc : blocks + kDeferBlocks;
+        int rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, behind, st);
+        if (rc) return rc;
+        made.from_range = blocks; made.from_list = list_blocks; made.whole = true;
+        return launch_general(kp, kp_dev, first, count, list_blocks, recs ? recs + blocks : nullptr, code, peak, list,
+                              &res->defer_count, true, behind, st);
     }
-    if (!ff) {
-        int rc = launch_general(kp, kp_dev, first, count, blocks, recs, code, peak, nullptr, nullptr,
-                                far_base(kp, ws, num_cus, max_blocks), st);
-        return rc ? -rc : blocks;
-    }
+    made.from_range = blocks;
+    if (!ff) return launch_general(kp, kp_dev, first, count, blocks, recs, code, peak, nullptr, nullptr, false, behind, st);
     const size_t lds = fast_lds_bytes(kp);
-    uint32_t *ring = (uint32_t *)((char *)ws + ring_offset(s.blocks, num_cus));
     int adapt = 0;
     const int stage = stage_words(kp, peak != nullptr, adapt);
     hipLaunchKernelGGL(ff, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, kp.eigen_tries, kp.retry_tries,
-                       list, &res->defer_count, kWsListCap, &res->overflow, ring, ring_words(kp), stage, adapt, (uint32_t *)((char *)ws + kWsLeftOff));
+                       list, &res->defer_count, kWsListCap, &res->overflow, behind, ring_words(kp), stage, adapt, (uint32_t *)((char *)ws + kWsLeftOff));
     int rc = (int)hipGetLastError();
-    if (rc) return -rc;
-    rc = launch_general(kp, kp_dev, first, count, kDeferBlocks, recs ? recs + blocks : nullptr, code, peak, list,
-                        &res->defer_count, nullptr, st);
-    return rc ? -rc : blocks + kDeferBlocks;
+    if (rc) return rc;
+    made.from_list = list_blocks;
+    return launch_general(kp, kp_dev, first, count, list_blocks, recs ? recs + blocks : nullptr, code, peak, list,
+                          &res->defer_count, false, nullptr, st);
 }
 
 int launch_eval(const KParams &kp, uint64_t first, uint64_t count, void *ws, int num_cus, int max_blocks, void *stream, uint64_t max_piece)
@@ -2279,12 +2317,13 @@ int launch_eval(const KParams &kp, uint64_t first, uint64_t count, void *ws, int
     // pieces of at most max_piece candidates, so that the lists of unfinished candidates stay small
     for (uint64_t done = 0; done < count;) {
         const uint64_t piece = count - done < max_piece ? count - done : max_piece;
-        int n = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, recs, nullptr, nullptr, false, st);
-        if (n < 0) return -n;
-        if (n > 0) {
-            hipLaunchKernelGGL(merge_kernel, dim3(1), dim3(kMergeThreads), 0, st, recs, n, res,
+        Records made;
+        int rc = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, recs, nullptr, nullptr, false, st, made);
+        if (rc) return rc;
+        if (made.from_range > 0) {
+            hipLaunchKernelGGL(merge_kernel, dim3(1), dim3(kMergeThreads), 0, st, recs, made.from_range, made.from_list, made.whole, res,
                                (uint32_t *)((char *)ws + kWsLeftOff));
-            int rc = (int)hipGetLastError();
+            rc = (int)hipGetLastError();
             if (rc) return rc;
         }
         done += piece;
@@ -2301,10 +2340,12 @@ int launch_score(const KParams &kp, uint64_t first, uint64_t count, int32_t *cod
     const uint64_t max_piece = kSafePerLaunch;
     for (uint64_t done = 0; done < count;) {
         const uint64_t piece = count - done < max_piece ? count - done : max_piece;
-        int n = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, nullptr, code + done, peak ? peak + done : nullptr, general, st);
-        if (n < 0) return -n;
+        Records made;
+        int rc = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, nullptr, code + done, peak ? peak + done : nullptr, general, st,
+                             made);
+        if (rc) return rc;
         hipLaunchKernelGGL(clear_defer_kernel, dim3(1), dim3(kWave), 0, st, res, (uint32_t *)((char *)ws + kWsLeftOff));
-        int rc = (int)hipGetLastError();
+        rc = (int)hipGetLastError();
         if (rc) return rc;
         done += piece;
     }
@@ -2351,7 +2392,7 @@ int scratch_workspace(void **ptr, size_t *bytes)
 int eval_blocks_that_fit(const KParams &kp, int num_cus, size_t bytes)
 {
     const size_t per_block = sizeof(BlockRec) + block_bytes(kp);
-    const size_t fixed = ring_offset(0, num_cus) + 512 + (kp.graph_ok ? (size_t)kDeferBlocks * far_bytes(kp) : 0);
+    const size_t fixed = ring_offset(eval_launch_shape(kp, num_cus, 0).list_blocks, num_cus) + 512;
     if (bytes < fixed + per_block) return 0;
     int blocks = (int)std::min<size_t>((bytes - fixed) / per_block, (size_t)num_cus * 16);
     while (blocks > 0 && eval_workspace_bytes(kp, num_cus, blocks) > bytes) blocks--;
