@@ -1465,8 +1465,8 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
     // the program is two register vectors: one loop for each, so that a store never has to choose between them
     // (`left_after`: how many candidates are still alive goes into the launch's histogram)
     auto note = [&](int wi) {
-        if (TP && MODE != 0 && left_after && wi + 1 < w_to) {
-            const uint32_t alive = (uint32_t)__builtin_popcountll(__ballot(repair ? worst <= C.M : building));
+        if (TP && repair && left_after && wi + 1 < w_to) {
+            const uint32_t alive = (uint32_t)__builtin_popcountll(__ballot(worst <= C.M));
             if (lane == 0) __hip_atomic_fetch_add(left_after + wi + 1, alive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     };
@@ -1603,13 +1603,15 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     uint32_t *ring1 = ring_base + (size_t)blockIdx.x * 3u * ring_words, *ring2 = ring1 + ring_words, *ring3 = ring2 + ring_words;
     uint32_t head1 = 0, count1 = 0, head2 = 0, count2 = 0, head3 = 0, count3 = 0, nretry = 0, nblocks = 0;           // wave-uniform
     const int nwords = C.nwords;
-    // Program words of phase A: `stage_words`, or, in the variants for blocks on several devices where the waves have many
+    // Program words of phase A: `stage_words`, or, in the repair variants for blocks on several devices where the waves have many
     // rounds of candidates to come (`adapt`), what the launch's first candidates ask for: the first two rounds are built in
     // one go; one wave in 16 adds to a histogram after how many words its candidates were out, and then every wave takes
     // the number of words that costs the fewest lane words: 64 w in phase A, and for the candidates alive then the rest of the words
     // and the way through the queue.  How early candidates leave depends on cap, times and leads, not on sizes: with a block
     // on all of four devices and 7 words a window the best number is 1 (0.36 of the time of building in one go), 2
-    // (0.50) or 7 (2 words: 1.00 to 1.04) by the cap alone.  (A wave that goes by its own 64 candidates is off by as much as
+    // (0.50) or 7 (2 words: 1.00 to 1.04) by the cap alone.  The way through the queue is counted, not fitted; what the waves
+    // choose is within 5 % of the best fixed number in launches of 60 rounds (13 % at worst: the two rounds of the start).  (A
+    // wave that goes by its own 64 candidates is off by as much as
     // the best number gains, and the launch ends with the slowest wave.  In the other variants the best number is near the one by
     // size, and the histogram's code costs them registers: 5 to 7 % of the time on 256 blocks.)
     int wordsA, chunksA;
@@ -1742,7 +1744,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
 
     const uint64_t stride = (uint64_t)gridDim.x * kWave;
     const uint64_t rounds = (count + stride - 1) / stride;          // the same trip count for every lane of the grid
-    const bool adapting = TP && MODE != 0 && adapt && (MODE == 1 || drop_mem) && rounds >= 12;        // (exhaustive spaces: the decode is most of it, and waves stop early as one)
+    const bool adapting = TP && MODE == 2 && adapt && drop_mem;
     if (adapting) set_stage(nwords);
     // phase A on the next 64 candidates of the wave's share
     auto build_new = [&](uint64_t r) {
@@ -1759,7 +1761,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
         nblocks += (uint32_t)__builtin_popcountll(__ballot(valid)) * (uint32_t)min(C.total, 6 * wordsA);
         if (!split) {
             finish_build(valid, idx, prog);
-            if (!(TP && MODE != 0) || !watch) return;
+            if (!(TP && MODE == 2) || !watch) return;
             if (r == 0) {
                 if (report && lane == 0) __hip_atomic_fetch_add(left_after, (uint32_t)kWave, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 return;
@@ -2197,20 +2199,36 @@ LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks)
 // that exceed the memory cap do so within the first blocks of the window).  Windows of ten words and more: 3 of 11, 6 of 22, 9 of
 // 32, 12 of 43, between the best numbers under tight and under wide caps (against two sevenths rounded up to four: 0.96 to
 // 1.00 of the time; smaller windows lose 5 to 10 % by a queue where most candidates fit, and gain as much where few do).
-// Blocks on several devices: two words, whose steps are the dearest; with `adapt` the waves of a long launch find the number
-// themselves (the kernel says how).
 // With repair, when every candidate's peak is wanted, none leaves early: all of the window, no queue (256 blocks on 8
 // devices 0.97 of the time; on up to 4 devices, whose queue moves half the words, 1.02, and they keep it).
-static int stage_words(const KParams &kp, bool peaks, int &adapt)
+// Blocks on several devices, with repair, by the rounds of candidates that a wave of the grid has.  (Geometric means over 2 to 8
+// devices, 2 to 4 micro-batches, five caps, blocks on all devices or two; windows of 3 to 12 words.)
+//   windows below ten words: all of the window in one round, else two words, whose steps are the dearest: 0.98 of the time of all
+//   of it in one round (0.74 to 1.10), 0.92 in 1.15 rounds, 0.79 in four, 0.69 in eleven; under caps that all candidates
+//   meet 1.02 to 1.05
+//   ten words and more: two sevenths rounded up to four words in up to two rounds, where a second phase for a few
+//   candidates of a wave takes as long as for 64 (two words: 1.15, at worst 1.9 of the time; all of it 1.4), else two words (0.97 in 2.5
+//   rounds, 0.78 in eleven)
+//   24 rounds and more: with `adapt` the waves find the number themselves (against two words: 1.05 in 12 rounds, 1.01 in 16,
+//   0.97 in 24, 0.90 in 60; the kernel says how)
+// Blocks on several devices without repair: all of the window, since a wave stops when its last candidate is out anyway and
+// the memory verdict has to wait (two words 1.00 to 1.05 of the time at 5,000 to 2,000,000 candidates).
+static int stage_words(const KParams &kp, bool peaks, uint64_t count, int blocks, int &adapt)
 {
     const int nwords = (kp.total + 5) / 6;
-    adapt = 1;
+    adapt = 0;
     if (const char *env = getenv("TESSEL_STAGE_WORDS")) {           // tuning knob
         const int want = atoi(env);
-        if (want >= 0 && want <= nwords) { adapt = 0; return want; }
+        if (want >= 0 && want <= nwords) return want;
     }
-    if (peaks && kp.space == kSampledRepair && (kp.fast_tp || kp.D > 4 || nwords < 10)) { adapt = 0; return nwords; }
-    if (kp.fast_tp) return nwords > 2 ? 2 : nwords;
+    if (peaks && kp.space == kSampledRepair && (kp.fast_tp || kp.D > 4 || nwords < 10)) return nwords;
+    if (kp.fast_tp) {
+        if (kp.space != kSampledRepair) return nwords;
+        const uint64_t round = (uint64_t)blocks * kWave;
+        adapt = count >= 24 * round;
+        if (nwords < 10) return nwords > 2 && count > round ? 2 : nwords;
+        return count > 2 * round ? 2 : (nwords * 2 / 7 + 3) / 4 * 4;
+    }
     return nwords >= 10 ? 3 + (nwords - 10) * 9 / 33 : nwords;
 }
 
@@ -2299,7 +2317,7 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
     if (!ff) return launch_general(kp, kp_dev, first, count, blocks, recs, code, peak, nullptr, nullptr, false, behind, st);
     const size_t lds = fast_lds_bytes(kp);
     int adapt = 0;
-    const int stage = stage_words(kp, peak != nullptr, adapt);
+    const int stage = stage_words(kp, peak != nullptr, count, s.blocks, adapt);
     hipLaunchKernelGGL(ff, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, kp.eigen_tries, kp.retry_tries,
                        list, &res->defer_count, kWsListCap, &res->overflow, behind, ring_words(kp), stage, adapt, (uint32_t *)((char *)ws + kWsLeftOff));
     int rc = (int)hipGetLastError();

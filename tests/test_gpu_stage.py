@@ -1,5 +1,5 @@
-"""The fast kernel's first build phase on problems with blocks on several devices, whose length long launches find from
-their own first candidates: the same best candidate and counts as with every length forced, and as the oracle on the
+"""The fast kernel's first build phase on problems with blocks on several devices, whose length goes by the rounds of
+candidates a wave has, and which long launches find from their own first candidates: the same best candidate and counts as with every length forced, and as the oracle on the
 start of the range; blocks on all devices and on some of them."""
 import pytest
 
@@ -33,7 +33,7 @@ SHAPES = [shared_block(2, 2, 4), shared_block(2, 4, 11), shared_block(4, 4, 6), 
 @pytest.mark.parametrize("prob", SHAPES, ids=["%s-nr%d-cap%d-%s" % (p["name"], p["NR"], p["M"], p["space"]) for p in SHAPES])
 def test_lengths_of_the_first_phase(gpu, monkeypatch, prob):
     _compare(gpu, prob, 1 << 30, 1500)
-    n, words = 3500000, (prob["K"] * prob["NR"] + 5) // 6      # enough rounds for the waves to choose
+    n, words = 7000000, (prob["K"] * prob["NR"] + 5) // 6      # enough rounds for the waves to choose (24 of 16 waves a CU)
 
     def best():
         g = gpu.Problem(prob)
@@ -45,3 +45,21 @@ def test_lengths_of_the_first_phase(gpu, monkeypatch, prob):
     for length in sorted({1, 2, words // 2, words} - {0}):
         monkeypatch.setenv("TESSEL_STAGE_WORDS", str(length))
         assert best() == want
+
+
+@pytest.mark.parametrize("prob", [shared_block(8, 4, 6), on_some(8, 4, 9), shared_block(4, 3, 6), shared_block(8, 4, 6, space="sampled_strict")],
+                         ids=lambda p: "%s-nr%d-cap%d-%s" % (p["name"], p["NR"], p["M"], p["space"]))
+def test_lengths_by_rounds(gpu, monkeypatch, prob):
+    """launches of half a round to eleven rounds: the same as in one phase"""
+    for n in (100001, 200003, 300007, 420001, 2100001):
+        got = []
+        for whole in (False, True):
+            if whole:
+                monkeypatch.setenv("TESSEL_STAGE_WORDS", str((prob["K"] * prob["NR"] + 5) // 6))
+            else:
+                monkeypatch.delenv("TESSEL_STAGE_WORDS", raising=False)
+            g = gpu.Problem(prob)
+            g.eval_candidates(1 << 31, n)
+            r = g.best()
+            got.append([r[k] for k in ("period", "index", "peak", "n_evaluated", "n_feasible", "n_reject")])
+        assert got[0] == got[1] and got[0][3] == n
