@@ -2199,8 +2199,11 @@ LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks)
 // that exceed the memory cap do so within the first blocks of the window).  Windows of ten words and more: 3 of 11, 6 of 22, 9 of
 // 32, 12 of 43, between the best numbers under tight and under wide caps (against two sevenths rounded up to four: 0.96 to
 // 1.00 of the time; smaller windows lose 5 to 10 % by a queue where most candidates fit, and gain as much where few do).
-// With repair, when every candidate's peak is wanted, none leaves early: all of the window, no queue (256 blocks on 8
-// devices 0.97 of the time; on up to 4 devices, whose queue moves half the words, 1.02, and they keep it).
+// With repair, when every candidate's peak is wanted, none leaves early: all of the window, no queue, on more than 4 devices where the
+// last round of candidates is full to five eighths or the only one (160 to 256 blocks on 5 to 8 devices: 0.98 of the time in up to one
+// round, 1.75, 2, 3 and 4 rounds; but 1.06, 1.04, 1.02 in 1.1, 1.3, 1.5 and 1.03, 1.02 in 2.1, 3.1, where the waves of a nearly empty round
+// share less of the chip with the queue's phases).  On up to 4 devices, whose queue moves half the words, 0.98 to 1.07 without an order to
+// it: they keep it.  Blocks on several devices: always (0.94 to 0.99).
 // Blocks on several devices, with repair, by the rounds of candidates that a wave of the grid has.  (Geometric means over 2 to 8
 // devices, 2 to 4 micro-batches, five caps, blocks on all devices or two; windows of 3 to 12 words.)
 //   windows below ten words: all of the window in one round, else two words, whose steps are the dearest: 0.98 of the time of all
@@ -2221,10 +2224,11 @@ static int stage_words(const KParams &kp, bool peaks, uint64_t count, int blocks
         const int want = atoi(env);
         if (want >= 0 && want <= nwords) return want;
     }
-    if (peaks && kp.space == kSampledRepair && (kp.fast_tp || kp.D > 4 || nwords < 10)) return nwords;
+    const uint64_t round = (uint64_t)blocks * kWave;
+    if (peaks && kp.space == kSampledRepair && (kp.fast_tp || (kp.D > 4 && (count <= round || 8 * ((count - 1) % round + 1) >= 5 * round))))
+        return nwords;
     if (kp.fast_tp) {
         if (kp.space != kSampledRepair) return nwords;
-        const uint64_t round = (uint64_t)blocks * kWave;
         adapt = count >= 24 * round;
         if (nwords < 10) return nwords > 2 && count > round ? 2 : nwords;
         return count > 2 * round ? 2 : (nwords * 2 / 7 + 3) / 4 * 4;

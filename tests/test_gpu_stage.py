@@ -3,6 +3,7 @@ candidates a wave has, and which long launches find from their own first candida
 start of the range; blocks on all devices and on some of them."""
 import pytest
 
+from paper_2311_15269_amd import workloads as W
 from tests.test_gpu_dag import _compare
 from tests.test_gpu_wide import shared_block
 
@@ -63,3 +64,18 @@ def test_lengths_by_rounds(gpu, monkeypatch, prob):
             r = g.best()
             got.append([r[k] for k in ("period", "index", "peak", "n_evaluated", "n_feasible", "n_reject")])
         assert got[0] == got[1] and got[0][3] == n
+
+
+@pytest.mark.parametrize("D", [4, 5, 8])
+def test_scores_by_rounds(gpu, monkeypatch, D):
+    """scores and peaks of launches that end with a nearly empty and with a nearly full round: the same as in one phase"""
+    prob = W.pipeline_problem(W.folded_placement(D), [1 + (3 * i) % 4 for i in range(2 * D)], [2 + (5 * i) % 7 for i in range(2 * D)],
+                              D, 4, 6, "sampled_repair", seed=9, lead_step_q16=8000)
+    g = gpu.Problem(prob)
+    for n in (200003, 262144, 300007, 470009):
+        monkeypatch.delenv("TESSEL_STAGE_WORDS", raising=False)
+        code, peak = g.score_candidates(12345, n)
+        for words in (4, (prob["K"] * 4 + 5) // 6):
+            monkeypatch.setenv("TESSEL_STAGE_WORDS", str(words))
+            c, p = g.score_candidates(12345, n)
+            assert bool((c == code).all()) and bool((p == peak).all())
