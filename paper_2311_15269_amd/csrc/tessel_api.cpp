@@ -156,13 +156,21 @@ static bool gen_leads(const tessel_problem &p, int K, int NR, std::vector<int8_t
 
 // Tables of the graph kernel (GraphTab).  Leaves ok = 0 where the problem is outside what they hold: more than kGraphOut
 // consumers or the fields of a type's word producers of one type, a type without any dependency, more than kGraphTp types
-// on several devices, memory prefixes beyond 16 bits, an LDS need beyond 64 KB.
+// on several devices, memory prefixes beyond 16 bits, an LDS need beyond 64 KB, and where the general kernel is faster.
 static void graph_tables(const tessel_problem &p, GraphTab &gt)
 {
     memset(&gt, 0, sizeof gt);
     const KParams &kp = p.kp;
     const int D = kp.D, K = kp.K, NR = kp.NR;
     if (!kp.dag) return;
+    // Exhaustive spaces on up to 8 devices and 32 types, where most candidates fall to their decode or their first blocks and the
+    // graph kernel's tables and the launch over its list are dear.  Against the general kernel (scores of 8 to 500,003 candidates,
+    // random graphs, fans, K-shape, diamond; geometric means over ranges of sizes): blocks on several devices 0.98 to 1.35 of its
+    // time, windows of one micro-batch 1.04 to 1.14, FACTORIAL 0.83 to 1.09: left to it.  CANONICAL 0.82 to 0.95, though
+    // up to 5 us longer where no candidate of a short call gets past its first blocks.  (More devices or types: 0.2 to 0.8 in both, as above
+    // 3 us longer at worst.)
+    const bool exhaustive = kp.space == kFactorial || kp.space == kCanonical;
+    if (exhaustive && D <= kMaxD && K <= kMaxK && (kp.tp || NR == 1 || kp.space == kFactorial)) return;
     int most = 0;
     for (int d = 0; d < D; d++) most = std::max(most, kp.ntd[d]);
     gt.np = most <= 2 ? 1 : most <= 4 ? 2 : 3;

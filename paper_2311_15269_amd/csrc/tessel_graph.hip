@@ -293,11 +293,13 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             else lds_add(b, (ls - ld) << (E >> 16));
         }
         if (space == kFactorial) status = dup ? kDup : tpm ? kTpMismatch : prop2 ? kProp2 : kOk;
+        // (exhaustive spaces: often none of a wave's candidates is left here, or after a few blocks)
+        const bool any = REPAIR || __ballot(valid && status == kOk) != 0;
         // ---- what may run, memory at the window entry (type i has handled micro-batches 0 .. lead - 1), heads
         uint32_t RD = 0, HD = 0;
         uint64_t hcnt = 0;                                       // TP: devices a type heads, six bits a type
         uint32_t rtp = 0;                                        // TP: such types that may run
-        for (int d = 0; d < D; d++) {
+        for (int d = 0; any && d < D; d++) {
             const uint32_t ra = rec0 + (uint32_t)d * RS + (NP + 1) * kRow;
             uint32_t runs = 0;
             int mem = 0;
@@ -477,11 +479,11 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             return entry;
         };
         const int full = total / 2;
-        bool whole = true;
-        for (int wi = 0; wi < full; wi++) {
+        bool whole = any;
+        for (int wi = 0; any && wi < full; wi++) {
             const uint32_t e0 = step(), e1 = step();
             prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
-            if ((wi & 7) == 7) {
+            if (!REPAIR || (wi & 7) == 7) {
                 const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
                 if (__ballot(going) == 0) { whole = false; break; }
             }

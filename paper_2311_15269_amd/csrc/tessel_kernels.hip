@@ -2305,12 +2305,9 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
     if (blocks < 1) return 0;
     uint32_t *behind = (uint32_t *)((char *)ws + ring_offset(s, num_cus));      // queues, slots, or the general kernel's state
     fast_fn ff = general ? nullptr : pick_fast(kp);
-    // (a few candidates of a few blocks: one launch instead of the graph kernel's and the list's; 8 candidates of 6 blocks
-    // 37.6 against 41.1 us a call)
-    const bool tiny = !wide_problem(kp) && kp.total <= 12 && count <= 4096;
-    if (!ff && kp.graph_ok && !general && !tiny) {
+    if (!ff && kp.graph_ok && !general) {
         // (every problem its tables hold: on 24 blocks of three devices 4.5 times the general kernel's rate, on 96 to 288
-        // blocks 34 to 78 times)
+        // blocks 34 to 78 times; one to 4,096 scores of 6 to 12 blocks 33 to 54 us against 39 to 82)
         int rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, behind, st);
         if (rc) return rc;
         made.from_range = blocks; made.from_list = list_blocks; made.whole = true;

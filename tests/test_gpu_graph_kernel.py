@@ -84,3 +84,24 @@ def test_periods_left_to_the_general_kernel(gpu, monkeypatch):
     monkeypatch.setenv("TESSEL_DAG_TRIES", "0")
     for prob in (W.kshape_problem(3, 5), vshape(12, 2, 2), inference(32, 2)):
         _compare(gpu, prob, 4242, 1500)
+
+
+def on_two(prob):
+    """the first type on the first two devices, and a last type that gives its memory back there"""
+    K = prob["K"]
+    return dict(prob, K=K + 2, t=prob["t"] + [2, 3], m=prob["m"] + [1, -1], dev_mask=prob["dev_mask"] + [3, 3],
+                deps=prob["deps"] + [(K, 0), (K - 1, K + 1)], name=prob["name"] + "-two")
+
+
+EXHAUSTIVE = [(W.kshape_problem(nr, 2), space, at) for nr in (1, 2, 3) for space in ("canonical", "factorial") for at in (0.0, 0.5)]
+EXHAUSTIVE += [(W.diamond_problem(2, 2), space, at) for space in ("canonical", "factorial") for at in (0.0, 0.6)]
+EXHAUSTIVE += [(on_two(W.kshape_problem(nr, 4)), space, 0.3) for nr in (1, 2) for space in ("canonical", "factorial")]
+EXHAUSTIVE += [(inference(9, 3), "factorial", 0.4), (inference(9, 2), "canonical", 0.0)]
+
+
+@pytest.mark.parametrize("prob,space,at", EXHAUSTIVE, ids=["%s-nr%d-%s-%g" % (p["name"], p["NR"], s, a) for p, s, a in EXHAUSTIVE])
+def test_exhaustive_spaces_on_both_sides_of_the_line(gpu, prob, space, at):
+    """the graph kernel takes some of them and leaves the others to the general kernel; waves without a candidate left"""
+    prob = dict(prob, space=space)
+    count = gpu.Problem(prob).candidate_count()
+    _compare(gpu, prob, int(count * at), 4000)
