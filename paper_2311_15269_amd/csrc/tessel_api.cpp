@@ -31,9 +31,8 @@ struct tessel_problem {
     std::vector<int32_t> dep_src, dep_dst;
     std::vector<int8_t> leadtab;        // CANONICAL
     std::vector<uint64_t> wtab;         // CANONICAL
-    std::vector<uint64_t> orders;       // CANONICAL with small tables: KParams::orders, leadrows
-    std::vector<uint32_t> leadrows;
-    std::vector<char> tables;           // the four in a row, each from a multiple of 256 bytes on, as the workspace gets them
+    std::vector<char> tables;           // CANONICAL: the two, and where they are small KParams::orders and leadrows, in a row, each from a
+                                        // multiple of 256 bytes on, as the workspace gets them
     size_t table_at[4] = {0, 0, 0, 0};
     uint64_t nlead = 0;
     uint64_t count = 0;
@@ -311,44 +310,70 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
     gt.ok = 1;
 }
 
-// The fast kernel's tables by rank for the CANONICAL space (KParams::ranked), where neither has more than kRankedMax
-// entries: every order of a device, in rank order (lexicographic), and for every lead vector what the build makes of it.
-static void ranked_tables(tessel_problem &p)
+// Sizes of the fast kernel's tables by rank for the CANONICAL space (KParams::ranked), in entries; false where neither is
+// made: the kernel then unranks symbol by symbol.
+static bool ranked_sizes(tessel_problem &p, size_t &orders, size_t &leadrows)
 {
     KParams &kp = p.kp;
-    kp.ranked = 0;
-    if (!kp.fast_ok || p.nlead > kRankedMax) return;
-    for (int d = 0; d < kp.D; d++) if (kp.cdev[d] > kRankedMax) return;
-    for (int n = 0; n <= kMaxLT; n++) {
-        bool used = false;
-        for (int d = 0; d < kp.D; d++) used = used || kp.ntd[d] == n;
-        kp.order_at[n] = (uint32_t)p.orders.size();
-        if (!used) continue;
-        std::vector<int> seq;
-        for (int y = 0; y < n; y++) seq.insert(seq.end(), (size_t)kp.NR, y);
-        do {
-            uint32_t lo = 0, hi = 0;
-            for (size_t pos = 0; pos < seq.size(); pos++) { lo |= (uint32_t)(seq[pos] & 1) << pos; hi |= (uint32_t)(seq[pos] >> 1) << pos; }
-            p.orders.push_back((uint64_t)lo | ((uint64_t)hi << 32));
-        } while (std::next_permutation(seq.begin(), seq.end()));
+    orders = leadrows = 0;
+    if (!kp.fast_ok || p.nlead > kRankedLeads) return false;
+    size_t by_types[kMaxLT + 1] = {0};
+    for (int d = 0; d < kp.D; d++) {
+        if (kp.cdev[d] > kRankedOrders) return false;
+        by_types[kp.ntd[d]] = kp.cdev[d];
     }
-    for (int d = 0; d < kp.D; d++) kp.recip[d] = kp.cdev[d] > 1 ? (uint32_t)(((uint64_t)1 << 32) / kp.cdev[d]) : 0u;
-    p.leadrows.assign((size_t)p.nlead * kLeadRow, 0);
+    // (at most 0.9 of the 1 MiB the workspace has for tables)
+    for (int n = 0; n <= kMaxLT; n++) { kp.order_at[n] = (uint32_t)orders; orders += by_types[n]; }
+    leadrows = p.nlead * kLeadRow;
+    return true;
+}
+
+// Every order of a device in rank order (lexicographic), and for every lead vector what the build makes of it, written
+// where the workspace's copy of them is made up (zeros so far).  Every handle pays for them: 16 us for 2,520 orders of four types
+// (std::next_permutation and vectors of their own: 58), 0.1 ms for 3,675 lead vectors of eight types (0.38).
+static void fill_ranked(const tessel_problem &p, uint64_t *orders, uint32_t *leadrows)
+{
+    const KParams &kp = p.kp;
+    bool done[kMaxLT + 1] = {false};
+    for (int d = 0; d < kp.D; d++) {
+        if (done[kp.ntd[d]]) continue;
+        done[kp.ntd[d]] = true;
+        uint64_t *out = orders + kp.order_at[kp.ntd[d]];
+        const int types = kp.ntd[d], len = types * kp.NR;
+        int left[kMaxLT];
+        for (int y = 0; y < types; y++) left[y] = kp.NR;
+        auto extend = [&](auto &self, int pos, uint64_t planes) -> void {
+            if (pos == len) { *out++ = planes; return; }
+            for (int y = 0; y < types; y++)
+                if (left[y] > 0) {
+                    left[y]--;
+                    self(self, pos + 1, planes | (uint64_t)(y & 1) << pos | (uint64_t)(y >> 1) << (32 + pos));
+                    left[y]++;
+                }
+        };
+        extend(extend, 0, 0);
+    }
+    struct Code { int g, a, word, shift; } code[kMaxK];
+    int codes = 0;
+    uint32_t absent[4] = {~0u, ~0u, ~0u, ~0u};                       // 15 where there is no type: a chain's first block never waits either
+    for (int d = 0; d < kp.D; d++)
+        for (int y = 0; y < kp.ntd[d]; y++) {
+            const int c = 4 * d + y, g = (int)((kp.type_of[d] >> (8 * y)) & 0xFFu), a = kp.pred[g];
+            code[codes++] = Code{g, a, c / 8, 4 * (c % 8)};
+            if (a >= 0) absent[c / 8] &= ~(15u << (4 * (c % 8)));
+        }
     for (uint64_t v = 0; v < p.nlead; v++) {
         const int8_t *lead = p.leadtab.data() + v * (uint64_t)kp.K;
-        uint32_t *row = p.leadrows.data() + v * kLeadRow;
-        for (int w = 4; w < 8; w++) row[w] = 0xFFFFFFFFu;            // 15: a chain's first block never waits
-        auto put = [&](uint32_t *words, int c, uint32_t x) { words[c / 8] = (words[c / 8] & ~(15u << (4 * (c % 8)))) | (x << (4 * (c % 8))); };
-        for (int d = 0; d < kp.D; d++)
-            for (int y = 0; y < kp.ntd[d]; y++) {
-                const int c = 4 * d + y, g = (int)((kp.type_of[d] >> (8 * y)) & 0xFFu), a = kp.pred[g];
-                put(row, c, (uint32_t)lead[g]);
-                const uint32_t wait = a < 0 ? 15u : (uint32_t)(lead[a] - lead[g]);
-                put(row + 4, c, wait);
-                if (wait) row[8] |= 1u << c;
-            }
+        uint32_t *row = leadrows + v * kLeadRow;
+        for (int w = 0; w < 4; w++) row[4 + w] = absent[w];
+        for (int k = 0; k < codes; k++) {
+            const Code &c = code[k];
+            const uint32_t wait = c.a < 0 ? 15u : (uint32_t)(lead[c.a] - lead[c.g]);
+            row[c.word] |= (uint32_t)lead[c.g] << c.shift;
+            row[4 + c.word] |= wait << c.shift;
+            row[8] |= (wait ? 1u : 0u) << (8 * c.word + c.shift / 4);
+        }
     }
-    kp.ranked = 1;
 }
 
 extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_problem **out)
@@ -699,13 +724,17 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
     kp.graph_ok = p->graph.ok; kp.graph_np = p->graph.np; kp.graph_chain = p->graph.chain; kp.graph_lds = p->graph.lds_bytes;
     kp.graph_slot_words = (uint32_t)(p->graph.meta + p->graph.nwords);
     if (desc->space == TESSEL_SPACE_CANONICAL) {
-        ranked_tables(*p);
-        const std::pair<const void *, size_t> tabs[] = {{p->leadtab.data(), p->leadtab.size()}, {p->wtab.data(), p->wtab.size() * 8},
-                                                        {p->orders.data(), p->orders.size() * 8}, {p->leadrows.data(), p->leadrows.size() * 4}};
-        for (int k = 0; k < 4; k++) {
-            p->table_at[k] = p->tables.size();
-            p->tables.resize((p->tables.size() + tabs[k].second + 255) & ~(size_t)255);
-            if (tabs[k].second) memcpy(p->tables.data() + p->table_at[k], tabs[k].first, tabs[k].second);
+        size_t orders, leadrows;
+        kp.ranked = ranked_sizes(*p, orders, leadrows);
+        const size_t bytes[4] = {p->leadtab.size(), p->wtab.size() * 8, orders * 8, leadrows * 4};
+        size_t total = 0;
+        for (int k = 0; k < 4; k++) { p->table_at[k] = total; total = (total + bytes[k] + 255) & ~(size_t)255; }
+        p->tables.resize(total);
+        memcpy(p->tables.data(), p->leadtab.data(), bytes[0]);
+        memcpy(p->tables.data() + p->table_at[1], p->wtab.data(), bytes[1]);
+        if (kp.ranked) {
+            fill_ranked(*p, (uint64_t *)(p->tables.data() + p->table_at[2]), (uint32_t *)(p->tables.data() + p->table_at[3]));
+            for (int d = 0; d < kp.D; d++) kp.recip[d] = kp.cdev[d] > 1 ? (uint32_t)(((uint64_t)1 << 32) / kp.cdev[d]) : 0u;
         }
     }
     *out = p;
