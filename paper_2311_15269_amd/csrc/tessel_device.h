@@ -56,9 +56,9 @@ constexpr int kMaxKW = 64;       // ... of any problem: more than kMaxK go the g
 constexpr int kMaxPos = kMaxLT * kMaxNR;   // blocks per device and window (32)
 constexpr int kMaxDeps = 128;     // dependencies of a micro-batch whose graph is not a set of chains
 constexpr int kLeadRow = 12;      // words of one row of KParams::leadrows
-// Most entries of the two.  Orders: 12,870 (two types, windows of 8) cost a handle nothing that can be measured beside its 0.6 ms and save
-// 13 us of a call over 64 candidates, 250 to 310 of 550 to 650 us over 4,000,003; 34,650 (three types, windows of 4) cost it 0.46 ms and save
-// as much.  Leads: 3,675 cost a handle 0.1 ms and save 90 us and more of every call (two chains on four devices, windows of 5);
+// Most entries of the two.  Orders: 12,870 (two types, windows of 8) cost a handle 0.2 ms beside its 0.55 ms and save 13 us of a call over
+// 64 candidates, 85 to 90 over 300,003, 250 to 310 of 550 to 650 us over 4,000,003; 34,650 (three types, windows of 4) cost it 0.46 ms and
+// save no more.  Leads: 3,675 cost a handle 0.1 ms and save 90 us and more of every call (two chains on four devices, windows of 5);
 // 10,976 cost 0.3 ms and save 16 us of a call over 64 to 5,000 candidates.
 constexpr uint32_t kRankedOrders = 16384, kRankedLeads = 4096;
 constexpr uint32_t kNoRing = 0xFFFFu;   // no ring of end times (KParams::tokbase)
