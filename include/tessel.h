@@ -31,7 +31,7 @@ extern "C" {
 /* ---- limits of this implementation -------------------------------------------------- */
 #define TESSEL_MAX_DEVICES        32   /* simulated devices D (more than 8, or more than 32
                                           block types: scored by the graph kernel or the
-                                          general one; no searched completion)                            */
+                                          general one; no searched completion)               */
 #define TESSEL_MAX_TYPES_PER_DEV  8    /* block types that occupy one device (more than 4:
                                           sampled spaces only; as for more than 8 devices);
                                           at most 32 blocks per device and window             */
@@ -131,7 +131,12 @@ typedef struct {
     uint64_t n_blocks_placed;                 /* blocks the builds placed in executable order: a candidate that
                                                  is over the cap early is not built to the end by
                                                  tessel_eval_candidates (exact in the REPAIR space, an upper
-                                                 bound elsewhere; 0 when another kernel did the scoring) */
+                                                 bound elsewhere; 0 when another kernel did the scoring).
+                                                 How early it is looked at goes by the size of the call and,
+                                                 with blocks on several devices in the REPAIR space and some
+                                                 millions of candidates, by counts that waves take from one
+                                                 another as they run: there this number differs a little from
+                                                 call to call; nothing else in the result does            */
 } tessel_result;
 
 /* A complete schedule of N micro-batches: warm-up, R copies of the best window, cool-down
@@ -159,8 +164,9 @@ int  tessel_candidate_count(const tessel_problem *p, uint64_t *count);
 
 /* Bytes of device workspace tessel_eval_candidates / tessel_score_candidates need: the running best, the list of
  * candidates left to the general kernel (8 MiB) and, for problems the fast kernel takes, three queues per resident
- * wave between the phases of the kernel (3 x 27 KB per wave for 256 blocks a window; a few hundred MB in all), for those the
- * graph kernel takes 192 programs per resident wave (about 100 KB for 256 blocks).  Sized for the current
+ * wave between the phases of the kernel (3 x 45 KB per wave for 256 blocks a window; a few hundred MB in all), for those the
+ * graph kernel takes 192 programs per resident wave (about 100 KB for 256 blocks) or, in the same place where that is
+ * more, the general kernel's programs and state.  Sized for the current
  * device (for 512 compute units where there is none to ask); a workspace too small for the device a call runs on is
  * refused there with TESSEL_E_WORKSPACE. */
 int  tessel_workspace_bytes(const tessel_problem *p, size_t *bytes);
@@ -200,7 +206,8 @@ int  tessel_score_candidates(tessel_problem *p, uint64_t first, uint64_t count,
  * nothing feasible has been scored (counters in *out are still valid).  If a launch left more
  * candidates to the general kernel than its list holds (2^20 of a range of up to 2^26: possible only
  * when most periods need more than the fast kernel's ten sweeps), every range scored since the last
- * reset is scored again here in smaller pieces before the result is returned.  WORKSPACE: the buffer
+ * reset is scored again here in smaller pieces before the result is returned (problems of the fast kernel; behind the graph
+ * kernel such a launch is scored whole by the general kernel at once).  WORKSPACE: the buffer
  * was bound to another handle in the meantime.  HIP: also when the period is not the least one of the decoded candidate's
  * orders (never expected; worked out on the host, apart from the kernels). */
 int  tessel_best(tessel_problem *p, tessel_result *out);
@@ -235,7 +242,8 @@ int  tessel_complete_schedule(tessel_problem *p, tessel_schedule *out);
  * they are for every candidate) and merges into the running best (makespan, lowest ordinal).  The first call
  * for a best window waits for it (as tessel_best does); the scoring itself is asynchronous on the stream of the
  * last tessel_eval_candidates call, in the workspace bound there.  A new best window, N or J restarts the
- * running best.  Errors: NO_FEASIBLE, RANGE (fewer than one window fits), INVALID_ARG,
+ * running best (a best window that came from the replay of a captured scoring call is seen once tessel_best has been
+ * called).  Errors: NO_FEASIBLE, RANGE (fewer than one window fits), INVALID_ARG,
  * TOOBIG (state of N micro-batches does not fit the LDS, N * sum of t exceeds 16 bits, N > 1023 or J > 63),
  * UNSUPPORTED (|m| > 127; more than 8 devices, 32 block types, 4 types on a device or 8 micro-batches per
  * window), HIP. */

@@ -1,6 +1,6 @@
 """The graph kernel at the edges of what its tables hold, element by element against the oracle: most producers a type's
-word has fields for and one more (which the general kernel takes), most consumers and one more, windows with an odd
-number of blocks, blocks on several devices of a branching graph, a type without dependencies, forward-only pipelines
+word has fields for and one more (which the general kernel takes), most consumers and one more and many more, windows with an odd
+number of blocks, an exhaustive space whole, blocks on several devices of a branching graph, a type without dependencies, forward-only pipelines
 (whose boundary values never grow alike), ranges around one wave, and every period left to the general kernel."""
 import numpy as np
 import pytest
@@ -31,6 +31,12 @@ def fan(width, nr, cap, space="sampled_repair", lonely=False):
             "fixed_leads": None}
 
 
+def branch(nr, cap, space):
+    """five stages on three devices, two of them a device but on the last: one feeds two, which feed one, which feeds the last"""
+    return {"name": "branch", "D": 3, "K": 5, "NR": nr, "M": cap, "t": [2, 3, 1, 4, 2], "m": [1, 1, 0, -1, -1], "dev_mask": [1, 2, 4, 1, 2],
+            "deps": [(0, 1), (0, 2), (1, 3), (2, 3), (3, 4)], "space": space, "seed": 0, "lead_step_q16": 0, "fixed_leads": None}
+
+
 SHAPES = [
     ("three-producers-nr16", fan(3, 16, 0), 5, 700),             # all fields of a word with five-bit counts
     ("four-producers-nr16", fan(4, 16, 0), 5, 400),              # one too many: the general kernel
@@ -39,7 +45,10 @@ SHAPES = [
     ("five-producers-nr4", fan(5, 4, 0), 9, 700),                # more consumers than the tables hold: the general kernel
     ("type-without-dependencies", fan(2, 3, 0, lonely=True), 3, 1000),
     ("odd-blocks", inference(9, 3), 11, 1500),
-    ("odd-blocks-canonical", fan(3, 3, 0, "canonical"), 0, 1),
+    ("odd-blocks-canonical", branch(3, 1, "canonical"), 0, 1 << 20),          # (the whole space)
+    ("odd-blocks-canonical-roomy", branch(3, 3, "canonical"), 0, 1 << 20),
+    ("nine-producers", fan(9, 3, 0), 6, 1500),                   # the best is decoded with all counts compared
+    ("sixteen-producers-strict", fan(16, 1, 0, "sampled_strict"), 6, 1500),
     ("forward-only-two-passes", {"name": "two-passes", "D": 9, "K": 18, "NR": 3, "M": 0, "t": [1 + (5 * i) % 7 for i in range(18)],
                                  "m": [0] * 18, "dev_mask": [1 << (i % 9) for i in range(18)],
                                  "deps": [(i, i + 1) for i in range(17)], "space": "sampled_repair", "seed": 77,

@@ -1,5 +1,7 @@
 """Problems with more than 8 devices, more than 32 block types or more than 4 block types on a device (Table I puts no
-bound on them; the boundary takes up to 32, 64 and 8): scored by the general kernel's path for graphs with the lanes' state in global memory.  HIP path against the oracle element by element:
+bound on them; the boundary takes up to 32, 64 and 8): scored by the graph kernel and, where its tables or its sweeps end, by the
+general kernel's path for graphs with the lanes' state in LDS or global memory (TESSEL_FAR_MODE forces it).  HIP path against the
+oracle element by element:
 V-shape pipelines on 12 and 16 devices, a forward-only pipeline on 32, a block on ten devices at once, the two
 exhaustive spaces, seeded random graphs on up to 24 devices, windows of 9 to 16 micro-batches; best candidate, its start
 times and its completion."""
