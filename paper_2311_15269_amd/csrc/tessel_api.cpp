@@ -723,6 +723,12 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
     if (!p->force_general && !getenv("TESSEL_FAR_MODE")) graph_tables(*p, p->graph);
     kp.graph_ok = p->graph.ok; kp.graph_np = p->graph.np; kp.graph_chain = p->graph.chain; kp.graph_lds = p->graph.lds_bytes;
     kp.graph_slot_words = (uint32_t)(p->graph.meta + p->graph.nwords);
+    {
+        int most_types = 0, most_in = 0;
+        for (int d = 0; d < D; d++) most_types = std::max(most_types, (int)kp.ntd[d]);
+        for (int i = 0; i < K; i++) most_in = std::max(most_in, kp.dag ? __builtin_popcountll(kp.predmask[i]) : 1);
+        kp.detail_lanes = detail_lanes(D, most_types, most_in);
+    }
     if (desc->space == TESSEL_SPACE_CANONICAL) {
         size_t orders, leadrows;
         kp.ranked = ranked_sizes(*p, orders, leadrows);
@@ -1046,7 +1052,7 @@ static int read_back(tessel_problem *p)
         if (now.period == p->result.period && now.index == p->result.index) { p->result = now; return TESSEL_OK; }
         p->best_dirty = true;
     }
-    int le = launch_detail(p->ws, p->stream);
+    int le = launch_detail(p->kp, p->ws, p->stream);
     if (le) return hip_fail(p, le);
     struct { unsigned char bytes[kWsDetailOff]; DevDetail detail; } both;
     static_assert(offsetof(decltype(both), detail) == kWsDetailOff && kWsResultOff == 0, "result and detail are copied in one piece");

@@ -74,4 +74,59 @@ __device__ __forceinline__ uint32_t even_bits32(uint32_t x)
     return x;
 }
 
+// a device's order while it is decoded: bit p of plane k = bit k of the symbol at position p
+template <int NP>
+struct Planes {
+    uint32_t p0, p1, p2;
+    __device__ __forceinline__ void clear() { p0 = p1 = p2 = 0; }
+    __device__ __forceinline__ void put(uint32_t y, uint32_t pos)
+    {
+        p0 |= (y & 1u) << pos;
+        if (NP > 1) p1 |= ((y >> 1) & 1u) << pos;
+        if (NP > 2) p2 |= (y >> 2) << pos;
+    }
+};
+
+// blocks of device d in the sampled spaces: a draw picks among the blocks left, types in ascending order
+template <int NP>
+__device__ __forceinline__ void sampled_order(uint32_t ka, uint32_t kb, int d, uint32_t ntd, uint32_t NR, Planes<NP> &o)
+{
+    const uint32_t n = ntd * NR;
+    o.clear();
+    // cumulative counts of the blocks left by type: one (shifted by 16) for two types; else bytes 0x80 - t, so that adding
+    // the replicated digit leaves "digit >= t" in bit 7 of every byte (t, digit <= 32)
+    uint32_t c = NR << 16, ta = 0, tb = 0, tc = 0;
+    if (NP > 1) {
+        auto cum = [&](uint32_t k) -> uint32_t { return min(k, ntd) * NR; };
+        ta = 0x808080u - (cum(1) | (cum(2) << 8) | (cum(3) << 16));
+        if (NP > 2) { tb = 0x808080u - (cum(4) | (cum(5) << 8) | (cum(6) << 16)); tc = 0x80u - cum(7); }
+    }
+    auto pick = [&](uint32_t draw, uint32_t left, uint32_t pos) {
+        if (NP == 1) {
+            const uint32_t prod = __umul24(draw, left);
+            const uint32_t y = prod >= c ? 1u : 0u;
+            c -= y ? 0u : 0x10000u;
+            o.p0 |= y << pos;
+            return;
+        }
+        const uint32_t digit = (uint32_t)(((uint64_t)draw * (uint64_t)((left << 16) & 0xFFFFFFu)) >> 32);   // 24-bit high multiply
+        const uint32_t ga = mad24(digit, 0x010101u, ta) & 0x808080u;
+        ta += (ga >> 7) ^ 0x010101u;                    // a threshold above the digit loses one block
+        uint32_t y = (uint32_t)__builtin_popcount(ga);
+        if (NP > 2) {
+            const uint32_t gb = mad24(digit, 0x010101u, tb) & 0x808080u;
+            tb += (gb >> 7) ^ 0x010101u;
+            const uint32_t gc = (tc + digit) & 0x80u;
+            tc += (gc >> 7) ^ 1u;
+            y += (uint32_t)__builtin_popcount(gb) + (gc >> 7);
+        }
+        o.put(y, pos);
+    };
+    for (uint32_t pos = 0; pos < n; pos += 2) {
+        const uint32_t word = stream_word(ka, kb, (kDrawOrdBase + 32u * (uint32_t)d + pos) >> 1);
+        pick(word & 0xFFFFu, n - pos, pos);
+        if (pos + 1 < n) pick(word >> 16, n - pos - 1u, pos + 1u);
+    }
+}
+
 }  // namespace tessel

@@ -6,7 +6,8 @@
 //
 // Bound by the chain of dependent instructions of a round.  One lane that walked the whole candidate and swept its
 // window again took 0.93 ms for 256 blocks on 8 devices and 2.9 ms on 16, longer than scoring 10^5 candidates; this
-// wave with counters in LDS 0.26 and 0.155 ms, with counters in registers 0.149 and 0.119 ms.
+// wave with counters in registers 0.149 and 0.119 ms.  Most problems have a lane for every block type of every device
+// (detail_lanes_kernel below, 0.038 and 0.032 ms); this one takes the others.
 // The period in the record is checked against the decoded orders by the host (check_period in tessel_api.cpp).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -116,6 +117,7 @@ __global__ __launch_bounds__(kWave) void detail_kernel(const KParams *__restrict
             } else if (e < K && P.succ[e] >= 0) {
                 edge[k] = true; src[k] = (uint32_t)e; dst[k] = (uint32_t)P.succ[e]; cross = P.cross_out[e] != 0; draw = P.edge_out[e];
             }
+            if (k == 1 && P.ndeps <= kWave) { edge[k] = false; step[k] = 0; continue; }
             step[k] = edge[k] && cross && stream_draw16(ka, kb, kDrawLeadBase + draw) < P.step_q16 ? 1u : 0u;
         }
         for (int round = 0; round < K; round++) {
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(kWave) void detail_kernel(const KParams *__restrict
         const int lo = y & 2u ? b : a, hi = y & 2u ? d : c;
         mem += y & 4u ? hi : lo;
         peak = max(peak, mem);
-        out->orders[dev][len++] = (int)type_at(y);
+        out->orders[dev][len++] = (uint8_t)type_at(y);
     };
     while (placed < total) {
         // the types whose producers are all ahead
@@ -237,9 +239,299 @@ __global__ __launch_bounds__(kWave) void detail_kernel(const KParams *__restrict
     if (lane == 0) { out->status = status; out->index = idx; }
 }
 
-int launch_detail(void *ws, void *stream)
+// ------------------------------------------------------------------ a lane per (device, block type)
+// Where 2^LG lanes a device (one for every type on it) fit one wave and no type has more than kLaneIn producers.  A lane
+// keeps the positions its type still has in its device's order and one word of fields with a guard bit each, occurrences left
+// and per producer the micro-batches waiting: one addition and one compare tell whether the type may run.  The earliest
+// entries of a device, and the earliest that may run, are minima over its lanes (cross-lane moves inside a group of eight),
+// and a round is two or three ballots with no table to look anything up in.
+//
+// Bound by the same chain of dependent instructions, which is shorter by that: a round takes 290 cycles.  256 blocks on 8
+// devices 149 -> 38 us, on 16 devices 119 -> 32; 288 on 12 devices 149 -> 39; 96 on 4 devices, six types each, 77 -> 20; 8 on two
+// devices 6.5 -> 4.5.  Code that runs once stays in loops: fetching it costs more than the cycles a longer body would save.
+constexpr int kLaneIn = 4;
+constexpr uint32_t kLaneOnes = 0x01041041u, kLaneAdd = 31u * kLaneOnes, kLaneGuard = 32u * kLaneOnes;      // five fields of five bits and a guard
+
+template <int LG>
+__device__ __forceinline__ uint32_t least_of_device(uint32_t x)
 {
-    hipLaunchKernelGGL(detail_kernel, dim3(1), dim3(kWave), 0, (hipStream_t)stream, (const KParams *)((char *)ws + kWsParamsOff),
+    if (LG >= 1) x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true));        // the other lane of a pair
+    if (LG >= 2) x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, true));        // the other pair of four
+    if (LG >= 3) x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xF, 0xF, true));       // eight lanes mirrored: the other four
+    return x;
+}
+
+// (WIDE: more than 32 lanes)
+template <int LG, bool TP, bool WIDE>
+__global__ __launch_bounds__(kWave) void detail_lanes_kernel(const KParams *__restrict__ Pp, const DevResult *__restrict__ res,
+                                                             DevDetail *__restrict__ out)
+{
+    constexpr uint32_t G = 1u << LG;
+    constexpr int NP = LG > 0 ? LG : 1;
+    __shared__ uint32_t lead[kMaxKW], home[kMaxKW], ahead[kMaxKW], after[kMaxKW];
+    __shared__ uint32_t mates[2 * kMaxKW];                       // by type: its lanes, below 32 and from 32 on
+    __shared__ uint64_t producers[kMaxKW];
+    __shared__ uint8_t order[kMaxDW * kMaxPos];    // symbols in device order
+    const KParams &P = *Pp;
+    const int lane = threadIdx.x, period = res->period, decoded = out->status;
+    const uint64_t idx = res->index, decoded_idx = out->index;
+    const int D = P.D, K = P.K, space = P.space;
+    const uint32_t NR = (uint32_t)P.NR;
+    const bool here = lane < D << LG, sampled = space == kSampledStrict || space == kSampledRepair;
+    const uint32_t dev = here ? (uint32_t)lane >> LG : 0u, y = (uint32_t)lane & (G - 1u);
+    const uint32_t ntd = (uint32_t)P.ntd[dev], n = ntd * NR;
+    const uint32_t types_lo = P.type_of[dev], types_hi = P.type_of_hi[dev];
+    // (what is read later by numbers known here: the loads are all on their way at once)
+    int delta[kMaxLTW];                                          // lane d: memory deltas of device d's symbols
+    const uint32_t own = (uint32_t)lane < kMaxDW ? (uint32_t)lane : 0u;
+    const uint32_t own_lo = P.type_of[own], own_hi = P.type_of_hi[own];
+    const int own_ntd = P.ntd[own];
+#pragma unroll
+    for (int s = 0; s < kMaxLTW; s++) delta[s] = P.m_of[own][s];
+    const int chain_pred = P.pred[lane & (kMaxK - 1)];
+    const uint64_t graph_pred = P.predmask[lane];
+    const int chain_succ = P.succ[lane & (kMaxK - 1)], chain_cross = P.cross_out[lane & (kMaxK - 1)], chain_edge = P.edge_out[lane & (kMaxK - 1)];
+    uint32_t src[2], dst[2], crosses[2];
+#pragma unroll
+    for (int k = 0; k < 2; k++) { src[k] = P.dsrc[lane + k * kWave]; dst[k] = P.ddst[lane + k * kWave]; crosses[k] = P.dcross[lane + k * kWave]; }
+    static_assert(kMaxDeps == 2 * kWave, "two dependencies a lane");
+    if (period == INT_MAX) return;                               // nothing feasible yet
+    if (decoded >= 0 && decoded_idx == idx) return;              // the running best has not changed since it was decoded
+    auto type_at = [&](uint32_t s) -> uint32_t { return byte_of(s < 4u ? types_lo : types_hi, s & 3u); };
+    const bool block = here && y < ntd;                          // the lane has a block type
+    const uint32_t type = block ? type_at(y) : 0u;
+    lead[lane] = 0; home[lane] = 63u; ahead[lane] = 0; after[lane] = (uint32_t)lane; mates[lane] = mates[kMaxKW + lane] = 0;
+    producers[lane] = lane >= K ? 0ull : P.dag ? graph_pred : chain_pred >= 0 ? 1ull << chain_pred : 0ull;
+    __syncthreads();
+    if (block) {
+        atomicMin(&home[type], (uint32_t)lane);
+        if (TP) atomicOr(&mates[lane < 32 ? type : kMaxKW + type], 1u << (lane & 31));
+    }
+    // ---- order of the lane's device
+    uint32_t ka = 0, kb = 0, firstlab = 0xFFFFFFFFu;
+    Planes<NP> o;
+    o.clear();
+    if (sampled) {
+        ka = stream_keys(P.seed, idx, kb);
+        sampled_order<NP>(ka, kb, (int)dev, ntd, NR, o);
+    } else {
+        uint64_t rest = idx, mine = 0;
+        for (int d = 0; d < D; d++) {
+            uint64_t r;
+            if ((rest | P.cdev[d]) >> 32) { r = rest % P.cdev[d]; rest /= P.cdev[d]; }
+            else { r = (uint32_t)rest % (uint32_t)P.cdev[d]; rest = (uint32_t)rest / (uint32_t)P.cdev[d]; }
+            if ((uint32_t)d == dev) mine = r;
+        }
+        if (space == kCanonical) {
+            if (P.ranked) {
+                const uint64_t planes = P.orders[P.order_at[ntd] + mine];
+                o.p0 = (uint32_t)planes; o.p1 = (uint32_t)(planes >> 32);
+            } else {
+                const uint32_t B = NR + 1;
+                uint32_t c[kMaxLT];
+#pragma unroll
+                for (int s = 0; s < kMaxLT; s++) c[s] = (uint32_t)s < ntd ? NR : 0u;
+                for (uint32_t pos = 0; pos < n; pos++) {
+                    bool chosen = false;
+#pragma unroll
+                    for (int s = 0; s < kMaxLT; s++) {
+                        if (!chosen && c[s] > 0) {
+                            c[s]--;
+                            const uint64_t w = P.wtab[((c[0] * B + c[1]) * B + c[2]) * B + c[3]];
+                            if (mine < w) { o.put((uint32_t)s, pos); chosen = true; } else { mine -= w; c[s]++; }
+                        }
+                    }
+                }
+            }
+            if (lane < K) lead[lane] = (uint32_t)P.leadtab[rest * (uint64_t)K + (uint64_t)lane];
+        } else {
+            uint32_t r = (uint32_t)mine;
+            uint64_t list = P.init_list[dev];
+            for (uint32_t pos = 0; pos < n; pos++) {
+                const uint32_t f = P.fact[n - 1 - pos], digit = r / f;
+                r -= digit * f;
+                const uint32_t code = (uint32_t)(list >> (5u * digit)) & 31u;
+                const uint64_t low = list & ((1ull << (5u * digit)) - 1ull);
+                list = low | (((list >> (5u * digit)) >> 5) << (5u * digit));
+                const uint32_t s = code >> 3, lab = code & 7u;
+                o.put(s, pos);
+                if (byte_of(firstlab, s) == 0xFFu) firstlab = (firstlab & ~(0xFFu << (8u * s))) | (lab << (8u * s));
+            }
+            if (block) lead[type] = byte_of(firstlab, y);        // (one lead per type: the candidate is feasible)
+        }
+    }
+    __syncthreads();
+    // ---- leads of the sampled spaces: the least solution of lead = min(N_R - 1, max over dependencies of (consumer's
+    // lead + step))
+    if (sampled && P.has_fixed) { if (lane < K) lead[lane] = P.fixed[lane]; }
+    else if (sampled) {
+        uint32_t step[2];
+        bool edge[2];
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const int e = lane + k * kWave;
+            uint32_t draw = (uint32_t)e;
+            bool cross = crosses[k] != 0;
+            edge[k] = P.dag && e < P.ndeps;
+            if (!P.dag) {
+                edge[k] = e < K && chain_succ >= 0;
+                src[k] = (uint32_t)e; dst[k] = (uint32_t)chain_succ & (kMaxKW - 1); cross = chain_cross != 0; draw = (uint32_t)chain_edge;
+            }
+            if (k == 1 && P.ndeps <= kWave) { edge[k] = false; step[k] = 0; continue; }
+            step[k] = edge[k] && cross && stream_draw16(ka, kb, kDrawLeadBase + draw) < P.step_q16 ? 1u : 0u;
+        }
+        if (!P.dag || P.graph_chain) {
+            // chains: the steps to the end of the chain, by doubling
+#pragma unroll
+            for (int k = 0; k < 2; k++)
+                if (edge[k]) { after[src[k]] = dst[k]; atomicMax(&ahead[src[k]], step[k]); }
+            __syncthreads();
+            int sum = (int)ahead[lane], next = (int)after[lane];
+            for (int far = 1; far < K; far *= 2) {
+                const int s = __shfl(sum, next), m = __shfl(next, next);
+                sum += next != lane ? s : 0;
+                next = m;
+            }
+            lead[lane] = min(NR - 1u, (uint32_t)sum);
+        } else
+            for (int round = 0; round < K; round++) {            // graphs: round by round from 0
+                bool grew = false;
+#pragma unroll
+                for (int k = 0; k < 2; k++)
+                    if (edge[k]) {
+                        const uint32_t v = min(NR - 1u, lead[dst[k]] + step[k]);
+                        if (v > lead[src[k]]) { atomicMax(&lead[src[k]], v); grew = true; }
+                    }
+                __syncthreads();
+                if (__ballot(grew) == 0) break;
+            }
+    }
+    __syncthreads();
+    // ---- the lane's type: its entries, its word, where its producers sit
+    const uint32_t alive = n >= 32u ? 0xFFFFFFFFu : (1u << n) - 1u;
+    uint32_t left = alive & (y & 1u ? o.p0 : ~o.p0);
+    if (NP > 1) left &= y & 2u ? o.p1 : ~o.p1;
+    if (NP > 2) left &= y & 4u ? o.p2 : ~o.p2;
+    if (!block) left = 0;
+    uint32_t word = block ? kLaneOnes - 1u + NR : 0u, minus = 1u, from[kLaneIn], plus[kLaneIn], nprod = 0;
+    {
+        uint64_t rest = block ? producers[type] : 0ull;
+#pragma unroll
+        for (int k = 0; k < kLaneIn; k++) {
+            from[k] = plus[k] = 0;
+            if (rest == 0) continue;
+            const uint32_t a = (uint32_t)__builtin_ctzll(rest), one = 1u << (6 * (k + 1));
+            rest &= rest - 1ull;
+            word += (lead[a] - lead[type] - 1u) * one;           // (Property 2: not negative; the field starts at 1)
+            minus |= one;
+            from[k] = home[a]; plus[k] = one;
+            nprod++;
+        }
+    }
+    uint32_t most_in = 0;
+    for (uint32_t k = 1; k <= (uint32_t)kLaneIn; k++) if (__ballot(nprod >= k) != 0) most_in = k;
+    // the lanes of the lane's type, where types sit on several devices
+    const uint32_t all_lo = TP ? mates[type] : 0u, all_hi = TP ? mates[kMaxKW + type] : 0u;
+    // ---- build
+    const uint64_t repair = space == kSampledRepair ? ~0ull : 0ull;
+    const uint32_t group = ((1u << G) - 1u) << ((uint32_t)lane & 31u & ~(G - 1u));       // the device's lanes, of 32
+    uint32_t at = dev * (uint32_t)kMaxPos;                       // the device's next place in `order`
+    for (;;) {
+        const uint32_t pos = low_bit(left);                      // (none left: the largest number)
+        const bool may = ((word + kLaneAdd) & kLaneGuard) == kLaneGuard;
+        const uint32_t head = least_of_device<LG>(pos), first = least_of_device<LG>(may ? pos : 0xFFFFFFFFu);
+        const uint64_t ready = __builtin_amdgcn_ballot_w64(may);
+        uint64_t heads = ready & __builtin_amdgcn_ballot_w64(pos == head);
+        // a block on several devices runs when it heads the list of all its devices
+        if (TP) heads &= __builtin_amdgcn_ballot_w64(((uint32_t)heads & all_lo) == all_lo && (!WIDE || ((uint32_t)(heads >> 32) & all_hi) == all_hi));
+        // nothing at the head of any list can run: the lowest device with a block that can places its earliest
+        const uint64_t can = ready & __builtin_amdgcn_ballot_w64(pos == first) & repair;
+        uint64_t one = can & (0ull - can);
+        if (TP && heads == 0 && can != 0) {
+            const int by = __builtin_ctzll(can);
+            one = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)all_lo, by) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)all_hi, by) << 32;
+        }
+        const uint64_t now = heads ? heads : one;
+        if (now == 0) break;
+        const uint32_t lo = (uint32_t)now, hi = (uint32_t)(now >> 32), half = WIDE && lane >= 32 ? hi : lo;
+        if (__builtin_amdgcn_inverse_ballot_w64(now)) {
+            order[at] = (uint8_t)y;
+            left &= left - 1u;
+            word -= minus;
+        }
+        at += half & group ? 1u : 0u;
+#pragma unroll
+        for (int k = 0; k < kLaneIn; k++) {
+            if (k > 0 && (uint32_t)k >= most_in) break;
+            word += plus[k] & (uint32_t)__builtin_amdgcn_sbfe((int)(WIDE && (from[k] & 32u) ? hi : lo), from[k], 1);
+        }
+    }
+    const uint64_t open = __ballot(left != 0);
+    __syncthreads();
+    // ---- lane d: the device's order and memory
+    int status = open ? kDeadlock : kOk;
+    {
+        const bool dev_lane = lane < D;
+        const int end = (int)__shfl(at, (lane << LG) & (kWave - 1)), len = dev_lane ? end - lane * kMaxPos : 0;
+        int mem = 0, peak = INT_MIN;
+#pragma unroll
+        for (int s = 0; s < kMaxLTW; s++)
+            if (s < own_ntd) mem += delta[s] * (int)lead[byte_of(s < 4 ? own_lo : own_hi, (uint32_t)s & 3u)];
+        // (a loop: the kernel runs its code once, and fetching it costs more than the few cycles a longer body would save)
+#pragma unroll 1
+        for (int k = 0; k < len; k++) {
+            const uint32_t s = order[own * kMaxPos + (uint32_t)k];
+            const int a = s & 1u ? delta[1] : delta[0], b = s & 1u ? delta[3] : delta[2], c = s & 1u ? delta[5] : delta[4], e = s & 1u ? delta[7] : delta[6];
+            const int low = s & 2u ? b : a, high = s & 2u ? e : c;
+            mem += s & 4u ? high : low;
+            peak = max(peak, mem);
+        }
+        if (peak == INT_MIN) peak = 0;                           // a device without blocks
+        if (status == kOk && __ballot(dev_lane && peak > P.M) != 0) status = kMem;
+        if (lane < kMaxDW) { out->peak[lane] = dev_lane ? peak : 0; out->order_len[lane] = len; }
+    }
+    // (places behind a device's last block hold nothing, and are not read)
+    for (int k = lane; k < D * kMaxPos; k += kWave) {
+        const int d = k / kMaxPos;
+        const uint32_t s = order[k] & 7u;
+        out->orders[d][k % kMaxPos] = (uint8_t)byte_of(s < 4u ? P.type_of[d] : P.type_of_hi[d], s & 3u);
+    }
+    if (lane < K) out->leads[lane] = (int)lead[lane];
+    if (lane == 0) { out->status = status; out->index = idx; }
+}
+
+typedef void (*detail_fn)(const KParams *, const DevResult *, DevDetail *);
+
+// lanes a device takes (log2), or -1: see detail_lanes_kernel
+int detail_lanes(int devices, int most_types, int most_producers)
+{
+    int lg = 0;
+    while ((1 << lg) < most_types) lg++;
+    return (devices << lg) <= kWave && most_producers <= kLaneIn ? lg : -1;
+}
+
+template <int LG>
+static detail_fn pick_lanes(const KParams &kp)
+{
+    const bool wide = (kp.D << LG) > 32;
+    return kp.tp ? (wide ? detail_lanes_kernel<LG, true, true> : detail_lanes_kernel<LG, true, false>)
+                 : (wide ? detail_lanes_kernel<LG, false, true> : detail_lanes_kernel<LG, false, false>);
+}
+
+static detail_fn pick_detail(const KParams &kp)
+{
+    switch (kp.detail_lanes) {
+    case 0: return pick_lanes<0>(kp);
+    case 1: return pick_lanes<1>(kp);
+    case 2: return pick_lanes<2>(kp);
+    case 3: return pick_lanes<3>(kp);
+    default: return detail_kernel;
+    }
+}
+
+int launch_detail(const KParams &kp, void *ws, void *stream)
+{
+    hipLaunchKernelGGL(pick_detail(kp), dim3(1), dim3(kWave), 0, (hipStream_t)stream, (const KParams *)((char *)ws + kWsParamsOff),
                        (const DevResult *)((char *)ws + kWsResultOff), (DevDetail *)((char *)ws + kWsDetailOff));
     return (int)hipGetLastError();
 }

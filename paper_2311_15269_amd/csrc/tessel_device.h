@@ -151,6 +151,8 @@ struct KParams {
     int32_t  graph_np, graph_chain;      // GraphTab::np, chain
     uint32_t graph_lds;          // GraphTab::lds_bytes
     uint32_t graph_slot_words;   // words of one candidate's slot: GraphTab::meta + nwords
+    int32_t  detail_lanes;       // log2 of the lanes a device takes in the wave that decodes the best candidate (one per type on it),
+                                 // -1: its devices, types or producers do not fit one wave so
     int32_t  many;               // some device holds more than kMaxLT block types (3-bit symbols; sampled spaces only)
     const int8_t   *leadtab;     // CANONICAL: [nlead][K] in device memory
     const uint64_t *wtab;        // CANONICAL: arrangements by remaining counts, base NR+1 digits
@@ -188,7 +190,7 @@ struct DevDetail {
     int32_t peak[kMaxDW];
     int32_t leads[kMaxKW];
     int32_t order_len[kMaxDW];
-    int32_t orders[kMaxDW][kMaxPos];
+    uint8_t orders[kMaxDW][kMaxPos];
 };
 
 // Searched completion (warm-up / cool-down orders as perturbed greedy schedules around the best window):
@@ -315,7 +317,8 @@ const void *graph_kernel(const KParams &kp);
 int launch_graph(const KParams &kp, uint64_t first, uint64_t count, int blocks, void *recs, int32_t *code, int32_t *peak, void *ws,
                  uint32_t *slots, void *stream);
 // tessel_detail.hip: decodes the candidate of the running best (if there is one) into the workspace's DevDetail
-int launch_detail(void *ws, void *stream);
+int launch_detail(const KParams &kp, void *ws, void *stream);
+int detail_lanes(int devices, int most_types, int most_producers);    // KParams::detail_lanes
 // kernels.hip
 // max_blocks: 0, or the most workgroups the workspace has queues for
 LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks);
