@@ -153,6 +153,88 @@ static bool gen_leads(const tessel_problem &p, int K, int NR, std::vector<int8_t
     return true;
 }
 
+// The same for chains on masks by code (GraphTab::codes); false: not such a problem, or a field of its records would not
+// hold it (memory prefixes, times of a window sweep in 16 bits; a dependency listed twice draws twice).
+static bool code_tables(const tessel_problem &p, GraphTab &gt, const std::vector<std::vector<int>> &in, const std::vector<std::vector<int>> &outs,
+                        long span_max)
+{
+    const KParams &kp = p.kp;
+    const int D = kp.D, K = kp.K, NR = kp.NR, nb = gt.np;
+    if (!gt.chain || kp.tp || (D << nb) > 64 || (kp.space != kSampledStrict && kp.space != kSampledRepair)) return false;
+    size_t distinct = 0;
+    for (int i = 0; i < K; i++) distinct += in[i].size();
+    if (distinct != p.dep_src.size()) return false;
+    if (span_max > (nb == 1 ? 8000 : nb == 2 ? 30000 : 120)) return false;
+    // end times of the last sweep of all: at most the serial time of the windows so far
+    if ((int64_t)kp.UB * (std::max(9, gt.retry_tries) + 1) > 65535) return false;
+    const bool packed = nb == 1 && NR <= 8;
+    const uint32_t row = kWave * 4, half = row / 2, ts = (D << nb) > 32 ? 256 : 128;
+    const int rows = packed ? 2 : nb == 1 ? 3 : nb + 3, row_w = packed ? 1 : nb + 1, row_l = nb == 1 ? row_w : nb + 2;
+    const int words = ts == 256 ? 6 : nb == 1 ? 4 : 5;
+    uint32_t at = (uint32_t)words * ts;
+    gt.sw = at; at += (uint32_t)K * 8;
+    gt.ntab = (int)(at / 4);
+    at = (at + row - 1) / row * row;
+    gt.slot_rows = at; at += row;
+    gt.rec = at;
+    const uint32_t build_end = at + (uint32_t)(D * rows) * row;
+    gt.state = at; at += (uint32_t)kp.nslots * half;
+    gt.prev = at; at += (uint32_t)D * half;
+    gt.strash = at; at += half;
+    at = (at + row - 1) / row * row;
+    gt.leads = at; at += (uint32_t)((kp.ntok + 3) / 4) * row;
+    gt.lds_bytes = std::max(build_end, at);
+    memset(gt.tab, 0, sizeof gt.tab);
+    gt.codes = ts == 256 ? 2 : 1;
+    gt.np = packed ? 0 : nb;
+    gt.code_rows = (uint32_t)rows;
+    std::vector<int> code(K, 0);
+    for (int d = 0; d < D; d++)
+        for (int y = 0; y < kp.ntd[d]; y++)
+            code[(y < 4 ? kp.type_of[d] >> (8 * y) : kp.type_of_hi[d] >> (8 * (y - 4))) & 0xFFu] = (d << nb) + y;
+    auto dev = [&](int g) -> int { return code[g] >> nb; };
+    auto sym = [&](int g) -> int { return code[g] & ((1 << nb) - 1); };
+    auto wait_at = [&](int g) -> int { return nb == 3 ? 4 * sym(g) : 5 * sym(g); };
+    auto lead_at = [&](int g) -> int { return nb == 1 ? 10 + 4 * sym(g) : nb == 2 ? 4 * sym(g) : 3 * sym(g); };
+    const int mem_at = nb == 1 ? 18 : nb == 2 ? 16 : 24;
+    auto word = [&](int w, int c) -> uint32_t & { return gt.tab[((uint32_t)w * ts) / 4 + (uint32_t)c]; };
+    auto rec_row = [&](int d, int r) -> uint32_t { return gt.rec + (uint32_t)(d * rows + r) * row; };
+    for (int g = 0; g < K; g++) {
+        const int c = code[g], h = outs[g].empty() ? -1 : outs[g][0];
+        const bool same = h >= 0 && dev(h) == dev(g);
+        const uint32_t mem = (uint32_t)p.m[g] << mem_at, inc = h >= 0 ? 1u << wait_at(h) : 0u;
+        word(0, c) = (nb == 1 ? mem : 0u) - (1u << wait_at(g)) + (same ? inc : 0u);
+        word(1, c) = h >= 0 && code[h] < 32 ? 1u << code[h] : 0u;
+        word(2, c) = rec_row(h >= 0 && !same ? dev(h) : dev(g), row_w) | ((uint32_t)g * 8u + ((uint32_t)(NR - 1) << 9)) << 16;
+        word(3, c) = same ? 0u : inc;
+        if (words > 4) word(4, c) = mem;
+        if (words > 5) word(5, c) = h >= 0 && code[h] >= 32 ? 1u << (code[h] - 32) : 0u;
+        auto ring_address = [&](int i) -> uint32_t { return gt.state + (uint32_t)kp.tokbase[i] * half; };
+        gt.tab[gt.sw / 4 + 2 * g] = (uint32_t)p.t[g];
+        gt.tab[gt.sw / 4 + 2 * g + 1] = (gt.state + (uint32_t)dev(g) * half) | ring_address(kp.tokbase[g] != kNoRing ? g : in[g][0]) << 16;
+    }
+    int n = 0;
+    for (int last = 0; last < K; last++) {
+        if (!outs[last].empty()) continue;
+        for (int g = last;; g = in[g][0]) {
+            uint32_t *e = gt.links[n++];
+            uint32_t number = 0, cross = 0;
+            for (int k = 0; k < kp.ndeps; k++) if (kp.dsrc[k] == g) { number = (uint32_t)k; cross = kp.dcross[k] != 0; }
+            e[0] = rec_row(dev(g), row_w) | number << 16 | cross << 24 | (uint32_t)outs[g].empty() << 25 | (uint32_t)in[g].empty() << 26;
+            e[1] = (uint32_t)wait_at(g) | (uint32_t)code[g] << 8 | (uint32_t)lead_at(g) << 16;
+            e[2] = (uint32_t)kp.fixed[g] << 28;
+            e[3] = (uint32_t)p.m[g] << mem_at;
+            if (in[g].empty()) break;
+        }
+    }
+    for (int r = 0; r < kp.ntok; r++) {
+        const int g = kp.ring_head[r];
+        gt.head[r] = rec_row(dev(g), row_l) | (uint32_t)lead_at(g) << 16 | (nb == 3 ? 3u : 4u) << 24;
+    }
+    gt.ok = 1;
+    return true;
+}
+
 // Tables of the graph kernel (GraphTab).  Leaves ok = 0 where the problem is outside what they hold: more than kGraphOut
 // consumers or the fields of a type's word producers of one type, a type without any dependency, more than kGraphTp types
 // on several devices, memory prefixes beyond 16 bits, an LDS need beyond 64 KB, and where the general kernel is faster.
@@ -211,6 +293,13 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
     for (int b = 0; b < K; b++)
         for (size_t s = 0; s < in[b].size(); s++)
             gt.edge[gt.nedge++] = (uint32_t)in[b][s] | (uint32_t)b << 8 | (uint32_t)(f * (1 + (int)s)) << 16;
+    gt.first_tries = std::min(kGraphTries, kp.dag_tries);
+    // (every period seen settled within eight sweeps or never; a wave waits for its slowest lane)
+    gt.retry_tries = kp.dag_tries + kp.dag_tries / 2;
+    gt.nwords = ((kp.total + 1) / 2 + 3) / 4 * 4;
+    gt.meta = 3 + (kp.ntok + 3) / 4;
+    for (int d = 0; d < D; d++) gt.busy |= (kp.ntd[d] > 0 ? 1u : 0u) << d;
+    for (int r = 0; r < kp.ntok; r++) gt.ring[r] = (uint32_t)kp.ring_base[r] | (uint32_t)kp.ring_kept[r] << 16;
     // LDS: code tables, sweep tables, tables of types on several devices, slot rows, then build and sweep state in one place
     const int cw = 2 + 2 * gt.maxout;                       // words of a code
     const uint32_t row = kWave * 4;
@@ -251,8 +340,8 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
     gt.leads = at; at += (uint32_t)((kp.ntok + 3) / 4) * row;
     gt.lds_bytes = std::max(build_end, at);
     if (gt.lds_bytes > 64 * 1024 - row) return;             // (16-bit LDS addresses, eight-bit row numbers)
-    gt.meta = 3 + (kp.ntok + 3) / 4;
-    gt.nwords = ((kp.total + 1) / 2 + 3) / 4 * 4;
+    if (code_tables(p, gt, in, outs, span_max)) return;
+    for (int r = 0; r < kp.ntok; r++) gt.head[r] = gt.wrow + (uint32_t)kp.ring_head[r] * row;
     auto type_at = [&](int d, int y) -> int { return (int)((y < 4 ? kp.type_of[d] >> (8 * y) : kp.type_of_hi[d] >> (8 * (y - 4))) & 0xFFu); };
     auto symbol_on = [&](int g, int d) -> int { for (int y = 0; y < kp.ntd[d]; y++) if (type_at(d, y) == g) return y; return 0; };
     auto lowest = [&](int g) -> int { return __builtin_ctz(p.mask[g]); };
@@ -304,9 +393,6 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
             gt.tab[gt.tpi / 4 + kMaxKW + tp_no[g]] = info;
             for (int d = 0; d < D; d++) if (p.mask[g] >> d & 1u) gt.tab[gt.tps / 4 + tp_no[g] * 32 + d] = (uint32_t)symbol_on(g, d);
         }
-    gt.first_tries = std::min(kGraphTries, kp.dag_tries);
-    // (every period seen settled within eight sweeps or never; a wave waits for its slowest lane)
-    gt.retry_tries = kp.dag_tries + kp.dag_tries / 2;
     gt.ok = 1;
 }
 
@@ -721,7 +807,7 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
     // (TESSEL_FAR_MODE chooses between placements of the general kernel's state: it takes the problem then)
     p->graph.ok = 0;
     if (!p->force_general && !getenv("TESSEL_FAR_MODE")) graph_tables(*p, p->graph);
-    kp.graph_ok = p->graph.ok; kp.graph_np = p->graph.np; kp.graph_chain = p->graph.chain; kp.graph_lds = p->graph.lds_bytes;
+    kp.graph_ok = p->graph.ok; kp.graph_np = p->graph.np; kp.graph_codes = p->graph.codes; kp.graph_chain = p->graph.chain; kp.graph_lds = p->graph.lds_bytes;
     kp.graph_slot_words = (uint32_t)(p->graph.meta + p->graph.nwords);
     {
         int most_types = 0, most_in = 0;

@@ -122,7 +122,17 @@ __device__ __forceinline__ void sampled_order(uint32_t ka, uint32_t kb, int d, u
         }
         o.put(y, pos);
     };
-    for (uint32_t pos = 0; pos < n; pos += 2) {
+    uint32_t pos = 0;
+    // (four draws at a time: the two words' hashes overlap)
+    for (; pos + 4 <= n; pos += 4) {
+        const uint32_t w0 = stream_word(ka, kb, (kDrawOrdBase + 32u * (uint32_t)d + pos) >> 1);
+        const uint32_t w1 = stream_word(ka, kb, ((kDrawOrdBase + 32u * (uint32_t)d + pos) >> 1) + 1u);
+        pick(w0 & 0xFFFFu, n - pos, pos);
+        pick(w0 >> 16, n - pos - 1u, pos + 1u);
+        pick(w1 & 0xFFFFu, n - pos - 2u, pos + 2u);
+        pick(w1 >> 16, n - pos - 3u, pos + 3u);
+    }
+    for (; pos < n; pos += 2) {
         const uint32_t word = stream_word(ka, kb, (kDrawOrdBase + 32u * (uint32_t)d + pos) >> 1);
         pick(word & 0xFFFFu, n - pos, pos);
         if (pos + 1 < n) pick(word >> 16, n - pos - 1u, pos + 1u);

@@ -149,6 +149,7 @@ struct KParams {
     uint64_t predmask_of[kMaxDW][kMaxLTW]; // producers of local symbol y of device d
     int32_t  graph_ok;           // the graph kernel takes the problem
     int32_t  graph_np, graph_chain;      // GraphTab::np, chain
+    int32_t  graph_codes;        // GraphTab::codes
     uint32_t graph_lds;          // GraphTab::lds_bytes
     uint32_t graph_slot_words;   // words of one candidate's slot: GraphTab::meta + nwords
     int32_t  detail_lanes;       // log2 of the lanes a device takes in the wave that decodes the best candidate (one per type on it),
@@ -298,6 +299,19 @@ struct GraphTab {
     uint32_t tpm, tpi, tps, smask;   // blocks on several devices: by type the device mask (0: one device) and 6 * number |
                                  // lowest device << 8 | devices << 16; symbol by number and device; by device the symbols of types
                                  // that sit on it alone
+    uint32_t busy;               // devices with block types
+    uint32_t ring[kMaxKW];       // by ring: its first row | first of the rows that keep the last boundary's values << 16 (rows from `state` on)
+    uint32_t head[kMaxKW];       // by ring: where the lead of its first type is found at the end of a build: LDS address | shift << 16 |
+                                 // bits << 24 (bits 0: the next micro-batch of the type's word, less N_R)
+    // Chains in the sampled spaces whose devices' symbols fit 64 codes (device << np | symbol): built on masks by code.
+    // `codes`: 0 not such, 1 up to 32 codes, 2 up to 64; np is 0 then where a device's order and its entries left share a word
+    int32_t  codes;
+    uint32_t code_rows;          // rows of a device record
+    uint32_t links[kMaxKW][4];   // block types, every chain from its last to its first: address of the word with the type's waiting
+                                 // micro-batches | number of the dependency to its consumer << 16 | that joins different device sets << 24 |
+                                 // nobody consumes it << 25 | nobody produces for it << 26 | type << 27 (fixed leads);
+                                 // shift of that count | code << 8 | shift of the lead << 16; what a lead of 1 adds to the word
+                                 // with the lead and the memory, times the lead (the last two may be one word); unused
     uint32_t lead_edge[kMaxDeps];// the dependencies, consumers' types first: src | dst << 8 | number << 16 | joins different device
                                  // sets << 24 | first of its source << 25 | last of it << 26
     uint32_t edge[kMaxDeps];     // distinct dependencies: src | dst << 8 | shift of the field in dst's word << 16

@@ -14,12 +14,16 @@
 // the record; the tables of the (device, symbol); words and records these name.
 //
 // Bound by the latency of those rounds at the few waves per CU that the LDS holds (a record is np + 2 rows of 256
-// bytes per device, a word one row per type).  Kernel times against the general kernel, which looks at every device's
-// head in turn and keeps counters for 64 types in registers: 200,003 candidates of a pipeline on 16 devices, 256 blocks
-// a window, 34.6 -> 0.441 ms; 100,003 of one on 12 devices, 288 blocks, 10.0 -> 0.250 ms; 300,007 with six types on each
-// of four devices, 96 blocks, 6.9 -> 0.203 ms; 2^22 of a graph of 6 types on three devices, 24 blocks, 3.48 -> 0.774 ms.
-// LDS decides how many waves hide each other's rounds, so tables are as large as the problem, not its limits, and slot
-// states are bytes: 13.0 -> 9.7 KB a wave took the last of these from 1.32 ms.
+// bytes per device, a word one row per type), and by VALU issue where there are four waves a SIMD.  Kernel times against the
+// general kernel, which looks at every device's head in turn and keeps counters for 64 types in registers: 2^22 candidates of a graph of
+// 6 types on three devices, 24 blocks, 3.48 -> 0.708 ms.  LDS decides how many waves hide each other's rounds, so tables are
+// as large as the problem, not its limits, and slot states are bytes.
+//
+// Chains in the sampled spaces (KIND 3 and 4; most wide problems are chains) keep masks by code in registers instead of words by
+// type in LDS, as the fast kernel does: two rounds a block instead of three, 40 to 55 % of the LDS, 16-bit times in the
+// sweeps.  Against words by type: 200,003 candidates of a pipeline on 16 devices, 256 blocks a window, 0.438 -> 0.255 ms
+// (general kernel 34.6); 100,003 of one on 12 devices, 288 blocks, 0.249 -> 0.176 (10.0); 300,007 with six types on each of four
+// devices, 96 blocks, 0.205 -> 0.152 (6.9); 3,849 on 15 devices, 360 blocks, 0.275 -> 0.195; 20,725 on 27 devices 0.135 -> 0.086.
 //
 // The program (block type and micro-batch, 16 bits a block) goes to global memory, [word][slot], a slot per candidate;
 // sweeps read it back four words ahead.  A wave owns kGraphSlots slots: candidates that survive the build keep theirs
@@ -50,12 +54,25 @@ __device__ __forceinline__ void lds_load2(uint32_t a, uint32_t &x, uint32_t &y)
     x = v.x; y = v.y;
 }
 typedef __attribute__((address_space(3))) uint8_t lds_byte;
+typedef __attribute__((address_space(3))) uint16_t lds_half;
+__device__ __forceinline__ uint32_t lds_load16(uint32_t a) { return *(const lds_half *)(uintptr_t)a; }
+__device__ __forceinline__ void lds_store16(uint32_t a, uint32_t v) { *(lds_half *)(uintptr_t)a = (uint16_t)v; }
 __device__ __forceinline__ uint32_t lds_load8(uint32_t a) { return *(const lds_byte *)(uintptr_t)a; }
 __device__ __forceinline__ void lds_store8(uint32_t a, uint32_t v) { *(lds_byte *)(uintptr_t)a = (uint8_t)v; }
 
-// KIND: 0 every type has at most one producer and one consumer, 1 any graph, 2 some block sits on several devices
+// the lowest set bit of a mask of up to 64 codes (not 0: any number below 64 then)
+__device__ __forceinline__ uint32_t low_bit(uint64_t x)
+{
+    return min(low_bit((uint32_t)x), low_bit((uint32_t)(x >> 32)) | 32u) & 63u;
+}
+template <bool W64> struct Codes { typedef uint32_t mask; };
+template <> struct Codes<true> { typedef uint64_t mask; };
+
+// KIND: 0 every type has at most one producer and one consumer, 1 any graph, 2 some block sits on several devices; 3 and 4
+// chains in the sampled spaces on masks by code, up to 32 and up to 64 codes (GraphTab::codes).  NP: bits of a symbol; 0
+// (with masks by code): one bit, order and entries left in one word.
 template <int NP, bool REPAIR, int KIND>
-__global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__restrict__ Pp, const GraphTab *__restrict__ Gp, uint64_t first,
+__global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(const KParams *__restrict__ Pp, const GraphTab *__restrict__ Gp, uint64_t first,
                                                            uint64_t count, BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
                                                            int32_t *__restrict__ peak_out, uint64_t *__restrict__ out_list,
                                                            uint32_t *__restrict__ out_count, uint32_t out_cap,
@@ -74,15 +91,22 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
     for (int j = 0; j < 3; j++) lds_store8(st_row + (uint32_t)(j * kWave + lane), 0u);
     __syncthreads();
 
-    constexpr bool TP = KIND == 2, CHAIN = KIND == 0;
+    constexpr bool TP = KIND == 2, CODES = KIND >= 3, CHAIN = KIND == 0 || CODES, W64 = KIND == 4;
     const uint32_t cw4 = CHAIN ? 16u : G.code_bytes;             // bytes of one code's table words
-    constexpr uint32_t RS = (NP + 2) * kRow;                     // bytes of one device record
+    constexpr uint32_t RS = CODES ? (NP == 0 ? 2 : NP == 1 ? 3 : NP + 3) * kRow : (NP + 2) * kRow;      // bytes of one device record
+    // rows of end times and device times: 16 bits with masks by code (the host sees that they fit)
+    constexpr uint32_t SROW = CODES ? kRow / 2 : kRow;
+    const uint32_t lane_s = CODES ? (uint32_t)lane * 2u : lane4;
+    auto time_load = [&](uint32_t a) -> uint32_t { return CODES ? lds_load16(a) : lds_load(a); };
+    auto time_store = [&](uint32_t a, uint32_t v) { if (CODES) lds_store16(a, v); else lds_store(a, v); };
     const int D = P.D, K = P.K, M = P.M, total = P.total, space = P.space, nwords = G.nwords;
     const uint32_t NR = (uint32_t)P.NR, ADD = G.add, GUARD = G.guard, mushift = (uint32_t)G.mushift;
     const uint32_t rec0 = G.rec + lane4, wrow0 = G.wrow + lane4;
     const int maxout = CHAIN ? 1 : G.maxout, ntp = TP ? G.ntp : 0;
     uint32_t *slots = slots_all + (size_t)blockIdx.x * (size_t)(G.meta + nwords) * kProgRow;
     uint32_t *progs = slots + (size_t)G.meta * kProgRow;
+    const uint32_t busy = G.busy;
+    const bool idle = __builtin_popcount(busy) < D;
     const bool drop_mem = REPAIR && peak_out == nullptr;         // a rejected candidate's peak is that of the whole window
 
     int best = INT_MAX;
@@ -117,6 +141,145 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         return n;
     };
 
+    // ---------------------------------------------------------------- chains on masks by code
+    // Decode and build of 64 candidates (KIND 3 and 4).  A type that gets a micro-batch may run unless its entries are used up,
+    // whatever else is true of it: masks by code in registers (R types that may run, HM heads, X used up) say so without a look
+    // at the consumer, whose record gets its micro-batch by an atomic nobody waits for.  Two dependent rounds of LDS reads a
+    // block (record, table words of the code) where the words by type need three, and less LDS: a device's types have no rows of
+    // their own.
+    auto build_codes = [&](uint32_t ka, uint32_t kb, bool valid, uint32_t *prog, int &status, int &worst, bool &whole) {
+        typedef typename Codes<W64>::mask mask_t;
+        constexpr int NB = NP == 0 ? 1 : NP;                     // bits of a symbol
+        constexpr uint32_t TS = W64 ? 256u : 128u;               // bytes of one table word over all codes
+        constexpr uint32_t DEV = (1u << (1 << NB)) - 1u;         // the codes of one device
+        constexpr bool ONE = NP <= 1;                            // waiting micro-batches, leads and memory in one word
+        constexpr uint32_t row_alive = NP == 0 ? 0u : NB, row_w = NP == 0 ? 1u : NB + 1, row_l = ONE ? row_w : NB + 2;
+        mask_t R = 0, HM = 0, X = 0;
+        for (int d = 0; d < D; d++) {
+            lds_store(rec0 + (uint32_t)d * RS + row_w * kRow, 0u);
+            if (!ONE) lds_store(rec0 + (uint32_t)d * RS + row_l * kRow, 0u);
+        }
+        // ---- leads, every chain from its last type to its first; a type's waiting micro-batches are what its producer's lead
+        // is ahead (no producer: more than it has blocks)
+        {
+            uint32_t lead = 0, at = ~0u, word = 0;
+            for (int k = 0; k < K; k++) {
+                const uint32_t c0 = G.links[k][0], c1 = G.links[k][1], c2 = G.links[k][2];
+                const bool last = c0 >> 25 & 1u, first_type = c0 >> 26 & 1u;
+                const uint32_t before = lead, e = c0 >> 16 & 255u;
+                if (P.has_fixed) lead = c2 >> 28;
+                else {
+                    uint32_t stepped = 0;
+                    if (c0 >> 24 & 1u) {
+                        const uint32_t wi = (kDrawLeadBase + e) >> 1;
+                        if (wi != at) { word = stream_word(ka, kb, wi); at = wi; }
+                        stepped = ((e & 1u) ? word >> 16 : word & 0xFFFFu) < P.step_q16 ? 1u : 0u;
+                    }
+                    lead = last ? 0u : min(NR - 1u, lead + stepped);
+                }
+                if (!last) {
+                    // the consumer, the entry before: its waiting micro-batches
+                    const uint32_t b0 = G.links[k - 1][0], b1 = G.links[k - 1][1], waits = lead - before;
+                    lds_add((b0 & 0xFFFFu) + lane4, waits << (b1 & 31u));
+                    R |= (mask_t)min(waits, 1u) << (b1 >> 8 & 63u);
+                }
+                if (first_type) {
+                    lds_add((c0 & 0xFFFFu) + lane4, (NR + 1u) << (c1 & 31u));
+                    R |= (mask_t)1u << (c1 >> 8 & 63u);
+                }
+                lds_add((c0 & 0xFFFFu) + (row_l - row_w) * kRow + lane4, (lead << (c1 >> 16 & 31u)) + lead * G.links[k][3]);
+            }
+        }
+        // ---- orders, by device
+        for (int d = 0; d < D; d++) {
+            const uint32_t ntd = (uint32_t)P.ntd[d], n = ntd * NR;
+            Planes<NB> o;
+            sampled_order<NB>(ka, kb, d, ntd, NR, o);
+            const uint32_t ra = rec0 + (uint32_t)d * RS, alive = n >= 32u ? 0xFFFFFFFFu : (1u << n) - 1u;
+            if (NP == 0) lds_store(ra, o.p0 | alive << 16);
+            else {
+                lds_store(ra, o.p0);
+                if (NB > 1) lds_store(ra + kRow, o.p1);
+                if (NB > 2) lds_store(ra + 2 * kRow, o.p2);
+                lds_store(ra + row_alive * kRow, alive);
+            }
+            const uint32_t y0 = (o.p0 & 1u) | (NB > 1 ? (o.p1 & 1u) << 1 : 0u) | (NB > 2 ? (o.p2 & 1u) << 2 : 0u);
+            if (n) HM |= (mask_t)1u << (((uint32_t)d << NB) + y0);
+        }
+        // ---- blocks in an executable sequence
+        bool building = REPAIR || valid;
+        const uint32_t last_dev = ((uint32_t)D - 1u) << NB;
+        auto step = [&]() -> uint32_t {
+            const mask_t hm = R & HM, sel = hm ? hm : (REPAIR ? R : (mask_t)0);
+            if (!REPAIR && building && sel == 0) { status = kDeadlock; building = false; }
+            // the device's first code
+            uint32_t d0 = low_bit(sel) & ~((1u << NB) - 1u);
+            d0 = REPAIR ? min(d0, last_dev) : building ? d0 : 0u;
+            TESSEL_PIN(d0);
+            const uint32_t ra = __umul24(d0, RS >> NB) + rec0;
+            const uint32_t p0 = lds_load(ra), p1 = NB > 1 ? lds_load(ra + kRow) : 0u, p2 = NB > 2 ? lds_load(ra + 2 * kRow) : 0u;
+            const uint32_t alive = NP == 0 ? p0 >> 16 : lds_load(ra + row_alive * kRow);
+            const uint32_t w = lds_load(ra + row_w * kRow), l = ONE ? w : lds_load(ra + row_l * kRow);
+            // earliest entry whose type may run: a multiplexer keyed by the planes.  (A device picked for its head: the head.)
+            const uint32_t may = W64 ? (d0 & 32u ? (uint32_t)((uint64_t)R >> 32) : (uint32_t)R) >> (d0 & 31u) : (uint32_t)R >> d0;
+            auto runs = [&](int y) -> uint32_t { return (uint32_t)__builtin_amdgcn_sbfe((int)may, y, 1); };
+            uint32_t gate;
+            if (NB == 1) gate = bfi(p0, runs(1), runs(0));
+            else {
+                gate = bfi(p1, bfi(p0, runs(3), runs(2)), bfi(p0, runs(1), runs(0)));
+                if (NB > 2) gate = bfi(p2, bfi(p1, bfi(p0, runs(7), runs(6)), bfi(p0, runs(5), runs(4))), gate);
+            }
+            const uint32_t p = low_bit(alive & gate);
+            // its symbol as all-or-nothing masks, its code
+            const uint32_t ly = (uint32_t)__builtin_amdgcn_sbfe((int)p0, p, 1), hy = NB > 1 ? (uint32_t)__builtin_amdgcn_sbfe((int)p1, p, 1) : 0u;
+            const uint32_t zy = NB > 2 ? (uint32_t)__builtin_amdgcn_sbfe((int)p2, p, 1) : 0u;
+            const uint32_t y = (ly & 1u) | (hy & 2u) | (zy & 4u), c = d0 + y, ca = c << 2;
+            const uint32_t t_add = lds_load(ca), t_next = lds_load(ca + TS), t_at = lds_load(ca + 2 * TS), t_inc = lds_load(ca + 3 * TS);
+            const uint32_t t_mem = ONE ? 0u : lds_load(ca + 4 * TS), t_next_hi = W64 ? lds_load(ca + 5 * TS) : 0u;
+            // (worked out while the table words are on their way) the entry out, the device's new head.  (A device that is empty
+            // now gets a meaningless bit, and a harmless one: its types are used up, and R holds no such type.)
+            const uint32_t left = alive & ~(1u << p), q = low_bit(left);
+            uint32_t y2 = __builtin_amdgcn_ubfe(p0, q, 1);
+            if (NB > 1) y2 |= __builtin_amdgcn_ubfe(p1, q, 1) << 1;
+            if (NB > 2) y2 |= __builtin_amdgcn_ubfe(p2, q, 1) << 2;
+            const mask_t hm_new = (HM & ~((mask_t)DEV << d0)) | (mask_t)1u << (d0 + y2);
+            uint32_t rest = left & ~(p0 ^ ly);                   // entries of the type that are left
+            if (NB > 1) rest &= ~(p1 ^ hy);
+            if (NB > 2) rest &= ~(p2 ^ zy);
+            const uint32_t at_w = NP == 3 ? 4u * y : NP == 2 ? 5u * y : ly & 5u;
+            const uint32_t more = __builtin_amdgcn_ubfe(w, at_w, NP == 3 ? 4 : 5);
+            const uint32_t lead = ONE ? __builtin_amdgcn_ubfe(l, (ly & 4u) | 10u, 4) : NP == 2 ? __builtin_amdgcn_ubfe(l, 4u * y, 4) : __builtin_amdgcn_ubfe(l, 3u * y, 3);
+            const mask_t onec = (mask_t)1u << c;
+            const bool used_up = rest == 0, stalled = used_up | (more < 2u);
+            const mask_t x_new = X | (used_up ? onec : (mask_t)0);
+            const mask_t next = W64 ? (mask_t)(t_next | (uint64_t)t_next_hi << 32) : (mask_t)t_next;
+            const mask_t r_new = (R & ~(stalled ? onec : (mask_t)0)) | (next & ~x_new);
+            const uint32_t w_new = w + t_add, l_new = ONE ? w_new : l + t_mem;
+            uint32_t entry = 0;
+            if (REPAIR || building) {
+                if (NP == 0) lds_store(ra, p0 & ~(0x10000u << p)); else lds_store(ra + row_alive * kRow, left);
+                lds_store(ra + row_w * kRow, w_new);
+                if (!ONE) lds_store(ra + row_l * kRow, l_new);
+                lds_add((t_at & 0xFFFFu) + lane4, t_inc);        // (no consumer: 0 to its own record)
+                worst = max(worst, (int)l_new >> (ONE ? 18 : NP == 2 ? 16 : 24));
+                R = r_new; X = x_new; HM = hm_new;
+                entry = ((lead - (uint32_t)__builtin_popcount(rest)) << 9) + (t_at >> 16);       // 8 type, micro-batch << 9: lead + N_R - 1 - entries left
+            }
+            return entry;
+        };
+        const int full = total / 2;
+        whole = true;
+        for (int wi = 0; wi < full; wi++) {
+            const uint32_t e0 = step(), e1 = step();
+            prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
+            if (!REPAIR || (wi & 7) == 7) {
+                const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
+                if (__ballot(going) == 0) { whole = false; break; }
+            }
+        }
+        if (whole && (total & 1)) prog[(size_t)full * kProgRow] = step();
+    };
+
     // ---------------------------------------------------------------- build: 64 new candidates
     auto build = [&](uint64_t idx, bool valid) {
         uint32_t slot = 0;
@@ -129,6 +292,10 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         uint64_t rest = idx;
         const bool sampled = space == kSampledStrict || space == kSampledRepair;
         if (sampled) ka = stream_keys(P.seed, idx, kb);
+        int worst = INT_MIN;
+        bool any = true, whole = true;
+        if constexpr (CODES) build_codes(ka, kb, valid, prog, status, worst, whole);
+        else {
         lds_store(G.trash + lane4, 0u);
         // ---- leads, by type
         for (int g = 0; g < K; g++) {
@@ -239,7 +406,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         }
         if (space == kFactorial) status = dup ? kDup : tpm ? kTpMismatch : prop2 ? kProp2 : kOk;
         // (exhaustive spaces: often none of a wave's candidates is left here, or after a few blocks)
-        const bool any = REPAIR || __ballot(valid && status == kOk) != 0;
+        any = REPAIR || __ballot(valid && status == kOk) != 0;
         // ---- what may run, memory at the window entry (type i has handled micro-batches 0 .. lead - 1), heads
         uint32_t RD = 0, HD = 0;
         uint64_t hcnt = 0;                                       // TP: devices a type heads, six bits a type
@@ -269,7 +436,6 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         }
         // ---- blocks in an executable sequence
         bool building = REPAIR || (valid && status == kOk);
-        int worst = INT_MIN;
         const uint32_t dlast = (uint32_t)D - 1u;
         // the head of a device list changed: TP types it left or reached
         auto head_moved = [&](uint32_t code0, uint32_t from, uint32_t to) {
@@ -424,7 +590,7 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             return entry;
         };
         const int full = total / 2;
-        bool whole = any;
+        whole = any;
         for (int wi = 0; any && wi < full; wi++) {
             const uint32_t e0 = step(), e1 = step();
             prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
@@ -434,10 +600,11 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             }
         }
         if (whole && (total & 1)) prog[(size_t)full * kProgRow] = step();
+        }
         // ---- verdict
         int peak = worst;
         if (status == kOk) {
-            for (int d = 0; d < D; d++) if (types_on(d) == 0) peak = max(peak, 0);      // a device without blocks holds nothing
+            if (idle) peak = max(peak, 0);                       // a device without blocks holds nothing
             if (peak > M) status = kMem;
         }
         const bool rejected = valid && status != kOk, ok = valid && status == kOk;
@@ -454,8 +621,10 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             // (all N_R occurrences are placed: next micro-batch - N_R is the lead)
             for (int r = 0; r < P.ntok; r += 4) {
                 uint32_t pack = 0;
-                for (int q = 0; q < 4 && r + q < P.ntok; q++)
-                    pack |= ((lds_load(wrow0 + (uint32_t)P.ring_head[r + q] * kRow) >> mushift) - NR) << (8 * q);
+                for (int q = 0; q < 4 && r + q < P.ntok; q++) {
+                    const uint32_t h = G.head[r + q], w = lds_load((h & 0xFFFFu) + lane4);
+                    pack |= (CODES ? __builtin_amdgcn_ubfe(w, h >> 16 & 31u, h >> 24) : (w >> mushift) - NR) << (8 * q);
+                }
                 meta[(size_t)(3 + r / 4) * kProgRow] = pack;
             }
             lds_store8(st_row + slot, 1u);
@@ -470,22 +639,24 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
         __syncthreads();
         const uint32_t n = slots_in(cls, true, slot);
         const bool have = (uint32_t)lane < n;
+        // (a lane without a candidate runs the first one's program and drops the result)
+        if (CODES && !have) slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
         const uint32_t *meta = slots + slot, *prog = progs + slot;
         __threadfence_block();                                   // the wave's other lanes wrote these words
         const uint64_t idx = have ? (uint64_t)meta[0] | ((uint64_t)meta[kProgRow] << 32) : first;
         const int pk = (int)meta[2 * kProgRow];
-        const uint32_t st0 = G.state + lane4;
+        const uint32_t st0 = G.state + lane_s, prev0 = G.prev + lane_s;
         for (int r = 0; r < P.ntok; r += 4) lds_store(G.leads + (uint32_t)(r / 4) * kRow + lane4, have ? meta[(size_t)(3 + r / 4) * kProgRow] : 0u);
-        for (int s = 0; s < P.nslots; s++) lds_store(st0 + (uint32_t)s * kRow, 0u);
-        for (int d = 0; d < D; d++) lds_store(G.prev + (uint32_t)d * kRow + lane4, 0u);
+        for (int s = 0; s < P.nslots; s++) time_store(st0 + (uint32_t)s * SROW, 0u);
+        for (int d = 0; d < D; d++) time_store(prev0 + (uint32_t)d * SROW, 0u);
         const int maxin = G.maxin;
         auto block = [&](uint32_t e, uint32_t A, uint32_t B, uint32_t pr) {
-            const uint32_t mu8 = (e >> 6) << 8, da = (B & 0xFFFFu) + lane4;
+            const uint32_t mu8 = (e >> 6) * SROW, da = (B & 0xFFFFu) + lane_s;
             if (CHAIN) {
-                const uint32_t ta = (B >> 16) + mu8 + lane4;
-                const uint32_t en = max(lds_load(da), lds_load(ta)) + (A & 0xFFFFFFu);
-                lds_store(da, en);
-                lds_store(ta, en);
+                const uint32_t ta = (B >> 16) + mu8 + lane_s;
+                const uint32_t en = max(time_load(da), time_load(ta)) + (A & 0xFFFFFFu);
+                time_store(da, en);
+                time_store(ta, en);
                 return;
             }
             const uint32_t g4 = (e & 63u) << 2;
@@ -502,6 +673,51 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             lds_store(da, en);
             for (uint32_t rest = mask; rest; rest &= rest - 1u) lds_store(st0 + (uint32_t)__builtin_ctz(rest) * kRow, en);
             lds_store((B >> 16) + (mu8 & (uint32_t)((int)A >> 31)) + lane4, en);
+        };
+        // Eight blocks of a chain problem's program.  A block's two times are read before the block before has written its own,
+        // which it takes from a register where they share the device or the ring entry (end times only grow, so the largest of the
+        // three is right): the reads' latency, two thirds of a block's time at one to three waves a SIMD, overlaps.
+        auto codes_word = [&](const uint32_t (&cur)[4], int left) {
+            constexpr uint32_t table = W64 ? 6u * 256u : (NP <= 1 ? 4u : 5u) * 128u;       // (GraphTab::sw)
+            uint32_t da[8], ta[8], t[8];
+            auto look_up = [&](bool all) {
+                uint32_t e[8], B[8];
+#pragma unroll
+                for (int q = 0; q < 8; q++) {
+                    // (a word past the last block was never written: its type is taken as 0, and nothing of it is used)
+                    e[q] = !all && q >= left ? 0u : q & 1 ? cur[q / 2] >> 16 : cur[q / 2] & 0xFFFFu;
+                    lds_load2((e[q] & 0x1F8u) + table, t[q], B[q]);
+                }
+                __builtin_amdgcn_sched_barrier(0);               // (all eight on their way before the first is waited for)
+#pragma unroll
+                for (int q = 0; q < 8; q++) {
+                    da[q] = (B[q] & 0xFFFFu) + lane_s;
+                    ta[q] = (B[q] >> 16) + ((e[q] >> 2 & 0xF80u) | lane_s);
+                }
+            };
+            uint32_t fr, tk, before = 0;
+            auto one = [&](int q, bool more) {
+                uint32_t fr2 = 0, tk2 = 0;
+                if (more) { fr2 = time_load(da[q + 1]); tk2 = time_load(ta[q + 1]); }
+                __builtin_amdgcn_sched_barrier(0);
+                const bool shared = q > 0 && (da[q] == da[q - (q > 0)] || ta[q] == ta[q - (q > 0)]);
+                const uint32_t en = max(max(fr, tk), shared ? before : 0u) + t[q];
+                time_store(da[q], en);
+                time_store(ta[q], en);
+                __builtin_amdgcn_sched_barrier(0);
+                before = en; fr = fr2; tk = tk2;
+            };
+            if (left >= 8) {
+                look_up(true);
+                fr = time_load(da[0]); tk = time_load(ta[0]);
+#pragma unroll
+                for (int q = 0; q < 8; q++) one(q, q < 7);
+            } else {
+                look_up(false);
+                fr = time_load(da[0]); tk = time_load(ta[0]);
+#pragma unroll
+                for (int q = 0; q < 7; q++) if (q < left) one(q, q + 1 < left);
+            }
         };
         uint32_t T = 0;
         bool done = !have;
@@ -523,8 +739,14 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
                 const int ahead = wi + 4 < nwords ? wi + 4 : wi;
 #pragma unroll
                 for (int q = 0; q < 4; q++) nxt[q] = prog[(size_t)(ahead + q) * kProgRow];
-                uint32_t e[8], A[8], B[8], pr[8];
                 const int left = total - 2 * wi;                 // blocks from here on
+                if constexpr (CODES) {
+                    codes_word(cur, left);
+#pragma unroll
+                    for (int q = 0; q < 4; q++) cur[q] = nxt[q];
+                    continue;
+                }
+                uint32_t e[8], A[8], B[8], pr[8];
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
                     // (a word past the last block was never written, and a lane without a candidate has stale ones: type and
@@ -547,58 +769,66 @@ __global__ __launch_bounds__(kWave) void eval_graph_kernel(const KParams *__rest
             // largest growth; and a value that grew by D got its time from one that grew by D the time before (that
             // one's growth bounds its own from above), which is again one of these, so following them closes a cycle
             // of ratio D.  (Forward-only pipelines need this: devices before the slowest keep a smaller growth for ever.)
-            bool same = true, seen = false;
-            uint32_t delta = 0;
-            auto grew = [&](uint32_t by, bool on) {
-                if (on) { if (!seen) { delta = by; seen = true; } else if (by != delta) same = false; }
-            };
+            // (Values by fours: their loads are on their way together.  One by one, with the loads' latency and the bookkeeping in
+            // lane masks, a boundary cost 40 to 60 % of the sweeps of graphs with many short rings.)
             auto in_flight = [&](int r) -> uint32_t {
                 return (lds_load(G.leads + (uint32_t)(r / 4) * kRow + lane4) >> (8 * (r & 3))) & 255u;
             };
-            uint32_t top = 0;
-            if (settle) {
-                for (int d = 0; d < D; d++)
-                    if (types_on(d) > 0) top = max(top, lds_load(st0 + (uint32_t)d * kRow) - lds_load(G.prev + (uint32_t)d * kRow + lane4));
+            auto values = [&](auto &&device, auto &&ring) {
+                for (int d = 0; d < D; d += 4) {
+                    uint32_t x[4], old[4];
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {                // (past the last one: the last one again)
+                        const uint32_t at = (uint32_t)min(d + q, D - 1) * SROW;
+                        x[q] = time_load(st0 + at); old[q] = time_load(prev0 + at);
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; q++) device(min(d + q, D - 1), x[q], x[q] - old[q]);
+                }
                 for (int r = 0; r < P.ntok; r++) {
-                    const uint32_t base = st0 + (uint32_t)P.ring_base[r] * kRow, kept = st0 + (uint32_t)P.ring_kept[r] * kRow, lg = in_flight(r);
-                    for (uint32_t m = 0; m < NR; m++) {
-                        const uint32_t by = lds_load(base + (m + NR) * kRow) - lds_load(kept + m * kRow);
-                        top = max(top, m < lg ? by : 0u);
+                    const uint32_t rows = G.ring[r], base = st0 + (rows & 0xFFFFu) * SROW, kept = st0 + (rows >> 16) * SROW, lg = in_flight(r);
+                    for (uint32_t m = 0; m < NR; m += 4) {
+                        uint32_t x[4], old[4];
+#pragma unroll
+                        for (uint32_t q = 0; q < 4; q++) {
+                            const uint32_t at = min(m + q, NR - 1u) * SROW;
+                            x[q] = time_load(base + at + NR * SROW); old[q] = time_load(kept + at);
+                        }
+#pragma unroll
+                        for (uint32_t q = 0; q < 4; q++) {
+                            const uint32_t n = min(m + q, NR - 1u);
+                            ring(base + n * SROW, kept + n * SROW, (uint32_t)D + (uint32_t)r * NR + n, n < lg, x[q], x[q] - old[q]);
+                        }
                     }
                 }
-            }
-            bool held = j > 0 && top == top_before;
-            uint64_t now_lo = 0, now_hi = 0;
-            uint32_t v = 0;                                      // number of the value (uniform)
-            auto keeps = [&](uint32_t by, bool on) {
-                if (!settle) return;
-                const uint64_t was = (v < 64u ? was_lo : was_hi) >> (v & 63u) & 1u, is = on && by == top ? 1u : 0u;
-                if (was && !is) held = false;
-                if (v < 64u) now_lo |= is << v; else now_hi |= is << (v & 63u);
-                v++;
             };
-            for (int d = 0; d < D; d++) {
-                const uint32_t x = lds_load(st0 + (uint32_t)d * kRow), pa = G.prev + (uint32_t)d * kRow + lane4, by = x - lds_load(pa);
-                lds_store(pa, x);
-                if (types_on(d) > 0) { grew(by, true); keeps(by, true); }
-            }
-            for (int r = 0; r < P.ntok; r++) {
-                const uint32_t base = st0 + (uint32_t)P.ring_base[r] * kRow, kept = st0 + (uint32_t)P.ring_kept[r] * kRow, lg = in_flight(r);
-                for (uint32_t m = 0; m < NR; m++) {
-                    const uint32_t x = lds_load(base + (m + NR) * kRow), by = x - lds_load(kept + m * kRow);
-                    grew(by, m < lg);
-                    keeps(by, m < lg);
-                    const uint32_t keep = m < lg ? x : 0u;
-                    lds_store(base + m * kRow, keep);
-                    lds_store(kept + m * kRow, keep);
-                    lds_store(base + (m + NR) * kRow, 0u);
-                }
-            }
+            uint32_t least = 0xFFFFFFFFu, top = 0;               // growths
+            auto grew = [&](uint32_t by, bool on) { least = min(least, on ? by : 0xFFFFFFFFu); top = max(top, on ? by : 0u); };
+            if (settle)
+                values([&](int d, uint32_t, uint32_t by) { grew(by, (busy >> d & 1u) != 0); },
+                       [&](uint32_t, uint32_t, uint32_t, bool on, uint32_t, uint32_t by) { grew(by, on); });
+            uint64_t now_lo = 0, now_hi = 0;                     // the values that grew by that much, a bit each
+            auto note = [&](uint32_t v, uint32_t by, bool on) {
+                if (!settle) { grew(by, on); return; }
+                if (v < 64u) now_lo |= on && by == top ? 1ull << v : 0ull; else now_hi |= on && by == top ? 1ull << (v & 63u) : 0ull;
+            };
+            values([&](int d, uint32_t x, uint32_t by) {
+                       time_store(prev0 + (uint32_t)d * SROW, x);
+                       note((uint32_t)d, by, (busy >> d & 1u) != 0);
+                   },
+                   [&](uint32_t base, uint32_t kept, uint32_t v, bool on, uint32_t x, uint32_t by) {
+                       note(v, by, on);
+                       const uint32_t keep = on ? x : 0u;
+                       time_store(base, keep);
+                       time_store(kept, keep);
+                       time_store(base + NR * SROW, 0u);
+                   });
             if (settle) {
+                const bool held = j > 0 && top == top_before && (was_lo & ~now_lo) == 0 && (was_hi & ~now_hi) == 0;
                 if (!done && held) { T = top; done = true; }
                 top_before = top; was_lo = now_lo; was_hi = now_hi;
             }
-            if (!done && same && seen) { T = delta; done = true; }
+            if (!done && least == top) { T = top; done = true; }
         }
         const bool scored = have && done, left_open = have && !done;
         const uint32_t ns = (uint32_t)__builtin_popcountll(__ballot(scored));
@@ -668,16 +898,19 @@ typedef void (*graph_fn)(const KParams *, const GraphTab *, uint64_t, uint64_t, 
 template <bool REPAIR, int KIND>
 static graph_fn pick_np(int np)
 {
+    if constexpr (KIND >= 3) if (np == 0) return eval_graph_kernel<0, REPAIR, KIND>;
     return np == 1 ? eval_graph_kernel<1, REPAIR, KIND> : np == 2 ? eval_graph_kernel<2, REPAIR, KIND> : eval_graph_kernel<3, REPAIR, KIND>;
 }
 
-static graph_fn pick_graph(const KParams &kp)
+template <bool REPAIR>
+static graph_fn pick_kind(const KParams &kp)
 {
-    const int kind = kp.tp ? 2 : kp.graph_chain ? 0 : 1;
-    if (kp.space == kSampledRepair)
-        return kind == 0 ? pick_np<true, 0>(kp.graph_np) : kind == 1 ? pick_np<true, 1>(kp.graph_np) : pick_np<true, 2>(kp.graph_np);
-    return kind == 0 ? pick_np<false, 0>(kp.graph_np) : kind == 1 ? pick_np<false, 1>(kp.graph_np) : pick_np<false, 2>(kp.graph_np);
+    if (kp.tp) return pick_np<REPAIR, 2>(kp.graph_np);
+    if (kp.graph_codes) return kp.graph_codes == 1 ? pick_np<REPAIR, 3>(kp.graph_np) : pick_np<REPAIR, 4>(kp.graph_np);
+    return kp.graph_chain ? pick_np<REPAIR, 0>(kp.graph_np) : pick_np<REPAIR, 1>(kp.graph_np);
 }
+
+static graph_fn pick_graph(const KParams &kp) { return kp.space == kSampledRepair ? pick_kind<true>(kp) : pick_kind<false>(kp); }
 
 const void *graph_kernel(const KParams &kp) { return (const void *)pick_graph(kp); }
 
