@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <climits>
 #include <cstdlib>
 #include <cstdint>
@@ -1122,32 +1123,110 @@ void check_period(tessel_problem *p)
 
 }  // namespace
 
+// ---- mail: small results straight from a kernel into pinned host memory ---------------------------------------------
+// A copy of 100 bytes to host memory through the runtime and the wait for it take 18 us, as long as scoring a thousand
+// candidates; a kernel's own stores and a look at the last of them take 3 after the kernel's launch.  A few boxes serve all handles, threads
+// and GPUs, one for the time of a call each; a call that finds none (or no pinned memory) copies as before.  The
+// memory is allocated with the first call that could use it and freed when the process ends.
+namespace {
+constexpr int kMailboxes = 16;
+std::mutex g_mail_mutex;
+DevMail *g_mail = nullptr;
+uint32_t g_mail_used = 0, g_mail_told = 0;
+
+void free_mail()
+{
+    std::lock_guard<std::mutex> lock(g_mail_mutex);
+    if (g_mail && g_mail_used == 0) (void)hipHostFree(g_mail);
+    g_mail = nullptr;
+    g_mail_used = ~0u;
+}
+
+class Mailbox {
+public:
+    DevMail *box = nullptr;
+    uint32_t told = 0;
+    Mailbox()
+    {
+        std::lock_guard<std::mutex> lock(g_mail_mutex);
+        if (!g_mail && g_mail_used == 0) {
+            void *mem = nullptr;
+            if (hipHostMalloc(&mem, kMailboxes * sizeof(DevMail), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+                (void)hipGetLastError();
+                return;
+            }
+            g_mail = (DevMail *)mem;
+            for (int k = 0; k < kMailboxes; k++) g_mail[k].told = 0;
+            std::atexit(free_mail);
+        }
+        const uint32_t left = ~g_mail_used & ((1u << kMailboxes) - 1u);
+        if (!g_mail || !left) return;
+        at = __builtin_ctz(left);
+        g_mail_used |= 1u << at;
+        if (++g_mail_told == 0) g_mail_told = 1;
+        told = g_mail_told;
+        box = g_mail + at;
+    }
+    ~Mailbox()
+    {
+        if (!box || lost) return;
+        std::lock_guard<std::mutex> lock(g_mail_mutex);
+        g_mail_used &= ~(1u << at);
+    }
+    Mailbox(const Mailbox &) = delete;
+    Mailbox &operator=(const Mailbox &) = delete;
+    // Until the mail is there: at first by looking at it, then by waiting for the stream, which also finds out about a failed
+    // launch.  A box whose launch failed may still be written to, and is not used again.
+    int wait(hipStream_t st)
+    {
+        const auto start = std::chrono::steady_clock::now();
+        for (int k = 1;; k++) {
+            if (__atomic_load_n(&box->told, __ATOMIC_ACQUIRE) == told) return 0;
+            if (k % 64 == 0 && std::chrono::steady_clock::now() - start > std::chrono::microseconds(200)) break;
+            __builtin_ia32_pause();
+        }
+        const hipError_t e = hipStreamSynchronize(st);
+        if (e != hipSuccess || __atomic_load_n(&box->told, __ATOMIC_ACQUIRE) != told) {
+            lost = true;
+            return e != hipSuccess ? (int)e : (int)hipErrorUnknown;
+        }
+        return 0;
+    }
+private:
+    int at = 0;
+    bool lost = false;
+};
+}  // namespace
+
 // The running best as it is on the device, into p->result and p->detail.  The record is read on every call: scoring
 // launches that the caller captured in a graph change it when they are replayed, without a call of this library.
-// Where nothing has been scored through this handle since the last reading, the record alone comes back, and the candidate
-// decoded then stands if the record still names it.  Else one launch and one copy: the candidate is decoded on
-// the device from the record there, and record and decoded candidate, which lie in a row, come back together.
+// One launch: the candidate is decoded on the device from the record there, unless the workspace has it already; record and
+// candidate come back by mail, the record alone where it names the candidate this handle has.
 static int read_back(tessel_problem *p)
 {
-    if (!p->best_dirty) {
-        DevResult now;
-        hipError_t e = hipMemcpyAsync(&now, (char *)p->ws + kWsResultOff, sizeof now, hipMemcpyDeviceToHost, p->stream);
+    Mailbox mail;
+    int le = launch_detail(p->kp, p->ws, mail.box, mail.told, p->result.period, p->result.index, p->stream);
+    if (le) return hip_fail(p, le);
+    if (mail.box) {
+        le = mail.wait(p->stream);
+        if (le) return hip_fail(p, le);
+        memcpy(&p->result, mail.box->words, sizeof p->result);
+        if (!mail.box->whole) return TESSEL_OK;
+        memcpy(&p->detail, mail.box->words + kMailDetail, sizeof p->detail);
+    } else {
+        struct { unsigned char bytes[kWsDetailOff]; DevDetail detail; } both;
+        static_assert(offsetof(decltype(both), detail) == kWsDetailOff && kWsResultOff == 0, "result and detail are copied in one piece");
+        hipError_t e = hipMemcpyAsync(&both, p->ws, sizeof both, hipMemcpyDeviceToHost, p->stream);
         if (e != hipSuccess) return hip_fail(p, (int)e);
         e = hipStreamSynchronize(p->stream);
         if (e != hipSuccess) return hip_fail(p, (int)e);
-        if (now.period == p->result.period && now.index == p->result.index) { p->result = now; return TESSEL_OK; }
-        p->best_dirty = true;
+        DevResult now;
+        memcpy(&now, both.bytes, sizeof now);
+        const bool known = now.period != INT_MAX && now.period == p->result.period && now.index == p->result.index;
+        p->result = now;
+        if (known) return TESSEL_OK;
+        p->detail = both.detail;
     }
-    int le = launch_detail(p->kp, p->ws, p->stream);
-    if (le) return hip_fail(p, le);
-    struct { unsigned char bytes[kWsDetailOff]; DevDetail detail; } both;
-    static_assert(offsetof(decltype(both), detail) == kWsDetailOff && kWsResultOff == 0, "result and detail are copied in one piece");
-    hipError_t e = hipMemcpyAsync(&both, p->ws, sizeof both, hipMemcpyDeviceToHost, p->stream);
-    if (e != hipSuccess) return hip_fail(p, (int)e);
-    e = hipStreamSynchronize(p->stream);
-    if (e != hipSuccess) return hip_fail(p, (int)e);
-    memcpy(&p->result, both.bytes, sizeof(DevResult));
-    p->detail = both.detail;
     if (p->result.period != INT_MAX) check_period(p);
     return TESSEL_OK;
 }
@@ -1504,11 +1583,20 @@ extern "C" int tessel_best_completion(tessel_problem *p, tessel_schedule *out, u
     if (!p->comp_ready || !p->ws) return TESSEL_E_NO_FEASIBLE;
     if (!owns_workspace(p)) return TESSEL_E_WORKSPACE;
     if (out->num_microbatches != p->comp.N) return TESSEL_E_INVALID_ARG;
-    hipError_t e = hipStreamSynchronize(p->stream);
-    if (e != hipSuccess) return hip_fail(p, (int)e);
     DevCompletion best;
-    e = hipMemcpy(&best, (char *)p->ws + kWsCompletionOff, sizeof best, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hip_fail(p, (int)e);
+    {
+        Mailbox mail;
+        if (mail.box) {
+            int le = launch_tell(p->ws, kWsCompletionOff, sizeof best, mail.box, mail.told, p->stream);
+            if (!le) le = mail.wait(p->stream);
+            if (le) return hip_fail(p, le);
+            memcpy(&best, mail.box->words, sizeof best);
+        } else {
+            hipError_t e = hipStreamSynchronize(p->stream);
+            if (e == hipSuccess) e = hipMemcpy(&best, (char *)p->ws + kWsCompletionOff, sizeof best, hipMemcpyDeviceToHost);
+            if (e != hipSuccess) return hip_fail(p, (int)e);
+        }
+    }
     if (best.makespan == INT_MAX) return TESSEL_E_NO_SCHEDULE;
     int rc = complete_with(p, out, best.ordinal, p->comp.J);
     if (rc) return rc;

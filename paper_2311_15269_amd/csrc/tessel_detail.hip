@@ -12,20 +12,59 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <limits.h>
+#include <stddef.h>
 
 #include "tessel_common.h"
 
 namespace tessel {
 
+// ------------------------------------------------------------------ mail
+// Words to pinned host memory: written through to it one by one (system scope), the last one when all others have arrived.
+__device__ __forceinline__ void mail_word(uint32_t *to, uint32_t v) { __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+__device__ __forceinline__ void mail_words(uint32_t *to, const void *from, int words)
+{
+    for (int w = threadIdx.x; w < words; w += kWave) mail_word(to + w, ((const uint32_t *)from)[w]);
+}
+__device__ __forceinline__ void mail_end(DevMail *mail, uint32_t told, bool whole)
+{
+    if (threadIdx.x == 0) mail_word(&mail->whole, whole ? 1u : 0u);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // (one wave: all lanes' words have arrived)
+    if (threadIdx.x == 0) mail_word(&mail->told, told);
+}
+// the record, and the candidate as the workspace has it unless the host has it already
+__device__ __forceinline__ void mail_stored(DevMail *mail, uint32_t told, const DevResult *res, const DevDetail *out, bool whole)
+{
+    if (!mail) return;
+    mail_words(mail->words, res, sizeof(DevResult) / 4);
+    if (whole) mail_words(mail->words + kMailDetail, out, sizeof(DevDetail) / 4);
+    mail_end(mail, told, whole);
+}
+
+__global__ __launch_bounds__(kWave) void tell_kernel(const uint32_t *__restrict__ from, int words, DevMail *mail, uint32_t told)
+{
+    mail_words(mail->words, from, words);
+    mail_end(mail, told, false);
+}
+
+int launch_tell(void *ws, size_t offset, size_t bytes, DevMail *mail, uint32_t told, void *stream)
+{
+    hipLaunchKernelGGL(tell_kernel, dim3(1), dim3(kWave), 0, (hipStream_t)stream, (const uint32_t *)((char *)ws + offset), (int)(bytes / 4), mail, told);
+    return (int)hipGetLastError();
+}
+
 __global__ __launch_bounds__(kWave) void detail_kernel(const KParams *__restrict__ Pp, const DevResult *__restrict__ res,
-                                                       DevDetail *__restrict__ out)
+                                                       DevDetail *out, DevMail *mail, uint32_t told, int known_period,
+                                                       uint64_t known_index)
 {
     __shared__ uint32_t lead[kMaxKW], mask[kMaxKW];
     __shared__ uint64_t producers[kMaxKW];
     const KParams &P = *Pp;
-    if (res->period == INT_MAX) return;                          // nothing feasible yet
     const uint64_t idx = res->index;
-    if (out->status >= 0 && out->index == idx) return;           // the running best has not changed since it was decoded
+    const bool feasible = res->period != INT_MAX, known = res->period == known_period && idx == known_index;
+    if (!feasible || (out->status >= 0 && out->index == idx)) {  // nothing feasible yet; the running best has not changed since it was decoded
+        mail_stored(mail, told, res, out, feasible && !known);
+        return;
+    }
     const int lane = threadIdx.x, D = P.D, K = P.K, space = P.space;
     const uint32_t NR = (uint32_t)P.NR;
     const bool here = lane < D, sampled = space == kSampledStrict || space == kSampledRepair;
@@ -237,6 +276,8 @@ __global__ __launch_bounds__(kWave) void detail_kernel(const KParams *__restrict
     if (lane < kMaxDW) { out->peak[lane] = here ? peak : 0; out->order_len[lane] = len; }
     if (lane < K) out->leads[lane] = (int)lead[lane];
     if (lane == 0) { out->status = status; out->index = idx; }
+    __threadfence();                                             // (read back below by other lanes)
+    mail_stored(mail, told, res, out, true);
 }
 
 // ------------------------------------------------------------------ a lane per (device, block type)
@@ -264,14 +305,18 @@ __device__ __forceinline__ uint32_t least_of_device(uint32_t x)
 // (WIDE: more than 32 lanes)
 template <int LG, bool TP, bool WIDE>
 __global__ __launch_bounds__(kWave) void detail_lanes_kernel(const KParams *__restrict__ Pp, const DevResult *__restrict__ res,
-                                                             DevDetail *__restrict__ out)
+                                                             DevDetail *out, DevMail *mail, uint32_t told, int known_period,
+                                                             uint64_t known_index)
 {
     constexpr uint32_t G = 1u << LG;
     constexpr int NP = LG > 0 ? LG : 1;
     __shared__ uint32_t lead[kMaxKW], home[kMaxKW], ahead[kMaxKW], after[kMaxKW];
     __shared__ uint32_t mates[2 * kMaxKW];                       // by type: its lanes, below 32 and from 32 on
     __shared__ uint64_t producers[kMaxKW];
-    __shared__ uint8_t order[kMaxDW * kMaxPos];    // symbols in device order
+    __shared__ __attribute__((aligned(4))) uint8_t order[kMaxDW * kMaxPos];        // symbols in device order
+    __shared__ uint32_t det[sizeof(DevDetail) / 4];              // DevDetail by words
+    static_assert(sizeof(DevDetail) / 4 == 4 + 2 * kMaxDW + kMaxKW + kMaxDW * kMaxPos / 4 && offsetof(DevDetail, peak) == 16 &&
+                  offsetof(DevDetail, leads) == 4 * (4 + kMaxDW) && offsetof(DevDetail, order_len) == 4 * (4 + kMaxDW + kMaxKW), "words of DevDetail");
     const KParams &P = *Pp;
     const int lane = threadIdx.x, period = res->period, decoded = out->status;
     const uint64_t idx = res->index, decoded_idx = out->index;
@@ -295,8 +340,10 @@ __global__ __launch_bounds__(kWave) void detail_lanes_kernel(const KParams *__re
 #pragma unroll
     for (int k = 0; k < 2; k++) { src[k] = P.dsrc[lane + k * kWave]; dst[k] = P.ddst[lane + k * kWave]; crosses[k] = P.dcross[lane + k * kWave]; }
     static_assert(kMaxDeps == 2 * kWave, "two dependencies a lane");
-    if (period == INT_MAX) return;                               // nothing feasible yet
-    if (decoded >= 0 && decoded_idx == idx) return;              // the running best has not changed since it was decoded
+    if (period == INT_MAX || (decoded >= 0 && decoded_idx == idx)) {      // nothing feasible yet; the running best has not changed since it was decoded
+        mail_stored(mail, told, res, out, period != INT_MAX && !(period == known_period && idx == known_index));
+        return;
+    }
     auto type_at = [&](uint32_t s) -> uint32_t { return byte_of(s < 4u ? types_lo : types_hi, s & 3u); };
     const bool block = here && y < ntd;                          // the lane has a block type
     const uint32_t type = block ? type_at(y) : 0u;
@@ -488,19 +535,33 @@ __global__ __launch_bounds__(kWave) void detail_lanes_kernel(const KParams *__re
         }
         if (peak == INT_MIN) peak = 0;                           // a device without blocks
         if (status == kOk && __ballot(dev_lane && peak > P.M) != 0) status = kMem;
-        if (lane < kMaxDW) { out->peak[lane] = dev_lane ? peak : 0; out->order_len[lane] = len; }
+        if (lane < kMaxDW) { det[4 + lane] = (uint32_t)(dev_lane ? peak : 0); det[4 + kMaxDW + kMaxKW + lane] = (uint32_t)len; }
     }
+    if (lane == 0) { det[0] = (uint32_t)status; det[1] = 0; det[2] = (uint32_t)idx; det[3] = (uint32_t)(idx >> 32); }
+    det[4 + kMaxDW + lane] = lane < K ? lead[lane] : 0u;
     // (places behind a device's last block hold nothing, and are not read)
-    for (int k = lane; k < D * kMaxPos; k += kWave) {
-        const int d = k / kMaxPos;
-        const uint32_t s = order[k] & 7u;
-        out->orders[d][k % kMaxPos] = (uint8_t)byte_of(s < 4u ? P.type_of[d] : P.type_of_hi[d], s & 3u);
+    for (int k = lane; k < D * kMaxPos / 4; k += kWave) {
+        const int d = k / (kMaxPos / 4);
+        const uint32_t lo = P.type_of[d], hi = P.type_of_hi[d], four = ((const uint32_t *)order)[k];
+        uint32_t types = 0;
+        for (int q = 0; q < 4; q++) {
+            const uint32_t s = four >> (8 * q) & 7u;
+            types |= byte_of(s < 4u ? lo : hi, s & 3u) << (8 * q);
+        }
+        det[4 + 2 * kMaxDW + kMaxKW + k] = types;
     }
-    if (lane < K) out->leads[lane] = (int)lead[lane];
-    if (lane == 0) { out->status = status; out->index = idx; }
+    __syncthreads();
+    // to the workspace, and to the host
+    const int words = 4 + 2 * kMaxDW + kMaxKW + D * kMaxPos / 4;
+    for (int w = lane; w < words; w += kWave) ((uint32_t *)out)[w] = det[w];
+    if (mail) {
+        mail_words(mail->words, res, sizeof(DevResult) / 4);
+        for (int w = lane; w < words; w += kWave) mail_word(mail->words + kMailDetail + w, det[w]);
+        mail_end(mail, told, true);
+    }
 }
 
-typedef void (*detail_fn)(const KParams *, const DevResult *, DevDetail *);
+typedef void (*detail_fn)(const KParams *, const DevResult *, DevDetail *, DevMail *, uint32_t, int, uint64_t);
 
 // lanes a device takes (log2), or -1: see detail_lanes_kernel
 int detail_lanes(int devices, int most_types, int most_producers)
@@ -529,10 +590,11 @@ static detail_fn pick_detail(const KParams &kp)
     }
 }
 
-int launch_detail(const KParams &kp, void *ws, void *stream)
+int launch_detail(const KParams &kp, void *ws, DevMail *mail, uint32_t told, int32_t known_period, uint64_t known_index, void *stream)
 {
     hipLaunchKernelGGL(pick_detail(kp), dim3(1), dim3(kWave), 0, (hipStream_t)stream, (const KParams *)((char *)ws + kWsParamsOff),
-                       (const DevResult *)((char *)ws + kWsResultOff), (DevDetail *)((char *)ws + kWsDetailOff));
+                       (const DevResult *)((char *)ws + kWsResultOff), (DevDetail *)((char *)ws + kWsDetailOff), mail, told, known_period,
+                       known_index);
     return (int)hipGetLastError();
 }
 

@@ -194,6 +194,18 @@ struct DevDetail {
     uint8_t orders[kMaxDW][kMaxPos];
 };
 
+// What a result call is told, written by the GPU into pinned host memory: words from the device, then `told` as the last one.
+constexpr int kMailWords = 512;
+struct DevMail {
+    uint32_t told;                   // the number the host gave with the launch, once everything else is there
+    uint32_t whole;                  // the decoded candidate is there too (else only the record: the host has that candidate)
+    uint32_t pad[14];
+    uint32_t words[kMailWords];      // DevResult, at kMailDetail DevDetail; or a completion's record
+};
+constexpr int kMailDetail = 64;
+static_assert(sizeof(DevResult) <= kMailDetail * 4 && kMailDetail * 4 + sizeof(DevDetail) <= kMailWords * 4, "mail holds record and candidate");
+static_assert(sizeof(DevResult) % 4 == 0 && sizeof(DevDetail) % 4 == 0, "mail is sent by words");
+
 // Searched completion (warm-up / cool-down orders as perturbed greedy schedules around the best window):
 // what the kernel needs of the problem and of the best candidate, by block type, and the running best.
 constexpr int kMaxSeq = kMaxK * kMaxNR;
@@ -331,7 +343,11 @@ const void *graph_kernel(const KParams &kp);
 int launch_graph(const KParams &kp, uint64_t first, uint64_t count, int blocks, void *recs, int32_t *code, int32_t *peak, void *ws,
                  uint32_t *slots, void *stream);
 // tessel_detail.hip: decodes the candidate of the running best (if there is one) into the workspace's DevDetail
-int launch_detail(const KParams &kp, void *ws, void *stream);
+// `mail` (may be null): record and candidate go there too, the candidate only if the record names another than `known_index`
+// at `known_period` (INT32_MAX: none)
+int launch_detail(const KParams &kp, void *ws, DevMail *mail, uint32_t told, int32_t known_period, uint64_t known_index, void *stream);
+// `bytes` of the workspace from `offset` on (multiples of four) to `mail`
+int launch_tell(void *ws, size_t offset, size_t bytes, DevMail *mail, uint32_t told, void *stream);
 int detail_lanes(int devices, int most_types, int most_producers);    // KParams::detail_lanes
 // kernels.hip
 // max_blocks: 0, or the most workgroups the workspace has queues for

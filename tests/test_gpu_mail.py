@@ -1,0 +1,73 @@
+"""Results that come back through pinned boxes: forty threads with a handle and a stream each (more than there are boxes: some calls copy instead),
+a running best that changes and one that stays between questions, a handle that has nothing to report, and one after a reset."""
+import threading
+
+import pytest
+
+from paper_2311_15269_amd import workloads as W
+from tests.test_gpu_dag import gpu  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+PROBLEMS = [W.config3(), W.kshape_problem(4, 4), W.config4(), W.config1()]
+
+
+def _answer(g):
+    b = g.best()
+    out = {k: b[k] for k in ("period", "index", "peak", "n_evaluated", "n_feasible", "n_reject", "feasible")}
+    if b["feasible"]:
+        c = g.best_candidate()
+        out["candidate"] = (c["leads"], c["orders"], c["starts"].tolist())
+    return out
+
+
+def _walk(gpu, prob, salt, stream=None):
+    """answers after each of six pieces of a range, asked twice, then of a new search"""
+    g, out = gpu.Problem(prob), []
+    space = min(g.candidate_count(), 1 << 30)
+    for k in range(6):
+        first = (salt * 7919 + k * 30011) % max(1, space - 600)
+        g.eval_candidates(first, 500, stream=stream)
+        out += [_answer(g), _answer(g)]
+    g.reset()
+    out.append(_answer(g))
+    g.eval_candidates(0, 500, stream=stream)
+    out.append(_answer(g))
+    return out
+
+
+def test_answers_of_many_threads(gpu):  # noqa: F811
+    import torch
+    want = {k: _walk(gpu, PROBLEMS[k % 4], k) for k in range(8)}
+    got, failed = {}, []
+
+    def work(k):
+        try:
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream):
+                got[k] = _walk(gpu, PROBLEMS[k % 4], k % 8, stream.cuda_stream)
+            stream.synchronize()
+        except Exception as e:          # noqa: BLE001 (reported below, with the thread's number)
+            failed.append((k, repr(e)))
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(40)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed
+    for k in range(40):
+        assert got[k] == want[k % 8], k
+
+
+@pytest.mark.parametrize("k", range(4))
+def test_one_question_after_another(gpu, k):  # noqa: F811
+    """asked after every piece, or once at the end: the same"""
+    prob = PROBLEMS[k]
+    g, once = gpu.Problem(prob), gpu.Problem(prob)
+    space = min(g.candidate_count(), 4000)
+    for at in range(0, space, 96):
+        n = min(96, space - at)
+        g.eval_candidates(at, n)
+        once.eval_candidates(at, n)
+        a = _answer(g)
+        assert a == _answer(g)
+    assert a == _answer(once)
