@@ -180,7 +180,7 @@ struct DevResult {
     uint32_t overflow;               // a list was too small at some point: results are incomplete
     uint32_t pad1;
     uint32_t defer_count;            // entries of the deferred list of the launch in flight
-    uint32_t pad2;
+    uint32_t arrived;                // workgroups of the pass over that list that are through
     uint64_t n_blocks;               // blocks placed by the builds of the fast kernel
 };
 

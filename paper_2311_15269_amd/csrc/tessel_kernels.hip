@@ -1831,7 +1831,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     }
     if (lane == 0) {
         BlockRec rr;
-        rr.period = best; rr.n_retried = nretry; rr.index = best_idx; rr.n_evaluated = nev; rr.n_sweeps = nsw; rr.n_blocks = nblocks; rr.pad = 0;
+        rr.period = best; rr.n_retried = nretry; rr.index = best_idx; rr.n_evaluated = nev; rr.n_sweeps = nsw; rr.n_blocks = nblocks; rr.n_blocks_high = 0;
 #pragma unroll
         for (int s = 0; s < kNumStatus; s++) rr.n_status[s] = cnt[s];
         recs[blockIdx.x] = rr;
@@ -1850,22 +1850,79 @@ __host__ __device__ inline size_t far_words(const KParams &P, int where)
     return ((state + prog + 255) & ~(size_t)255) / 4;
 }
 
+// What one launch adds to the running best: the sum of records, a wave at a time.
+struct Tally {
+    int best;
+    uint32_t nre, nev, cnt[kNumStatus];
+    uint64_t best_idx, nsw, nbl;
+    __device__ __forceinline__ void clear()
+    {
+        best = INT_MAX; best_idx = 0; nre = nev = 0; nsw = nbl = 0;
+#pragma unroll
+        for (int s = 0; s < kNumStatus; s++) cnt[s] = 0;
+    }
+    __device__ __forceinline__ void add(const BlockRec &r)
+    {
+        if (key_less(r.period, r.index, best, best_idx)) { best = r.period; best_idx = r.index; }
+        nre += r.n_retried; nev += r.n_evaluated; nsw += r.n_sweeps; nbl += (uint64_t)r.n_blocks_high << 32 | r.n_blocks;
+#pragma unroll
+        for (int s = 0; s < kNumStatus; s++) cnt[s] += r.n_status[s];
+    }
+    __device__ __forceinline__ static uint64_t from(uint64_t v, int off)
+    {
+        const uint32_t lo = __shfl_xor((uint32_t)v, off), hi = __shfl_xor((uint32_t)(v >> 32), off);
+        return ((uint64_t)hi << 32) | lo;
+    }
+    // the wave's sum, in every lane
+    __device__ __forceinline__ void fold()
+    {
+#pragma unroll 1
+        for (int off = kWave / 2; off >= 1; off >>= 1) {
+            const int op = __shfl_xor(best, off);
+            const uint64_t oi = from(best_idx, off);
+            if (key_less(op, oi, best, best_idx)) { best = op; best_idx = oi; }
+            nre += __shfl_xor(nre, off); nev += __shfl_xor(nev, off); nsw += from(nsw, off); nbl += from(nbl, off);
+#pragma unroll
+            for (int s = 0; s < kNumStatus; s++) cnt[s] += __shfl_xor(cnt[s], off);
+        }
+    }
+};
+
+// What the pass over the list also does: it adds up the launch, its own records and those of the kernel before it, and
+// clears the list's counter and the histogram for the next launch (scores of every candidate: the latter alone).
+struct Finish {
+    DevResult *res;              // null: nothing of this
+    uint32_t *left_after;
+    BlockRec *range_recs;        // records of the kernel over the range; null: scores
+    int from_range;
+};
+
 template <int DM, int VM>
 __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__ Pp, uint64_t first, uint64_t count,
-                                                     BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
-                                                     int32_t *__restrict__ peak_out, const uint64_t *__restrict__ list, const uint32_t *__restrict__ list_count,
-                                                     bool whole, uint32_t *far, int where)
+                                                     BlockRec *recs, int32_t *__restrict__ code_out,
+                                                     int32_t *__restrict__ peak_out, const uint64_t *__restrict__ list, const uint32_t *list_count,
+                                                     bool whole, uint32_t *far, int where, Finish fin)
 {
     const KParams &P = *Pp;
     extern __shared__ uint32_t lds[];
     constexpr bool wide = DM > kMaxD;
     // with a list: score the listed candidates (all inside [first, first + count)) instead of the range; `whole`: the range
     // after all where the list was too short for them.  (A workgroup without a candidate leaves no record.)
+    // Who takes part in the pass over a list: a workgroup for every 64 candidates on it, and for every 64 records of the kernel over
+    // the range, as far as the grid goes.  (The count is cleared by the last one that takes part; one that reads it
+    // later sees a smaller number, and takes no part either way.)
+    uint32_t parts = gridDim.x;
+    bool again = false;
     if (list) {
         const uint32_t listed = *list_count;
-        if (whole && listed > kWsListCap) list = nullptr;
-        else count = min(listed, kWsListCap);
-        if ((uint64_t)blockIdx.x * kWave >= count) return;
+        again = whole && listed > kWsListCap;
+        if (again) list = nullptr;
+        else {
+            count = min(listed, kWsListCap);
+            const uint32_t records = fin.range_recs ? (uint32_t)(fin.from_range + kWave - 1) / kWave : 0u;
+            parts = min(parts, max(max((uint32_t)((count + kWave - 1) / kWave), records), 1u));
+            if (blockIdx.x >= parts) return;
+        }
     }
     constexpr int KT = wide ? kMaxKW : kMaxK;             // entries of a table by type
     int32_t *t_tab = (int32_t *)lds;
@@ -1919,31 +1976,59 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
         if (code_out) code_out[k] = status == kOk ? period : -status;
         if (peak_out) peak_out[k] = pk;
     }
-    if (!recs) return;
-    // wave argmin over the total order (period, index); sums of the counters
+    Tally a;
+    a.best = best; a.best_idx = best_idx; a.nre = 0; a.nev = nev; a.nsw = 0; a.nbl = 0;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        int op = __shfl_xor(best, off);
-        uint32_t ilo = __shfl_xor((uint32_t)best_idx, off), ihi = __shfl_xor((uint32_t)(best_idx >> 32), off);
-        uint64_t oi = ((uint64_t)ihi << 32) | ilo;
-        if (key_less(op, oi, best, best_idx)) { best = op; best_idx = oi; }
+    for (int s = 0; s < kNumStatus; s++) a.cnt[s] = cnt[s];
+    // (in a launch whose range this kernel scored again, the records of the kernel before it are void)
+    if (fin.range_recs && !again)
+        for (uint32_t r = blockIdx.x * kWave + (uint32_t)lane; r < (uint32_t)fin.from_range; r += parts * kWave) a.add(fin.range_recs[r]);
+    if (recs) {
+        a.fold();
+        if (lane == 0) {
+            BlockRec r;
+            r.period = a.best; r.n_retried = a.nre; r.index = a.best_idx; r.n_evaluated = a.nev; r.n_sweeps = (uint32_t)a.nsw;
+            r.n_blocks = (uint32_t)a.nbl; r.n_blocks_high = (uint32_t)(a.nbl >> 32);
 #pragma unroll
-        for (int s = 0; s < kNumStatus; s++) cnt[s] += __shfl_xor(cnt[s], off);
-        nev += __shfl_xor(nev, off);
+            for (int s = 0; s < kNumStatus; s++) r.n_status[s] = a.cnt[s];
+            recs[blockIdx.x] = r;
+        }
     }
-    if (lane == 0) {
-        BlockRec r;
-        r.period = best; r.n_retried = 0; r.index = best_idx; r.n_evaluated = nev; r.n_sweeps = 0; r.n_blocks = 0; r.pad = 0;
-#pragma unroll
-        for (int s = 0; s < kNumStatus; s++) r.n_status[s] = cnt[s];
-        recs[blockIdx.x] = r;
+    if (!fin.res) return;
+    // ---- the workgroup that comes last adds the records up
+    DevResult *res = fin.res;
+    if (parts > 1) {
+        uint32_t before = 0;
+        __threadfence();
+        if (lane == 0) before = __hip_atomic_fetch_add(&res->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) + 1u != parts) return;
+        __threadfence();
+        if (recs) {
+            a.clear();
+            for (uint32_t r = (uint32_t)lane; r < parts; r += kWave) a.add(recs[r]);
+            a.fold();
+        }
     }
+    fin.left_after[lane] = 0;
+    if (lane != 0) return;
+    if (recs) {
+        if (key_less(a.best, a.best_idx, res->period, res->index)) { res->period = a.best; res->index = a.best_idx; }
+        res->n_retried += a.nre;
+        res->n_deferred += min(res->defer_count, kWsListCap);
+        res->n_evaluated += a.nev;
+        res->n_sweeps += a.nsw;
+        res->n_blocks += a.nbl;
+#pragma unroll
+        for (int s = 0; s < kNumStatus; s++) res->n_status[s] += a.cnt[s];
+    }
+    res->defer_count = 0;
+    res->arrived = 0;
 }
 
 // The two instantiations for problems beyond the fast kernel's limits (16 and 32 devices) take as long to compile as
 // everything else in this file: tessel_wide.hip includes this file up to here and holds them, so that the two halves
 // build side by side.
-#define TESSEL_EVAL_KERNEL_ARGS const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *, bool, uint32_t *, int
+#define TESSEL_EVAL_KERNEL_ARGS const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *, bool, uint32_t *, int, Finish
 #ifdef TESSEL_WIDE_INSTANTIATIONS
 template __global__ void eval_kernel<16, 1>(TESSEL_EVAL_KERNEL_ARGS);
 template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
@@ -1951,78 +2036,29 @@ template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
 extern template __global__ void eval_kernel<16, 1>(TESSEL_EVAL_KERNEL_ARGS);
 extern template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
 
-// Merges the block records of one launch into the running best: one workgroup, a record per thread and round, waves
-// first.  Bound by the latency of the record loads: 4,160 records took one wave 14.6 us (65 dependent rounds), eight
-// waves take 9 to 10.
+// Merges the block records of a launch of the general kernel alone into the running best: one workgroup, a record per thread and
+// round, waves first.  (Behind the other two kernels the pass over the list does that: one launch less.)  Bound by the
+// latency of the record loads: 4,160 records took one wave 14.6 us (65 dependent rounds), eight waves take 9 to 10.
 constexpr int kMergeThreads = 512;
-// `from_range` records of the kernel over the range, then those of the kernel over the list: one for every 64 candidates on
-// it, `from_list` at most.  `whole`: where the list was too short, the second kernel scored the range, and its
-// `from_list` records are all there is.
-__global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__restrict__ recs, int from_range, int from_list, bool whole,
-                                                                 DevResult *__restrict__ res, uint32_t *__restrict__ left_after)
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__restrict__ recs, int nrecs, DevResult *__restrict__ res)
 {
-    if (threadIdx.x < kWave) left_after[threadIdx.x] = 0;        // for the next launch
-    const uint32_t listed = res->defer_count;
-    const bool again = whole && listed > kWsListCap;
-    const int start = again ? from_range : 0;
-    const int nrecs = from_range + min(from_list, (int)((min(listed, kWsListCap) + kWave - 1) / kWave));
-
-    struct Sum { int best; uint32_t nre; uint64_t best_idx, nev, nsw, nbl, cnt[kNumStatus]; };
-    __shared__ Sum part[kMergeThreads / kWave];
-    Sum a;
-    a.best = INT_MAX; a.nre = 0; a.best_idx = 0; a.nev = a.nsw = a.nbl = 0;
-#pragma unroll
-    for (int s = 0; s < kNumStatus; s++) a.cnt[s] = 0;
-    for (int k = start + threadIdx.x; k < nrecs; k += kMergeThreads) {
-        const BlockRec r = recs[k];
-        if (key_less(r.period, r.index, a.best, a.best_idx)) { a.best = r.period; a.best_idx = r.index; }
-        a.nre += r.n_retried;
-        a.nev += r.n_evaluated;
-        a.nsw += r.n_sweeps;
-        a.nbl += r.n_blocks;
-#pragma unroll
-        for (int s = 0; s < kNumStatus; s++) a.cnt[s] += r.n_status[s];
-    }
-    auto from = [](uint64_t v, int off) -> uint64_t {
-        const uint32_t lo = __shfl_xor((uint32_t)v, off), hi = __shfl_xor((uint32_t)(v >> 32), off);
-        return ((uint64_t)hi << 32) | lo;
-    };
-    auto fold = [&](int width) {
-        for (int off = width / 2; off >= 1; off >>= 1) {
-            const int op = __shfl_xor(a.best, off);
-            const uint64_t oi = from(a.best_idx, off);
-            if (key_less(op, oi, a.best, a.best_idx)) { a.best = op; a.best_idx = oi; }
-            a.nre += __shfl_xor(a.nre, off);
-            a.nev += from(a.nev, off); a.nsw += from(a.nsw, off); a.nbl += from(a.nbl, off);
-#pragma unroll
-            for (int s = 0; s < kNumStatus; s++) a.cnt[s] += from(a.cnt[s], off);
-        }
-    };
-    fold(kWave);
+    __shared__ Tally part[kMergeThreads / kWave];
+    Tally a;
+    a.clear();
+    for (int k = threadIdx.x; k < nrecs; k += kMergeThreads) a.add(recs[k]);
+    a.fold();
     if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = a;
     __syncthreads();
-    if (threadIdx.x >= kWave) return;
-    a = part[threadIdx.x & (kMergeThreads / kWave - 1)];
-    fold(kMergeThreads / kWave);
-    if (threadIdx.x == 0) {
-        if (key_less(a.best, a.best_idx, res->period, res->index)) { res->period = a.best; res->index = a.best_idx; }
-        // the pass over the list of deferred candidates has run (stream order)
-        res->n_retried += a.nre;
-        res->n_deferred += min(res->defer_count, kWsListCap);
-        res->defer_count = 0;
-        res->n_evaluated += a.nev;
-        res->n_sweeps += a.nsw;
-        res->n_blocks += a.nbl;
-#pragma unroll
-        for (int s = 0; s < kNumStatus; s++) res->n_status[s] += a.cnt[s];
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < kMergeThreads / kWave; w++) {
+        const Tally &o = part[w];
+        if (key_less(o.best, o.best_idx, a.best, a.best_idx)) { a.best = o.best; a.best_idx = o.best_idx; }
+        a.nev += o.nev;
+        for (int s = 0; s < kNumStatus; s++) a.cnt[s] += o.cnt[s];
     }
-}
-
-// only the counter of the deferred list and the histogram (after a per-candidate scoring call; one wave)
-__global__ void clear_defer_kernel(DevResult *res, uint32_t *left_after)
-{
-    left_after[threadIdx.x] = 0;
-    if (threadIdx.x == 0) res->defer_count = 0;
+    if (key_less(a.best, a.best_idx, res->period, res->index)) { res->period = a.best; res->index = a.best_idx; }
+    res->n_evaluated += a.nev;
+    for (int s = 0; s < kNumStatus; s++) res->n_status[s] += a.cnt[s];
 }
 
 __global__ void reset_kernel(DevResult *res, DevDetail *detail, uint32_t *left_after)
@@ -2031,14 +2067,14 @@ __global__ void reset_kernel(DevResult *res, DevDetail *detail, uint32_t *left_a
         detail->status = -1;                     // no candidate decoded yet
         for (int w = 0; w < kWave; w++) left_after[w] = 0;
         res->period = INT_MAX; res->pad = 0; res->index = ~0ull; res->n_evaluated = 0; res->n_sweeps = 0; res->n_blocks = 0;
-        res->n_retried = 0; res->n_deferred = 0; res->overflow = 0; res->defer_count = 0;
+        res->n_retried = 0; res->n_deferred = 0; res->overflow = 0; res->defer_count = 0; res->arrived = 0;
         for (int s = 0; s < kNumStatus; s++) res->n_status[s] = 0;
     }
 }
 
 // ------------------------------------------------------------------ launchers
 typedef void (*eval_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *,
-                        bool, uint32_t *, int);
+                        bool, uint32_t *, int, Finish);
 typedef void (*fast_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, int, int, uint64_t *, uint32_t *,
                         uint32_t, uint32_t *, uint32_t *, uint32_t, int, int, uint32_t *);
 
@@ -2271,7 +2307,7 @@ size_t eval_workspace_bytes(const KParams &kp, int num_cus, int max_blocks)
 
 static int launch_general(const KParams &kp, const KParams *kp_dev, uint64_t first, uint64_t count, int blocks, BlockRec *recs,
                           int32_t *code, int32_t *peak, const uint64_t *list, const uint32_t *list_count, bool whole,
-                          uint32_t *far, hipStream_t st)
+                          uint32_t *far, const Finish &fin, hipStream_t st)
 {
     const int where = far_mode(kp);
     if (where && !far) return (int)hipErrorInvalidValue;
@@ -2281,23 +2317,21 @@ static int launch_general(const KParams &kp, const KParams *kp_dev, uint64_t fir
         hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, list, list_count, whole, far, where);
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, list, list_count, whole, far, where, fin);
     return (int)hipGetLastError();
 }
-
-// block records of one pass, as merge_kernel takes them
-struct Records { int from_range = 0, from_list = 0; bool whole = false; };
 
 // Scores [first, first+count).  Where the problem allows it: the fast kernel (a short eigenvector search, a longer one
 // for the candidates that did not converge) or the graph kernel, then the general kernel over what these could not finish (next
 // to nothing in most problems).  Otherwise the general kernel alone.  `recs` may be null: per-candidate outputs only.
 // Returns 0 or a HIP error.
 static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *ws, int num_cus, int max_blocks, BlockRec *recs,
-                       int32_t *code, int32_t *peak, bool general, hipStream_t st, Records &made)
+                       int32_t *code, int32_t *peak, bool general, hipStream_t st)
 {
     const KParams *kp_dev = (const KParams *)((char *)ws + kWsParamsOff);
     DevResult *res = (DevResult *)((char *)ws + kWsResultOff);
     uint64_t *list = (uint64_t *)((char *)ws + kWsListOff);
+    uint32_t *left_after = (uint32_t *)((char *)ws + kWsLeftOff);
     const LaunchShape s = eval_launch_shape(kp, num_cus, max_blocks);
     const uint64_t need = (count + kWave - 1) / kWave;
     const int blocks = need < (uint64_t)s.blocks ? (int)need : s.blocks;
@@ -2305,46 +2339,39 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
     if (blocks < 1) return 0;
     uint32_t *behind = (uint32_t *)((char *)ws + ring_offset(s, num_cus));      // queues, slots, or the general kernel's state
     fast_fn ff = general ? nullptr : pick_fast(kp);
-    if (!ff && kp.graph_ok && !general) {
+    const bool graph = !ff && kp.graph_ok && !general;
+    if (!ff && !graph) {
+        int rc = launch_general(kp, kp_dev, first, count, blocks, recs, code, peak, nullptr, nullptr, false, behind, Finish{}, st);
+        if (rc || !recs) return rc;
+        hipLaunchKernelGGL(merge_kernel, dim3(1), dim3(kMergeThreads), 0, st, recs, blocks, res);
+        return (int)hipGetLastError();
+    }
+    int rc;
+    if (graph)
         // (every problem its tables hold: on 24 blocks of three devices 4.5 times the general kernel's rate, on 96 to 288
         // blocks 34 to 78 times; one to 4,096 scores of 6 to 12 blocks 33 to 54 us against 39 to 82)
-        int rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, behind, st);
-        if (rc) return rc;
-        made.from_range = blocks; made.from_list = list_blocks; made.whole = true;
-        return launch_general(kp, kp_dev, first, count, list_blocks, recs ? recs + blocks : nullptr, code, peak, list,
-                              &res->defer_count, true, behind, st);
+        rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, behind, st);
+    else {
+        int adapt = 0;
+        const int stage = stage_words(kp, peak != nullptr, count, s.blocks, adapt);
+        hipLaunchKernelGGL(ff, dim3(blocks), dim3(kWave), fast_lds_bytes(kp), st, kp_dev, first, count, recs, code, peak, kp.eigen_tries,
+                           kp.retry_tries, list, &res->defer_count, kWsListCap, &res->overflow, behind, ring_words(kp), stage, adapt, left_after);
+        rc = (int)hipGetLastError();
     }
-    made.from_range = blocks;
-    if (!ff) return launch_general(kp, kp_dev, first, count, blocks, recs, code, peak, nullptr, nullptr, false, behind, st);
-    const size_t lds = fast_lds_bytes(kp);
-    int adapt = 0;
-    const int stage = stage_words(kp, peak != nullptr, count, s.blocks, adapt);
-    hipLaunchKernelGGL(ff, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, kp.eigen_tries, kp.retry_tries,
-                       list, &res->defer_count, kWsListCap, &res->overflow, behind, ring_words(kp), stage, adapt, (uint32_t *)((char *)ws + kWsLeftOff));
-    int rc = (int)hipGetLastError();
     if (rc) return rc;
-    made.from_list = list_blocks;
-    return launch_general(kp, kp_dev, first, count, list_blocks, recs ? recs + blocks : nullptr, code, peak, list,
-                          &res->defer_count, false, nullptr, st);
+    const Finish fin = {res, left_after, recs, blocks};
+    return launch_general(kp, kp_dev, first, count, list_blocks, recs ? recs + blocks : nullptr, code, peak, list, &res->defer_count, graph,
+                          graph ? behind : nullptr, fin, st);
 }
 
 int launch_eval(const KParams &kp, uint64_t first, uint64_t count, void *ws, int num_cus, int max_blocks, void *stream, uint64_t max_piece)
 {
-    hipStream_t st = (hipStream_t)stream;
     BlockRec *recs = (BlockRec *)((char *)ws + kWsBlockRecOff);
-    DevResult *res = (DevResult *)((char *)ws + kWsResultOff);
     // pieces of at most max_piece candidates, so that the lists of unfinished candidates stay small
     for (uint64_t done = 0; done < count;) {
         const uint64_t piece = count - done < max_piece ? count - done : max_piece;
-        Records made;
-        int rc = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, recs, nullptr, nullptr, false, st, made);
+        int rc = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, recs, nullptr, nullptr, false, (hipStream_t)stream);
         if (rc) return rc;
-        if (made.from_range > 0) {
-            hipLaunchKernelGGL(merge_kernel, dim3(1), dim3(kMergeThreads), 0, st, recs, made.from_range, made.from_list, made.whole, res,
-                               (uint32_t *)((char *)ws + kWsLeftOff));
-            rc = (int)hipGetLastError();
-            if (rc) return rc;
-        }
         done += piece;
     }
     return 0;
@@ -2353,18 +2380,12 @@ int launch_eval(const KParams &kp, uint64_t first, uint64_t count, void *ws, int
 int launch_score(const KParams &kp, uint64_t first, uint64_t count, int32_t *code, int32_t *peak, void *ws, int num_cus,
                  int max_blocks, bool general, void *stream)
 {
-    hipStream_t st = (hipStream_t)stream;
-    DevResult *res = (DevResult *)((char *)ws + kWsResultOff);
     // pieces in which no list can overflow: the per-candidate outputs of a dropped candidate would stay unwritten
     const uint64_t max_piece = kSafePerLaunch;
     for (uint64_t done = 0; done < count;) {
         const uint64_t piece = count - done < max_piece ? count - done : max_piece;
-        Records made;
-        int rc = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, nullptr, code + done, peak ? peak + done : nullptr, general, st,
-                             made);
-        if (rc) return rc;
-        hipLaunchKernelGGL(clear_defer_kernel, dim3(1), dim3(kWave), 0, st, res, (uint32_t *)((char *)ws + kWsLeftOff));
-        rc = (int)hipGetLastError();
+        int rc = launch_pass(kp, first + done, piece, ws, num_cus, max_blocks, nullptr, code + done, peak ? peak + done : nullptr, general,
+                             (hipStream_t)stream);
         if (rc) return rc;
         done += piece;
     }
