@@ -737,6 +737,7 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
         }
         for (int d = 0; d < D; d++) {
             kp.vtab[d] = (uint32_t)d | (1u << 6) | ((uint32_t)(kp.ntd[d] > 0) << 17);
+            kp.code_mask |= ((1u << kp.ntd[d]) - 1u) << (4 * d);
             for (int y = 0; y < kp.ntd[d]; y++) kp.mpack[d] |= ((uint32_t)kp.m_of[d][y] & 0xFFu) << (8 * y);
         }
         int v = D, path = 0;

@@ -29,7 +29,11 @@ __device__ __forceinline__ bool key_less(int pa, uint64_t ia, int pb, uint64_t i
     return pa < pb || (pa == pb && ia < ib);
 }
 
-__device__ __forceinline__ uint32_t bfi(uint32_t sel, uint32_t a, uint32_t b) { return (sel & a) | (~sel & b); }
+// Rates of this chip, measured with independent chains in all waves of a SIMD (T lane-operations/s of the chip): add, sub, and, or, xor, right
+// shifts and bitop3 on vector registers, literals and small constants run at 60; left shifts, minimum and maximum, compares and selects,
+// bit-field and three-operand instructions, multiplies (the 32-bit ones too), and anything that reads a scalar
+// register, a part of a word or another lane at 35.
+__device__ __forceinline__ uint32_t bfi(uint32_t sel, uint32_t a, uint32_t b) { return __builtin_amdgcn_bitop3_b32(sel, a, b, 0xCA); }
 
 // position of the lowest set bit; all ones for 0, which "& 28", shift counts and bit-field offsets (all of them use the
 // low five bits) read as 31: no guard bit has to be set first
@@ -61,17 +65,6 @@ __device__ __forceinline__ void lds_store(uint32_t a, uint32_t v) { *(lds_word *
 __device__ __forceinline__ uint32_t lds_fetch_add(uint32_t a, uint32_t v)
 {
     return __hip_atomic_fetch_add((lds_word *)(uintptr_t)a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// even bits of a 32-bit word, compacted (bit 2p -> bit p)
-__device__ __forceinline__ uint32_t even_bits32(uint32_t x)
-{
-    x &= 0x55555555u;
-    x = (x | (x >> 1)) & 0x33333333u;
-    x = (x | (x >> 2)) & 0x0F0F0F0Fu;
-    x = (x | (x >> 4)) & 0x00FF00FFu;
-    x = (x | (x >> 8)) & 0x0000FFFFu;
-    return x;
 }
 
 // a device's order while it is decoded: bit p of plane k = bit k of the symbol at position p

@@ -853,7 +853,7 @@ struct FastLds {
     uint32_t *sw_tab;     // [32]  by code, for the sweeps of problems without blocks on several devices:
                           //       t << 16 | LDS address of the time of the code's device (lane 0)
     uint32_t *ch_tab;     // [32]  by code, right behind sw_tab: LDS address of the first token of the code's chain (lane 0)
-    uint32_t *in_tab;     // [32]  by code, behind ch_tab: 1 << s | s, s = 16 + 4 * symbol: counter increment and field position
+    uint32_t *in_tab;     // [32]  by code, behind ch_tab: 1 << s | s - 8, s = 16 + 4 * symbol: counter increment; shift that leaves the field times 256
     uint4 *tt_tab;        // [32]  by code, for the sweeps of the TP variants: x: t, y: byte offset of the first token slot of the code's
                           //       chain, z: byte offset of its device's words, w: bit offset of its micro-batch counter, bit 31: on several devices
     uint32_t *type_tab;   // [4][64], code in the low half of every 64: what placing one block of the type does:
@@ -862,7 +862,7 @@ struct FastLds {
                           //   word 1: one-hot mask of the consumer's code (0: none)
                           //   word 2: consumer on another device: LDS address of the last word of that device's record
                           //      (lane 0); otherwise, TP variants: 0xFFFFFFFF, else that of the type's own device
-                          //      (word 3 is 0 then).  Not TP: 4 * symbol of the type in bits 16-19
+                          //      (word 3 is 0 then).  Not TP: plus 4 * symbol of the type (rows are 256 bytes)
                           //   word 3: the increment of that word (one waiting micro-batch of the consumer)
                           // the upper halves hold chain_tab, vtab, cum_tab, predbit_tab
     uint32_t *chain_tab;  // [32]  KParams::chain_tab
@@ -948,9 +948,9 @@ __device__ __forceinline__ void rec_store(uint32_t a, const uint4 v)
 // everything older is seen.
 // Table word of a code: t << 16 | LDS address of its device's time (lane 0); with several chains (MC) a second
 // table holds the LDS address of the chain's first token (lane 0).  A device's counter word holds the next micro-batch
-// of its four types in its upper half, four bits each; the third table word of a code, 1 << s | s with s = 16 +
-// 4 * symbol, is both the increment of the atomic (the low half of the counter word only collects the s, below 2^16
-// over a window) and, by its low five bits, the position of the field.
+// of its four types in its upper half, four bits each; the third table word of a code, 1 << s | s - 8 with s =
+// 16 + 4 * symbol, is both the increment of the atomic (the low half of the counter word only collects the s - 8, below 2^16
+// over a window) and, by its low five bits, the shift that leaves the field times 256.
 // Past the last block the stages T, A and R run on code 0 (a counter that the window boundary resets anyway, reads
 // inside the arrays); stage W does not.
 template <int DM, bool MC>
@@ -980,8 +980,8 @@ __device__ __forceinline__ void sweep_blocks(const FastConst<DM> &C, const FastL
     auto stage_r = [&](const Ast &x) -> Rst {
         Rst o;
         o.tt = x.tt; o.fa = x.fa;
-        const uint32_t mu = __builtin_amdgcn_ubfe(x.cnt, x.w2, 4);      // (the offset is the low five bits of w2)
-        o.ta = MC ? (mu << 8) + lane4 + x.ch : (mu << 8) + lane_tok;
+        const uint32_t mu = (x.cnt >> (x.w2 & 31u)) & 0xF00u;           // times 256
+        o.ta = MC ? mu + lane4 + x.ch : mu + lane_tok;
         o.fr = lds_load(x.fa);
         o.tk = lds_load(o.ta);
         return o;
@@ -1195,26 +1195,36 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
             // bytes: 0x60 <= 0x80 - t + digit < 0xA0).
             const uint32_t c1 = C.ntd[d] > 0 ? NR : 0u, c2 = c1 + (C.ntd[d] > 1 ? NR : 0u), c3 = c2 + (C.ntd[d] > 2 ? NR : 0u);
             uint32_t tq = 0x808080u - (c1 | (c2 << 8) | (c3 << 16));
-            // the 2-bit symbols are collected 16 to a word and split into the two planes at the end
-            uint32_t acc[2] = {0u, 0u};
+            // The outcomes of the three comparisons are collected as they are, eight positions to a word: byte k holds "at or above
+            // threshold k" of the eight.  The symbol is their number, so its high bit is the second byte, its low bit the three
+            // bytes' exclusive or.  (Symbols counted and collected by pairs of bits took a count a position and 110 cycles a device
+            // to split into planes.)
+            uint32_t seen[4] = {0u, 0u, 0u, 0u};
             auto pick = [&](uint32_t draw, uint32_t left, uint32_t &into, uint32_t at) {
                 const uint32_t digit = (uint32_t)(((uint64_t)draw * (uint64_t)((left << 16) & 0xFFFFFFu)) >> 32);    // (draw * left) >> 16 as a
                                                                                                        // 24-bit high multiply (left <= 32)
-                const uint32_t ge = mad24(digit, 0x010101u, tq) & 0x808080u;
-                tq += (ge >> 7) ^ 0x010101u;                     // a threshold above the digit loses one block
-                into |= (uint32_t)__builtin_popcount(ge) << (2u * at);   // symbol = number of thresholds at or below the digit
+                const uint32_t ge = (mad24(digit, 0x010101u, tq) & 0x808080u) >> 7;
+                tq += ge ^ 0x010101u;                            // a threshold above the digit loses one block
+                into |= ge << at;
             };
 #pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const uint32_t from = 16u * (uint32_t)h, to = min(n, from + 16u);
+            for (int h = 0; h < 4; h++) {
+                const uint32_t from = 8u * (uint32_t)h, to = min(n, from + 8u);
                 for (uint32_t pos = from; pos < to; pos += 2) {
                     const uint32_t word = stream_word(ka, kb, (kDrawOrdBase + 32u * (uint32_t)d + pos) >> 1);
-                    pick(word & 0xFFFFu, n - pos, acc[h], pos - from);
-                    if (pos + 1 < n) pick(word >> 16, n - pos - 1u, acc[h], pos + 1u - from);
+                    pick(word & 0xFFFFu, n - pos, seen[h], pos - from);
+                    if (pos + 1 < n) pick(word >> 16, n - pos - 1u, seen[h], pos + 1u - from);
                 }
             }
-            const uint32_t lo = even_bits32(acc[0]) | (even_bits32(acc[1]) << 16);
-            const uint32_t hi = even_bits32(acc[0] >> 1) | (even_bits32(acc[1] >> 1) << 16);
+            // (bytes 0 of the four words to one, bytes 1 likewise)
+            uint32_t low[4];
+#pragma unroll
+            for (int h = 0; h < 4; h++) low[h] = seen[h] ^ (seen[h] >> 8) ^ (seen[h] >> 16);
+            auto bytes = [](uint32_t a, uint32_t b, uint32_t c, uint32_t e, uint32_t pair) -> uint32_t {
+                return __builtin_amdgcn_perm(__builtin_amdgcn_perm(e, c, pair), __builtin_amdgcn_perm(b, a, pair), 0x05040100u);
+            };
+            const uint32_t lo = bytes(low[0], low[1], low[2], low[3], 0x0C0C0400u);
+            const uint32_t hi = bytes(seen[0], seen[1], seen[2], seen[3], 0x0C0C0501u);
             plo[d] = lo; phi[d] = hi; nlen[d] = (int)n;
         }
         if (C.has_fixed)
@@ -1274,8 +1284,7 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
             if (d >= C.D) continue;
             uint32_t mud = 0, qd = 0;
 #pragma unroll
-            for (int y = 0; y < kMaxLT; y++) {
-                if (y >= C.ntd[d]) continue;
+            for (int y = 0; y < kMaxLT; y++) {               // (a code without a type has no bits in the tables: lead 0, never read)
                 const int c = 4 * d + y;
                 const uint32_t pb = L.predbit_tab[c];
                 const uint32_t cnt = (uint32_t)__builtin_popcount(S & L.cum_tab[c]);
@@ -1289,6 +1298,7 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
             if (d < 4) { mu.lo |= (uint64_t)mud << (16 * d); Q.lo = (Q.lo & ~(0xFFFFull << (16 * d))) | ((uint64_t)qd << (16 * d)); }
             else { mu.hi |= (uint64_t)mud << (16 * (d - 4)); Q.hi = (Q.hi & ~(0xFFFFull << (16 * (d - 4)))) | ((uint64_t)qd << (16 * (d - 4))); }
         }
+        R &= P.code_mask;
     } else if (!sampled && P.ranked) {
         const uint4 a = ((const uint4 *)row)[0], b = ((const uint4 *)row)[1];
         mu.lo = (uint64_t)a.x | ((uint64_t)a.y << 32); mu.hi = (uint64_t)a.z | ((uint64_t)a.w << 32);
@@ -1322,13 +1332,10 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
         if (d >= C.D) continue;
         const uint32_t mud = (uint32_t)((d < 4 ? mu.lo : mu.hi) >> (16 * (d & 3))) & 0xFFFFu;
         const uint32_t qd = (uint32_t)((d < 4 ? Q.lo : Q.hi) >> (16 * (d & 3))) & 0xFFFFu;
-        int mem0 = 0;
-#pragma unroll
-        for (int y = 0; y < kMaxLT; y++) {
-            if (y >= C.ntd[d]) continue;
-            const uint32_t lead = (mud >> (4 * y)) & 15u;
-            mem0 += ((int)(C.mpack[d] << (24 - 8 * y)) >> 24) * (int)lead;     // blocks that ran before the window
-        }
+        // blocks that ran before the window: leads as bytes times the device's memory deltas
+        uint32_t leads4 = (mud & 0xFFu) | ((mud & 0xFF00u) << 8);
+        leads4 = (leads4 | (leads4 << 4)) & 0x0F0F0F0Fu;
+        const int mem0 = __builtin_amdgcn_sdot4((int)leads4, (int)C.mpack[d], 0, false);
         const uint32_t alive = nlen[d] >= 32 ? 0xFFFFFFFFu : (1u << nlen[d]) - 1u;
         rec_store(L.rec + (uint32_t)d * kRecDevStep + (uint32_t)lane * 4u, make_uint4(plo[d], phi[d], alive, qd | ((uint32_t)mem0 << 16)));
         if (nlen[d] > 0) HM |= 1u << (4 * d + ((plo[d] & 1u) | ((phi[d] & 1u) << 1)));
@@ -1378,33 +1385,37 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
             const uint32_t r0 = (uint32_t)__builtin_amdgcn_sbfe(r4, 0, 1), r1 = (uint32_t)__builtin_amdgcn_sbfe(r4, 1, 1),
                            r2 = (uint32_t)__builtin_amdgcn_sbfe(r4, 2, 1), r3 = (uint32_t)__builtin_amdgcn_sbfe(r4, 3, 1);
             const uint32_t gate = bfi(a.y, bfi(a.x, r3, r2), bfi(a.x, r1, r0));
-            const uint32_t p = low_bit(a.z & gate);
+            const uint32_t cand = a.z & gate, p = low_bit(cand);
             // its symbol, as two all-or-nothing masks
             const uint32_t ly = (uint32_t)__builtin_amdgcn_sbfe((int)a.x, p, 1), hy = (uint32_t)__builtin_amdgcn_sbfe((int)a.y, p, 1);
-            // c = d4 + y with y = (ly & 1) | (hy & 2): ly, hy are 0 or -1, so c = d4 - ly - 2 hy
-            uint32_t c;
-            asm("v_mad_i32_i24 %0, %1, -2, %2" : "=v"(c) : "v"(hy), "v"(d4 - ly));
+            // c = d4 | (ly & 1) | (hy & 2)
+            const uint32_t c = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(ly, hy, 1u, 0xE4), 3u, d4, 0xEA);
             const uint32_t c4 = c << 2;
             const uint4 e = rec_load(c4);                      // (the table of the types starts the kernel's LDS, at address 0)
             // take the entry out; new head of the device.  (When the device is empty now the bit set below is
             // meaningless, and harmless: all its types are exhausted, and R never holds an exhausted type.)
-            const uint32_t alive = a.z & ~(1u << p);
+            // (The step's instructions are chosen by rate, tessel_common.h: masks from signs instead of compares and selects,
+            // right shifts instead of bit fields, the entry's bit by subtraction.  With the decode's part: 2^26 candidates of
+            // 256 blocks on 8 devices 32.7 -> 32.0 ms, of 40 with two on all of four devices 6.03 -> 5.72.)
+            const uint32_t alive = __builtin_amdgcn_bitop3_b32(a.z, cand, 0u - cand, 0x70);        // a & ~(b & c)
             const uint32_t p2 = low_bit(alive);
-            const uint32_t y2 = __builtin_amdgcn_ubfe(a.x, p2, 1) | (__builtin_amdgcn_ubfe(a.y, p2, 1) << 1);
-            const uint32_t hm_new = (HM & ~(15u << d4)) | (1u << (d4 + y2));
+            const uint32_t h2 = a.y >> (p2 & 31u);
+            const uint32_t c2 = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(a.x >> (p2 & 31u), h2 + h2, 1u, 0xE4), 3u, d4, 0xEA);
+            const uint32_t hm_new = (HM & ~(15u << d4)) | (1u << c2);
             // one waiting micro-batch is consumed; the type stays runnable while another one waits and
             // entries of it remain; its consumer gets one more and becomes runnable
             // remaining entries of the same type: alive & ~(lo ^ ly) & ~(hi ^ hy)
             const uint32_t rest = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(alive, a.x, ly, 0x90), a.y, hy, 0x90);
-            // two or more were waiting (the shift, 4 * symbol, comes with the table entry where no type sits on several devices)
-            const uint32_t more = (a.w >> (TP ? 4u * (c & 3u) : e.z >> 16)) & 14u;
+            // two or more were waiting (the shift, 4 * symbol, is in the low bits of the table entry where no type sits on several devices)
+            const uint32_t more = (a.w >> (TP ? 4u * (c & 3u) : e.z & 31u)) & 14u;
             const uint32_t onec = 1u << c;
             // exhausted: no entry of the type is left; it stays runnable only if entries are left and another
-            // micro-batch waits
-            const bool exhausted = rest == 0, stalled = exhausted | (more == 0);
-            uint32_t x_new = X | (exhausted ? onec : 0u);
+            // micro-batch waits.  (Masks, all ones: entries are left; another one waits.)
+            const uint32_t some = (uint32_t)((int)(rest | (0u - rest)) >> 31), waits = (uint32_t)((int)(0u - more) >> 31);
+            uint32_t x_new = __builtin_amdgcn_bitop3_b32(X, onec, some, 0xF4);              // a | (b & ~c)
             TESSEL_PIN(x_new);          // (the old X dies here: no second copy of the mask across the step)
-            const uint32_t r_new = __builtin_amdgcn_bitop3_b32(R, stalled ? onec : 0u, e.y & ~x_new, 0xBA);      // (R & ~t) | z
+            const uint32_t stalled = __builtin_amdgcn_bitop3_b32(onec, some, waits, 0x70);
+            const uint32_t r_new = __builtin_amdgcn_bitop3_b32(R, stalled, e.y & ~x_new, 0xBA);      // (R & ~t) | z
             // the record's last word: waiting counts (16 bits) and the device's memory prefix (upper 16 bits,
             // signed); one sum updates both
             const uint32_t w_new = a.w + e.x;
@@ -1415,7 +1426,7 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
                 lds_store(ra + 3u * kRecWordStep, w_new);
                 // (without blocks on several devices every table entry names a word: a type without a consumer on
                 // another device adds 0 to its own record)
-                if (!TP) lds_fetch_add((e.z & 0xFFFFu) + lane4, e.w);
+                if (!TP) lds_fetch_add(__builtin_amdgcn_bitop3_b32(e.z, ~31u, lane4, 0xEA), e.w);       // (a & b) | c: rows of 256 bytes
                 else if (e.z != 0xFFFFFFFFu) lds_fetch_add(e.z + lane4, e.w);
                 worst = max(worst, (int)w_new >> 16);
                 // the program names a type by its code on its lowest device
@@ -1551,8 +1562,8 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
             else
                 e = make_uint4(((uint32_t)m << 16) - (1u << (4u * y)) + (same ? inc : 0u),
                                has_su ? 1u << (su & 31u) : 0u,
-                               has_su && !same ? last + (su >> 2) * kRecDevStep + (TP ? 0u : y << 18)
-                                               : TP ? 0xFFFFFFFFu : last + (dev < (uint32_t)DM ? dev : 0u) * kRecDevStep + (y << 18),
+                               has_su && !same ? last + (su >> 2) * kRecDevStep + (TP ? 0u : 4u * y)
+                                               : TP ? 0xFFFFFFFFu : last + (dev < (uint32_t)DM ? dev : 0u) * kRecDevStep + 4u * y,
                                has_su && !same ? inc : 0u);
             L.type_tab[lane] = e.x; L.type_tab[2 * kMaxK + lane] = e.y; L.type_tab[4 * kMaxK + lane] = e.z; L.type_tab[6 * kMaxK + lane] = e.w;
         }
@@ -1562,7 +1573,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
             const uint32_t dev = used ? (uint32_t)lane >> 2 : 0u, rel = used ? ((inf >> 12) & 63u) - (uint32_t)P.D : 0u;
             L.sw_tab[lane] = ((uint32_t)P.t_loc[lane] << 16) | (lds_address(L.dfree) + dev * (kWave * 4u));
             L.ch_tab[lane] = lds_address(L.dfree) + (2u * DM + rel) * (kWave * 4u);
-            L.in_tab[lane] = (1u << (16u + 4u * ((uint32_t)lane & 3u))) | (16u + 4u * ((uint32_t)lane & 3u));
+            L.in_tab[lane] = (1u << (16u + 4u * ((uint32_t)lane & 3u))) | (8u + 4u * ((uint32_t)lane & 3u));
         }
         L.chain_tab[lane] = P.chain_tab[lane];
         L.vtab[lane] = lane < 24 ? P.vtab[lane] : 0u;
