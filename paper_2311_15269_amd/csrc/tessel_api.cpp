@@ -1450,8 +1450,8 @@ static void window_matrix(const CompParams &cp, CompMatrix &cm)
         for (size_t j = 0; j < in.size(); j++) any = any || cm.a[o][j] != kNoPath;
         if (!any) return;
     }
-    for (size_t j = 0; j < in.size(); j++) cm.in_slot[j] = (uint16_t)in[j];
-    for (size_t o = 0; o < out.size(); o++) cm.out_slot[o] = (uint16_t)out[o];
+    for (size_t j = 0; j < in.size(); j++) cm.in_slot[j] = (uint32_t)in[j];
+    for (size_t o = 0; o < out.size(); o++) cm.out_slot[o] = (uint32_t)out[o];
     cm.nin = (int32_t)in.size(); cm.nout = (int32_t)out.size();
 }
 
@@ -1545,7 +1545,7 @@ static int bind_completion(tessel_problem *p, int N, int J)
     if (const char *env = getenv("TESSEL_REPLAY_BLOCKS")) {        // test knob: replay the windows block by block
         if (env[0] == '1') p->comp_matrix.nin = 0;
     }
-    if (completion_lds_bytes(cp, p->comp_matrix) > 64 * 1024) return TESSEL_E_TOOBIG;
+    if (!completion_fits(cp, p->comp_matrix)) return TESSEL_E_TOOBIG;
     hipError_t e = hipMemcpyAsync((char *)p->ws + kWsCompParamsOff, &cp, sizeof cp, hipMemcpyHostToDevice, p->stream);
     if (e != hipSuccess) return hip_fail(p, (int)e);
     e = hipMemcpyAsync((char *)p->ws + kWsCompMatrixOff, &p->comp_matrix, sizeof(CompMatrix), hipMemcpyHostToDevice, p->stream);

@@ -67,6 +67,11 @@ __device__ __forceinline__ uint32_t lds_fetch_add(uint32_t a, uint32_t v)
     return __hip_atomic_fetch_add((lds_word *)(uintptr_t)a, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// half words.  (A row that is written by halves is also read by words: its accesses must not be reordered as if types told them apart.)
+typedef __attribute__((address_space(3), may_alias)) uint16_t lds_half;
+__device__ __forceinline__ uint32_t lds_load16(uint32_t a) { return *(const lds_half *)(uintptr_t)a; }
+__device__ __forceinline__ void lds_store16(uint32_t a, uint32_t v) { *(lds_half *)(uintptr_t)a = (uint16_t)v; }
+
 // a device's order while it is decoded: bit p of plane k = bit k of the symbol at position p
 template <int NP>
 struct Planes {

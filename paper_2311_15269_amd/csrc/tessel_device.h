@@ -235,8 +235,8 @@ constexpr int kMatIn = 16, kMatOut = 32;
 constexpr int32_t kNoPath = -(1 << 24);
 struct CompMatrix {
     int32_t  nin, nout;              // nin = 0: not available (the kernel replays the windows block by block)
-    uint16_t in_slot[kMatIn];        // state slots (numbering of the kernel), in the order of the columns
-    uint16_t out_slot[kMatOut];
+    uint32_t in_slot[kMatIn];        // state slots (numbering of the kernel), in the order of the columns
+    uint32_t out_slot[kMatOut];
     int32_t  a[kMatOut][kMatIn];     // kNoPath: no path; columns from nin on are kNoPath
 };
 struct DevCompletion {
@@ -363,7 +363,7 @@ int scratch_workspace(void **ptr, size_t *bytes);
 int eval_blocks_that_fit(const KParams &kp, int num_cus, size_t bytes);
 int launch_reset(void *ws, void *stream);
 // completion search: S = state words per lane; returns 0 or a HIP error (negative: LDS need exceeds the device's)
-size_t completion_lds_bytes(const CompParams &cp, const CompMatrix &cm);
+bool completion_fits(const CompParams &cp, const CompMatrix &cm);      // within the size that the completion kernels take
 int launch_completions(const CompParams &cp, const CompMatrix &cm, uint64_t first, uint64_t count, int32_t *makespan_out, void *ws, int num_cus,
                        void *stream);
 int launch_completion_reset(void *ws, void *stream);

@@ -54,9 +54,6 @@ __device__ __forceinline__ void lds_load2(uint32_t a, uint32_t &x, uint32_t &y)
     x = v.x; y = v.y;
 }
 typedef __attribute__((address_space(3))) uint8_t lds_byte;
-typedef __attribute__((address_space(3))) uint16_t lds_half;
-__device__ __forceinline__ uint32_t lds_load16(uint32_t a) { return *(const lds_half *)(uintptr_t)a; }
-__device__ __forceinline__ void lds_store16(uint32_t a, uint32_t v) { *(lds_half *)(uintptr_t)a = (uint16_t)v; }
 __device__ __forceinline__ uint32_t lds_load8(uint32_t a) { return *(const lds_byte *)(uintptr_t)a; }
 __device__ __forceinline__ void lds_store8(uint32_t a, uint32_t v) { *(lds_byte *)(uintptr_t)a = (uint8_t)v; }
 

@@ -2460,13 +2460,242 @@ int eval_blocks_that_fit(const KParams &kp, int num_cus, size_t bytes)
 // block with the smallest (earliest start + jitter, micro-batch, type id) is appended at its earliest
 // start.  jitter(type, mu) = (draw * (J + 1)) >> 16 with draw number type*N + mu of the stream keyed by the
 // ordinal; ordinal 0 has no jitter (the plain greedy schedule).
-// Per-lane state in LDS [slot][lane], 16-bit words: end time of the latest block of every micro-batch in flight
-// (a ring per chain), free time and memory of every device, next micro-batch and its jitter of every type; behind
-// it, for problems with every type on one device, one 32-bit sort key per type.
-constexpr int kCompParamWords = 352;       // start of the LDS: the parameter block's copy, then three tables of kMaxK words at the end
-static_assert(sizeof(CompParams) <= (kCompParamWords - 3 * kMaxK) * 4, "parameter block and per-type tables share the start of the LDS");
+// ---- every type on one device, chains, at most eight of them (all pipeline placements without tensor parallelism) ----------------
+// One lane a candidate; all lanes of a wave place the same number of blocks a phase, one a step.  Per lane, in LDS [row][lane]:
+//   offer  per block type (rows by device and symbol): the block it offers, as the sort key it has by its producer alone, (end of
+//          the producer's block + jitter) << 15 | micro-batch << 5 | type; bit 31: its producer has not handled that micro-batch;
+//          all ones: nothing left to offer in this phase
+//   device free time (16 bits) | memory << 16; the jitters of the blocks its types offer, a byte each; the smallest key of its types
+//   token  end times of the micro-batches in flight, a ring a chain, 16 bits
+// The key of an offer is max(offer, (free time + jitter) << 15 | the same low bits), with bit 31 where its memory does not fit.  A
+// step changes the keys of the block's own device, worked out anew (four at most), and the offer of its consumer, if that waits
+// for this very micro-batch: with the block's end and the jitter it has already.  So a pick is the smallest of eight words, not of the
+// keys of all types, which were kept in LDS before and of which a step changed up to five: 115 vector instructions a step now.
+// Bound by the steps' own chain at two waves a SIMD (LDS: 17.7 KB a wave for 8 devices and 32 types): five rounds of LDS reads with 115
+// vector instructions between them, which issue for half of the time.  2^20 candidates of 64 micro-batches on 8 devices, as a call:
+// 2.47 -> 1.42 ms; 41 000 of 40 on 7 devices: 326 -> 202 us.
+template <int DM, int SY>
+struct ChainRows {
+    static constexpr uint32_t kRowB = kWave * 4u;
+    static constexpr uint32_t types = 0, more = 512, mpos = 640, init = 704, rows = 1024;      // tables: by type, by type, by device, by code
+    static constexpr uint32_t least = rows, dev = least + DM * kRowB, jit = dev + DM * kRowB, offer = jit + DM * kRowB;
+    static constexpr uint32_t ones = offer + DM * SY * kRowB, token = ones + kRowB;
+};
 
-__global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__restrict__ cpg, const CompMatrix *__restrict__ cmg,
+template <int DM, int SY>
+__global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams *__restrict__ cpg, const CompMatrix *__restrict__ cmg,
+                                                               uint64_t first, uint64_t count, CompRec *__restrict__ recs,
+                                                               int32_t *__restrict__ makespan_out)
+{
+    typedef ChainRows<DM, SY> L;
+    extern __shared__ uint32_t lds[];
+    const int lane = threadIdx.x;
+    // (all LDS addresses below are offsets from 0: nothing else of the kernel lies in front of this array)
+    if (lds_address(lds) != 0u) {
+        if (recs && lane == 0) { recs[blockIdx.x].makespan = INT_MAX; recs[blockIdx.x].ordinal = ~0ull; }
+        return;
+    }
+    const uint32_t lane4 = (uint32_t)lane * 4u, lane2 = (uint32_t)lane * 2u;
+    const int D = cpg->D, K = cpg->K, N = cpg->N, NR = cpg->NR, M = cpg->M, J = cpg->J, R = cpg->R, TR = cpg->tok_ring, nseq = cpg->nseq;
+    const uint32_t ring_rows = (uint32_t)(cpg->npaths * TR), tmask = (uint32_t)(TR - 1) << 7, oFree = ring_rows;
+    const uint32_t seed_lo = cpg->seed_lo, seed_hi = cpg->seed_hi;
+    const uint32_t replay = L::token + ((ring_rows * (uint32_t)(kWave * 2) + 255u) & ~255u);      // words of the windows' blocks (no matrix)
+    const int nin = cmg->nin, nout = cmg->nout;
+    // ---- tables, a type a lane (the parameter block is read from a copy behind the tables)
+    {
+        uint32_t *copy = lds + L::rows / 4;
+        for (int w = lane; w < (int)(sizeof(CompParams) / 4); w += kWave) copy[w] = ((const uint32_t *)cpg)[w];
+        for (int w = lane; w < (int)(L::rows / 4); w += kWave) lds[w] = 0;
+        __syncthreads();
+        const CompParams &cp = *(const CompParams *)copy;
+        auto device_of = [&](int i) -> uint32_t { return (uint32_t)__builtin_ctz((uint32_t)cp.mask[i]); };
+        auto symbol_of = [&](int i) -> uint32_t { uint32_t y = 0; for (int j = 0; j < i; j++) y += cp.mask[j] == cp.mask[i] ? 1u : 0u; return y; };
+        auto offer_of = [&](int i) -> uint32_t { return L::offer + (device_of(i) * SY + symbol_of(i)) * L::kRowB; };
+        if (lane < K) {
+            const int i = lane, a = cp.pred[i];
+            int c = -1;
+            for (int j = 0; j < K; j++) if (cp.pred[j] == i) c = j;
+            const uint32_t d = device_of(i), y = symbol_of(i);
+            lds[L::types / 4 + 4 * i] = (d << 8) | ((uint32_t)cp.path[i] * (uint32_t)TR * (uint32_t)(kWave * 2) + L::token) << 16;
+            lds[L::types / 4 + 4 * i + 1] = (uint32_t)cp.t[i] | (uint32_t)cp.m[i] << 16;
+            lds[L::types / 4 + 4 * i + 2] = offer_of(i) | (c >= 0 ? offer_of(c) : L::ones) << 16;
+            lds[L::types / 4 + 4 * i + 3] = (uint32_t)max(c, 0) | (c >= 0 ? device_of(c) << 8 | 8u * symbol_of(c) << 16 : 0u) | 8u * y << 24 | (a >= 0 ? 1u << 30 : 0u);
+            // (how many micro-batches the phase has of the type, times 32, comes in with the phase)
+            lds[L::more / 4 + i] = (a >= 0 ? offer_of(a) : L::ones) | (c >= 0 ? (uint32_t)max((int)cp.m[c], 0) : 0u);
+            atomicOr(&lds[L::mpos / 4 + d], (uint32_t)max((int)cp.m[i], 0) << (8u * y));
+            // by code: type, lead, no producer, its micro-batch after the windows is there already, a type
+            lds[L::init / 4 + d * SY + y] = (uint32_t)i | (uint32_t)cp.lead[i] << 8 | (a < 0 ? 1u << 16 : 0u) |
+                                            (a < 0 || cp.lead[a < 0 ? 0 : a] > cp.lead[i] ? 1u << 17 : 0u) | 1u << 18;
+        }
+        if (nin == 0) {
+            // one word per block of the window: device (3 bits), micro-batch within the first window (8), chain (3), has a producer, t (16)
+            for (int s = lane; s < nseq; s += kWave) {
+                const int i = cp.seq[s];
+                lds_store(replay + 4u * (uint32_t)s, device_of(i) | ((uint32_t)cp.lead[i] + (uint32_t)cp.occ[s]) << 3 | (uint32_t)cp.path[i] << 11 |
+                                                     (cp.pred[i] >= 0 ? 1u << 14 : 0u) | (uint32_t)cp.t[i] << 16);
+            }
+        }
+        __syncthreads();
+    }
+    auto uniform_word = [&](uint32_t a) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_load(a)); };
+    int best = INT_MAX;
+    uint64_t best_ord = 0;
+    const uint64_t stride = (uint64_t)gridDim.x * kWave;
+    const uint64_t rounds = (count + stride - 1) / stride;          // the same trip count for every lane of the grid
+    for (uint64_t r = 0; r < rounds; r++) {
+        const uint64_t kk = r * stride + (uint64_t)blockIdx.x * kWave + lane;
+        const bool live = kk < count;
+        const uint64_t c = first + (live ? kk : 0);                 // (a lane past the end scores the first candidate and drops it)
+        uint32_t kb;
+        const uint32_t ka = stream_keys(((uint64_t)seed_hi << 32) | seed_lo, c, kb);
+        const uint32_t jmul = c != 0 ? (uint32_t)(J + 1) : 0u;      // ordinal 0 has no jitter
+        auto jitter = [&](uint32_t n) -> uint32_t { return __umul24(stream_draw16(ka, kb, n), jmul) >> 16; };
+        for (uint32_t s = 0; s < ring_rows; s++) lds_store16(L::token + s * (kWave * 2u) + lane2, 0u);
+        for (int d = 0; d < DM; d++) { lds_store(L::dev + (uint32_t)d * L::kRowB + lane4, 0u); lds_store(L::least + (uint32_t)d * L::kRowB + lane4, ~0u); }
+        lds_store(L::ones + lane4, ~0u);
+        bool fail = false;
+        // the smallest key of a device whose types' offers are at `at`: free time, jitters, memory left (not below 0)
+        auto least_key = [&](uint32_t at, uint32_t fr, uint32_t jits, int room, uint32_t mp) -> uint32_t {
+            uint32_t low = ~0u;
+#pragma unroll
+            for (int y = 0; y < SY; y++) {
+                const uint32_t o = lds_load(at + (uint32_t)y * L::kRowB);
+                const uint32_t key = max(o, ((fr + (jits >> (8 * y) & 255u)) << 15) | (o & 0x7FFFu));
+                low = min(low, (uint32_t)__builtin_amdgcn_bitop3_b32((uint32_t)(room - (int)(mp >> (8 * y) & 255u)), 0x80000000u, key, 0xEA));
+            }
+            return low;
+        };
+        for (int phase = 0; phase < 2; phase++) {
+            // ---- what every type offers at first: warm-up from micro-batch 0, cool-down from where the windows end
+            int left = 0;                                           // blocks of this phase
+            for (int d = 0; d < D; d++) {
+                uint32_t jits = 0;
+                const uint32_t dd = (uint32_t)d * L::kRowB + lane4;
+                for (uint32_t y = 0; y < (uint32_t)SY; y++) {
+                    const uint32_t I = uniform_word(L::init + ((uint32_t)d * SY + y) * 4u);
+                    const uint32_t id = I & 31u, lead = I >> 8 & 255u, mu = phase ? lead + (uint32_t)(NR * R) : 0u, hi = phase ? (uint32_t)N : lead;
+                    uint32_t o = ~0u;
+                    if ((I >> 18 & 1u) && mu < hi) {
+                        left += (int)(hi - mu);
+                        const uint32_t j = jitter(id * (uint32_t)N + mu);
+                        jits |= j << (8u * y);
+                        const bool there = I >> (phase ? 17 : 16) & 1u;
+                        const uint32_t tok = uniform_word(L::types + 16u * id) >> 16;
+                        const uint32_t from = I >> 16 & 1u ? 0u : lds_load16(tok + (mu << 7 & tmask) + lane2);
+                        o = (there ? (from + j) << 15 : 0x80000000u) | mu << 5 | id;
+                    }
+                    if (I >> 18 & 1u) {
+                        const uint32_t a = L::more + 4u * id, was = uniform_word(a);
+                        if (lane == 0) lds_store(a, (was & 0xFFFFu) | hi << 21);
+                    }
+                    lds_store(L::offer + ((uint32_t)d * SY + y) * L::kRowB + lane4, o);
+                }
+                lds_store(L::jit + dd, jits);
+                const uint32_t fm = lds_load(L::dev + dd);
+                lds_store(L::least + dd, least_key(L::offer + (uint32_t)d * SY * L::kRowB + lane4, fm & 0xFFFFu, jits, max(M - ((int)fm >> 16), 0),
+                                                   uniform_word(L::mpos + 4u * (uint32_t)d)));
+            }
+            __syncthreads();
+            // ---- a block a step
+            for (int s = 0; s < left; s++) {
+                uint32_t pick = ~0u;
+#pragma unroll
+                for (int d = 0; d < DM; d++) pick = min(pick, lds_load(L::least + (uint32_t)d * L::kRowB + lane4));
+                const bool placed = (int)pick >= 0;
+                fail = fail | !placed;                              // blocks left, none eligible: no schedule
+                if (!placed) continue;                              // (such a lane's state stays as it is, and it never places again)
+                const uint32_t b = pick & 31u, low = pick & 0x7FE0u, low1 = low + 32u;
+                const uint32_t T0 = lds_load(L::types + 16u * b), T1 = lds_load(L::types + 16u * b + 4u), T2 = lds_load(L::types + 16u * b + 8u),
+                               T3 = lds_load(L::types + 16u * b + 12u), U = lds_load(L::more + 4u * b);
+                const uint32_t jn = jitter(__umul24(b, (uint32_t)N) + (low1 >> 5));
+                // (second round: everything these words name)
+                const uint32_t dd = (T0 & 0xF00u) + lane4, cd = (T3 & 0xF00u) + lane4, ring = (T0 >> 16) + lane2, oc = (T2 >> 16) + lane4;
+                uint32_t fm = lds_load(L::dev + dd), jits = lds_load(L::jit + dd), mp = lds_load(L::mpos + ((T0 & 0xF00u) >> 6));
+                uint32_t off_c = lds_load(oc), fm_c = lds_load(L::dev + cd), jits_c = lds_load(L::jit + cd);
+                uint32_t off_p = lds_load((U & 0xFF00u) + lane4), tk = lds_load16(ring + (low1 << 2 & tmask));
+                TESSEL_PIN(fm); TESSEL_PIN(jits); TESSEL_PIN(mp); TESSEL_PIN(off_c); TESSEL_PIN(fm_c); TESSEL_PIN(jits_c); TESSEL_PIN(off_p); TESSEL_PIN(tk);
+                const uint32_t yb = T3 >> 24 & 31u;
+                const uint32_t en = (pick >> 15) - (jits >> yb & 255u) + (T1 & 0xFFFFu);
+                const uint32_t fm_new = ((fm + (T1 & 0xFFFF0000u)) & 0xFFFF0000u) | en;
+                const uint32_t jits_new = (jits & ~(255u << yb)) | jn << yb;
+                // the type's next micro-batch: there if its producer's offer is beyond it (nothing left to offer: all ones)
+                const uint32_t from = T3 >> 30 & 1u ? tk : 0u, low_b = low1 | b;
+                uint32_t off_b = (off_p & 0x7FE0u) > low1 ? (from + jn) << 15 | low_b : 0x80000000u | low_b;
+                off_b = low1 >= U >> 16 ? ~0u : off_b;
+                lds_store(L::dev + dd, fm_new);
+                lds_store(L::jit + dd, jits_new);
+                lds_store16(ring + (low << 2 & tmask), en);
+                lds_store((T2 & 0xFFFFu) + lane4, off_b);
+                // its consumer, if that waits for this block.  (No consumer: a row of all ones, which no block matches.)
+                {
+                    const uint32_t jc = jits_c >> (T3 >> 16 & 31u) & 255u, low_c = off_c & 0x7FFFu;
+                    const bool waits = off_c == (0x80000000u | low | (T3 & 31u));
+                    const uint32_t now = (en + jc) << 15 | low_c;
+                    lds_store(oc, waits ? now : off_c);
+                    const int room = max(M - ((int)fm_c >> 16), 0) - (int)(U & 127u);
+                    const uint32_t key = __builtin_amdgcn_bitop3_b32((uint32_t)room, 0x80000000u, max(now, ((fm_c & 0xFFFFu) + jc) << 15 | low_c), 0xEA);
+                    // (on the block's own device the store below follows)
+                    __hip_atomic_fetch_min((lds_word *)(uintptr_t)(L::least + cd), waits ? key : ~0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                lds_store(L::least + dd, least_key((T0 & 0xF00u) * SY + L::offer + lane4, en, jits_new, max(M - ((int)fm_new >> 16), 0), mp));
+            }
+            __syncthreads();
+            if (phase == 1) break;
+            // ---- the R windows: the same blocks at the same micro-batches in every lane.  (Without the memory, which a whole
+            // window leaves as it was: the deltas on a device sum to zero, and the window itself was scored against the cap.)
+            auto slot_address = [&](uint32_t s) -> uint32_t {
+                return s < oFree ? L::token + s * (kWave * 2u) + lane2 : L::dev + (s - oFree) * L::kRowB + lane4;
+            };
+            if (nin > 0) {
+                // all R windows at once: every slot they write = max over the slots they read first of (value + longest path);
+                // rows and slots are the same in every lane and come by scalar loads
+                int x[kMatIn];
+#pragma unroll
+                for (int j = 0; j < kMatIn; j++) x[j] = j < nin ? (int)lds_load16(slot_address(cmg->in_slot[j])) : 0;
+                for (int o = 0; o < nout; o++) {
+                    int acc = 0;                         // (every output has a path from some input, and times are >= 0)
+#pragma unroll
+                    for (int j = 0; j < kMatIn; j++) acc = max(acc, x[j] + cmg->a[o][j]);
+                    lds_store16(slot_address(cmg->out_slot[o]), (uint32_t)acc);
+                }
+            } else
+                for (int w = 0; w < R; w++)
+                    for (int s = 0; s < nseq; s++) {
+                        const uint32_t rw = uniform_word(replay + 4u * (uint32_t)s);
+                        const uint32_t mu = (rw >> 3 & 255u) + (uint32_t)(NR * w), fr = L::dev + (rw & 7u) * L::kRowB + lane4;
+                        const uint32_t tok = L::token + (rw >> 11 & 7u) * (uint32_t)TR * (kWave * 2u) + (mu << 7 & tmask) + lane2;
+                        uint32_t est = lds_load16(fr);
+                        if (rw >> 14 & 1u) est = max(est, lds_load16(tok));
+                        const uint32_t en = est + (rw >> 16);
+                        lds_store16(fr, en);
+                        lds_store16(tok, en);
+                    }
+            __syncthreads();
+        }
+        int makespan = 0;
+        for (int d = 0; d < D; d++) makespan = max(makespan, (int)(lds_load(L::dev + (uint32_t)d * L::kRowB + lane4) & 0xFFFFu));
+        if (fail) makespan = INT_MAX;
+        if (live && makespan_out) makespan_out[kk] = makespan;
+        if (live && (makespan < best || (makespan == best && c < best_ord))) { best = makespan; best_ord = c; }
+    }
+    if (!recs) return;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        int om = __shfl_xor(best, off);
+        uint32_t ilo = __shfl_xor((uint32_t)best_ord, off), ihi = __shfl_xor((uint32_t)(best_ord >> 32), off);
+        uint64_t oo = ((uint64_t)ihi << 32) | ilo;
+        if (key_less(om, oo, best, best_ord)) { best = om; best_ord = oo; }
+    }
+    if (lane == 0) { CompRec rr; rr.makespan = best; rr.pad = 0; rr.ordinal = best_ord; recs[blockIdx.x] = rr; }
+}
+
+// ---- any other problem: blocks on several devices, graphs, more than eight chains ------------------------------------------
+// Per-lane state in LDS [slot][lane], 16-bit words: end time of the latest block of every micro-batch in flight (a ring per
+// chain or consumed type), free time and memory of every device, next micro-batch and its jitter of every type.
+constexpr int kCompParamWords = 256;       // start of the LDS: the parameter block's copy
+static_assert(sizeof(CompParams) <= kCompParamWords * 4, "parameter block's copy");
+
+__global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__restrict__ cpg, const CompMatrix *__restrict__,
                                                          uint64_t first, uint64_t count,
                                                          CompRec *__restrict__ recs, int32_t *__restrict__ makespan_out)
 {
@@ -2480,55 +2709,9 @@ __global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__res
     // a type's next micro-batch (low 10 bits) and the jitter of that block (high 6 bits) share a word: N < 1024 and
     // J < 64 (checked by the host)
     const int TR = cp.tok_ring, tmask = TR - 1;          // end times of the micro-batches in flight: [chain][mu mod TR]
-    const int trs = __builtin_ctz((uint32_t)TR);         // (a power of two)
-    // (one more slot behind the state and one more row behind the keys take the stores of lanes that have nothing to
-    // store, so that no store needs a branch)
+    // (one more slot behind the state takes stores that nobody reads)
     const int oTok = 0, oFree = cp.npaths * TR, oMem = oFree + D, oNext = oMem + D, oTrash = oNext + K, nstate = oTrash + 1;
-    // Problems with every type on one device (and at most 8 chains) take a path that keeps, per type, the sort key of
-    // its offered block in LDS and touches only the types a scheduled block can change: its own type and its consumers
-    // are recomputed (`redo`); of the other types on its device (`aff`) a key that exists only moves to the device's new
-    // free time and is checked against its new memory.  Tables, per type: `ptab` lead (8 bits), memory delta (8,
-    // signed), producer + 1 (6), device (3), chain (3), 1 (a type of the problem) in one word.
-    bool single_dev = cp.npaths <= 8 && !cp.dag;
-    for (int i = 0; i < K; i++) single_dev = single_dev && (cp.mask[i] & (cp.mask[i] - 1)) == 0 && cp.mask[i] != 0;
-    uint32_t *ptab = lds + kCompParamWords - 3 * kMaxK, *aff = lds + kCompParamWords - 2 * kMaxK, *redo = lds + kCompParamWords - kMaxK;
-    if (lane < kMaxK) {
-        uint32_t pw = 0, af = 0, rd = 0;
-        if (lane < K) {
-            pw = (uint32_t)cp.lead[lane] | ((uint32_t)(uint8_t)cp.m[lane] << 8) | ((uint32_t)(cp.pred[lane] + 1) << 16) |
-                 ((uint32_t)__builtin_ctz((uint32_t)cp.mask[lane] | 0x100u) << 22) | ((uint32_t)cp.path[lane] << 25) | 1u << 28;
-            rd = 1u << lane;
-            for (int j = 0; j < K; j++) {
-                if (cp.pred[j] == lane) rd |= 1u << j;
-                if ((cp.mask[j] & cp.mask[lane]) != 0) af |= 1u << j;
-            }
-            af &= ~rd;
-        }
-        ptab[lane] = pw; aff[lane] = af; redo[lane] = rd;
-    }
-    // some type has several consumers, or more than three other types on its device (wave-uniform)
-    const bool crowded = __ballot(lane < K && (__builtin_popcount(redo[lane]) > 2 || __builtin_popcount(aff[lane]) > 3)) != 0;
     __syncthreads();
-    uint32_t *ckey = lds + kCompParamWords + (nstate + 1) / 2 * kWave + lane;      // [type][lane], behind the 16-bit state
-    // ... and behind the keys what the replay of the R windows needs.  Either their (max, +) matrix: kMatIn slot
-    // numbers of the inputs, kMatOut of the outputs, then one row of kMatIn path lengths per output; or (no matrix: too
-    // many values cross the windows) one word per block of the window: device (3 bits), chain (3), micro-batch within
-    // the first window = lead + occurrence (8), has a producer (1), t (16)
-    uint32_t *rtab = lds + kCompParamWords + (nstate + 1) / 2 * kWave + (K + 1) * kWave;
-    const int nin = single_dev ? cmg->nin : 0, nout = cmg->nout;
-    if (nin > 0) {
-        for (int s = lane; s < kMatIn; s += kWave) rtab[s] = cmg->in_slot[s];
-        for (int s = lane; s < kMatOut; s += kWave) rtab[kMatIn + s] = cmg->out_slot[s];
-        for (int s = lane; s < nout * kMatIn; s += kWave) rtab[kMatIn + kMatOut + s] = (uint32_t)cmg->a[s / kMatIn][s % kMatIn];
-        __syncthreads();
-    } else if (single_dev) {
-        for (int s = lane; s < cp.nseq; s += kWave) {
-            const uint32_t pw = ptab[cp.seq[s]];
-            rtab[s] = (pw >> 22 & 7u) | (pw >> 25 & 7u) << 3 | ((pw & 255u) + (uint32_t)cp.occ[s]) << 6 |
-                      ((pw >> 16 & 63u) != 0 ? 1u << 14 : 0u) | (uint32_t)cp.t[cp.seq[s]] << 16;
-        }
-        __syncthreads();
-    }
 #define TESSEL_ST(slot) state[(slot) * kWave]
     int best = INT_MAX;
     uint64_t best_ord = 0;
@@ -2554,133 +2737,6 @@ __global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__res
                 TESSEL_ST(oNext + i) = (uint16_t)((uint32_t)mu | (mu < hi ? jitter(i, mu) : 0u) << 10);
                 left += max(hi - mu, 0);
             }
-            // sort key of the block type i offers, (start + jitter, micro-batch, type) in one word, smallest first:
-            // start + jitter < 2^16 (checked by the host) in bits 15-30, micro-batch < 2^10, type < 2^5.  All ones:
-            // nothing offered, or its producer has not handled the micro-batch yet; bit 31 on a key: offered, but its
-            // memory does not fit now (the key below stays valid)
-            auto offer_key = [&](int i) -> uint32_t {
-                const uint32_t pw = ptab[i];
-                const bool has_a = (pw >> 16 & 63u) != 0;
-                const int hi = phase ? N : (int)(pw & 255u), a = (int)(pw >> 16 & 63u) - 1, d = (int)(pw >> 22 & 7u);
-                const int mi = (int)(int8_t)(pw >> 8);
-                const int nj = (int)TESSEL_ST(oNext + i), mu = nj & 1023;
-                const int na = (int)TESSEL_ST(oNext + (has_a ? a : i)) & 1023;
-                const int fr = (int)TESSEL_ST(oFree + d), me = (int)(int16_t)TESSEL_ST(oMem + d);
-                const int tk = (int)TESSEL_ST(oTok + ((int)(pw >> 25 & 7u) << trs) + (mu & tmask));
-                const bool offered = (mu < hi) & (!has_a | (na > mu)), fits = (mi <= 0) | (me + mi <= M);
-                const uint32_t key = (uint32_t)(max(has_a ? tk : 0, fr) + (nj >> 10));
-                return offered ? (key << 15) | ((uint32_t)mu << 5) | (uint32_t)i | (fits ? 0u : 0x80000000u) : 0xFFFFFFFFu;
-            };
-            if (single_dev) {
-                // ---- every type on one device: one straight-line step per scheduled block
-                for (int i = 0; i < K; i++) ckey[i * kWave] = offer_key(i);
-                for (;;) {
-                    const bool busy = live && !fail && left > 0;
-                    if (__ballot(busy) == 0) break;
-                    uint32_t bestp = 0xFFFFFFFFu;
-#pragma unroll 8
-                    for (int i = 0; i < K; i++) bestp = min(bestp, ckey[i * kWave]);
-                    const bool placed = busy && bestp < 0x80000000u;
-                    fail = fail | (busy && !placed);              // blocks left, none eligible: no schedule
-                    // A lane that places nothing goes through the step with type 0 and writes nothing.  The step is
-                    // three rounds of LDS reads, each issued as a whole before anything waits for it (the values are
-                    // pinned so that no read sinks into a branch): (1) the table words of the block's type; (2) what
-                    // they name: the memory of its device, the table word and counter of its consumer, key, table word
-                    // and counter of the other types on its device, its producer's counter and the end time its own
-                    // next micro-batch waits for; (3) after the writes of the block, the consumer's device and token.
-                    const int b = placed ? (int)(bestp & 31u) : 0, bmu = (int)(bestp >> 5 & 1023u), mu1 = bmu + 1;
-                    uint32_t pw = ptab[b], rdw = redo[b], af = aff[b], tb = (uint32_t)cp.t[b], njb = TESSEL_ST(oNext + b);
-                    TESSEL_PIN(pw); TESSEL_PIN(rdw); TESSEL_PIN(af); TESSEL_PIN(tb); TESSEL_PIN(njb);
-                    const uint32_t rd = rdw & ~(1u << b), af1 = af & (af - 1u), af2 = af1 & (af1 - 1u);
-                    const bool has_c = placed && rd != 0, h0 = placed && af != 0, h1 = placed && af1 != 0, h2 = placed && af2 != 0;
-                    const int c = has_c ? __builtin_ctz(rd) : b;
-                    const int a0 = h0 ? __builtin_ctz(af) : b, a1 = h1 ? __builtin_ctz(af1) : b, a2 = h2 ? __builtin_ctz(af2) : b;
-                    const int d = (int)(pw >> 22 & 7u), mi_b = (int)(int8_t)(pw >> 8), hi_b = phase ? N : (int)(pw & 255u);
-                    const bool has_ab = (pw >> 16 & 63u) != 0;
-                    uint32_t me_old = TESSEL_ST(oMem + d), pwc = ptab[c], njc = TESSEL_ST(oNext + c);
-                    uint32_t k0 = ckey[a0 * kWave], p0 = ptab[a0], n0 = TESSEL_ST(oNext + a0);
-                    uint32_t k1 = ckey[a1 * kWave], p1 = ptab[a1], n1 = TESSEL_ST(oNext + a1);
-                    uint32_t k2 = ckey[a2 * kWave], p2 = ptab[a2], n2 = TESSEL_ST(oNext + a2);
-                    uint32_t napb = TESSEL_ST(oNext + (has_ab ? (int)(pw >> 16 & 63u) - 1 : b));
-                    uint32_t tkb = TESSEL_ST(oTok + ((int)(pw >> 25 & 7u) << trs) + (mu1 & tmask));
-                    TESSEL_PIN(me_old); TESSEL_PIN(pwc); TESSEL_PIN(njc); TESSEL_PIN(k0); TESSEL_PIN(p0); TESSEL_PIN(n0);
-                    TESSEL_PIN(k1); TESSEL_PIN(p1); TESSEL_PIN(n1); TESSEL_PIN(k2); TESSEL_PIN(p2); TESSEL_PIN(n2);
-                    TESSEL_PIN(napb); TESSEL_PIN(tkb);
-                    const int en = (int)(bestp >> 15) - (int)(njb >> 10) + (int)tb;
-                    const int me_new = (int)(int16_t)me_old + mi_b;
-                    uint32_t jn = (stream_draw16(ka, kb, (uint32_t)(b * N + mu1)) * (uint32_t)(J + 1)) >> 16;
-                    TESSEL_PIN(jn);
-                    jn = noisy ? jn : 0u;
-                    const uint32_t njb_new = (uint32_t)mu1 | (mu1 < hi_b ? jn : 0u) << 10;
-                    TESSEL_ST(placed ? oFree + d : oTrash) = (uint16_t)en;
-                    TESSEL_ST(placed ? oMem + d : oTrash) = (uint16_t)me_new;
-                    TESSEL_ST(placed ? oTok + ((int)(pw >> 25 & 7u) << trs) + (bmu & tmask) : oTrash) = (uint16_t)en;
-                    TESSEL_ST(placed ? oNext + b : oTrash) = (uint16_t)njb_new;
-                    left -= placed ? 1 : 0;
-                    // round 3: the consumer's device and the end time of the micro-batch it waits for, as they are now
-                    const int dc = (int)(pwc >> 22 & 7u), muc = (int)(njc & 1023u);
-                    uint32_t frc = TESSEL_ST(oFree + dc), mec = TESSEL_ST(oMem + dc);
-                    uint32_t tkc = TESSEL_ST(oTok + ((int)(pwc >> 25 & 7u) << trs) + (muc & tmask));
-                    TESSEL_PIN(frc); TESSEL_PIN(mec); TESSEL_PIN(tkc);
-                    // The scheduled block changes what its own type and its consumer offer (recomputed; the block's
-                    // own values are at hand), and for the other types on its device (three at most) the free time and
-                    // the memory: start = max(end of the producer's block, device free), and the device was free no
-                    // later than now before, so the new key is max(old key, new free time + jitter); the same
-                    // micro-batch stays offered.
-                    const uint32_t blocked = 0x80000000u;
-                    uint32_t key_b, key_c;
-                    {
-                        const bool offered = (mu1 < hi_b) & (!has_ab | ((int)(napb & 1023u) > mu1));
-                        const bool fits = (mi_b <= 0) | (me_new + mi_b <= M);
-                        const uint32_t key = (uint32_t)max(has_ab ? (int)tkb : 0, en) + (njb_new >> 10);
-                        uint32_t word = (key << 15) | ((uint32_t)mu1 << 5) | (uint32_t)b | (fits ? 0u : blocked);
-                        TESSEL_PIN(word);                  // (computed in every lane: cheaper than a branch around it)
-                        key_b = offered ? word : 0xFFFFFFFFu;
-                    }
-                    {
-                        const int hic = phase ? N : (int)(pwc & 255u), mic = (int)(int8_t)(pwc >> 8);
-                        const bool offered = (muc < hic) & (mu1 > muc);            // (its producer is the block's type)
-                        const bool fits = (mic <= 0) | ((int)(int16_t)mec + mic <= M);
-                        const uint32_t key = max(tkc, frc) + (njc >> 10);
-                        uint32_t word = (key << 15) | ((uint32_t)muc << 5) | (uint32_t)c | (fits ? 0u : blocked);
-                        TESSEL_PIN(word);
-                        key_c = offered ? word : 0xFFFFFFFFu;
-                    }
-                    auto moved = [&](uint32_t k, uint32_t pwi, uint32_t nji) -> uint32_t {
-                        const int mi = (int)(int8_t)(pwi >> 8);
-                        const uint32_t start = max(k << 1 >> 16, (uint32_t)en + (nji >> 10));
-                        const bool fits = (mi <= 0) | (me_new + mi <= M);
-                        uint32_t word = (start << 15) | (k & 0x7FFFu) | (fits ? 0u : blocked);
-                        TESSEL_PIN(word);
-                        return k == 0xFFFFFFFFu ? k : word;
-                    };
-                    k0 = moved(k0, p0, n0); k1 = moved(k1, p1, n1); k2 = moved(k2, p2, n2);
-                    ckey[(placed ? b : K) * kWave] = key_b;
-                    ckey[(has_c ? c : K) * kWave] = key_c;
-                    ckey[(h0 ? a0 : K) * kWave] = k0;
-                    ckey[(h1 ? a1 : K) * kWave] = k1;
-                    ckey[(h2 ? a2 : K) * kWave] = k2;
-                    if (crowded) {
-                        // a type with several consumers, or more than four types on a device: the rest one by one
-                        uint32_t todo = placed ? rd & (rd - 1u) : 0u;
-                        while (__ballot(todo != 0u) != 0) {
-                            if (todo != 0u) {
-                                const int i = __builtin_ctz(todo);
-                                todo &= todo - 1u;
-                                ckey[i * kWave] = offer_key(i);
-                            }
-                        }
-                        todo = placed ? af2 & (af2 - 1u) : 0u;
-                        while (__ballot(todo != 0u) != 0) {
-                            if (todo != 0u) {
-                                const int i = __builtin_ctz(todo);
-                                todo &= todo - 1u;
-                                ckey[i * kWave] = moved(ckey[i * kWave], ptab[i], TESSEL_ST(oNext + i));
-                            }
-                        }
-                    }
-                }
-            } else
             for (;;) {
                 int bi = -1, bmu = 0, best_est = 0, bkey = 0;
                 const bool any = left > 0;
@@ -2729,38 +2785,7 @@ __global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__res
                 }
             }
             if (phase == 1) break;
-            // ---- the R windows: the same blocks at the same micro-batches in every lane.  (Every type on one device:
-            // from the per-type table, and without the memory, which a whole window leaves as it was: the deltas on a
-            // device sum to zero, and the window itself was scored against the cap.)
-            if (nin > 0) {
-                // all R windows at once: every slot they write = max over the slots they read first of (value + longest path)
-                int x[kMatIn];
-#pragma unroll
-                for (int j = 0; j < kMatIn; j++) x[j] = j < nin ? (int)TESSEL_ST(__builtin_amdgcn_readfirstlane((int)rtab[j])) : 0;
-                for (int o = 0; o < nout; o++) {
-                    const int4 *row = (const int4 *)(rtab + kMatIn + kMatOut + o * kMatIn);
-                    int acc = 0;                         // (every output has a path from some input, and times are >= 0)
-#pragma unroll
-                    for (int q = 0; q < kMatIn / 4; q++) {
-                        const int4 a = row[q];
-                        acc = max(acc, max(x[4 * q] + a.x, x[4 * q + 1] + a.y));
-                        acc = max(acc, max(x[4 * q + 2] + a.z, x[4 * q + 3] + a.w));
-                    }
-                    TESSEL_ST(__builtin_amdgcn_readfirstlane((int)rtab[kMatIn + o])) = (uint16_t)acc;
-                }
-            } else if (single_dev) {
-                for (int k = 0; k < R; k++)
-                    for (int s = 0; s < cp.nseq; s++) {
-                        const uint32_t rw = (uint32_t)__builtin_amdgcn_readfirstlane((int)rtab[s]);
-                        const int mu = (int)(rw >> 6 & 255u) + NR * k, d = (int)(rw & 7u);
-                        const int tok = oTok + ((int)(rw >> 3 & 7u) << trs) + (mu & tmask);
-                        int est = (int)TESSEL_ST(oFree + d);
-                        if (rw >> 14 & 1u) est = max(est, (int)TESSEL_ST(tok));
-                        const int en = est + (int)(rw >> 16);
-                        TESSEL_ST(oFree + d) = (uint16_t)en;
-                        TESSEL_ST(tok) = (uint16_t)en;
-                    }
-            } else
+            // ---- the R windows: the same blocks at the same micro-batches in every lane
             for (int k = 0; k < R; k++)
                 for (int s = 0; s < cp.nseq; s++) {
                     const int i = cp.seq[s], mu = (int)cp.lead[i] + (int)cp.occ[s] + NR * k;
@@ -2822,35 +2847,62 @@ __global__ void completion_reset_kernel(DevCompletion *res)
     if (threadIdx.x == 0 && blockIdx.x == 0) { res->makespan = INT_MAX; res->pad = 0; res->ordinal = ~0ull; }
 }
 
-size_t completion_lds_bytes(const CompParams &cp, const CompMatrix &cm)
+typedef void (*comp_fn)(const CompParams *, const CompMatrix *, uint64_t, uint64_t, CompRec *, int32_t *);
+
+// The kernel and the LDS of a workgroup.  Chains whose types sit on one device each: rows for 4 or 8 devices with 2 or 4 types each, then
+// the ring of every chain, then (no matrix) one word per block of the window.  Others: 16-bit state and parameters.
+constexpr size_t kCompLds = 64 * 1024;
+static comp_fn pick_completion(const CompParams &cp, const CompMatrix &cm, size_t &lds)
 {
-    // 16-bit state, then one 32-bit sort key per type, then the windows' matrix or one word per block of the window
+    bool chain = cp.npaths <= 8 && !cp.dag;
+    int on[kMaxD] = {0}, most = 0;
+    for (int i = 0; i < cp.K; i++) {
+        chain = chain && cp.mask[i] != 0 && (cp.mask[i] & (cp.mask[i] - 1)) == 0;
+        if (chain) most = std::max(most, ++on[__builtin_ctz((unsigned)cp.mask[i])]);
+    }
+    const size_t replay = cm.nin > 0 ? 0 : (size_t)cp.nseq * 4;
+    const size_t behind = (((size_t)cp.npaths * cp.tok_ring * kWave * 2 + 255) & ~(size_t)255) + ((replay + 15) & ~(size_t)15);
+    const size_t rows = cp.D <= 4 ? (most <= 2 ? ChainRows<4, 2>::token : ChainRows<4, 4>::token) : (most <= 2 ? ChainRows<8, 2>::token : ChainRows<8, 4>::token);
+    lds = rows + behind;
+    if (!chain || most > 4) {
+        lds = (size_t)kCompParamWords * 4 + (size_t)((cp.npaths * cp.tok_ring + 2 * cp.D + cp.K + 1 + 1) / 2 * 2) * kWave * 2;
+        return complete_kernel;
+    }
+    if (cp.D <= 4) return most <= 2 ? complete_chain_kernel<4, 2> : complete_chain_kernel<4, 4>;
+    return most <= 2 ? complete_chain_kernel<8, 2> : complete_chain_kernel<8, 4>;
+}
+
+// Problems are taken up to 64 KB of parameters, 16-bit state, a key a type and the windows' words.  (What passes has rings of 320 rows at
+// most, five chains of which one has 25 types or more: with 384 and the 30 types that takes on 8 devices the sum is above it.  So the rows
+// of the chain kernel, 16 KB, have room behind 40.)
+bool completion_fits(const CompParams &cp, const CompMatrix &cm)
+{
     const size_t replay = cm.nin > 0 ? (size_t)(kMatIn + kMatOut + cm.nout * kMatIn) * 4 : (size_t)cp.nseq * 4;
-    return (size_t)kCompParamWords * 4 + (size_t)((cp.npaths * cp.tok_ring + 2 * cp.D + cp.K + 1 + 1) / 2 * 2) * kWave * 2 +
-           (size_t)(cp.K + 1) * kWave * 4 +
-           ((replay + 15) & ~(size_t)15);
+    return (size_t)1408 + (size_t)((cp.npaths * cp.tok_ring + 2 * cp.D + cp.K + 1 + 1) / 2 * 2) * kWave * 2 +
+           (size_t)(cp.K + 1) * kWave * 4 + ((replay + 15) & ~(size_t)15) <= kCompLds;
 }
 
 int launch_completions(const CompParams &cp, const CompMatrix &cm, uint64_t first, uint64_t count, int32_t *makespan_out, void *ws,
                        int num_cus, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    const size_t lds = completion_lds_bytes(cp, cm);
-    if (lds > 64 * 1024) return -1;
-    static bool attr_set = false;
-    if (!attr_set && lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)complete_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+    size_t lds;
+    comp_fn fn = pick_completion(cp, cm, lds);
+    if (lds > kCompLds) return -1;
+    if (lds > 48 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCompLds);
         if (e != hipSuccess) return (int)e;
-        attr_set = true;
     }
     int per_cu = (int)((160 * 1024) / ((lds + 511) / 512 * 512));
     if (per_cu > 16) per_cu = 16;
     if (per_cu < 1) per_cu = 1;
+    // a multiple of 4, the same number on every SIMD: 9 a CU (3, 2, 2, 2) took 1.25 times as long a round of candidates as 8
+    if (fn != complete_kernel && per_cu > 4) per_cu &= ~3;
     uint64_t need = (count + kWave - 1) / kWave;
     const int blocks = need < (uint64_t)(num_cus * per_cu) ? (int)need : num_cus * per_cu;
     if (blocks < 1) return 0;
     CompRec *recs = makespan_out ? nullptr : (CompRec *)((char *)ws + kWsBlockRecOff);
-    hipLaunchKernelGGL(complete_kernel, dim3(blocks), dim3(kWave), lds, st, (const CompParams *)((char *)ws + kWsCompParamsOff),
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, st, (const CompParams *)((char *)ws + kWsCompParamsOff),
                        (const CompMatrix *)((char *)ws + kWsCompMatrixOff), first,
                        count, recs, makespan_out);
     int rc = (int)hipGetLastError();
