@@ -178,7 +178,7 @@ def main():
                           "best_ordinal": found["ordinal"]},
                "blocks_scheduled_per_s": rate * blocks,
                "roofline": {"bound": "alu", "achieved": ops * rate / 1e12, "peak": PEAK_INT32_OPS, "unit": "Tint32op/s",
-                            "frac": ops * rate / 1e12 / PEAK_INT32_OPS, "traffic": None, "kernel": "complete_kernel",
+                            "frac": ops * rate / 1e12 / PEAK_INT32_OPS, "traffic": None, "kernel": "complete_chain_kernel<8, 4>",
                             "algorithmic_ops_per_candidate": ops,
                             "limited_by": "latency: every scheduled block of the greedy phases is a chain of dependent per-lane "
                                           "decisions through LDS, at two waves per SIMD "
