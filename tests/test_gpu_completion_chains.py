@@ -57,3 +57,16 @@ def test_completions_of_chains(gpu, monkeypatch, name, replay):  # noqa: F811
     else:
         got = g.best_completion(N)
         assert (got["makespan"], got["ordinal"]) == (best, ordinal), name
+
+
+@pytest.mark.parametrize("n", [64, 65, 64 * 1024 - 1, 64 * 1024, 64 * 1024 + 1, 64 * 1025 + 3])
+def test_the_best_of_many_workgroups(gpu, n):  # noqa: F811
+    """the search's best = the first least makespan of the same range, around the number of records that are read at a time"""
+    prob, N, J = CASES["5dev-2types"]
+    g = gpu.Problem(prob)
+    g.eval_candidates(0, 3000)
+    first = 12345
+    scores = g.score_completions(N, J, first, n).cpu().numpy()
+    g.search_completions(N, J, first, n)
+    got = g.best_completion(N)
+    assert (got["makespan"], got["ordinal"]) == (int(scores.min()), first + int(scores.argmin()))
