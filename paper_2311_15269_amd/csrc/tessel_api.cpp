@@ -1176,9 +1176,21 @@ public:
     }
     Mailbox(const Mailbox &) = delete;
     Mailbox &operator=(const Mailbox &) = delete;
-    // Until the mail is there: at first by looking at it, then by waiting for the stream, which also finds out about a failed
-    // launch.  A box whose launch failed may still be written to, and is not used again.
-    int wait(hipStream_t st)
+    // `launched`: the status of the launch that sends the mail.  Waits until the mail is there: at first by looking at it, then by
+    // waiting for the stream, which also finds out about a kernel that failed.  A box whose launch or kernel failed may still
+    // be written to, and is not used again.
+    int wait(int launched, hipStream_t st)
+    {
+        lost = true;
+        if (launched) return launched;
+        const int rc = arrived(st);
+        lost = rc != 0;
+        return rc;
+    }
+private:
+    int at = 0;
+    bool lost = false;
+    int arrived(hipStream_t st) const
     {
         const auto start = std::chrono::steady_clock::now();
         for (int k = 1;; k++) {
@@ -1187,15 +1199,9 @@ public:
             __builtin_ia32_pause();
         }
         const hipError_t e = hipStreamSynchronize(st);
-        if (e != hipSuccess || __atomic_load_n(&box->told, __ATOMIC_ACQUIRE) != told) {
-            lost = true;
-            return e != hipSuccess ? (int)e : (int)hipErrorUnknown;
-        }
-        return 0;
+        if (e != hipSuccess) return (int)e;
+        return __atomic_load_n(&box->told, __ATOMIC_ACQUIRE) == told ? 0 : (int)hipErrorUnknown;
     }
-private:
-    int at = 0;
-    bool lost = false;
 };
 }  // namespace
 
@@ -1207,10 +1213,9 @@ static int read_back(tessel_problem *p)
 {
     Mailbox mail;
     int le = launch_detail(p->kp, p->ws, mail.box, mail.told, p->result.period, p->result.index, p->stream);
+    if (mail.box) le = mail.wait(le, p->stream);
     if (le) return hip_fail(p, le);
     if (mail.box) {
-        le = mail.wait(p->stream);
-        if (le) return hip_fail(p, le);
         memcpy(&p->result, mail.box->words, sizeof p->result);
         if (!mail.box->whole) return TESSEL_OK;
         memcpy(&p->detail, mail.box->words + kMailDetail, sizeof p->detail);
@@ -1588,8 +1593,7 @@ extern "C" int tessel_best_completion(tessel_problem *p, tessel_schedule *out, u
     {
         Mailbox mail;
         if (mail.box) {
-            int le = launch_tell(p->ws, kWsCompletionOff, sizeof best, mail.box, mail.told, p->stream);
-            if (!le) le = mail.wait(p->stream);
+            const int le = mail.wait(launch_tell(p->ws, kWsCompletionOff, sizeof best, mail.box, mail.told, p->stream), p->stream);
             if (le) return hip_fail(p, le);
             memcpy(&best, mail.box->words, sizeof best);
         } else {

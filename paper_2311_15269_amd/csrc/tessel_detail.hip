@@ -13,6 +13,7 @@
 #include <stdint.h>
 #include <limits.h>
 #include <stddef.h>
+#include <tuple>
 
 #include "tessel_common.h"
 
@@ -46,10 +47,22 @@ __global__ __launch_bounds__(kWave) void tell_kernel(const uint32_t *__restrict_
     mail_end(mail, told, false);
 }
 
+// One wave; the launch's own status.  (hipGetLastError() would also report a call that failed before on this thread, and the caller would
+// take back the mail of a kernel that is on its way.)
+template <typename... Params, typename... Args>
+static int launch_wave(void (*kernel)(Params...), void *stream, Args... args)
+{
+    std::tuple<Params...> params(args...);
+    void *at[sizeof...(Params)];
+    std::apply([&](Params &...one) { int k = 0; ((at[k++] = (void *)&one), ...); }, params);
+    const hipError_t e = hipLaunchKernel((const void *)kernel, dim3(1), dim3(kWave), at, 0, (hipStream_t)stream);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return (int)e;
+}
+
 int launch_tell(void *ws, size_t offset, size_t bytes, DevMail *mail, uint32_t told, void *stream)
 {
-    hipLaunchKernelGGL(tell_kernel, dim3(1), dim3(kWave), 0, (hipStream_t)stream, (const uint32_t *)((char *)ws + offset), (int)(bytes / 4), mail, told);
-    return (int)hipGetLastError();
+    return launch_wave(tell_kernel, stream, (const uint32_t *)((char *)ws + offset), (int)(bytes / 4), mail, told);
 }
 
 __global__ __launch_bounds__(kWave) void detail_kernel(const KParams *__restrict__ Pp, const DevResult *__restrict__ res,
@@ -592,10 +605,8 @@ static detail_fn pick_detail(const KParams &kp)
 
 int launch_detail(const KParams &kp, void *ws, DevMail *mail, uint32_t told, int32_t known_period, uint64_t known_index, void *stream)
 {
-    hipLaunchKernelGGL(pick_detail(kp), dim3(1), dim3(kWave), 0, (hipStream_t)stream, (const KParams *)((char *)ws + kWsParamsOff),
-                       (const DevResult *)((char *)ws + kWsResultOff), (DevDetail *)((char *)ws + kWsDetailOff), mail, told, known_period,
-                       known_index);
-    return (int)hipGetLastError();
+    return launch_wave(pick_detail(kp), stream, (const KParams *)((char *)ws + kWsParamsOff), (const DevResult *)((char *)ws + kWsResultOff),
+                       (DevDetail *)((char *)ws + kWsDetailOff), mail, told, known_period, known_index);
 }
 
 }  // namespace tessel

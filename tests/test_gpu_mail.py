@@ -71,3 +71,32 @@ def test_one_question_after_another(gpu, k):  # noqa: F811
         a = _answer(g)
         assert a == _answer(g)
     assert a == _answer(once)
+
+
+def _hip_runtime():
+    """the HIP runtime this process has loaded"""
+    import ctypes as C
+    return C.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+
+
+def test_error_of_an_earlier_call(gpu):  # noqa: F811
+    """A call that failed on this thread before (a device number there is not) is no failure of the launch that sends the mail: the box
+    would go back while the kernel is on its way.  More questions than there are boxes, changing answers, a completion each."""
+    hip = _hip_runtime()
+    g, want = gpu.Problem(W.config3()), gpu.Problem(W.config3())
+
+    def behind_an_error(ask):
+        assert hip.hipSetDevice(1000) != 0
+        try:
+            return ask()
+        finally:
+            hip.hipGetLastError()
+
+    for k in range(40):
+        for p in (g, want):
+            p.reset()
+            p.eval_candidates(5003 * k, 400 + k)
+        assert behind_an_error(lambda: _answer(g)) == _answer(want), k
+        for p in (g, want):
+            p.search_completions(16, 2, 70 * k, 64)
+        assert behind_an_error(lambda: g.best_completion(16)["ordinal"]) == want.best_completion(16)["ordinal"], k
