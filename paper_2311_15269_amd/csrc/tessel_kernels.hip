@@ -2597,13 +2597,16 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
             }
             __syncthreads();
             // ---- a block a step
-            for (int s = 0; s < left; s++) {
+            // (Sixteen steps at a time while some candidate of the wave still has a schedule: under a tight cap whole waves are stuck after a
+            // few.  2^20 candidates of 250 blocks, all stuck: a call of 256 us without, 190 with it.  Looked at in every step it cost the others 8 %.)
+            for (int from = 0; from < left && __ballot(live && !fail) != 0; from += 16)
+            for (int s = from; s < min(left, from + 16); s++) {
                 uint32_t pick = ~0u;
 #pragma unroll
                 for (int d = 0; d < DM; d++) pick = min(pick, lds_load(L::least + (uint32_t)d * L::kRowB + lane4));
                 const bool placed = (int)pick >= 0;
                 fail = fail | !placed;                              // blocks left, none eligible: no schedule
-                if (!placed) continue;                              // (such a lane's state stays as it is, and it never places again)
+                if (!placed) continue;                              // (such a lane's state stays as it is to the end of the phase)
                 const uint32_t b = pick & 31u, low = pick & 0x7FE0u, low1 = low + 32u;
                 const uint32_t T0 = lds_load(L::types + 16u * b), T1 = lds_load(L::types + 16u * b + 4u), T2 = lds_load(L::types + 16u * b + 8u),
                                T3 = lds_load(L::types + 16u * b + 12u), U = lds_load(L::more + 4u * b);
@@ -2640,7 +2643,7 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
                 lds_store(L::least + dd, least_key((T0 & 0xF00u) * SY + L::offer + lane4, en, jits_new, max(M - ((int)fm_new >> 16), 0), mp));
             }
             __syncthreads();
-            if (phase == 1) break;
+            if (phase == 1 || __ballot(live && !fail) == 0) break;
             // ---- the R windows: the same blocks at the same micro-batches in every lane.  (Without the memory, which a whole
             // window leaves as it was: the deltas on a device sum to zero, and the window itself was scored against the cap.)
             auto slot_address = [&](uint32_t s) -> uint32_t {

@@ -70,3 +70,25 @@ def test_the_best_of_many_workgroups(gpu, n):  # noqa: F811
     g.search_completions(N, J, first, n)
     got = g.best_completion(N)
     assert (got["makespan"], got["ordinal"]) == (int(scores.min()), first + int(scores.argmin()))
+
+
+STUCK = {"all": (_chains([[2, 1, 1, 2, 0, 0, 2, 1, 1, 2]], 3, 8, 2, 612), 25, 6),
+         "most-waves": (_chains([[1, 0, 0, 1, 1, 0, 0, 1]], 2, 4, 2, 846), 25, 6)}
+
+
+@pytest.mark.parametrize("n", [1, 64, 65, 4100])
+@pytest.mark.parametrize("name", STUCK)
+def test_waves_that_get_stuck(gpu, name, n):  # noqa: F811
+    """whole waves without a schedule stop early; waves with one candidate that has one, and a last wave with lanes to spare, do not"""
+    from oracle import Oracle
+    prob, N, J = STUCK[name]
+    g, o = gpu.Problem(prob), Oracle(prob)
+    g.eval_candidates(0, 3000)
+    status, leads, orders = o.decode(g.best()["index"])
+    want, best, ordinal = o.completion_scores(leads, orders, N, 0, n, J)
+    assert (best is None) == (name == "all" or n < 100)
+    assert np.array_equal(g.score_completions(N, J, 0, n).cpu().numpy(), want)
+    g.search_completions(N, J, 0, n)
+    if best is not None:
+        got = g.best_completion(N)
+        assert (got["makespan"], got["ordinal"]) == (best, ordinal)
