@@ -1332,10 +1332,18 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
         if (d >= C.D) continue;
         const uint32_t mud = (uint32_t)((d < 4 ? mu.lo : mu.hi) >> (16 * (d & 3))) & 0xFFFFu;
         const uint32_t qd = (uint32_t)((d < 4 ? Q.lo : Q.hi) >> (16 * (d & 3))) & 0xFFFFu;
-        // blocks that ran before the window: leads as bytes times the device's memory deltas
-        uint32_t leads4 = (mud & 0xFFu) | ((mud & 0xFF00u) << 8);
-        leads4 = (leads4 | (leads4 << 4)) & 0x0F0F0F0Fu;
-        const int mem0 = __builtin_amdgcn_sdot4((int)leads4, (int)C.mpack[d], 0, false);
+        // blocks that ran before the window: leads as bytes times the device's memory deltas.  (One dot product; in the exhaustive
+        // spaces, which spill scalar registers around it, four products: 2,000,003 candidates of the factorial space of two
+        // micro-batches of 16 types on 8 devices 316 -> 271 us.)
+        int mem0 = 0;
+        if (sampled) {
+            uint32_t leads4 = (mud & 0xFFu) | ((mud & 0xFF00u) << 8);
+            leads4 = (leads4 | (leads4 << 4)) & 0x0F0F0F0Fu;
+            mem0 = __builtin_amdgcn_sdot4((int)leads4, (int)C.mpack[d], 0, false);
+        } else {
+#pragma unroll
+            for (int y = 0; y < kMaxLT; y++) mem0 += ((int)(C.mpack[d] << (24 - 8 * y)) >> 24) * (int)(mud >> (4 * y) & 15u);
+        }
         const uint32_t alive = nlen[d] >= 32 ? 0xFFFFFFFFu : (1u << nlen[d]) - 1u;
         rec_store(L.rec + (uint32_t)d * kRecDevStep + (uint32_t)lane * 4u, make_uint4(plo[d], phi[d], alive, qd | ((uint32_t)mem0 << 16)));
         if (nlen[d] > 0) HM |= 1u << (4 * d + ((plo[d] & 1u) | ((phi[d] & 1u) << 1)));
