@@ -1143,7 +1143,15 @@ __device__ __forceinline__ int period_fast(const FastConst<DM> &C, const FastLds
     return done ? T : -1;        // -1: no eigenvector within the sweeps allowed (the caller hands the candidate on)
 }
 
-// even bits of a 64-bit word, compacted (bit 2p -> bit p)
+// even bits of a word, compacted (bit 2p -> bit p)
+__device__ __forceinline__ uint32_t even_bits(uint32_t x)
+{
+    x &= 0x55555555u;
+    x = (x | (x >> 1)) & 0x33333333u;
+    x = (x | (x >> 2)) & 0x0F0F0F0Fu;
+    x = (x | (x >> 4)) & 0x00FF00FFu;
+    return (x | (x >> 8)) & 0x0000FFFFu;
+}
 __device__ __forceinline__ uint32_t even_bits(uint64_t x)
 {
     x &= 0x5555555555555555ull;
@@ -1195,36 +1203,46 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
             // bytes: 0x60 <= 0x80 - t + digit < 0xA0).
             const uint32_t c1 = C.ntd[d] > 0 ? NR : 0u, c2 = c1 + (C.ntd[d] > 1 ? NR : 0u), c3 = c2 + (C.ntd[d] > 2 ? NR : 0u);
             uint32_t tq = 0x808080u - (c1 | (c2 << 8) | (c3 << 16));
-            // The outcomes of the three comparisons are collected as they are, eight positions to a word: byte k holds "at or above
-            // threshold k" of the eight.  The symbol is their number, so its high bit is the second byte, its low bit the three
-            // bytes' exclusive or.  (Symbols counted and collected by pairs of bits took a count a position and 110 cycles a device
-            // to split into planes.)
-            uint32_t seen[4] = {0u, 0u, 0u, 0u};
-            auto pick = [&](uint32_t draw, uint32_t left, uint32_t &into, uint32_t at) {
+            // Outcomes of the three comparisons, one in bit 7 of each byte: the symbol is their number.
+            auto pick = [&](uint32_t draw, uint32_t left) -> uint32_t {
                 const uint32_t digit = (uint32_t)(((uint64_t)draw * (uint64_t)((left << 16) & 0xFFFFFFu)) >> 32);    // (draw * left) >> 16 as a
                                                                                                        // 24-bit high multiply (left <= 32)
-                const uint32_t ge = (mad24(digit, 0x010101u, tq) & 0x808080u) >> 7;
-                tq += ge ^ 0x010101u;                            // a threshold above the digit loses one block
-                into |= ge << at;
+                const uint32_t ge = mad24(digit, 0x010101u, tq) & 0x808080u;
+                tq += (ge >> 7) ^ 0x010101u;                     // a threshold above the digit loses one block
+                return ge;
             };
+            // With repair they are collected as they are, eight positions to a word: byte k holds "at or above threshold k" of the
+            // eight, so the symbols' high bits are the second byte, their low bits the three bytes' exclusive or.  (A count a position,
+            // and 110 cycles a device to split pairs of bits into planes, less.)  Without repair the symbols are counted and
+            // collected by pairs of bits, 16 to a word: together with the build step's other form (build_words) 1,000,003 scores of one or two
+            // micro-batches of 10 to 16 types on 5 to 8 devices take 0.96 to 0.98 of the time.
+            constexpr uint32_t kPer = MODE == 2 ? 8u : 16u;
+            uint32_t seen[32u / kPer] = {};
 #pragma unroll
-            for (int h = 0; h < 4; h++) {
-                const uint32_t from = 8u * (uint32_t)h, to = min(n, from + 8u);
+            for (uint32_t h = 0; h < 32u / kPer; h++) {
+                const uint32_t from = kPer * h, to = min(n, from + kPer);
+                auto collect = [&](uint32_t ge, uint32_t at) { seen[h] |= MODE == 2 ? (ge >> 7) << at : (uint32_t)__builtin_popcount(ge) << (2u * at); };
                 for (uint32_t pos = from; pos < to; pos += 2) {
                     const uint32_t word = stream_word(ka, kb, (kDrawOrdBase + 32u * (uint32_t)d + pos) >> 1);
-                    pick(word & 0xFFFFu, n - pos, seen[h], pos - from);
-                    if (pos + 1 < n) pick(word >> 16, n - pos - 1u, seen[h], pos + 1u - from);
+                    collect(pick(word & 0xFFFFu, n - pos), pos - from);
+                    if (pos + 1 < n) collect(pick(word >> 16, n - pos - 1u), pos + 1u - from);
                 }
             }
-            // (bytes 0 of the four words to one, bytes 1 likewise)
-            uint32_t low[4];
+            uint32_t lo, hi;
+            if constexpr (MODE == 2) {
+                // (bytes 0 of the four words to one, bytes 1 likewise)
+                uint32_t low[4];
 #pragma unroll
-            for (int h = 0; h < 4; h++) low[h] = seen[h] ^ (seen[h] >> 8) ^ (seen[h] >> 16);
-            auto bytes = [](uint32_t a, uint32_t b, uint32_t c, uint32_t e, uint32_t pair) -> uint32_t {
-                return __builtin_amdgcn_perm(__builtin_amdgcn_perm(e, c, pair), __builtin_amdgcn_perm(b, a, pair), 0x05040100u);
-            };
-            const uint32_t lo = bytes(low[0], low[1], low[2], low[3], 0x0C0C0400u);
-            const uint32_t hi = bytes(seen[0], seen[1], seen[2], seen[3], 0x0C0C0501u);
+                for (int h = 0; h < 4; h++) low[h] = seen[h] ^ (seen[h] >> 8) ^ (seen[h] >> 16);
+                auto bytes = [](uint32_t a, uint32_t b, uint32_t c, uint32_t e, uint32_t pair) -> uint32_t {
+                    return __builtin_amdgcn_perm(__builtin_amdgcn_perm(e, c, pair), __builtin_amdgcn_perm(b, a, pair), 0x05040100u);
+                };
+                lo = bytes(low[0], low[1], low[2], low[3], 0x0C0C0400u);
+                hi = bytes(seen[0], seen[1], seen[2], seen[3], 0x0C0C0501u);
+            } else {
+                lo = even_bits(seen[0]) | (even_bits(seen[1]) << 16);
+                hi = even_bits(seen[0] >> 1) | (even_bits(seen[1] >> 1) << 16);
+            }
             plo[d] = lo; phi[d] = hi; nlen[d] = (int)n;
         }
         if (C.has_fixed)
@@ -1396,19 +1414,25 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
             const uint32_t cand = a.z & gate, p = low_bit(cand);
             // its symbol, as two all-or-nothing masks
             const uint32_t ly = (uint32_t)__builtin_amdgcn_sbfe((int)a.x, p, 1), hy = (uint32_t)__builtin_amdgcn_sbfe((int)a.y, p, 1);
-            // c = d4 | (ly & 1) | (hy & 2)
-            const uint32_t c = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(ly, hy, 1u, 0xE4), 3u, d4, 0xEA);
+            // c = d4 | (ly & 1) | (hy & 2); as ly, hy are 0 or -1, also d4 - ly - 2 hy
+            uint32_t c;
+            if (repair) c = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(ly, hy, 1u, 0xE4), 3u, d4, 0xEA);
+            else asm("v_mad_i32_i24 %0, %1, -2, %2" : "=v"(c) : "v"(hy), "v"(d4 - ly));
             const uint32_t c4 = c << 2;
             const uint4 e = rec_load(c4);                      // (the table of the types starts the kernel's LDS, at address 0)
             // take the entry out; new head of the device.  (When the device is empty now the bit set below is
             // meaningless, and harmless: all its types are exhausted, and R never holds an exhausted type.)
-            // (The step's instructions are chosen by rate, tessel_common.h: masks from signs instead of compares and selects,
+            // (With repair the step's instructions are chosen by rate, tessel_common.h: masks from signs instead of compares and selects,
             // right shifts instead of bit fields, the entry's bit by subtraction.  With the decode's part: 2^26 candidates of
-            // 256 blocks on 8 devices 32.7 -> 32.0 ms, of 40 with two on all of four devices 6.03 -> 5.72.)
-            const uint32_t alive = __builtin_amdgcn_bitop3_b32(a.z, cand, 0u - cand, 0x70);        // a & ~(b & c)
+            // 256 blocks on 8 devices 32.7 -> 32.0 ms, of 40 with two on all of four devices 6.03 -> 5.72.  Without repair, where a wave
+            // ends with its last candidate and more masks are alive, they are fewer: build_begin has the figures.)
+            const uint32_t alive = repair ? (uint32_t)__builtin_amdgcn_bitop3_b32(a.z, cand, 0u - cand, 0x70) : a.z & ~(1u << p);      // 0x70: a & ~(b & c)
             const uint32_t p2 = low_bit(alive);
-            const uint32_t h2 = a.y >> (p2 & 31u);
-            const uint32_t c2 = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(a.x >> (p2 & 31u), h2 + h2, 1u, 0xE4), 3u, d4, 0xEA);
+            uint32_t c2;
+            if (repair) {
+                const uint32_t h2 = a.y >> (p2 & 31u);
+                c2 = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(a.x >> (p2 & 31u), h2 + h2, 1u, 0xE4), 3u, d4, 0xEA);
+            } else c2 = d4 + (__builtin_amdgcn_ubfe(a.x, p2, 1) | (__builtin_amdgcn_ubfe(a.y, p2, 1) << 1));
             const uint32_t hm_new = (HM & ~(15u << d4)) | (1u << c2);
             // one waiting micro-batch is consumed; the type stays runnable while another one waits and
             // entries of it remain; its consumer gets one more and becomes runnable
@@ -1420,9 +1444,9 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
             // exhausted: no entry of the type is left; it stays runnable only if entries are left and another
             // micro-batch waits.  (Masks, all ones: entries are left; another one waits.)
             const uint32_t some = (uint32_t)((int)(rest | (0u - rest)) >> 31), waits = (uint32_t)((int)(0u - more) >> 31);
-            uint32_t x_new = __builtin_amdgcn_bitop3_b32(X, onec, some, 0xF4);              // a | (b & ~c)
+            uint32_t x_new = repair ? (uint32_t)__builtin_amdgcn_bitop3_b32(X, onec, some, 0xF4) : X | (rest == 0 ? onec : 0u);        // 0xF4: a | (b & ~c)
             TESSEL_PIN(x_new);          // (the old X dies here: no second copy of the mask across the step)
-            const uint32_t stalled = __builtin_amdgcn_bitop3_b32(onec, some, waits, 0x70);
+            const uint32_t stalled = repair ? (uint32_t)__builtin_amdgcn_bitop3_b32(onec, some, waits, 0x70) : (rest == 0 || more == 0) ? onec : 0u;
             const uint32_t r_new = __builtin_amdgcn_bitop3_b32(R, stalled, e.y & ~x_new, 0xBA);      // (R & ~t) | z
             // the record's last word: waiting counts (16 bits) and the device's memory prefix (upper 16 bits,
             // signed); one sum updates both
