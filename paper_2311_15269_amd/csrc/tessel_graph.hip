@@ -782,6 +782,26 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
 #pragma unroll
                     for (int q = 0; q < 4; q++) device(min(d + q, D - 1), x[q], x[q] - old[q]);
                 }
+                if (NR <= 2u) {
+                    // (few values a ring: two rings at a time.  Fours of one ring, the same value up to four times, cost graphs of one
+                    // micro-batch a window 12 % of the kernel.)
+                    for (int r = 0; r < P.ntok; r += 2)
+                        for (uint32_t m = 0; m < NR; m++) {
+                            uint32_t x[2], old[2], base[2], kept[2];
+#pragma unroll
+                            for (int q = 0; q < 2; q++) {
+                                const uint32_t rows = G.ring[min(r + q, P.ntok - 1)];
+                                base[q] = st0 + ((rows & 0xFFFFu) + m) * SROW; kept[q] = st0 + ((rows >> 16) + m) * SROW;
+                                x[q] = time_load(base[q] + NR * SROW); old[q] = time_load(kept[q]);
+                            }
+#pragma unroll
+                            for (int q = 0; q < 2; q++) {
+                                const int rq = min(r + q, P.ntok - 1);
+                                ring(base[q], kept[q], (uint32_t)D + (uint32_t)rq * NR + m, m < in_flight(rq), x[q], x[q] - old[q]);
+                            }
+                        }
+                    return;
+                }
                 for (int r = 0; r < P.ntok; r++) {
                     const uint32_t rows = G.ring[r], base = st0 + (rows & 0xFFFFu) * SROW, kept = st0 + (rows >> 16) * SROW, lg = in_flight(r);
                     for (uint32_t m = 0; m < NR; m += 4) {

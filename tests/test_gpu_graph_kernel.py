@@ -114,3 +114,16 @@ def test_exhaustive_spaces_on_both_sides_of_the_line(gpu, prob, space, at):
     prob = dict(prob, space=space)
     count = gpu.Problem(prob).candidate_count()
     _compare(gpu, prob, int(count * at), 4000)
+
+
+@pytest.mark.parametrize("tries", ["1", "8"])
+@pytest.mark.parametrize("nr", [1, 2, 3])
+@pytest.mark.parametrize("prob", [lambda nr: fan(2, nr, 0), lambda nr: fan(3, nr, 0), lambda nr: fan(4, nr, 0), lambda nr: W.kshape_problem(nr, nr + 1),
+                                  lambda nr: W.diamond_problem(nr, nr + 1), lambda nr: vshape(9, nr, nr + 1), lambda nr: shared_block(9, nr, nr + 4)],
+                         ids=["fan2", "fan3", "fan4", "kshape", "diamond", "chain", "shared"])
+def test_values_of_a_window_boundary(gpu, monkeypatch, prob, nr, tries):
+    """one, an odd and an even number of rings, a device or two more than the reads go by, windows of one to three micro-batches;
+    with one sweep at first most periods are settled in the longer search"""
+    monkeypatch.setenv("TESSEL_DAG_TRIES", tries)
+    for space in ("sampled_repair", "sampled_strict"):
+        _compare(gpu, dict(prob(nr), space=space), 77, 1100)
