@@ -1931,20 +1931,14 @@ struct Tally {
     }
 };
 
-// What the pass over the list also does: it adds up the launch, its own records and those of the kernel before it, and
-// clears the list's counter and the histogram for the next launch (scores of every candidate: the latter alone).
-struct Finish {
-    DevResult *res;              // null: nothing of this
-    uint32_t *left_after;
-    BlockRec *range_recs;        // records of the kernel over the range; null: scores
-    int from_range;
-};
-
+// `from_range` < 0: scores the range.  Else the pass over the list, in the workspace `ws`, of the kernel before it in the launch; it also adds up the launch, its own records and the `from_range` of the kernel over the range
+// right in front of them, and clears the list's counter and the histogram for the next launch (scores of every candidate: the
+// latter alone).  (Addresses in the workspace are worked out where they are needed: as arguments of their own they were spilled
+// around the loop over candidates, 4 % of 331,776 scores of an exhaustive space.)
 template <int DM, int VM>
 __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__ Pp, uint64_t first, uint64_t count,
                                                      BlockRec *recs, int32_t *__restrict__ code_out,
-                                                     int32_t *__restrict__ peak_out, const uint64_t *__restrict__ list, const uint32_t *list_count,
-                                                     bool whole, uint32_t *far, int where, Finish fin)
+                                                     int32_t *__restrict__ peak_out, bool whole, uint32_t *far, int where, char *ws, int from_range)
 {
     const KParams &P = *Pp;
     extern __shared__ uint32_t lds[];
@@ -1955,14 +1949,13 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
     // the range, as far as the grid goes.  (The count is cleared by the last one that takes part; one that reads it
     // later sees a smaller number, and takes no part either way.)
     uint32_t parts = gridDim.x;
-    bool again = false;
-    if (list) {
-        const uint32_t listed = *list_count;
-        again = whole && listed > kWsListCap;
-        if (again) list = nullptr;
-        else {
+    bool listing = false;
+    if (from_range >= 0) {
+        const uint32_t listed = ((const DevResult *)(ws + kWsResultOff))->defer_count;
+        listing = !(whole && listed > kWsListCap);
+        if (listing) {
             count = min(listed, kWsListCap);
-            const uint32_t records = fin.range_recs ? (uint32_t)(fin.from_range + kWave - 1) / kWave : 0u;
+            const uint32_t records = (uint32_t)(from_range + kWave - 1) / kWave;
             parts = min(parts, max(max((uint32_t)((count + kWave - 1) / kWave), records), 1u));
             if (blockIdx.x >= parts) return;
         }
@@ -1999,7 +1992,7 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
 
     const uint64_t stride = (uint64_t)gridDim.x * kWave;
     for (uint64_t kk = (uint64_t)blockIdx.x * kWave + lane; kk < count; kk += stride) {
-        const uint64_t idx = list ? list[kk] : first + kk;
+        const uint64_t idx = listing ? ((const uint64_t *)(ws + kWsListOff))[kk] : first + kk;
         const uint64_t k = idx - first;
         int period, peak[DM];
         int status;
@@ -2024,8 +2017,8 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
 #pragma unroll
     for (int s = 0; s < kNumStatus; s++) a.cnt[s] = cnt[s];
     // (in a launch whose range this kernel scored again, the records of the kernel before it are void)
-    if (fin.range_recs && !again)
-        for (uint32_t r = blockIdx.x * kWave + (uint32_t)lane; r < (uint32_t)fin.from_range; r += parts * kWave) a.add(fin.range_recs[r]);
+    if (listing)
+        for (int r = (int)blockIdx.x * kWave + lane; r < from_range; r += (int)parts * kWave) a.add(recs[r - from_range]);
     if (recs) {
         a.fold();
         if (lane == 0) {
@@ -2037,9 +2030,9 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
             recs[blockIdx.x] = r;
         }
     }
-    if (!fin.res) return;
+    if (from_range < 0) return;
     // ---- the workgroup that comes last adds the records up
-    DevResult *res = fin.res;
+    DevResult *res = (DevResult *)(ws + kWsResultOff);
     if (parts > 1) {
         uint32_t before = 0;
         __threadfence();
@@ -2052,7 +2045,7 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
             a.fold();
         }
     }
-    fin.left_after[lane] = 0;
+    ((uint32_t *)(ws + kWsLeftOff))[lane] = 0;
     if (lane != 0) return;
     if (recs) {
         if (key_less(a.best, a.best_idx, res->period, res->index)) { res->period = a.best; res->index = a.best_idx; }
@@ -2071,7 +2064,7 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
 // The two instantiations for problems beyond the fast kernel's limits (16 and 32 devices) take as long to compile as
 // everything else in this file: tessel_wide.hip includes this file up to here and holds them, so that the two halves
 // build side by side.
-#define TESSEL_EVAL_KERNEL_ARGS const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *, bool, uint32_t *, int, Finish
+#define TESSEL_EVAL_KERNEL_ARGS const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, bool, uint32_t *, int, char *, int
 #ifdef TESSEL_WIDE_INSTANTIATIONS
 template __global__ void eval_kernel<16, 1>(TESSEL_EVAL_KERNEL_ARGS);
 template __global__ void eval_kernel<32, 1>(TESSEL_EVAL_KERNEL_ARGS);
@@ -2116,8 +2109,7 @@ __global__ void reset_kernel(DevResult *res, DevDetail *detail, uint32_t *left_a
 }
 
 // ------------------------------------------------------------------ launchers
-typedef void (*eval_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, const uint64_t *, const uint32_t *,
-                        bool, uint32_t *, int, Finish);
+typedef void (*eval_fn)(TESSEL_EVAL_KERNEL_ARGS);
 typedef void (*fast_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, int, int, uint64_t *, uint32_t *,
                         uint32_t, uint32_t *, uint32_t *, uint32_t, int, int, uint32_t *);
 
@@ -2348,9 +2340,8 @@ size_t eval_workspace_bytes(const KParams &kp, int num_cus, int max_blocks)
     return ring_offset(s, num_cus) + (own > list ? own : list);
 }
 
-static int launch_general(const KParams &kp, const KParams *kp_dev, uint64_t first, uint64_t count, int blocks, BlockRec *recs,
-                          int32_t *code, int32_t *peak, const uint64_t *list, const uint32_t *list_count, bool whole,
-                          uint32_t *far, const Finish &fin, hipStream_t st)
+static int launch_general(const KParams &kp, void *ws, uint64_t first, uint64_t count, int blocks, BlockRec *recs,
+                          int32_t *code, int32_t *peak, bool whole, uint32_t *far, int from_range, hipStream_t st)
 {
     const int where = far_mode(kp);
     if (where && !far) return (int)hipErrorInvalidValue;
@@ -2360,7 +2351,8 @@ static int launch_general(const KParams &kp, const KParams *kp_dev, uint64_t fir
         hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, st, kp_dev, first, count, recs, code, peak, list, list_count, whole, far, where, fin);
+    hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, st, (const KParams *)((char *)ws + kWsParamsOff), first, count, recs, code, peak, whole, far,
+                       where, (char *)ws, from_range);
     return (int)hipGetLastError();
 }
 
@@ -2384,7 +2376,7 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
     fast_fn ff = general ? nullptr : pick_fast(kp);
     const bool graph = !ff && kp.graph_ok && !general;
     if (!ff && !graph) {
-        int rc = launch_general(kp, kp_dev, first, count, blocks, recs, code, peak, nullptr, nullptr, false, behind, Finish{}, st);
+        int rc = launch_general(kp, ws, first, count, blocks, recs, code, peak, false, behind, -1, st);
         if (rc || !recs) return rc;
         hipLaunchKernelGGL(merge_kernel, dim3(1), dim3(kMergeThreads), 0, st, recs, blocks, res);
         return (int)hipGetLastError();
@@ -2402,9 +2394,8 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
         rc = (int)hipGetLastError();
     }
     if (rc) return rc;
-    const Finish fin = {res, left_after, recs, blocks};
-    return launch_general(kp, kp_dev, first, count, list_blocks, recs ? recs + blocks : nullptr, code, peak, list, &res->defer_count, graph,
-                          graph ? behind : nullptr, fin, st);
+    return launch_general(kp, ws, first, count, list_blocks, recs ? recs + blocks : nullptr, code, peak, graph, graph ? behind : nullptr,
+                          recs ? blocks : 0, st);
 }
 
 int launch_eval(const KParams &kp, uint64_t first, uint64_t count, void *ws, int num_cus, int max_blocks, void *stream, uint64_t max_piece)
