@@ -16,7 +16,7 @@ struct BlockRec {
     uint32_t n_evaluated;
     uint32_t n_sweeps;           // window sweeps spent on period computations
     uint32_t n_blocks;           // blocks placed by the build (fast kernel)
-    uint32_t n_blocks_high;      // (sums of records)
+    uint32_t n_high;             // (sums of records) bits of n_sweeps above 32 << 16 | those of n_blocks
 };
 
 constexpr uint32_t kDrawLeadBase = 0u;

@@ -264,6 +264,7 @@ constexpr int kDeferBlocks = 64;                                // grid of the g
 constexpr int kFirstPassTries = 2;                              // sweeps before a candidate queues for the longer search
 constexpr uint64_t kMaxPerLaunch = 1ull << 26;                  // candidates per pass of the kernels
 constexpr uint64_t kSafePerLaunch = 1ull << 20;                 // ... at which no list can overflow (<= both list capacities)
+constexpr int kMostTries = 64;                                  // (both can be set up to this for tests)
 constexpr int kRetryTries = 8;                                  // ... and before the general kernel gets it
 
 // queues between the phases of the fast kernel: three rings per wave behind the block records

@@ -901,7 +901,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
     if (lane == 0) {
         BlockRec rr;
         // (window sweeps and blocks placed are reported for the fast kernel only)
-        rr.period = best; rr.n_retried = nretry; rr.index = best_idx; rr.n_evaluated = nev; rr.n_sweeps = 0; rr.n_blocks = 0; rr.n_blocks_high = 0;
+        rr.period = best; rr.n_retried = nretry; rr.index = best_idx; rr.n_evaluated = nev; rr.n_sweeps = 0; rr.n_blocks = 0; rr.n_high = 0;
 #pragma unroll
         for (int s = 0; s < kNumStatus; s++) rr.n_status[s] = cnt[s];
         recs[blockIdx.x] = rr;

@@ -1874,7 +1874,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     }
     if (lane == 0) {
         BlockRec rr;
-        rr.period = best; rr.n_retried = nretry; rr.index = best_idx; rr.n_evaluated = nev; rr.n_sweeps = nsw; rr.n_blocks = nblocks; rr.n_blocks_high = 0;
+        rr.period = best; rr.n_retried = nretry; rr.index = best_idx; rr.n_evaluated = nev; rr.n_sweeps = nsw; rr.n_blocks = nblocks; rr.n_high = 0;
 #pragma unroll
         for (int s = 0; s < kNumStatus; s++) rr.n_status[s] = cnt[s];
         recs[blockIdx.x] = rr;
@@ -1893,7 +1893,10 @@ __host__ __device__ inline size_t far_words(const KParams &P, int where)
     return ((state + prog + 255) & ~(size_t)255) / 4;
 }
 
-// What one launch adds to the running best: the sum of records, a wave at a time.
+// What one launch adds to the running best: the sum of records, a wave at a time.  Candidates are counted in 32 bits (a launch has at
+// most 2^26), sweeps and blocks in 64, also in the record of a part of the launch.
+static_assert(kMaxPerLaunch <= 0xFFFFFFFFu, "candidates of a launch are counted in 32 bits");
+static_assert(((kMaxPerLaunch * 2 * kMostTries) >> 48) == 0 && ((kMaxPerLaunch * kMaxKW * kMaxNRW) >> 48) == 0, "BlockRec::n_high holds what is above 32 bits");
 struct Tally {
     int best;
     uint32_t nre, nev, cnt[kNumStatus];
@@ -1907,7 +1910,7 @@ struct Tally {
     __device__ __forceinline__ void add(const BlockRec &r)
     {
         if (key_less(r.period, r.index, best, best_idx)) { best = r.period; best_idx = r.index; }
-        nre += r.n_retried; nev += r.n_evaluated; nsw += r.n_sweeps; nbl += (uint64_t)r.n_blocks_high << 32 | r.n_blocks;
+        nre += r.n_retried; nev += r.n_evaluated; nsw += (uint64_t)(r.n_high >> 16) << 32 | r.n_sweeps; nbl += (uint64_t)(r.n_high & 0xFFFFu) << 32 | r.n_blocks;
 #pragma unroll
         for (int s = 0; s < kNumStatus; s++) cnt[s] += r.n_status[s];
     }
@@ -2024,7 +2027,7 @@ __global__ __launch_bounds__(kWave) void eval_kernel(const KParams *__restrict__
         if (lane == 0) {
             BlockRec r;
             r.period = a.best; r.n_retried = a.nre; r.index = a.best_idx; r.n_evaluated = a.nev; r.n_sweeps = (uint32_t)a.nsw;
-            r.n_blocks = (uint32_t)a.nbl; r.n_blocks_high = (uint32_t)(a.nbl >> 32);
+            r.n_blocks = (uint32_t)a.nbl; r.n_high = (uint32_t)(a.nsw >> 32) << 16 | (uint32_t)(a.nbl >> 32);
 #pragma unroll
             for (int s = 0; s < kNumStatus; s++) r.n_status[s] = a.cnt[s];
             recs[blockIdx.x] = r;

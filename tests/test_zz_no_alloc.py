@@ -99,3 +99,16 @@ def test_noalloc_refuses_what_it_cannot_hold(gpu):
     with pytest.raises(gpu.TesselError) as err:
         g2.eval_candidates_noalloc(500, 100)               # outside the 576 candidates of the space
     assert err.value.code == -8                            # TESSEL_E_RANGE
+
+
+def test_noalloc_counts_a_whole_launch(gpu):
+    """2^26 candidates on the hundred workgroups whose queues the buffer holds: two of them add up records with more than 2^32 blocks;
+    the counters are those of the whole grid"""
+    prob, n = W.config5(), 1 << 26
+    g, ref = gpu.Problem(prob), gpu.Problem(prob)
+    g.eval_candidates_noalloc(0, n)
+    ref.eval_candidates(0, n)
+    got, want = g.best(), ref.best()
+    assert want["n_blocks_placed"] > 1 << 33
+    for key in KEYS + ("n_blocks_placed", "n_window_sweeps"):
+        assert got[key] == want[key], key
