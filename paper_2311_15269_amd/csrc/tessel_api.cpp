@@ -44,6 +44,7 @@ struct tessel_problem {
     hipStream_t stream = nullptr;
     int last_hip = 0;
     bool force_general = false;         // TESSEL_FORCE_GENERAL=1: score with the general kernel only
+    bool mail = true;                   // TESSEL_MAIL=0 (test knob): results are copied, as where no box is free
     DevDetail detail;
     DevResult result;
     std::vector<int32_t> starts;        // least start times of the decoded candidate, by type * N_R + occurrence
@@ -805,6 +806,7 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
     }
     p->result.period = INT_MAX;
     { const char *fg = getenv("TESSEL_FORCE_GENERAL"); p->force_general = fg && fg[0] == '1'; }
+    { const char *ml = getenv("TESSEL_MAIL"); p->mail = !(ml && ml[0] == '0'); }
     if (p->force_general) kp.fast_ok = 0;
     // (TESSEL_FAR_MODE chooses between placements of the general kernel's state: it takes the problem then)
     p->graph.ok = 0;
@@ -1147,8 +1149,9 @@ class Mailbox {
 public:
     DevMail *box = nullptr;
     uint32_t told = 0;
-    Mailbox()
+    explicit Mailbox(bool use)
     {
+        if (!use) return;
         std::lock_guard<std::mutex> lock(g_mail_mutex);
         if (!g_mail && g_mail_used == 0) {
             void *mem = nullptr;
@@ -1211,7 +1214,7 @@ private:
 // candidate come back by mail, the record alone where it names the candidate this handle has.
 static int read_back(tessel_problem *p)
 {
-    Mailbox mail;
+    Mailbox mail(p->mail);
     int le = launch_detail(p->kp, p->ws, mail.box, mail.told, p->result.period, p->result.index, p->stream);
     if (mail.box) le = mail.wait(le, p->stream);
     if (le) return hip_fail(p, le);
@@ -1591,7 +1594,7 @@ extern "C" int tessel_best_completion(tessel_problem *p, tessel_schedule *out, u
     if (out->num_microbatches != p->comp.N) return TESSEL_E_INVALID_ARG;
     DevCompletion best;
     {
-        Mailbox mail;
+        Mailbox mail(p->mail);
         if (mail.box) {
             const int le = mail.wait(launch_tell(p->ws, kWsCompletionOff, sizeof best, mail.box, mail.told, p->stream), p->stream);
             if (le) return hip_fail(p, le);

@@ -100,3 +100,26 @@ def test_error_of_an_earlier_call(gpu):  # noqa: F811
         for p in (g, want):
             p.search_completions(16, 2, 70 * k, 64)
         assert behind_an_error(lambda: g.best_completion(16)["ordinal"]) == want.best_completion(16)["ordinal"], k
+
+
+@pytest.mark.parametrize("k", range(4))
+def test_copied_results(gpu, monkeypatch, k):  # noqa: F811
+    """a call that finds no box copies: the same answers, to questions asked twice, after a reset, with and without anything to report, and
+    the same completion"""
+    want = _walk(gpu, PROBLEMS[k], 3 + k)
+    monkeypatch.setenv("TESSEL_MAIL", "0")
+    assert _walk(gpu, PROBLEMS[k], 3 + k) == want
+    copied = gpu.Problem(W.config3())
+    monkeypatch.delenv("TESSEL_MAIL")
+    mailed = gpu.Problem(W.config3())
+    got = []
+    for g in (mailed, copied):
+        with pytest.raises(gpu.TesselError) as e:
+            g.best_completion(16)                                # nothing searched yet
+        assert e.value.code == -7
+        g.eval_candidates(100 * k, 400)
+        for _ in range(2):
+            g.search_completions(16, 2, 7 * k, 50 + k)
+            b = g.best_completion(16)
+            got.append((b["makespan"], b["ordinal"], b["start"].tolist()))
+    assert got[:2] == got[2:]
