@@ -342,7 +342,9 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
     gt.leads = at; at += (uint32_t)((kp.ntok + 3) / 4) * row;
     gt.lds_bytes = std::max(build_end, at);
     if (gt.lds_bytes > 64 * 1024 - row) return;             // (16-bit LDS addresses, eight-bit row numbers)
-    if (code_tables(p, gt, in, outs, span_max)) return;
+    const char *words = getenv("TESSEL_GRAPH_WORDS");        // test knob: 1 = a word a type for all problems, 0 = for none (left to the general kernel)
+    if (!(words && words[0] == '1') && code_tables(p, gt, in, outs, span_max)) return;
+    if (words && words[0] == '0') return;
     for (int r = 0; r < kp.ntok; r++) gt.head[r] = gt.wrow + (uint32_t)kp.ring_head[r] * row;
     auto type_at = [&](int d, int y) -> int { return (int)((y < 4 ? kp.type_of[d] >> (8 * y) : kp.type_of_hi[d] >> (8 * (y - 4))) & 0xFFu); };
     auto symbol_on = [&](int g, int d) -> int { for (int y = 0; y < kp.ntd[d]; y++) if (type_at(d, y) == g) return y; return 0; };

@@ -58,3 +58,13 @@ def test_many_rounds(gpu, prob):  # noqa: F811
     code, peak = whole.score_candidates(5, n)
     ok = code > 0
     assert int(ok.sum()) == a["n_feasible"] and int(code[ok].min()) == a["period"] and int((code == a["period"]).nonzero()[0][0]) + 5 == a["index"]
+
+
+@pytest.mark.parametrize("k", [0, 1, 3, 5, 9, 11, 13, 16, 17, 19, 24, 28])
+def test_against_words_by_type(gpu, monkeypatch, k):  # noqa: F811
+    """the same scores and peaks by masks by code and by a word a type, of full waves and a last one that is not"""
+    prob, n = SHAPES[k][0], 20011
+    codes = gpu.Problem(prob).score_candidates(1 << 20, n)
+    monkeypatch.setenv("TESSEL_GRAPH_WORDS", "1")
+    words = gpu.Problem(prob).score_candidates(1 << 20, n)
+    assert (codes[0] == words[0]).all() and (codes[1] == words[1]).all()
