@@ -16,7 +16,8 @@
  * handle's result calls then return TESSEL_E_WORKSPACE and its next scoring call starts a new search.
  * Every function returns TESSEL_OK (0) or a negative TESSEL_E_* code; nothing aborts or
  * throws across this boundary.  One problem handle must not be used from two host threads
- * at once; the only state shared between handles is the table of which handle a workspace belongs to.
+ * at once; the only state shared between handles is the table of which handle a workspace belongs to and the
+ * pinned memory through which results come back (tessel_best).
  */
 #ifndef TESSEL_H
 #define TESSEL_H
@@ -186,7 +187,8 @@ int  tessel_eval_candidates(tessel_problem *p, uint64_t first, uint64_t count,
  * (TESSEL_NOALLOC_SCRATCH_BYTES of device memory on every GPU the library runs on, held until the process
  * ends); the grid shrinks to the workgroups whose queues fit it (about a hundred of the 4096 the chip holds
  * for windows of 256 blocks, all of them for small windows), so this call can be much slower than the one above.  No hipMalloc, hipFree or other allocating call
- * is made.  Every call on a GPU shares that GPU's buffer: it serves one handle at a time like any workspace
+ * is made here.  (The first result call of a process allocates pinned host memory, see tessel_best; one made beforehand, on any handle, keeps that
+ * out of a section without allocations.)  Every call on a GPU shares that GPU's buffer: it serves one handle at a time like any workspace
  * (another handle's call ends this handle's search), and calls that overlap on one GPU, from different
  * streams or threads, race.  tessel_best, tessel_reset, tessel_best_candidate, tessel_complete_schedule and
  * the completion search apply as after tessel_eval_candidates.
@@ -202,7 +204,12 @@ int  tessel_score_candidates(tessel_problem *p, uint64_t first, uint64_t count,
                              int32_t *code_dev, int32_t *peak_dev,
                              void *workspace_dev, size_t workspace_bytes, void *hip_stream);
 
-/* Waits for the stream of the last call, then returns the running best.  NO_FEASIBLE when
+/* Returns the running best as it is when everything queued on the stream of the last call is done, which the call
+ * waits for.  (One kernel on that stream decodes the best candidate and stores it with the counters into pinned host memory, where
+ * this thread looks for it.  All work queued before is complete and visible by then; the kernel itself may take some microseconds more
+ * to end, so that a query of the stream right after the call may still say busy.  The first result call of a process
+ * allocates that memory, 34 KB by hipHostMalloc, held until the process ends; where that is refused, or all of its sixteen
+ * boxes are in use by other threads, the results are copied instead.)  NO_FEASIBLE when
  * nothing feasible has been scored (counters in *out are still valid).  If a launch left more
  * candidates to the general kernel than its list holds (2^20 of a range of up to 2^26: possible only
  * when most periods need more than the fast kernel's ten sweeps), every range scored since the last
@@ -326,8 +333,8 @@ int  tessel_search_run(const tessel_problem_desc *desc, tessel_search *io, void 
                        size_t workspace_bytes, void *hip_stream, tessel_problem **best_out);
 
 /* Measurement aid, not part of the method: launches a kernel of `blocks` x 256 threads in which
- * every lane runs `rounds` rounds of 32 independent full-rate 32-bit integer VALU operations
- * (add, unsigned max), asynchronously on `hip_stream`.  *lane_ops (host, may be NULL) receives the
+ * every lane runs `rounds` rounds of 32 independent 32-bit integer VALU operations
+ * (additions and unsigned maxima in equal parts, one operand a scalar register), asynchronously on `hip_stream`.  *lane_ops (host, may be NULL) receives the
  * number of lane operations of the launch; divided by the launch's duration it is the integer
  * VALU rate the chip sustains in practice, the second denominator beside the published peak.
  * out_dev: device buffer of blocks*256 uint32 (overwritten).  Errors: INVALID_ARG, WORKSPACE

@@ -323,9 +323,9 @@ struct GraphTab {
     uint32_t code_rows;          // rows of a device record
     uint32_t links[kMaxKW][4];   // block types, every chain from its last to its first: address of the word with the type's waiting
                                  // micro-batches | number of the dependency to its consumer << 16 | that joins different device sets << 24 |
-                                 // nobody consumes it << 25 | nobody produces for it << 26 | type << 27 (fixed leads);
-                                 // shift of that count | code << 8 | shift of the lead << 16; what a lead of 1 adds to the word
-                                 // with the lead and the memory, times the lead (the last two may be one word); unused
+                                 // nobody consumes it << 25 | nobody produces for it << 26; shift of that count | code << 8 | shift of
+                                 // the lead << 16; fixed lead << 28; memory delta at its place in the word with the leads and the
+                                 // memory (added once a micro-batch of the lead)
     uint32_t lead_edge[kMaxDeps];// the dependencies, consumers' types first: src | dst << 8 | number << 16 | joins different device
                                  // sets << 24 | first of its source << 25 | last of it << 26
     uint32_t edge[kMaxDeps];     // distinct dependencies: src | dst << 8 | shift of the field in dst's word << 16

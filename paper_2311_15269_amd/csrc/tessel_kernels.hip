@@ -2903,7 +2903,7 @@ static comp_fn pick_completion(const CompParams &cp, const CompMatrix &cm, size_
     const size_t behind = (((size_t)cp.npaths * cp.tok_ring * kWave * 2 + 255) & ~(size_t)255) + ((replay + 15) & ~(size_t)15);
     const size_t rows = cp.D <= 4 ? (most <= 2 ? ChainRows<4, 2>::token : ChainRows<4, 4>::token) : (most <= 2 ? ChainRows<8, 2>::token : ChainRows<8, 4>::token);
     lds = rows + behind;
-    if (!chain || most > 4) {
+    if (!chain) {
         lds = (size_t)kCompParamWords * 4 + (size_t)((cp.npaths * cp.tok_ring + 2 * cp.D + cp.K + 1 + 1) / 2 * 2) * kWave * 2;
         return complete_kernel;
     }
@@ -2911,9 +2911,11 @@ static comp_fn pick_completion(const CompParams &cp, const CompMatrix &cm, size_
     return most <= 2 ? complete_chain_kernel<8, 2> : complete_chain_kernel<8, 4>;
 }
 
-// Problems are taken up to 64 KB of parameters, 16-bit state, a key a type and the windows' words.  (What passes has rings of 320 rows at
-// most, five chains of which one has 25 types or more: with 384 and the 30 types that takes on 8 devices the sum is above it.  So the rows
-// of the chain kernel, 16 KB, have room behind 40.)
+// Problems are taken up to 64 KB of parameters, 16-bit state, a key a type and the windows' words.  (The kernels need less: the last two are
+// those of an earlier one, and what it refused is still refused.  Only graphs and blocks on several devices come near, with a ring of 16
+// rows for every consumed type; rings of chains have at most 16 rows too, the next power of two from twice the micro-batches of a window on,
+// and there are at most eight.)
+static_assert(ChainRows<8, 4>::token + 8 * 16 * kWave * 2 + kMaxSeq * 4 <= kCompLds && 2 * kMaxNR <= 16, "LDS of the completion kernel for chains");
 bool completion_fits(const CompParams &cp, const CompMatrix &cm)
 {
     const size_t replay = cm.nin > 0 ? (size_t)(kMatIn + kMatOut + cm.nout * kMatIn) * 4 : (size_t)cp.nseq * 4;
