@@ -20,8 +20,11 @@
 namespace tessel {
 
 // ------------------------------------------------------------------ mail
-// Words to pinned host memory: written through to it one by one (system scope), the last one when all others have arrived.
-__device__ __forceinline__ void mail_word(uint32_t *to, uint32_t v) { __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+// Words to pinned host memory: written through to it one by one (system scope), the last one when all others have arrived.  What goes to the
+// workspace is written through too: the caller may hand that memory on once it has the mail, before the kernel has ended and its
+// L2 is written back.
+template <typename T>
+__device__ __forceinline__ void mail_word(T *to, T v) { __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
 __device__ __forceinline__ void mail_words(uint32_t *to, const void *from, int words)
 {
     for (int w = threadIdx.x; w < words; w += kWave) mail_word(to + w, ((const uint32_t *)from)[w]);
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(kWave) void detail_kernel(const KParams *__restrict
         const int lo = y & 2u ? b : a, hi = y & 2u ? d : c;
         mem += y & 4u ? hi : lo;
         peak = max(peak, mem);
-        out->orders[dev][len++] = (uint8_t)type_at(y);
+        mail_word(&out->orders[dev][len++], (uint8_t)type_at(y));
     };
     while (placed < total) {
         // the types whose producers are all ahead
@@ -286,9 +289,9 @@ __global__ __launch_bounds__(kWave) void detail_kernel(const KParams *__restrict
     }
     if (peak == INT_MIN) peak = 0;                               // a device without blocks
     if (status == kOk && __ballot(here && peak > P.M) != 0) status = kMem;
-    if (lane < kMaxDW) { out->peak[lane] = here ? peak : 0; out->order_len[lane] = len; }
-    if (lane < K) out->leads[lane] = (int)lead[lane];
-    if (lane == 0) { out->status = status; out->index = idx; }
+    if (lane < kMaxDW) { mail_word(&out->peak[lane], here ? peak : 0); mail_word(&out->order_len[lane], len); }
+    if (lane < K) mail_word(&out->leads[lane], (int)lead[lane]);
+    if (lane == 0) { mail_word(&out->status, status); mail_word(&out->index, idx); }
     __threadfence();                                             // (read back below by other lanes)
     mail_stored(mail, told, res, out, true);
 }
@@ -566,7 +569,7 @@ __global__ __launch_bounds__(kWave) void detail_lanes_kernel(const KParams *__re
     __syncthreads();
     // to the workspace, and to the host
     const int words = 4 + 2 * kMaxDW + kMaxKW + D * kMaxPos / 4;
-    for (int w = lane; w < words; w += kWave) ((uint32_t *)out)[w] = det[w];
+    for (int w = lane; w < words; w += kWave) mail_word((uint32_t *)out + w, det[w]);
     if (mail) {
         mail_words(mail->words, res, sizeof(DevResult) / 4);
         for (int w = lane; w < words; w += kWave) mail_word(mail->words + kMailDetail + w, det[w]);
