@@ -17,7 +17,10 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_INT32_OPS = 256 * 64 * 2.4e9 / 1e12      # T int32 lane-ops/s: 256 CUs x 64 lanes x 2.4 GHz, full-rate VALU ops
+PEAK_INT32_OPS = 256 * 64 * 2.4e9 / 1e12      # T int32 lane-ops/s: 256 CUs x 64 lanes x 2.4 GHz, an instruction of a wave every four cycles
+# Rates sustained by chains of one instruction, T lane-ops/s (profiles/instruction_rates.md): adds, bitwise operations and right shifts of vector
+# registers; left shifts, minima, maxima, compares, selects, multiplies, bit fields
+FASTER_OPS, SLOWER_OPS = 58.0, 37.7
 PEAK_LDS_OPS = 256 * 32 * 2.4e9 / 1e12        # T 32-bit LDS lane accesses/s: 256 CUs x 32 banks x 2.4 GHz
 COUNTERS_MD = os.path.join(ROOT, "profiles", "eval_fast_kernel_cfg5_counters.md")
 
@@ -37,6 +40,7 @@ def profiled_traffic():
 
 
 DECODE_OPS, BUILD_OPS, SWEEP_OPS = 17, 34, 2   # per block: see algorithmic_ops
+DECODE_FASTER, BUILD_FASTER, SWEEP_FASTER = 11, 21, 1     # ... of which some instruction of the faster class does so many
 
 
 def algorithmic_ops(prob, n_candidates, n_blocks_placed, n_sweeps):
@@ -46,6 +50,14 @@ def algorithmic_ops(prob, n_candidates, n_blocks_placed, n_sweeps):
     (one max, one add) per block and executed window sweep."""
     n = prob["K"] * prob["NR"]
     return n_candidates * n * DECODE_OPS + n_blocks_placed * BUILD_OPS + n_sweeps * n * SWEEP_OPS
+
+
+def peak_of_the_mix(prob, n_candidates, n_blocks_placed, n_sweeps):
+    """T operations/s that the chip's instruction rates allow for the operations algorithmic_ops counts, each in the faster class if it can be"""
+    n = prob["K"] * prob["NR"]
+    ops = algorithmic_ops(prob, n_candidates, n_blocks_placed, n_sweeps)
+    faster = n_candidates * n * DECODE_FASTER + n_blocks_placed * BUILD_FASTER + n_sweeps * n * SWEEP_FASTER
+    return ops / (faster / FASTER_OPS + (ops - faster) / SLOWER_OPS)
 
 
 def host_threads():
@@ -179,6 +191,7 @@ def main():
                "blocks_scheduled_per_s": rate * blocks,
                "roofline": {"bound": "alu", "achieved": ops * rate / 1e12, "peak": PEAK_INT32_OPS, "unit": "Tint32op/s",
                             "frac": ops * rate / 1e12 / PEAK_INT32_OPS, "traffic": None, "kernel": "complete_chain_kernel<8, 4>",
+                            "peak_is": "nominal rate of the slower class (maxima, compares, shifts left), to which most of the operations belong",
                             "algorithmic_ops_per_candidate": ops,
                             "limited_by": "latency: every scheduled block of the greedy phases is a chain of dependent per-lane "
                                           "decisions through LDS, at two waves per SIMD "
@@ -235,8 +248,9 @@ def main():
     ops_per_launch = algorithmic_ops(prob, chunk, blocks_per_cand * chunk, sweeps_per_cand * chunk)
     ops_whole_window = algorithmic_ops(prob, chunk, total_blocks * chunk, sweeps_per_cand * chunk)
     achieved = ops_per_launch / avg_launch_s / 1e12
+    peak = peak_of_the_mix(prob, chunk, blocks_per_cand * chunk, sweeps_per_cand * chunk)
 
-    # practical ceiling: independent full-rate integer adds/maxes on every lane of the chip
+    # what the slower class of instructions sustains in this run: independent adds and maxima of scalar registers on every lane
     from paper_2311_15269_amd.binding import alu_probe
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
     probe_ops, probe_out = alu_probe(n_cu * 16, 256)
@@ -263,15 +277,17 @@ def main():
         "result": {"best_period": best["period"], "best_index": best["index"], "lower_bound": best["lower_bound"],
                    "peak_mem": best["peak"], "n_feasible": best["n_feasible"], "n_reject": best["n_reject"],
                    "makespan_%d_microbatches" % N: sched["makespan"], "windows": sched["num_windows"]},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_INT32_OPS, "unit": "Tint32op/s",
-                     "frac": achieved / PEAK_INT32_OPS,
-                     "peak_measured": peak_measured, "frac_of_measured": achieved / peak_measured,
+        "roofline": {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "Tint32op/s",
+                     "frac": achieved / peak,
+                     "peak_is": "the counted operations at the rates of their instructions, %.0f and %.1f T/s" % (FASTER_OPS, SLOWER_OPS),
+                     "slower_class_nominal": PEAK_INT32_OPS, "slower_class_measured": peak_measured,
                      "traffic": traffic if chunk == 1 << 26 else None, "traffic_measured_at_commit": traffic_commit,
                      "kernel": "eval_fast_kernel<8, 16, 2, false>", "avg_launch_ms": avg_launch_s * 1e3,
                      "algorithmic_ops_per_candidate": ops_per_launch / chunk,
                      "blocks_placed_per_candidate": blocks_per_cand,
                      "window_sweeps_per_candidate": sweeps_per_cand,
-                     "frac_if_every_candidate_priced_at_the_whole_window": ops_whole_window / avg_launch_s / 1e12 / PEAK_INT32_OPS},
+                     "frac_if_every_candidate_priced_at_the_whole_window":
+                         ops_whole_window / avg_launch_s / 1e12 / peak_of_the_mix(prob, chunk, total_blocks * chunk, sweeps_per_cand * chunk)},
     }
 
     if not args.no_cpu_baseline:

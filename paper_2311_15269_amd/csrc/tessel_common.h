@@ -30,9 +30,9 @@ __device__ __forceinline__ bool key_less(int pa, uint64_t ia, int pb, uint64_t i
 }
 
 // Rates of this chip, measured with independent chains in all waves of a SIMD (T lane-operations/s of the chip): add, sub, and, or, xor, right
-// shifts and bitop3 on vector registers, literals and small constants run at 60; left shifts, minimum and maximum, compares and selects,
-// bit-field and three-operand instructions, multiplies (the 32-bit ones too), and anything that reads a scalar
-// register, a part of a word or another lane at 35.
+// shifts and bitop3 on vector registers, literals and small constants run at 58 (53 to 69); left shifts, minimum and maximum, compares and
+// selects, bit-field and three-operand instructions, multiplies (the 32-bit ones too), and anything that reads a scalar
+// register, a part of a word or another lane at 37.7.  (Program and table: profiles/instruction_rates.md.)
 __device__ __forceinline__ uint32_t bfi(uint32_t sel, uint32_t a, uint32_t b) { return __builtin_amdgcn_bitop3_b32(sel, a, b, 0xCA); }
 
 // position of the lowest set bit; all ones for 0, which "& 28", shift counts and bit-field offsets (all of them use the

@@ -2959,10 +2959,10 @@ int launch_completion_reset(void *ws, void *stream)
     return (int)hipGetLastError();
 }
 
-// ------------------------------------------------------------------ achievable VALU rate
+// ------------------------------------------------------------------ a rate of the VALU
 // Sixteen independent accumulators per lane, one add and one unsigned max each per round: 32
-// full-rate integer VALU instructions per round with no dependency closer than 16 instructions.
-// What this kernel sustains is the practical ceiling the scoring kernels are compared with.
+// integer VALU instructions per round with no dependency closer than 16 instructions.  One operand of each is a scalar
+// register: both are of the slower class (tessel_common.h), and what this kernel sustains, 38 T lane-operations/s, is that class's rate.
 constexpr int kProbeAcc = 16;
 
 __global__ __launch_bounds__(256) void alu_probe_kernel(uint32_t *out, int rounds, uint32_t inc, uint32_t floor_)
