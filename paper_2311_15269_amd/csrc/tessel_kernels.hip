@@ -2499,7 +2499,7 @@ int eval_blocks_that_fit(const KParams &kp, int num_cus, size_t bytes)
 // keys of all types, which were kept in LDS before and of which a step changed up to five: 115 vector instructions a step now.
 // Bound by the steps' own chain at two waves a SIMD (LDS: 17.7 KB a wave for 8 devices and 32 types): five rounds of LDS reads with 115
 // vector instructions between them, which issue for half of the time.  2^20 candidates of 64 micro-batches on 8 devices, as a call:
-// 2.47 -> 1.42 ms; 41 000 of 40 on 7 devices: 326 -> 202 us.
+// 2.47 -> 1.38 ms; 41 000 of 40 on 7 devices: 326 -> 202 us.
 template <int DM, int SY>
 struct ChainRows {
     static constexpr uint32_t kRowB = kWave * 4u;
@@ -2528,6 +2528,7 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
     const uint32_t replay = L::token + ((ring_rows * (uint32_t)(kWave * 2) + 255u) & ~255u);      // words of the windows' blocks (no matrix)
     const int nin = cmg->nin, nout = cmg->nout;
     // ---- tables, a type a lane (the parameter block is read from a copy behind the tables)
+    uint32_t my_lead = 0, my_more = 0;
     {
         uint32_t *copy = lds + L::rows / 4;
         for (int w = lane; w < (int)(sizeof(CompParams) / 4); w += kWave) copy[w] = ((const uint32_t *)cpg)[w];
@@ -2546,8 +2547,9 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
             lds[L::types / 4 + 4 * i + 1] = (uint32_t)cp.t[i] | (uint32_t)cp.m[i] << 16;
             lds[L::types / 4 + 4 * i + 2] = offer_of(i) | (c >= 0 ? offer_of(c) : L::ones) << 16;
             lds[L::types / 4 + 4 * i + 3] = (uint32_t)max(c, 0) | (c >= 0 ? device_of(c) << 8 | 8u * symbol_of(c) << 16 : 0u) | 8u * y << 24 | (a >= 0 ? 1u << 30 : 0u);
-            // (how many micro-batches the phase has of the type, times 32, comes in with the phase)
-            lds[L::more / 4 + i] = (a >= 0 ? offer_of(a) : L::ones) | (c >= 0 ? (uint32_t)max((int)cp.m[c], 0) : 0u);
+            // (goes to `more` when a phase starts, with the micro-batches the phase has of the type, times 32)
+            my_more = (a >= 0 ? offer_of(a) : L::ones) | (c >= 0 ? (uint32_t)max((int)cp.m[c], 0) : 0u);
+            my_lead = (uint32_t)cp.lead[i];
             atomicOr(&lds[L::mpos / 4 + d], (uint32_t)max((int)cp.m[i], 0) << (8u * y));
             // by code: type, lead, no producer, its micro-batch after the windows is there already, a type
             lds[L::init / 4 + d * SY + y] = (uint32_t)i | (uint32_t)cp.lead[i] << 8 | (a < 0 ? 1u << 16 : 0u) |
@@ -2564,6 +2566,14 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
         __syncthreads();
     }
     auto uniform_word = [&](uint32_t a) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_load(a)); };
+    // What the start of a phase goes by, a word a lane: by code, by type, by device.  (A phase visits the codes that block types have.  All of a
+    // device's codes with their words read from LDS one by one: 1 to 4 us of a call of 20 us for problems with fewer types than that.)
+    const uint32_t by_code = lane < DM * SY ? lds_load(L::init + lane4) : 0u, by_type = lane < K ? lds_load(L::types + 4u * lane4) : 0u,
+                   by_dev = lane < DM ? lds_load(L::mpos + lane4) : 0u;
+    auto word_of = [](uint32_t words, uint32_t of) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)words, (int)of); };
+    const uint32_t codes = (uint32_t)__ballot(by_code != 0u);
+    for (uint32_t k = 0; k < (uint32_t)(DM * SY); k++) lds_store(L::offer + k * L::kRowB + lane4, ~0u);
+    lds_store(L::ones + lane4, ~0u);
     int best = INT_MAX;
     uint64_t best_ord = 0;
     const uint64_t stride = (uint64_t)gridDim.x * kWave;
@@ -2578,7 +2588,6 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
         auto jitter = [&](uint32_t n) -> uint32_t { return __umul24(stream_draw16(ka, kb, n), jmul) >> 16; };
         for (uint32_t s = 0; s < ring_rows; s++) lds_store16(L::token + s * (kWave * 2u) + lane2, 0u);
         for (int d = 0; d < DM; d++) { lds_store(L::dev + (uint32_t)d * L::kRowB + lane4, 0u); lds_store(L::least + (uint32_t)d * L::kRowB + lane4, ~0u); }
-        lds_store(L::ones + lane4, ~0u);
         bool fail = false;
         // the smallest key of a device whose types' offers are at `at`: free time, jitters, memory left (not below 0)
         auto least_key = [&](uint32_t at, uint32_t fr, uint32_t jits, int room, uint32_t mp) -> uint32_t {
@@ -2594,32 +2603,29 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
         for (int phase = 0; phase < 2; phase++) {
             // ---- what every type offers at first: warm-up from micro-batch 0, cool-down from where the windows end
             int left = 0;                                           // blocks of this phase
-            for (int d = 0; d < D; d++) {
+            if (lane < K) lds_store(L::more + lane4, my_more | (phase ? (uint32_t)N : my_lead) << 21);
+            for (uint32_t rest = codes; rest;) {
+                const uint32_t d = (uint32_t)__builtin_ctz(rest) / SY, mine = rest >> (d * SY) & ((1u << SY) - 1u), dd = d * L::kRowB + lane4;
                 uint32_t jits = 0;
-                const uint32_t dd = (uint32_t)d * L::kRowB + lane4;
-                for (uint32_t y = 0; y < (uint32_t)SY; y++) {
-                    const uint32_t I = uniform_word(L::init + ((uint32_t)d * SY + y) * 4u);
+                rest ^= mine << (d * SY);
+                for (uint32_t y = 0; mine >> y; y++) {              // (a device's symbols start at 0)
+                    const uint32_t I = word_of(by_code, d * SY + y);
                     const uint32_t id = I & 31u, lead = I >> 8 & 255u, mu = phase ? lead + (uint32_t)(NR * R) : 0u, hi = phase ? (uint32_t)N : lead;
                     uint32_t o = ~0u;
-                    if ((I >> 18 & 1u) && mu < hi) {
+                    if (mu < hi) {
                         left += (int)(hi - mu);
                         const uint32_t j = jitter(id * (uint32_t)N + mu);
                         jits |= j << (8u * y);
                         const bool there = I >> (phase ? 17 : 16) & 1u;
-                        const uint32_t tok = uniform_word(L::types + 16u * id) >> 16;
-                        const uint32_t from = I >> 16 & 1u ? 0u : lds_load16(tok + (mu << 7 & tmask) + lane2);
+                        const uint32_t from = I >> 16 & 1u ? 0u : lds_load16((word_of(by_type, id) >> 16) + (mu << 7 & tmask) + lane2);
                         o = (there ? (from + j) << 15 : 0x80000000u) | mu << 5 | id;
                     }
-                    if (I >> 18 & 1u) {
-                        const uint32_t a = L::more + 4u * id, was = uniform_word(a);
-                        if (lane == 0) lds_store(a, (was & 0xFFFFu) | hi << 21);
-                    }
-                    lds_store(L::offer + ((uint32_t)d * SY + y) * L::kRowB + lane4, o);
+                    lds_store(L::offer + (d * SY + y) * L::kRowB + lane4, o);
                 }
                 lds_store(L::jit + dd, jits);
                 const uint32_t fm = lds_load(L::dev + dd);
-                lds_store(L::least + dd, least_key(L::offer + (uint32_t)d * SY * L::kRowB + lane4, fm & 0xFFFFu, jits, max(M - ((int)fm >> 16), 0),
-                                                   uniform_word(L::mpos + 4u * (uint32_t)d)));
+                lds_store(L::least + dd, least_key(L::offer + d * SY * L::kRowB + lane4, fm & 0xFFFFu, jits, max(M - ((int)fm >> 16), 0),
+                                                   word_of(by_dev, d)));
             }
             __syncthreads();
             // ---- a block a step

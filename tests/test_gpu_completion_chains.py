@@ -31,6 +31,9 @@ CASES = {
     "8dev-8chains": (_chains([[k, (k + 3) % 8, (k + 3) % 8, k] for k in range(8)], 8, 2, 5, 6), 19, 63),
     "some-without-schedule": (_chains([[1, 4, 0, 0, 4, 1], [3, 3, 3, 3], [0, 2, 1, 1, 2, 0]], 5, 3, 3, 271), 25, 6),
     "no-schedule": (_chains([[1, 0, 1, 1, 0, 1]], 2, 3, 2, 178), 25, 6),
+    "8dev-few-types": (_chains([[6], [1, 1]], 8, 3, 4, 7), 21, 5),
+    "8dev-idle-between": (_chains([[7, 2, 2, 7], [2, 5, 2]], 8, 4, 4, 8), 26, 11),
+    "4dev-idle-first": (_chains([[3, 1, 1, 3]], 4, 2, 3, 9), 18, 2),
     "longest": (W.xshape_problem(4, 1, 2, 2, 4), 1023, 6),
 }
 
