@@ -466,6 +466,31 @@ static void fill_ranked(const tessel_problem &p, uint64_t *orders, uint32_t *lea
     }
 }
 
+// The pairs of devices that a dependency joins (KParams::npairs), their tables behind the others in the `room` that is left.
+static void list_pairs(tessel_problem &p, size_t room)
+{
+    KParams &kp = p.kp;
+    kp.npairs = 0;
+    kp.pair_words = kp.pair_bits = 0;
+    bool joined[kMaxD][kMaxD] = {};
+    for (int g = 0; g < kp.K; g++)
+        if (kp.pred[g] >= 0) {
+            const int a = __builtin_ctz(p.mask[kp.pred[g]]), b = __builtin_ctz(p.mask[g]);
+            if (a != b) joined[std::min(a, b)][std::max(a, b)] = true;
+        }
+    uint64_t words = 0, bits = 0;
+    for (int d = 0; d < kp.D; d++)
+        for (int e = d + 1; e < kp.D; e++) {
+            const uint64_t both = kp.cdev[d] * kp.cdev[e];          // (16,384 orders each at most)
+            if (!joined[d][e] || both <= 1) continue;
+            kp.pair_of[kp.npairs][0] = (uint8_t)d; kp.pair_of[kp.npairs][1] = (uint8_t)e;
+            kp.pair_at[kp.npairs++] = (uint32_t)words;
+            words += (both + 63) / 64 * 2; bits += both;
+            if (words * 4 > room) { kp.npairs = 0; return; }
+        }
+    kp.pair_words = (uint32_t)words; kp.pair_bits = (uint32_t)bits; kp.pair_room = (uint32_t)(room / 4);
+}
+
 extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_problem **out)
 {
     if (!desc || !out) return TESSEL_E_INVALID_ARG;
@@ -833,6 +858,7 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
         if (kp.ranked) {
             fill_ranked(*p, (uint64_t *)(p->tables.data() + p->table_at[2]), (uint32_t *)(p->tables.data() + p->table_at[3]));
             for (int d = 0; d < kp.D; d++) kp.recip[d] = kp.cdev[d] > 1 ? (uint32_t)(((uint64_t)1 << 32) / kp.cdev[d]) : 0u;
+            if (!kp.fast_tp) list_pairs(*p, kWsTablesMax - total);
         }
     }
     *out = p;
@@ -913,6 +939,7 @@ static int bind_workspace(tessel_problem *p, void *ws, size_t bytes, hipStream_t
         p->kp.wtab = (const uint64_t *)(base + p->table_at[1]);
         p->kp.orders = (const uint64_t *)(base + p->table_at[2]);
         p->kp.leadrows = (const uint32_t *)(base + p->table_at[3]);
+        p->kp.pair_tab = (uint32_t *)(base + ((p->tables.size() + 255) & ~(size_t)255));
     }
     hipError_t pe = hipMemcpyAsync((char *)ws + kWsParamsOff, &p->kp, sizeof(KParams), hipMemcpyHostToDevice, st);
     if (pe != hipSuccess) return hip_fail(p, (int)pe);

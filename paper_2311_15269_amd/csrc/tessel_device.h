@@ -61,6 +61,7 @@ constexpr int kLeadRow = 12;      // words of one row of KParams::leadrows
 // save no more.  Leads: 3,675 cost a handle 0.1 ms and save 90 us and more of every call (two chains on four devices, windows of 5);
 // 10,976 cost 0.3 ms and save 16 us of a call over 64 to 5,000 candidates.
 constexpr uint32_t kRankedOrders = 16384, kRankedLeads = 4096;
+constexpr int kMaxPairs = 28;            // pairs of devices of the fast kernel's problems
 constexpr uint32_t kNoRing = 0xFFFFu;   // no ring of end times (KParams::tokbase)
 constexpr int kNumStatus = 6;
 constexpr int kWave = 64;
@@ -166,6 +167,14 @@ struct KParams {
     const uint64_t *orders;      // low plane | high plane << 32, in rank order
     const uint32_t *leadrows;    // kLeadRow words a vector: leads by code (4 bits each, 4 words), micro-batches waiting (4), types that
                                  // may run (1), three unused
+    // ... and the pairs of devices that a dependency joins: by pair two bits sets of which orders go together (order_pairs_kernel).  Both
+    // devices of the pair, the lower one first; where its bits start in a lead vector's table (words); words and bits of such a table;
+    // words that the workspace has for tables
+    int32_t  npairs;             // 0: no tables
+    uint8_t  pair_of[kMaxPairs][2];
+    uint32_t pair_at[kMaxPairs];
+    uint32_t pair_words, pair_bits, pair_room;
+    uint32_t *pair_tab;
 };
 
 // Running best + counters of one search; lives at the start of the caller's workspace.

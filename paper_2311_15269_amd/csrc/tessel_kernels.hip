@@ -1143,6 +1143,16 @@ __device__ __forceinline__ int period_fast(const FastConst<DM> &C, const FastLds
     return done ? T : -1;        // -1: no eigenvector within the sweeps allowed (the caller hands the candidate on)
 }
 
+// the quotient by n of a number below 2^32, of which the remainder stays: `inv` = floor(2^32 / n), 0 for n = 1
+__device__ __forceinline__ uint32_t take_digit(uint32_t &x, uint32_t n, uint32_t inv)
+{
+    if (inv == 0) { const uint32_t q = x; x = 0; return q; }
+    uint32_t q = __umulhi(x, inv);                            // the true one or one less
+    x -= q * n;
+    if (x >= n) { x -= n; q++; }
+    return q;
+}
+
 // even bits of a word, compacted (bit 2p -> bit p)
 __device__ __forceinline__ uint32_t even_bits(uint32_t x)
 {
@@ -1261,11 +1271,8 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
             uint32_t rank = 0;
             if (inv != 0) {                                       // (one arrangement: nothing to take off the index)
                 if ((last_idx >> 32) == 0) {
-                    // the quotient of the reciprocal rounded down is the true one or one less
-                    uint32_t x = (uint32_t)rest, q = __umulhi(x, inv);
-                    rank = x - q * n;
-                    if (rank >= n) { rank -= n; q++; }
-                    rest = q;
+                    rank = (uint32_t)rest;
+                    rest = take_digit(rank, n, inv);
                 } else { rank = (uint32_t)(rest % n); rest /= n; }
             }
             const uint64_t o = P.orders[P.order_at[C.ntd[d]] + rank];
@@ -1372,9 +1379,11 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
 }
 
 // Places the blocks of program words [w_from, w_to) (six blocks a word).  `live`: the lane holds a candidate.
-template <int DM, int MODE, bool TP>
+// FREE: whether the orders of some devices go together at all.  The devices of the codes `free` run their blocks in any order: all of
+// their types stand at the head (HM keeps their bits), and no program is written.
+template <int DM, int MODE, bool TP, bool FREE = false>
 __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM> &C, const FastLds &L, int lane, bool live,
-                                            int w_from, int w_to, FastProgram &prog, BuildState &S, uint32_t *left_after)
+                                            int w_from, int w_to, FastProgram &prog, BuildState &S, uint32_t *left_after, uint32_t free = 0)
 {
     // With repair every candidate has an executable order (the blocks not yet placed form a DAG, so some type
     // is always runnable): no lane ever stops building, not even one without a candidate of the range (it scores
@@ -1433,7 +1442,7 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
                 const uint32_t h2 = a.y >> (p2 & 31u);
                 c2 = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(a.x >> (p2 & 31u), h2 + h2, 1u, 0xE4), 3u, d4, 0xEA);
             } else c2 = d4 + (__builtin_amdgcn_ubfe(a.x, p2, 1) | (__builtin_amdgcn_ubfe(a.y, p2, 1) << 1));
-            const uint32_t hm_new = (HM & ~(15u << d4)) | (1u << c2);
+            const uint32_t hm_new = (HM & ~(15u << d4)) | (1u << c2) | (FREE ? free : 0u);
             // one waiting micro-batch is consumed; the type stays runnable while another one waits and
             // entries of it remain; its consumer gets one more and becomes runnable
             // remaining entries of the same type: alive & ~(lo ^ ly) & ~(hi ^ hy)
@@ -1513,6 +1522,11 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
             if (lane == 0) __hip_atomic_fetch_add(left_after + wi + 1, alive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     };
+    if constexpr (FREE) {
+        for (int wi = w_from; wi < w_to && __ballot(building) != 0; wi++) (void)word(wi);
+        S.status = status;
+        return;
+    }
     for (int wi = w_from; wi < min(w_to, 32); wi++) {
         if (!repair && __ballot(building) == 0) break;
         prog.a[wi] = word(wi);
@@ -1540,6 +1554,86 @@ __device__ __forceinline__ int build_end(const FastConst<DM> &C, const BuildStat
     return worst > C.M ? kMem : kOk;
 }
 
+// What placing a block of the type with code `lane` does: its words of FastLds::type_tab; `rec`: LDS address of the records.
+template <int DM, bool TP>
+__device__ __forceinline__ void fill_type_tab(const KParams &P, uint32_t *type_tab, uint32_t rec, int lane)
+{
+    const uint32_t inf = P.info_loc[lane];
+    const uint32_t su = inf & 63u, dev = (uint32_t)lane >> 2, y = (uint32_t)lane & 3u;
+    const int32_t m = (int32_t)(inf << 6) >> 24;
+    const bool has_su = su != 63u, same = has_su && (su >> 2) == dev;
+    const uint32_t inc = has_su ? 1u << (4u * (su & 3u)) : 0u;
+    const uint32_t last = rec + 3u * kRecWordStep;            // last word of device 0's record, lane 0
+    uint4 e;
+    if (TP && ((P.slow_mask >> lane) & 1u))
+        // a type on several devices, or with such a consumer: the step's slow path does the consumer's part
+        e = make_uint4(((uint32_t)m << 16) - (1u << (4u * y)), has_su ? P.grp_code[su & 31u] : 0u, 0xFFFFFFFFu, (uint32_t)m);
+    else
+        e = make_uint4(((uint32_t)m << 16) - (1u << (4u * y)) + (same ? inc : 0u),
+                       has_su ? 1u << (su & 31u) : 0u,
+                       has_su && !same ? last + (su >> 2) * kRecDevStep + (TP ? 0u : 4u * y)
+                                       : TP ? 0xFFFFFFFFu : last + (dev < (uint32_t)DM ? dev : 0u) * kRecDevStep + 4u * y,
+                       has_su && !same ? inc : 0u);
+    type_tab[lane] = e.x; type_tab[2 * kMaxK + lane] = e.y; type_tab[4 * kMaxK + lane] = e.z; type_tab[6 * kMaxK + lane] = e.w;
+}
+
+// ------------------------------------------------------------------ which orders go together (CANONICAL, tables by rank)
+// Next to all candidates of an exhaustive space deadlock (99.1 % of 2.88 G of a 4-stage pipeline with four micro-batches), and they
+// share their deadlocks: the orders of two devices that cannot go together under some leads are the same two in all candidates that
+// have them.  So a launch first finds out, for every lead vector of its range and every pair of devices that a dependency joins, which
+// pairs of orders run to the end where all other devices run their blocks in any order (a necessary condition, whatever the
+// other orders are), a bit each; the kernel over the range looks its candidates up there, 32 at a time, and builds those only
+// that all their pairs leave (eval_fast_kernel, `pairs`).  In a pipeline these are the ones that do run; elsewhere a few more.
+// 2^26 candidates of 4 stages and four micro-batches, by where the range lies: 1,810 to 2,350 us a call without, 153 to 378 with; all
+// 5.8 M of three micro-batches 220 -> 62.
+// One bit a lane: lead vectors x pairs x orders of the two.
+template <int DM>
+__global__ __launch_bounds__(kWave) void order_pairs_kernel(const KParams *__restrict__ Pp, uint32_t lead0, uint32_t chunks, uint32_t *__restrict__ tab)
+{
+    extern __shared__ uint32_t lds[];
+    const KParams &P = *Pp;
+    const int lane = threadIdx.x;
+    FastLds L;
+    L.type_tab = lds;
+    L.rec = lds_address(lds) + kFastTableWords * 4u;
+    if (lds_address(lds) != 0u) {                             // (the build's table starts at address 0; without it every bit stays set)
+        for (uint32_t w = blockIdx.x * kWave + (uint32_t)lane; w < 2u * chunks; w += gridDim.x * kWave) tab[w] = ~0u;
+        return;
+    }
+    if (lane < kMaxK) fill_type_tab<DM, false>(P, L.type_tab, L.rec, lane);
+    __syncthreads();
+    FastConst<DM> C;
+    C.D = P.D; C.total = P.total; C.M = 0; C.ntp = 0;
+    const uint32_t per_lead = P.pair_words / 2u;
+    for (uint32_t chunk = blockIdx.x; chunk < chunks; chunk += gridDim.x) {
+        const uint32_t lead = chunk / per_lead, at = (chunk - lead * per_lead) * 2u;
+        int k = 0;
+        while (k + 1 < P.npairs && P.pair_at[k + 1] <= at) k++;
+        const int d = P.pair_of[k][0], e = P.pair_of[k][1];
+        const uint32_t n = (uint32_t)P.cdev[d], bit = (at - P.pair_at[k]) * 32u + (uint32_t)lane;
+        const bool valid = bit < n * (uint32_t)P.cdev[e];
+        uint32_t rank_d = valid ? bit : 0u;
+        const uint32_t rank_e = take_digit(rank_d, n, P.recip[d]);
+        const uint32_t *row = P.leadrows + (size_t)(lead0 + lead) * kLeadRow;
+        BuildState S;
+        const uint32_t free = ~(15u << (4 * d) | 15u << (4 * e));
+        S.R = row[8]; S.HM = free; S.X = 0; S.worst = INT_MIN; S.status = kOk;
+#pragma unroll
+        for (int dd = 0; dd < DM; dd++) {
+            if (dd >= P.D) continue;
+            const uint32_t len = (uint32_t)(P.ntd[dd] * P.NR);
+            const uint64_t o = P.orders[P.order_at[P.ntd[dd]] + (dd == d ? rank_d : dd == e ? rank_e : 0u)];
+            const uint32_t lo = (uint32_t)o, hi = (uint32_t)(o >> 32), waits = row[4 + dd / 2] >> (16 * (dd & 1)) & 0xFFFFu;
+            rec_store(L.rec + (uint32_t)dd * kRecDevStep + (uint32_t)lane * 4u, make_uint4(lo, hi, len >= 32u ? 0xFFFFFFFFu : (1u << len) - 1u, waits));
+            if (len > 0) S.HM |= 1u << (4 * dd + ((lo & 1u) | (hi & 1u) << 1));
+        }
+        FastProgram none;
+        build_words<DM, 0, false, true>(P, C, L, lane, valid, 0, (P.total + 5) / 6, none, S, nullptr, free);
+        const uint64_t run = __ballot(valid && S.status == kOk);
+        if (lane < 2) tab[2u * chunk + (uint32_t)lane] = (uint32_t)(run >> (32 * lane));
+    }
+}
+
 // (Waves per SIMD: what the registers of the variant allow without spills in the loops; the TP variants with four waves
 // and 24 boundary values, or 8 devices, spilled up to 600 registers.)
 template <int DM, int VM, int MODE, bool TP = false>
@@ -1548,7 +1642,8 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
                                                           int32_t *__restrict__ peak_out, int tries, int retry_tries,
                                                           uint64_t *__restrict__ out_list, uint32_t *__restrict__ out_count,
                                                           uint32_t out_cap, uint32_t *__restrict__ overflow, uint32_t *ring_base,
-                                                          uint32_t ring_words, int stage_words, int adapt, uint32_t *left_after)
+                                                          uint32_t ring_words, int stage_words, int adapt, uint32_t *left_after,
+                                                          const uint32_t *__restrict__ pairs, uint32_t lead0)
 {
     extern __shared__ uint32_t lds[];
     // the sweeps address their tables by LDS byte address from 0: the kernel has no other LDS in front of this array
@@ -1581,24 +1676,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
         if (TP) L.tt_tab[lane] = make_uint4((uint32_t)P.t_loc[lane], ((((inf >> 12) & 63u) - (uint32_t)P.D + 2u * DM) << 8),
                                     ((uint32_t)lane >> 2) * (kWave * 4u),
                                     (16u + 4u * ((uint32_t)lane & 3u)) | ((P.grp_code[lane] & (P.grp_code[lane] - 1u)) ? 0x80000000u : 0u));
-        {
-            const uint32_t su = inf & 63u, dev = (uint32_t)lane >> 2, y = (uint32_t)lane & 3u;
-            const int32_t m = (int32_t)(inf << 6) >> 24;
-            const bool has_su = su != 63u, same = has_su && (su >> 2) == dev;
-            const uint32_t inc = has_su ? 1u << (4u * (su & 3u)) : 0u;
-            const uint32_t last = L.rec + 3u * kRecWordStep;          // last word of device 0's record, lane 0
-            uint4 e;
-            if (TP && ((P.slow_mask >> lane) & 1u))
-                // a type on several devices, or with such a consumer: the step's slow path does the consumer's part
-                e = make_uint4(((uint32_t)m << 16) - (1u << (4u * y)), has_su ? P.grp_code[su & 31u] : 0u, 0xFFFFFFFFu, (uint32_t)m);
-            else
-                e = make_uint4(((uint32_t)m << 16) - (1u << (4u * y)) + (same ? inc : 0u),
-                               has_su ? 1u << (su & 31u) : 0u,
-                               has_su && !same ? last + (su >> 2) * kRecDevStep + (TP ? 0u : 4u * y)
-                                               : TP ? 0xFFFFFFFFu : last + (dev < (uint32_t)DM ? dev : 0u) * kRecDevStep + 4u * y,
-                               has_su && !same ? inc : 0u);
-            L.type_tab[lane] = e.x; L.type_tab[2 * kMaxK + lane] = e.y; L.type_tab[4 * kMaxK + lane] = e.z; L.type_tab[6 * kMaxK + lane] = e.w;
-        }
+        fill_type_tab<DM, TP>(P, L.type_tab, L.rec, lane);
         {
             // codes no block type has: device 0, chain 0, t = 0 (the pipeline of the sweeps reads code 0 past the end)
             const bool used = P.t_loc[lane] != 0;
@@ -1786,13 +1864,88 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     };
 
     const uint64_t stride = (uint64_t)gridDim.x * kWave;
-    const uint64_t rounds = (count + stride - 1) / stride;          // the same trip count for every lane of the grid
+    uint64_t rounds = (count + stride - 1) / stride;                // the same trip count for every lane of the grid
+    // With tables of the orders that go together (`pairs`): candidates come from there.  A unit is 32 neighbours in the order of the
+    // first device, their other orders and leads alike: a bit each by the pairs that device is in, all or none by the others.
+    // Those that are left go to a list of the wave, as offsets (in ring 1, which a window built in one go leaves free), until there are
+    // 64.  The units of a wave's lanes lie far apart, so that every wave gets its share: the ones with anything left lie together.
+    constexpr bool kPairs = MODE == 0 && !TP;
+    static_assert(63 + 32 * kWave <= (4 + kStageMetaWords + 4 * 2) * (int)kRingSlots, "the list of a wave fits its ring");
+    uint32_t *const left_list = ring1;
+    uint32_t nleft = 0, out = 0;                                     // candidates on it; per lane: candidates that the tables reject
+    uint32_t n0 = 0, wpr = 0, group0 = 0, units = 0, unit_lanes = 0, unit_rounds = 0, unit_round = blockIdx.x;
+    if (kPairs && pairs) {
+        n0 = (uint32_t)P.cdev[0];
+        wpr = (n0 + 31u) / 32u;
+        group0 = (uint32_t)(first / n0);
+        units = ((uint32_t)((first + count - 1) / n0) - group0 + 1u) * wpr;
+        unit_lanes = min((units + gridDim.x - 1u) / gridDim.x, (uint32_t)kWave);
+        unit_rounds = (units + unit_lanes - 1u) / unit_lanes;
+        rounds = 0;
+    }
+    auto look_up = [&]() {
+        const uint32_t unit = (uint32_t)lane * unit_rounds + unit_round;
+        unit_round += gridDim.x;
+        uint32_t left = 0, at0 = 0;
+        if ((uint32_t)lane < unit_lanes && unit < units) {
+            const uint32_t row = unit / wpr, w = unit - row * wpr;
+            uint32_t rank[DM], lead = group0 + row;
+            rank[0] = 0;
+#pragma unroll
+            for (int d = 1; d < DM; d++) {
+                rank[d] = lead;
+                lead = d < C.D ? take_digit(rank[d], (uint32_t)P.cdev[d], P.recip[d]) : lead;
+            }
+            // the members of the unit that are in the range
+            const uint64_t base = (uint64_t)(group0 + row) * n0 + 32u * w;
+            const uint32_t members = min(32u, n0 - 32u * w);
+            uint32_t in = members < 32u ? (1u << members) - 1u : 0xFFFFFFFFu;
+            if (base < first) in = first - base < 32 ? in & (0xFFFFFFFFu << (uint32_t)(first - base)) : 0u;
+            const uint64_t behind = first + count;
+            if (base + 32 > behind) in = behind > base ? in & ((1u << (uint32_t)(behind - base)) - 1u) : 0u;
+            const uint32_t *tab = pairs + (size_t)(lead - lead0) * P.pair_words;
+            left = in;
+            for (int k = 0; k < P.npairs; k++) {
+                const int d = P.pair_of[k][0], e = P.pair_of[k][1];
+                uint32_t rd = 0, re = 0;
+#pragma unroll
+                for (int dd = 0; dd < DM; dd++) { rd = dd == d ? rank[dd] : rd; re = dd == e ? rank[dd] : re; }
+                const uint32_t bit = re * (uint32_t)P.cdev[d] + (d == 0 ? 32u * w : rd);
+                const uint32_t *word = tab + P.pair_at[k] + (bit >> 5);
+                // (the unit's members end inside the table, so a second word is read only where there is one)
+                if (d == 0) {
+                    const bool more = (bit & 31u) + members > 32u;
+                    left &= __builtin_amdgcn_alignbit(more ? word[1] : 0u, word[0], bit & 31u);
+                } else left = word[0] >> (bit & 31u) & 1u ? left : 0u;
+            }
+            out += (uint32_t)__builtin_popcount(in & ~left);
+            at0 = (uint32_t)(base - first);                          // (below 0 for the first unit: its first members are out of the range)
+        }
+        for (;;) {
+            const uint64_t some = __ballot(left != 0u);
+            if (some == 0) break;
+            if (left != 0u) {
+                left_list[nleft + rank_in(some)] = at0 + (uint32_t)__builtin_ctz(left);
+                left &= left - 1u;
+            }
+            nleft += (uint32_t)__builtin_popcountll(some);
+        }
+    };
     const bool adapting = TP && MODE == 2 && adapt && drop_mem;
     if (adapting) set_stage(nwords);
     // phase A on the next 64 candidates of the wave's share
     auto build_new = [&](uint64_t r) {
-        const uint64_t kk = r * stride + (uint64_t)blockIdx.x * kWave + lane;
-        const bool valid = kk < count;
+        uint64_t kk = r * stride + (uint64_t)blockIdx.x * kWave + lane;
+        bool valid = kk < count;
+        if (kPairs && pairs) {
+            while (nleft < (uint32_t)kWave && unit_round < unit_rounds) look_up();
+            const uint32_t n = min(nleft, (uint32_t)kWave);
+            if (n == 0) return;
+            __threadfence_block();
+            valid = (uint32_t)lane < n;
+            nleft -= n;
+            kk = valid ? left_list[nleft + (uint32_t)lane] : 0u;
+        }
         const uint64_t idx = valid ? first + kk : first;
         __builtin_amdgcn_s_setprio(0);
         build_begin<DM, MODE, TP>(P, C, idx, first + count - 1, L, lane, lead_code, S);
@@ -1854,7 +2007,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     // Later phases first: a ring is served as soon as it holds 64 candidates, so that it never holds more than 127;
     // when the wave's share is used up the rings are drained on partial waves.  Every condition is wave-uniform.
     for (uint64_t r = 0;;) {
-        const bool fresh = r < rounds;
+        const bool fresh = r < rounds || (kPairs && (unit_round < unit_rounds || nleft > 0));
         // (one call for both rings of programs, so that the sweeps exist once in the code)
         const bool again = count3 >= (uint32_t)kWave || (!fresh && count1 == 0 && count2 == 0 && count3 > 0);
         const bool sweep = again || count2 >= (uint32_t)kWave || (!fresh && count1 == 0 && count2 > 0);
@@ -1871,7 +2024,9 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
         uint64_t oi = ((uint64_t)ihi << 32) | ilo;
         if (key_less(op, oi, best, best_idx)) { best = op; best_idx = oi; }
         nsw += __shfl_xor(nsw, off);
+        if (kPairs) out += __shfl_xor(out, off);
     }
+    if (kPairs) { nev += out; cnt[kDeadlock] += out; }
     if (lane == 0) {
         BlockRec rr;
         rr.period = best; rr.n_retried = nretry; rr.index = best_idx; rr.n_evaluated = nev; rr.n_sweeps = nsw; rr.n_blocks = nblocks; rr.n_high = 0;
@@ -2114,7 +2269,8 @@ __global__ void reset_kernel(DevResult *res, DevDetail *detail, uint32_t *left_a
 // ------------------------------------------------------------------ launchers
 typedef void (*eval_fn)(TESSEL_EVAL_KERNEL_ARGS);
 typedef void (*fast_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, int, int, uint64_t *, uint32_t *,
-                        uint32_t, uint32_t *, uint32_t *, uint32_t, int, int, uint32_t *);
+                        uint32_t, uint32_t *, uint32_t *, uint32_t, int, int, uint32_t *, const uint32_t *, uint32_t);
+typedef void (*pairs_fn)(const KParams *, uint32_t, uint32_t, uint32_t *);
 
 // problems too wide for the fast kernel and the chain path (their state stays in LDS where 64 KB hold it)
 static bool wide_problem(const KParams &kp) { return kp.D > kMaxD || kp.K > kMaxK || kp.many || kp.NR > kMaxNR; }
@@ -2159,6 +2315,30 @@ static fast_fn pick_fast(const KParams &kp)
     if (kp.D <= 2) return V <= 4 ? eval_fast_kernel<2, 4, 0> : eval_fast_kernel<2, 24, 0>;
     if (kp.D <= 4) return V <= 8 ? eval_fast_kernel<4, 8, 0> : eval_fast_kernel<4, 24, 0>;
     return V <= 16 ? eval_fast_kernel<8, 16, 0> : eval_fast_kernel<8, 24, 0>;
+}
+
+// Whether a launch looks its candidates up in tables of the orders that go together (order_pairs_kernel), and for how many lead vectors
+// from which on.  Tables and a launch for them cost a call 8 to 12 us, and a bit as much as a candidate that gets far: calls of 2^18 candidates
+// take 30 to 59 us without them and 30 to 65 with (pipelines of 3 to 8 devices, two to five micro-batches), of 2^20 56 to 81 and 29 to 71;
+// 2^22 candidates 147 and 150 us where the tables have 1.7 M bits (924 orders on each of three devices), 2^24 497 and 156.
+constexpr uint64_t kPairCandidates = 1u << 19;
+static uint32_t pair_leads(const KParams &kp, uint64_t first, uint64_t count, uint32_t &lead0)
+{
+    lead0 = 0;
+    if (kp.npairs == 0 || kp.cdev[0] < 2) return 0;
+    uint64_t orders = 1;
+    for (int d = 0; d < kp.D; d++)
+        if (__builtin_mul_overflow(orders, kp.cdev[d], &orders)) return 0;
+    const uint64_t l0 = first / orders, n = (first + count - 1) / orders - l0 + 1;
+    if ((first + count - 1) / kp.cdev[0] >= 0xFFFFFFFFull || n * kp.pair_words > kp.pair_room) return 0;
+    int always = 0;
+    if (const char *env = getenv("TESSEL_PAIRS")) {                 // tuning knob
+        if (atoi(env) == 0) return 0;
+        always = 1;
+    }
+    if (!always && (count < kPairCandidates || n * kp.pair_bits * 4 > count)) return 0;
+    lead0 = (uint32_t)l0;
+    return (uint32_t)n;
 }
 
 // state and program of the general kernel's lanes: in LDS, except for wide problems that 64 KB do not hold
@@ -2391,9 +2571,21 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
         rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, behind, st);
     else {
         int adapt = 0;
-        const int stage = stage_words(kp, peak != nullptr, count, s.blocks, adapt);
+        int stage = stage_words(kp, peak != nullptr, count, s.blocks, adapt);
+        uint32_t lead0 = 0;
+        const uint32_t leads = code ? 0u : pair_leads(kp, first, count, lead0);
+        if (leads) {
+            const uint32_t chunks = leads * (kp.pair_words / 2);
+            const pairs_fn pf = kp.D <= 2 ? order_pairs_kernel<2> : kp.D <= 4 ? order_pairs_kernel<4> : order_pairs_kernel<8>;
+            hipLaunchKernelGGL(pf, dim3(std::min<uint32_t>(chunks, (uint32_t)num_cus * 12u)), dim3(kWave),
+                               (size_t)kFastTableWords * 4 + (size_t)fast_dm(kp) * kWave * 16, st, kp_dev, lead0, chunks, kp.pair_tab);
+            rc = (int)hipGetLastError();
+            if (rc) return rc;
+            stage = (kp.total + 5) / 6;                             // (what is left mostly runs to the end)
+        }
         hipLaunchKernelGGL(ff, dim3(blocks), dim3(kWave), fast_lds_bytes(kp), st, kp_dev, first, count, recs, code, peak, kp.eigen_tries,
-                           kp.retry_tries, list, &res->defer_count, kWsListCap, &res->overflow, behind, ring_words(kp), stage, adapt, left_after);
+                           kp.retry_tries, list, &res->defer_count, kWsListCap, &res->overflow, behind, ring_words(kp), stage, adapt, left_after,
+                           leads ? kp.pair_tab : nullptr, lead0);
         rc = (int)hipGetLastError();
     }
     if (rc) return rc;
