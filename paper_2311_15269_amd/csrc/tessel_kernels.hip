@@ -844,7 +844,8 @@ struct FastProgram {
 constexpr int kFastTableWords = 16 * kMaxK;      // uniform tables at the start of the fast kernel's LDS
 constexpr int kSweepTabWord = 12 * kMaxK;        // ... of which the sweeps' three tables by code; a multiple of 64 words, so
                                                  // that one two-address LDS read fetches a code's first and third word
-constexpr int kTpTableWords = 5 * kMaxK + kMaxD; // the TP variants' own tables behind them
+constexpr int kTpListWord = 5 * kMaxK + kMaxD;
+constexpr int kTpTableWords = kTpListWord + 2 * kWave;       // the TP variants' own tables behind them, and their list of candidates
 // Everything a lane reads by a run-time index lies word by word: word w of entry i at w * 64 + i words, so that
 // lanes with different entries hit different banks, a lane's words of one entry come with two-address reads
 // (stride 64 words), and an LDS atomic on one word of the records meets no bank twice.
@@ -1180,6 +1181,52 @@ __device__ __forceinline__ uint32_t even_bits(uint64_t x)
 // Builds the candidate's window: validity, memory, the program of the window in executable order and the leads by
 // code.  Returns kOk or the reason of the rejection; the period is the sweeps' business (period_fast).
 // what the build carries from block to block besides the per-device records in LDS
+// Sampled leads: every dependency between different device sets steps the lead with probability step_q16 / 65536; a lead is
+// the number of steps from its type to the end of the chain, capped at N_R - 1.  The steps, a bit each:
+template <int DM>
+__device__ __forceinline__ uint32_t lead_steps(const KParams &P, const FastConst<DM> &C, uint32_t ka, uint32_t kb)
+{
+    uint32_t S = 0;
+    for (int e = 0; e < C.ndeps; e += 2) {
+        const uint32_t wv = stream_word(ka, kb, (kDrawLeadBase + (uint32_t)e) >> 1);
+        // (the dependency's bit through scalar loads: the index is the same in every lane)
+        const uint32_t b0 = P.dep_bit[e], b1 = e + 1 < C.ndeps ? P.dep_bit[e + 1] : 0u;
+        S |= (wv & 0xFFFFu) < C.step_q16 ? b0 : 0u;
+        S |= (wv >> 16) < C.step_q16 ? b1 : 0u;
+    }
+    return S;
+}
+
+// blocks that ran before the window: a device's leads, four bits each, times its memory deltas
+__device__ __forceinline__ int entry_memory(uint32_t leads, uint32_t mpack)
+{
+    uint32_t leads4 = (leads & 0xFFu) | ((leads & 0xFF00u) << 8);
+    leads4 = (leads4 | (leads4 << 4)) & 0x0F0F0F0Fu;
+    return __builtin_amdgcn_sdot4((int)leads4, (int)mpack, 0, false);
+}
+
+// Sampled spaces with drawn leads: whether the memory at the window entry alone exceeds the cap on some device.  A device is back
+// there after its last block (its deltas add up to nothing over a window), so the candidate's peak does too, whatever its orders.
+// Its own phase in front of the decode for problems with blocks on several devices, whose memory is held on all of them at once: 86 % of 2^26
+// candidates of 40 blocks with two on all of four devices leave here, 5.69 -> 1.68 ms.  In the others next to no lead vector
+// exceeds a cap that any candidate meets.
+template <int DM>
+__device__ __forceinline__ bool entry_over(const KParams &P, const FastConst<DM> &C, const FastLds &L, uint64_t idx)
+{
+    uint32_t kb;
+    const uint32_t ka = stream_keys(C.seed, idx, kb), S = lead_steps<DM>(P, C, ka, kb);
+    int most = INT_MIN;
+#pragma unroll
+    for (int d = 0; d < DM; d++) {
+        if (d >= C.D || C.ntd[d] == 0) continue;
+        uint32_t leads = 0;
+#pragma unroll
+        for (int y = 0; y < kMaxLT; y++) leads |= min((uint32_t)C.NR - 1u, (uint32_t)__builtin_popcount(S & L.cum_tab[4 * d + y])) << (4 * y);
+        most = max(most, entry_memory(leads, C.mpack[d]));
+    }
+    return most > C.M;
+}
+
 struct BuildState {
     uint32_t R, HM, X;               // by code: runnable types, heads of the devices, exhausted types
     int worst;                       // largest memory prefix over all devices so far (Eq. 1 [2])
@@ -1294,16 +1341,7 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
     uint32_t R = 0, HM = 0, X = 0;
     const bool draw_leads = sampled && !C.has_fixed;
     if (draw_leads) {
-        // every dependency between different device sets steps the lead with probability step_q16 / 65536;
-        // a lead is the number of steps from its type to the end of the chain, capped at N_R - 1
-        uint32_t S = 0;
-        for (int e = 0; e < C.ndeps; e += 2) {
-            const uint32_t wv = stream_word(ka, kb, (kDrawLeadBase + (uint32_t)e) >> 1);
-            // (the dependency's bit through scalar loads: the index is the same in every lane)
-            const uint32_t b0 = P.dep_bit[e], b1 = e + 1 < C.ndeps ? P.dep_bit[e + 1] : 0u;
-            S |= (wv & 0xFFFFu) < C.step_q16 ? b0 : 0u;
-            S |= (wv >> 16) < C.step_q16 ? b1 : 0u;
-        }
+        const uint32_t S = lead_steps<DM>(P, C, ka, kb);
 #pragma unroll
         for (int d = 0; d < DM; d++) {
             if (d >= C.D) continue;
@@ -1361,11 +1399,8 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
         // spaces, which spill scalar registers around it, four products: 2,000,003 candidates of the factorial space of two
         // micro-batches of 16 types on 8 devices 316 -> 271 us.)
         int mem0 = 0;
-        if (sampled) {
-            uint32_t leads4 = (mud & 0xFFu) | ((mud & 0xFF00u) << 8);
-            leads4 = (leads4 | (leads4 << 4)) & 0x0F0F0F0Fu;
-            mem0 = __builtin_amdgcn_sdot4((int)leads4, (int)C.mpack[d], 0, false);
-        } else {
+        if (sampled) mem0 = entry_memory(mud, C.mpack[d]);
+        else {
 #pragma unroll
             for (int y = 0; y < kMaxLT; y++) mem0 += ((int)(C.mpack[d] << (24 - 8 * y)) >> 24) * (int)(mud >> (4 * y) & 15u);
         }
@@ -1934,9 +1969,36 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     const bool adapting = TP && MODE == 2 && adapt && drop_mem;
     if (adapting) set_stage(nwords);
     // phase A on the next 64 candidates of the wave's share
-    auto build_new = [&](uint64_t r) {
+    uint64_t r = 0;
+    uint32_t built = 0;                                              // phases A so far
+    bool sieve = TP && MODE == 2 && drop_mem && !C.has_fixed && rounds > 1;
+    uint32_t *const tp_list = lds + kFastTableWords + kTpListWord;
+    auto build_new = [&]() {
         uint64_t kk = r * stride + (uint64_t)blockIdx.x * kWave + lane;
         bool valid = kk < count;
+        if (TP && MODE == 2) {
+            // leads first: 64 candidates at a time, until 64 are left whose entry memory fits
+            while (sieve && nleft < (uint32_t)kWave && r < rounds) {
+                kk = r++ * stride + (uint64_t)blockIdx.x * kWave + lane;
+                valid = kk < count;
+                const uint64_t idx = first + (valid ? kk : 0u);
+                const bool over = entry_over<DM>(P, C, L, idx);
+                reject(valid && over, idx, kMem, 0);
+                const uint64_t fits = __ballot(valid && !over);
+                if (valid && !over) tp_list[nleft + rank_in(fits)] = (uint32_t)kk;
+                nleft += (uint32_t)__builtin_popcountll(fits);
+                // (a look at the leads costs a sixth of what it saves of a candidate that it rejects)
+                if (r == 1) sieve = __builtin_popcountll(fits) <= 52;
+            }
+            if (nleft > 0 || sieve) {
+                const uint32_t n = min(nleft, (uint32_t)kWave);
+                if (n == 0) return;
+                __threadfence_block();
+                valid = (uint32_t)lane < n;
+                nleft -= n;
+                kk = valid ? tp_list[nleft + (uint32_t)lane] : 0u;
+            } else r++;
+        } else r++;
         if (kPairs && pairs) {
             while (nleft < (uint32_t)kWave && unit_round < unit_rounds) look_up();
             const uint32_t n = min(nleft, (uint32_t)kWave);
@@ -1951,14 +2013,15 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
         build_begin<DM, MODE, TP>(P, C, idx, first + count - 1, L, lane, lead_code, S);
         FastProgram prog;
         __builtin_amdgcn_s_setprio(1);
-        const bool watch = adapting && r < 2;
-        const bool report = watch && r == 0 && (blockIdx.x & 15u) == 0;
+        const uint32_t nth = built++;
+        const bool watch = adapting && nth < 2;
+        const bool report = watch && nth == 0 && (blockIdx.x & 15u) == 0;
         build_words<DM, MODE, TP>(P, C, L, lane, valid, 0, wordsA, prog, S, report ? left_after : nullptr);
         nblocks += (uint32_t)__builtin_popcountll(__ballot(valid)) * (uint32_t)min(C.total, 6 * wordsA);
         if (!split) {
             finish_build(valid, idx, prog);
             if (!(TP && MODE == 2) || !watch) return;
-            if (r == 0) {
+            if (nth == 0) {
                 if (report && lane == 0) __hip_atomic_fetch_add(left_after, (uint32_t)kWave, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 return;
             }
@@ -2006,14 +2069,14 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
 
     // Later phases first: a ring is served as soon as it holds 64 candidates, so that it never holds more than 127;
     // when the wave's share is used up the rings are drained on partial waves.  Every condition is wave-uniform.
-    for (uint64_t r = 0;;) {
-        const bool fresh = r < rounds || (kPairs && (unit_round < unit_rounds || nleft > 0));
+    for (;;) {
+        const bool fresh = r < rounds || nleft > 0 || (kPairs && unit_round < unit_rounds);
         // (one call for both rings of programs, so that the sweeps exist once in the code)
         const bool again = count3 >= (uint32_t)kWave || (!fresh && count1 == 0 && count2 == 0 && count3 > 0);
         const bool sweep = again || count2 >= (uint32_t)kWave || (!fresh && count1 == 0 && count2 > 0);
         if (sweep) sweep_from_ring(min(again ? count3 : count2, (uint32_t)kWave), again);
         else if (count1 >= (uint32_t)kWave || (!fresh && count1 > 0)) build_from_ring(min(count1, (uint32_t)kWave));
-        else if (fresh) build_new(r++);
+        else if (fresh) build_new();
         else break;
     }
     if (!recs) return;
