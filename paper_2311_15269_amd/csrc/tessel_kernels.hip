@@ -1094,9 +1094,15 @@ __device__ __forceinline__ void reset_sweep_state(const FastConst<DM> &C, const 
 // cycle ratio, exactly.  Almost every candidate gets there within two or three sweeps; one that has
 // not after the sweeps allowed (`tries`) is handed on by the caller: to a queue of candidates that get more
 // sweeps, from there to the general kernel (Karp's formula).
+// `settle`, in the longer search: the period is also found when the largest growth D was that of the boundary before and every value
+// that grew by D then grew by D now.  No cycle ratio exceeds the largest growth; and a value that grew by D got its time from one that
+// grew by D the time before (that one's growth bounds its own from above), which is again one of these, so following them
+// closes a cycle of ratio D.  (Pipelines whose devices before the slowest one keep a smaller growth for ever: 8.7 M candidates of 70 blocks on
+// five devices left so many to the general kernel that its pass took 563 of 1,690 us; a call 1,590 -> 1,090 us.  Not in the
+// variants for 24 values, which have no registers left for it: 2 to 5 % slower over 48 to 112 blocks.)
 template <int DM, int VM, bool TP>
 __device__ __forceinline__ int period_fast(const FastConst<DM> &C, const FastLds &L, const FastProgram &prog, int lane,
-                                           const Mu &lead_code, bool want, int tries,
+                                           const Mu &lead_code, bool want, int tries, bool settle,
                                            uint32_t &nsweeps_used)
 {
     const int V = C.nsweeps - 1;
@@ -1121,10 +1127,30 @@ __device__ __forceinline__ int period_fast(const FastConst<DM> &C, const FastLds
     for (int v = 0; v < VM; v++) prev[v] = 0;
     int T = 0;
     bool done = !want;
+    uint32_t top_before = 0, was = 0;
     for (int j = 0; j < tries; j++) {
         if (__ballot(!done) == 0) break;
         sweep_fast<DM, TP>(C, L, prog, lane, lead_code, !done);
         nsweeps_used += done ? 0u : 1u;
+        if (VM <= 16 && settle) {
+            uint32_t top = 0, now = 0;                    // the largest growth, and the values that have it
+#pragma unroll
+            for (int v = 0; v < VM; v++) {
+                if (v < V) {
+                    const uint32_t x = *(const uint32_t *)((const char *)L.dfree + value_offset(L.vtab[v]));
+                    const uint32_t dv = live >> v & 1u ? x - prev[v] : 0u;
+                    prev[v] = x;
+                    now = dv > top ? 0u : now;
+                    top = max(top, dv);
+                    now |= (dv == top ? 1u : 0u) << v;
+                }
+            }
+            now &= live;
+            const bool held = j > 0 && top == top_before && (was & ~now) == 0;
+            if (!done && (held || now == live) && live) { T = (int)top; done = true; }
+            top_before = top; was = now;
+            continue;
+        }
         bool same = true, have = false;
         uint32_t delta = 0;
 #pragma unroll
@@ -1841,7 +1867,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
             }
         if (again) { head3 = (head3 + n) & (kRingSlots - 1u); count3 -= n; }
         else { head2 = (head2 + n) & (kRingSlots - 1u); count2 -= n; }
-        const int T = period_fast<DM, VM, TP>(C, L, prog, lane, lead_code, have, again ? retry_tries : tries, nsw);
+        const int T = period_fast<DM, VM, TP>(C, L, prog, lane, lead_code, have, again ? retry_tries : tries, again, nsw);
         const bool open = have && T < 0;                  // no eigenvector within the sweeps allowed
         if (!again) {
             const uint32_t k = push_program(open, idx, pk, prog, ring3, head3 + count3);
