@@ -237,6 +237,93 @@ static bool code_tables(const tessel_problem &p, GraphTab &gt, const std::vector
     return true;
 }
 
+// The same for graphs with up to two producers and two consumers a type, on single devices with up to two types, 32 codes, windows of 8
+// micro-batches and 16 types (a lead is four bits of one register pair).
+static bool graph_code_tables(const tessel_problem &p, GraphTab &gt, const std::vector<std::vector<int>> &in, const std::vector<std::vector<int>> &outs,
+                              long span_max)
+{
+    const KParams &kp = p.kp;
+    const int D = kp.D, K = kp.K, NR = kp.NR;
+    if (gt.chain || kp.tp || gt.np != 1 || 2 * D > 32 || K > 16 || NR > 8 || gt.maxin > 2 || gt.maxout > 2) return false;
+    if (kp.space != kSampledStrict && kp.space != kSampledRepair) return false;
+    size_t distinct = 0;
+    for (int i = 0; i < K; i++) distinct += in[i].size();
+    if (distinct != p.dep_src.size() || span_max > 30000) return false;
+    if ((int64_t)kp.UB * (std::max(9, gt.retry_tries) + 1) > 65535) return false;
+    constexpr int rows = 3, words = 8, mem_at = 16;
+    const uint32_t row = kWave * 4, half = row / 2, ts = 128;
+    uint32_t at = (uint32_t)words * ts;
+    gt.sw = at; at += (uint32_t)K * 16;
+    gt.ntab = (int)(at / 4);
+    at = (at + row - 1) / row * row;
+    gt.slot_rows = at; at += row;
+    gt.rec = at;
+    const uint32_t build_end = at + (uint32_t)(D * rows) * row;
+    gt.state = at; at += (uint32_t)kp.nslots * half;
+    gt.prev = at; at += (uint32_t)D * half;
+    gt.strash = at; at += (uint32_t)(2 * NR) * half;             // (a ring that nobody reads)
+    at = (at + row - 1) / row * row;
+    gt.leads = at; at += (uint32_t)((kp.ntok + 3) / 4) * row;
+    if (std::max(build_end, at) > 64 * 1024 - row) return false;
+    gt.lds_bytes = std::max(build_end, at);
+    memset(gt.tab, 0, sizeof gt.tab);
+    gt.codes = 3;
+    gt.np = 0;
+    gt.code_rows = rows;
+    std::vector<int> code(K, 0);
+    for (int d = 0; d < D; d++)
+        for (int y = 0; y < kp.ntd[d]; y++) code[kp.type_of[d] >> (8 * y) & 0xFFu] = 2 * d + y;
+    auto dev = [&](int g) -> int { return code[g] >> 1; };
+    auto wait_at = [&](int g, int slot) -> int { return 10 * (code[g] & 1) + 5 * slot; };
+    auto slot_of = [&](int g, int h) -> int { return (int)(std::find(in[h].begin(), in[h].end(), g) - in[h].begin()); };
+    auto word = [&](int w, int c) -> uint32_t & { return gt.tab[((uint32_t)w * ts) / 4 + (uint32_t)c]; };
+    auto rec_row = [&](int d, int r) -> uint32_t { return gt.rec + (uint32_t)(d * rows + r) * row; };
+    gt.free0 = gt.free1 = 0;
+    for (int g = 0; g < K; g++) {
+        const int c = code[g];
+        for (int s = (int)in[g].size(); s < 2; s++) {
+            (s ? gt.free1 : gt.free0) |= 1u << c;
+            gt.waits[dev(g)] += (uint32_t)(NR + 1) << wait_at(g, s);                  // (never used up)
+        }
+        word(0, c) = 0u - (1u << wait_at(g, 0)) - (1u << wait_at(g, 1));
+        word(1, c) = (uint32_t)p.m[g] << mem_at;
+        for (int k = 0; k < 2; k++) {
+            uint32_t to = rec_row(dev(g), 1), inc = 0;
+            if (k < (int)outs[g].size()) {
+                const int h = outs[g][k], s = slot_of(g, h);
+                word(2 + s, c) |= 1u << code[h];
+                if (dev(h) == dev(g)) word(0, c) += 1u << wait_at(h, s);
+                else { to = rec_row(dev(h), 1); inc = 1u << wait_at(h, s); }
+            }
+            word(4 + 2 * k, c) = to | (k ? 0u : ((uint32_t)g * 8u + ((uint32_t)(NR - 1) << 9)) << 16);
+            word(5 + 2 * k, c) = inc;
+        }
+        auto ring_address = [&](int i) -> uint32_t { return gt.state + (uint32_t)kp.tokbase[i] * half; };
+        const uint32_t to = kp.tokbase[g] != kNoRing ? ring_address(g) : gt.strash;
+        uint32_t from[2];
+        for (int s = 0; s < 2; s++) from[s] = in[g].empty() ? to : ring_address(in[g][s < (int)in[g].size() ? s : 0]);
+        uint32_t *e = &gt.tab[gt.sw / 4 + 4 * g];
+        e[0] = (uint32_t)p.t[g];
+        e[1] = (gt.state + (uint32_t)dev(g) * half) | to << 16;
+        e[2] = from[0] | from[1] << 16;
+        uint32_t *l = gt.links[g];
+        l[0] = rec_row(dev(g), 1);
+        l[1] = (uint32_t)(4 * (c & 1)) | (uint32_t)c << 8;
+        l[2] = 0;
+        l[3] = (uint32_t)p.m[g] << mem_at;
+    }
+    gt.nedge = 0;
+    for (int b = 0; b < K; b++)
+        for (size_t s = 0; s < in[b].size(); s++)
+            gt.edge[gt.nedge++] = (uint32_t)in[b][s] | (uint32_t)b << 8 | (uint32_t)wait_at(b, (int)s) << 16 | (uint32_t)s << 24;
+    for (int r = 0; r < kp.ntok; r++) {
+        const int g = kp.ring_head[r];
+        gt.head[r] = rec_row(dev(g), 2) | (uint32_t)(4 * (code[g] & 1)) << 16 | 4u << 24;
+    }
+    gt.ok = 1;
+    return true;
+}
+
 // Tables of the graph kernel (GraphTab).  Leaves ok = 0 where the problem is outside what they hold: more than kGraphOut
 // consumers or the fields of a type's word producers of one type, a type without any dependency, more than kGraphTp types
 // on several devices, memory prefixes beyond 16 bits, an LDS need beyond 64 KB, and where the general kernel is faster.
@@ -342,8 +429,10 @@ static void graph_tables(const tessel_problem &p, GraphTab &gt)
     gt.leads = at; at += (uint32_t)((kp.ntok + 3) / 4) * row;
     gt.lds_bytes = std::max(build_end, at);
     if (gt.lds_bytes > 64 * 1024 - row) return;             // (16-bit LDS addresses, eight-bit row numbers)
-    const char *words = getenv("TESSEL_GRAPH_WORDS");        // test knob: 1 = a word a type for all problems, 0 = for none (left to the general kernel)
+    // (test knob: 1 = a word a type for all problems, 0 = for none, and masks by code for chains alone (the others left to the general kernel))
+    const char *words = getenv("TESSEL_GRAPH_WORDS");
     if (!(words && words[0] == '1') && code_tables(p, gt, in, outs, span_max)) return;
+    if (!words && graph_code_tables(p, gt, in, outs, span_max)) return;
     if (words && words[0] == '0') return;
     for (int r = 0; r < kp.ntok; r++) gt.head[r] = gt.wrow + (uint32_t)kp.ring_head[r] * row;
     auto type_at = [&](int d, int y) -> int { return (int)((y < 4 ? kp.type_of[d] >> (8 * y) : kp.type_of_hi[d] >> (8 * (y - 4))) & 0xFFu); };

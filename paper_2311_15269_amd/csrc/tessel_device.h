@@ -328,8 +328,11 @@ struct GraphTab {
                                  // bits << 24 (bits 0: the next micro-batch of the type's word, less N_R)
     // Chains in the sampled spaces whose devices' symbols fit 64 codes (device << np | symbol): built on masks by code.
     // `codes`: 0 not such, 1 up to 32 codes, 2 up to 64; np is 0 then where a device's order and its entries left share a word
+    // 3: such graphs, with up to two producers and two consumers a type
     int32_t  codes;
     uint32_t code_rows;          // rows of a device record
+    uint32_t free0, free1;       // graphs: codes without a first, a second producer
+    uint32_t waits[kMaxDW];      // graphs: by device its word of waiting micro-batches where all producers have none ahead
     uint32_t links[kMaxKW][4];   // block types, every chain from its last to its first: address of the word with the type's waiting
                                  // micro-batches | number of the dependency to its consumer << 16 | that joins different device sets << 24 |
                                  // nobody consumes it << 25 | nobody produces for it << 26; shift of that count | code << 8 | shift of

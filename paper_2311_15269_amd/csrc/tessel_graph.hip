@@ -25,6 +25,12 @@
 // (general kernel 34.6); 100,003 of one on 12 devices, 288 blocks, 0.249 -> 0.176 (10.0); 300,007 with six types on each of four
 // devices, 96 blocks, 0.205 -> 0.152 (6.9); 3,849 on 15 devices, 360 blocks, 0.275 -> 0.195; 20,725 on 27 devices 0.135 -> 0.086.
 //
+// Graphs with up to two producers and two consumers a type, small devices and windows (KIND 5) do likewise: a mask by code for either
+// producer says whose micro-batch waits, and the two masks and the types that are not used up tell what may run, without a look at any other type's word.
+// Two rounds of LDS reads and 60 vector instructions a block instead of three and 105, a third of the LDS, 16-bit times: 2^22 candidates of the K-shape
+// (24 blocks on three devices) 497 -> 312 us a call under a tight cap and 769 -> 581 under a wide one, of the diamond at eight
+// micro-batches (64 blocks on four) 2,372 -> 899; 64 to 100,003 candidates 0.73 to 0.89 of the time.
+//
 // The program (block type and micro-batch, 16 bits a block) goes to global memory, [word][slot], a slot per candidate;
 // sweeps read it back four words ahead.  A wave owns kGraphSlots slots: candidates that survive the build keep theirs
 // until 64 wait, are swept on full waves, and the few whose boundary values have not settled wait again for a longer
@@ -66,8 +72,8 @@ template <bool W64> struct Codes { typedef uint32_t mask; };
 template <> struct Codes<true> { typedef uint64_t mask; };
 
 // KIND: 0 every type has at most one producer and one consumer, 1 any graph, 2 some block sits on several devices; 3 and 4
-// chains in the sampled spaces on masks by code, up to 32 and up to 64 codes (GraphTab::codes).  NP: bits of a symbol; 0
-// (with masks by code): one bit, order and entries left in one word.
+// chains in the sampled spaces on masks by code, up to 32 and up to 64 codes (GraphTab::codes); 5 such graphs, up to 32 codes.
+// NP: bits of a symbol; 0 (with masks by code): one bit, order and entries left in one word.
 template <int NP, bool REPAIR, int KIND>
 __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(const KParams *__restrict__ Pp, const GraphTab *__restrict__ Gp, uint64_t first,
                                                            uint64_t count, BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
@@ -88,9 +94,9 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
     for (int j = 0; j < 3; j++) lds_store8(st_row + (uint32_t)(j * kWave + lane), 0u);
     __syncthreads();
 
-    constexpr bool TP = KIND == 2, CODES = KIND >= 3, CHAIN = KIND == 0 || CODES, W64 = KIND == 4;
+    constexpr bool TP = KIND == 2, CODES = KIND >= 3, GRAPH = KIND == 5, CHAIN = KIND == 0 || (CODES && !GRAPH), W64 = KIND == 4;
     const uint32_t cw4 = CHAIN ? 16u : G.code_bytes;             // bytes of one code's table words
-    constexpr uint32_t RS = CODES ? (NP == 0 ? 2 : NP == 1 ? 3 : NP + 3) * kRow : (NP + 2) * kRow;      // bytes of one device record
+    constexpr uint32_t RS = GRAPH ? 3 * kRow : CODES ? (NP == 0 ? 2 : NP == 1 ? 3 : NP + 3) * kRow : (NP + 2) * kRow;      // bytes of one device record
     // rows of end times and device times: 16 bits with masks by code (the host sees that they fit)
     constexpr uint32_t SROW = CODES ? kRow / 2 : kRow;
     const uint32_t lane_s = CODES ? (uint32_t)lane * 2u : lane4;
@@ -277,6 +283,101 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
         if (whole && (total & 1)) prog[(size_t)full * kProgRow] = step();
     };
 
+    // ---------------------------------------------------------------- graphs on masks by code
+    // The same with two producers and two consumers a type (KIND 5): W0 and W1 types for which a micro-batch of the first, of the second
+    // producer waits (of one that is not there: always), so that W0 & W1 & ~X may run.  A device's record: order and entries left; the
+    // waiting micro-batches, five bits a producer; leads and memory.
+    auto build_graph = [&](uint32_t ka, uint32_t kb, bool valid, uint32_t *prog, int &status, int &worst, bool &whole) {
+        constexpr uint32_t TS = 128u;                            // bytes of one table word over all codes
+        uint32_t W0 = G.free0, W1 = G.free1, HM = 0, X = 0;
+        // ---- leads, four bits a type, consumers before producers
+        uint64_t leads = 0;
+        if (P.has_fixed)
+            for (int g = 0; g < K; g++) leads |= (uint64_t)P.fixed[g] << (4 * g);
+        else {
+            uint32_t lead = 0, at = ~0u, word = 0;
+            for (int k = 0; k < G.nlead; k++) {
+                const uint32_t E = G.lead_edge[k], src = E & 255u, dst = E >> 8 & 255u, e = E >> 16 & 255u;
+                if (E >> 25 & 1u) lead = 0;
+                uint32_t stepped = 0;
+                if (E >> 24 & 1u) {
+                    const uint32_t wi = (kDrawLeadBase + e) >> 1;
+                    if (wi != at) { word = stream_word(ka, kb, wi); at = wi; }
+                    stepped = ((e & 1u) ? word >> 16 : word & 0xFFFFu) < P.step_q16 ? 1u : 0u;
+                }
+                lead = max(lead, ((uint32_t)(leads >> (4 * dst)) & 15u) + stepped);
+                if (E >> 26 & 1u) { lead = min(NR - 1u, lead); leads |= (uint64_t)lead << (4 * src); }
+            }
+        }
+        auto lead_of = [&](uint32_t g) -> uint32_t { return (uint32_t)(leads >> (4 * g)) & 15u; };
+        // ---- records
+        for (int d = 0; d < D; d++) {
+            const uint32_t ntd = (uint32_t)P.ntd[d], n = ntd * NR;
+            Planes<1> o;
+            sampled_order<1>(ka, kb, d, ntd, NR, o);
+            const uint32_t ra = rec0 + (uint32_t)d * RS;
+            lds_store(ra, o.p0 | ((1u << n) - 1u) << 16);        // (16 entries at most)
+            lds_store(ra + kRow, G.waits[d]);
+            lds_store(ra + 2 * kRow, 0u);
+            if (n) HM |= 1u << (2u * (uint32_t)d + (o.p0 & 1u));
+        }
+        for (int g = 0; g < K; g++)
+            lds_add(G.links[g][0] + kRow + lane4, (lead_of((uint32_t)g) << (G.links[g][1] & 31u)) + lead_of((uint32_t)g) * G.links[g][3]);
+        for (int k = 0; k < G.nedge; k++) {
+            const uint32_t E = G.edge[k], dst = E >> 8 & 255u, ahead = lead_of(E & 255u) - lead_of(dst), bit = min(ahead, 1u) << (G.links[dst][1] >> 8 & 31u);
+            lds_add(G.links[dst][0] + lane4, ahead << (E >> 16 & 31u));
+            if (E >> 24) W1 |= bit; else W0 |= bit;
+        }
+        // ---- blocks in an executable sequence
+        bool building = REPAIR || valid;
+        const uint32_t last_dev = ((uint32_t)D - 1u) << 1;
+        auto step = [&]() -> uint32_t {
+            const uint32_t R = __builtin_amdgcn_bitop3_b32(W0, W1, X, 0x40), hm = R & HM, sel = hm ? hm : (REPAIR ? R : 0u);        // a & b & ~c
+            if (!REPAIR && building && sel == 0) { status = kDeadlock; building = false; }
+            uint32_t d0 = low_bit(sel) & ~1u;                    // the device's first code
+            d0 = REPAIR ? min(d0, last_dev) : building ? d0 : 0u;
+            TESSEL_PIN(d0);
+            const uint32_t ra = __umul24(d0, RS / 2) + rec0;
+            const uint32_t p0 = lds_load(ra), w = lds_load(ra + kRow), l = lds_load(ra + 2 * kRow), alive = p0 >> 16;
+            const uint32_t may = R >> d0;
+            const uint32_t gate = bfi(p0, (uint32_t)__builtin_amdgcn_sbfe((int)may, 1, 1), (uint32_t)__builtin_amdgcn_sbfe((int)may, 0, 1));
+            const uint32_t p = low_bit(alive & gate), ly = (uint32_t)__builtin_amdgcn_sbfe((int)p0, p, 1), c = d0 - ly, ca = c << 2;
+            const uint32_t t_add = lds_load(ca), t_mem = lds_load(ca + TS), t_next0 = lds_load(ca + 2 * TS), t_next1 = lds_load(ca + 3 * TS);
+            const uint32_t t_at = lds_load(ca + 4 * TS), t_inc = lds_load(ca + 5 * TS), t_at2 = lds_load(ca + 6 * TS), t_inc2 = lds_load(ca + 7 * TS);
+            // (worked out while the table words are on their way)
+            const uint32_t left = alive & ~(1u << p), q = low_bit(left), y2 = __builtin_amdgcn_ubfe(p0, q, 1);
+            const uint32_t hm_new = (HM & ~(3u << d0)) | 1u << (d0 + y2), rest = left & ~(p0 ^ ly);
+            const uint32_t waits = w >> (ly & 10u), lead = __builtin_amdgcn_ubfe(l, ly & 4u, 4), onec = 1u << c;
+            const uint32_t w_new = w + t_add, l_new = l + t_mem;
+            uint32_t entry = 0;
+            if (REPAIR || building) {
+                lds_store(ra, p0 & ~(0x10000u << p));
+                lds_store(ra + kRow, w_new);
+                lds_store(ra + 2 * kRow, l_new);
+                lds_add((t_at & 0xFFFFu) + lane4, t_inc);        // (no such consumer: 0 to its own record)
+                lds_add(t_at2 + lane4, t_inc2);
+                worst = max(worst, (int)l_new >> 16);
+                W0 = (W0 & ~(waits & 30u ? 0u : onec)) | t_next0;
+                W1 = (W1 & ~(waits & (30u << 5) ? 0u : onec)) | t_next1;
+                X |= rest == 0 ? onec : 0u;
+                HM = hm_new;
+                entry = ((lead - (uint32_t)__builtin_popcount(rest)) << 9) + (t_at >> 16);       // 8 type, micro-batch << 9
+            }
+            return entry;
+        };
+        const int full = total / 2;
+        whole = true;
+        for (int wi = 0; wi < full; wi++) {
+            const uint32_t e0 = step(), e1 = step();
+            prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
+            if (!REPAIR || (wi & 7) == 7) {
+                const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
+                if (__ballot(going) == 0) { whole = false; break; }
+            }
+        }
+        if (whole && (total & 1)) prog[(size_t)full * kProgRow] = step();
+    };
+
     // ---------------------------------------------------------------- build: 64 new candidates
     auto build = [&](uint64_t idx, bool valid) {
         uint32_t slot = 0;
@@ -291,7 +392,8 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
         if (sampled) ka = stream_keys(P.seed, idx, kb);
         int worst = INT_MIN;
         bool any = true, whole = true;
-        if constexpr (CODES) build_codes(ka, kb, valid, prog, status, worst, whole);
+        if constexpr (GRAPH) build_graph(ka, kb, valid, prog, status, worst, whole);
+        else if constexpr (CODES) build_codes(ka, kb, valid, prog, status, worst, whole);
         else {
         lds_store(G.trash + lane4, 0u);
         // ---- leads, by type
@@ -675,43 +777,50 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
         // which it takes from a register where they share the device or the ring entry (end times only grow, so the largest of the
         // three is right): the reads' latency, two thirds of a block's time at one to three waves a SIMD, overlaps.
         auto codes_word = [&](const uint32_t (&cur)[4], int left) {
-            constexpr uint32_t table = W64 ? 6u * 256u : (NP <= 1 ? 4u : 5u) * 128u;       // (GraphTab::sw)
-            uint32_t da[8], ta[8], t[8];
+            // (GraphTab::sw)
+            constexpr uint32_t table = GRAPH ? 8u * 128u : W64 ? 6u * 256u : (NP <= 1 ? 4u : 5u) * 128u;
+            uint32_t da[8], ta[8], t[8], pa[8], pb[8];           // (graphs: ta is written only, and the two producers' entries are read)
             auto look_up = [&](bool all) {
-                uint32_t e[8], B[8];
+                uint32_t e[8], B[8], from[8];
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
                     // (a word past the last block was never written: its type is taken as 0, and nothing of it is used)
                     e[q] = !all && q >= left ? 0u : q & 1 ? cur[q / 2] >> 16 : cur[q / 2] & 0xFFFFu;
-                    lds_load2((e[q] & 0x1F8u) + table, t[q], B[q]);
+                    const uint32_t at = GRAPH ? ((e[q] & 0x1F8u) << 1) + table : (e[q] & 0x1F8u) + table;
+                    lds_load2(at, t[q], B[q]);
+                    from[q] = GRAPH ? lds_load(at + 8u) : 0u;
                 }
                 __builtin_amdgcn_sched_barrier(0);               // (all eight on their way before the first is waited for)
 #pragma unroll
                 for (int q = 0; q < 8; q++) {
                     da[q] = (B[q] & 0xFFFFu) + lane_s;
-                    ta[q] = (B[q] >> 16) + ((e[q] >> 2 & 0xF80u) | lane_s);
+                    const uint32_t mu = (e[q] >> 2 & 0xF80u) | lane_s;
+                    ta[q] = (B[q] >> 16) + mu;
+                    pa[q] = GRAPH ? (from[q] & 0xFFFFu) + mu : ta[q];
+                    pb[q] = GRAPH ? (from[q] >> 16) + mu : 0u;
                 }
             };
-            uint32_t fr, tk, before = 0;
+            uint32_t fr, tk, tk_b = 0, before = 0;
             auto one = [&](int q, bool more) {
-                uint32_t fr2 = 0, tk2 = 0;
-                if (more) { fr2 = time_load(da[q + 1]); tk2 = time_load(ta[q + 1]); }
+                uint32_t fr2 = 0, tk2 = 0, tk_b2 = 0;
+                if (more) { fr2 = time_load(da[q + 1]); tk2 = time_load(pa[q + 1]); if (GRAPH) tk_b2 = time_load(pb[q + 1]); }
                 __builtin_amdgcn_sched_barrier(0);
-                const bool shared = q > 0 && (da[q] == da[q - (q > 0)] || ta[q] == ta[q - (q > 0)]);
-                const uint32_t en = max(max(fr, tk), shared ? before : 0u) + t[q];
+                const uint32_t wrote = ta[q - (q > 0)];
+                const bool shared = q > 0 && (da[q] == da[q - (q > 0)] || pa[q] == wrote || (GRAPH && pb[q] == wrote));
+                const uint32_t en = max(max(GRAPH ? max(fr, tk_b) : fr, tk), shared ? before : 0u) + t[q];
                 time_store(da[q], en);
                 time_store(ta[q], en);
                 __builtin_amdgcn_sched_barrier(0);
-                before = en; fr = fr2; tk = tk2;
+                before = en; fr = fr2; tk = tk2; tk_b = tk_b2;
             };
             if (left >= 8) {
                 look_up(true);
-                fr = time_load(da[0]); tk = time_load(ta[0]);
+                fr = time_load(da[0]); tk = time_load(pa[0]); if (GRAPH) tk_b = time_load(pb[0]);
 #pragma unroll
                 for (int q = 0; q < 8; q++) one(q, q < 7);
             } else {
                 look_up(false);
-                fr = time_load(da[0]); tk = time_load(ta[0]);
+                fr = time_load(da[0]); tk = time_load(pa[0]); if (GRAPH) tk_b = time_load(pb[0]);
 #pragma unroll
                 for (int q = 0; q < 7; q++) if (q < left) one(q, q + 1 < left);
             }
@@ -923,6 +1032,7 @@ template <bool REPAIR>
 static graph_fn pick_kind(const KParams &kp)
 {
     if (kp.tp) return pick_np<REPAIR, 2>(kp.graph_np);
+    if (kp.graph_codes == 3) return eval_graph_kernel<0, REPAIR, 5>;
     if (kp.graph_codes) return kp.graph_codes == 1 ? pick_np<REPAIR, 3>(kp.graph_np) : pick_np<REPAIR, 4>(kp.graph_np);
     return kp.graph_chain ? pick_np<REPAIR, 0>(kp.graph_np) : pick_np<REPAIR, 1>(kp.graph_np);
 }
