@@ -10,7 +10,7 @@ import tempfile
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "libtessel_hip.so")
-SOURCES = ["tessel_kernels.hip", "tessel_wide.hip", "tessel_graph.hip", "tessel_detail.hip", "tessel_api.cpp"]
+SOURCES = ["tessel_kernels.hip", "tessel_wide.hip", "tessel_graph.hip", "tessel_mail.hip", "tessel_api.cpp"]
 HEADERS = ["tessel_device.h", "tessel_common.h", os.path.join("..", "..", "include", "tessel.h")]
 
 HIPCC_FLAGS = [

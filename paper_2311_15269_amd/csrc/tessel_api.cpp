@@ -45,7 +45,7 @@ struct tessel_problem {
     int last_hip = 0;
     bool force_general = false;         // TESSEL_FORCE_GENERAL=1: score with the general kernel only
     bool mail = true;                   // TESSEL_MAIL=0 (test knob): results are copied, as where no box is free
-    DevDetail detail;
+    Detail detail;
     DevResult result;
     std::vector<int32_t> starts;        // least start times of the decoded candidate, by type * N_R + occurrence
     bool period_right = false;          // ... and whether the record's period is its least one
@@ -929,12 +929,6 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
     if (!p->force_general && !getenv("TESSEL_FAR_MODE")) graph_tables(*p, p->graph);
     kp.graph_ok = p->graph.ok; kp.graph_np = p->graph.np; kp.graph_codes = p->graph.codes; kp.graph_chain = p->graph.chain; kp.graph_lds = p->graph.lds_bytes;
     kp.graph_slot_words = (uint32_t)(p->graph.meta + p->graph.nwords);
-    {
-        int most_types = 0, most_in = 0;
-        for (int d = 0; d < D; d++) most_types = std::max(most_types, (int)kp.ntd[d]);
-        for (int i = 0; i < K; i++) most_in = std::max(most_in, kp.dag ? __builtin_popcountll(kp.predmask[i]) : 1);
-        kp.detail_lanes = detail_lanes(D, most_types, most_in);
-    }
     if (desc->space == TESSEL_SPACE_CANONICAL) {
         size_t orders, leadrows;
         kp.ranked = ranked_sizes(*p, orders, leadrows);
@@ -1168,7 +1162,7 @@ void sort_edges(Window &w, const std::vector<int> &rank)
 }
 
 // `rank`: number of block type * N_R + occurrence in the window; false: the device orders cannot be executed
-bool make_window(const tessel_problem *p, const DevDetail &c, Window &w, std::vector<int> &rank)
+bool make_window(const tessel_problem *p, const Detail &c, Window &w, std::vector<int> &rank)
 {
     const int NR = p->kp.NR, K = p->kp.K, D = p->kp.D;
     w.blocks = K * NR; w.most = p->kp.UB;
@@ -1229,6 +1223,163 @@ bool is_least_period(const Window &w, int T, std::vector<int> &s)
     std::vector<int> other;
     if (!in_sequence(w, [&](const Edge &e) { return s[e.u] + e.w - e.lag * T == s[e.v]; }, other)) return true;
     return !least_starts(w, T - 1, other);
+}
+
+// ---- the candidate of the running best -----------------------------------------------------------------------------
+// Leads, device orders after repair and peaks of one candidate from its index.  The blocks of one candidate follow one another, a few
+// dependent instructions each: 256 blocks on 8 devices take a core 10 us, and took a wave of the GPU, a lane for every block
+// type of every device, 38 (a call that scores 200,003 candidates of 16 devices and asks for the best 336 -> 307 us).
+void decode_candidate(const tessel_problem *p, uint64_t idx, Detail &c)
+{
+    const KParams &kp = p->kp;
+    const int D = kp.D, K = kp.K, NR = kp.NR;
+    const bool sampled = kp.space == kSampledStrict || kp.space == kSampledRepair;
+    uint8_t type[kMaxDW][kMaxLTW] = {}, order[kMaxDW][kMaxPos];
+    for (int d = 0; d < D; d++)
+        for (int y = 0; y < kp.ntd[d]; y++) type[d][y] = (uint8_t)((y < 4 ? kp.type_of[d] >> (8 * y) : kp.type_of_hi[d] >> (8 * (y - 4))) & 0xFFu);
+    memset(&c, 0, sizeof c);
+    c.index = idx;
+    // producers and consumers
+    uint64_t producers[kMaxKW] = {}, consumers[kMaxKW] = {};
+    for (size_t e = 0; e < p->dep_src.size(); e++) {
+        producers[p->dep_dst[e]] |= 1ull << p->dep_src[e];
+        consumers[p->dep_src[e]] |= 1ull << p->dep_dst[e];
+    }
+    // ---- orders as drawn or unranked
+    uint32_t ka = 0, kb = 0;
+    if (sampled) ka = stream_keys(kp.seed, idx, kb);
+    uint64_t rest = idx;
+    for (int d = 0; d < D; d++) {
+        const int types = kp.ntd[d], n = types * NR;
+        if (sampled) {
+            int left[kMaxLTW];
+            for (int y = 0; y < types; y++) left[y] = NR;
+            uint32_t word = 0;
+            for (int pos = 0; pos < n; pos++) {
+                const uint32_t j = kDrawOrdBase + 32u * (uint32_t)d + (uint32_t)pos;
+                if ((pos & 1) == 0) word = stream_word(ka, kb, j >> 1);
+                int digit = (int)((((word >> (16u * (j & 1u))) & 0xFFFFu) * (uint32_t)(n - pos)) >> 16), y = 0;
+                while (digit >= left[y]) digit -= left[y++];
+                left[y]--;
+                order[d][pos] = (uint8_t)y;
+            }
+        } else if (kp.space == kCanonical) {
+            const uint32_t B = (uint32_t)NR + 1;
+            uint64_t r = rest % kp.cdev[d];
+            rest /= kp.cdev[d];
+            uint32_t left[kMaxLT];
+            for (int y = 0; y < kMaxLT; y++) left[y] = y < types ? (uint32_t)NR : 0u;
+            for (int pos = 0; pos < n; pos++)
+                for (int y = 0; y < types; y++) {
+                    if (left[y] == 0) continue;
+                    left[y]--;
+                    const uint64_t w = p->wtab[((left[0] * B + left[1]) * B + left[2]) * B + left[3]];
+                    if (r < w) { order[d][pos] = (uint8_t)y; break; }
+                    r -= w;
+                    left[y]++;
+                }
+        } else {
+            uint32_t r = (uint32_t)(rest % kp.cdev[d]);
+            rest /= kp.cdev[d];
+            uint64_t list = kp.init_list[d];
+            bool seen[kMaxLT] = {};
+            for (int pos = 0; pos < n; pos++) {
+                const uint32_t f = kp.fact[n - 1 - pos], digit = r / f;
+                r -= digit * f;
+                const uint32_t code = (uint32_t)(list >> (5u * digit)) & 31u, y = code >> 3;
+                const uint64_t low = list & ((1ull << (5u * digit)) - 1ull);
+                list = low | (((list >> (5u * digit)) >> 5) << (5u * digit));
+                order[d][pos] = (uint8_t)y;
+                if (!seen[y]) { c.leads[type[d][y]] = (int)(code & 7u); seen[y] = true; }       // (one lead per type: the candidate is feasible)
+            }
+        }
+    }
+    // ---- leads
+    if (kp.space == kCanonical)
+        for (int g = 0; g < K; g++) c.leads[g] = p->leadtab[rest * (uint64_t)K + (uint64_t)g];
+    else if (sampled && kp.has_fixed)
+        for (int g = 0; g < K; g++) c.leads[g] = kp.fixed[g];
+    else if (sampled) {
+        // the least solution of lead = min(N_R - 1, largest consumer's lead + step)
+        uint8_t step[kMaxDeps];
+        const int deps = (int)p->dep_src.size();
+        for (int e = 0; e < deps; e++)
+            step[e] = p->mask[p->dep_src[e]] != p->mask[p->dep_dst[e]] && stream_draw16(ka, kb, kDrawLeadBase + (uint32_t)e) < kp.step_q16;
+        for (bool grew = true; grew;) {
+            grew = false;
+            for (int e = deps - 1; e >= 0; e--) {
+                const int v = std::min(NR - 1, c.leads[p->dep_dst[e]] + step[e]);
+                if (v > c.leads[p->dep_src[e]]) { c.leads[p->dep_src[e]] = v; grew = true; }
+            }
+        }
+    }
+    // ---- blocks in an executable sequence: heads first, else (repair) the lowest device's earliest that may run
+    uint32_t alive[kMaxDW], at[kMaxDW][kMaxLTW] = {};               // entries not yet placed, by device and by type
+    uint64_t here[kMaxDW] = {};                                     // the types of a device
+    int mem[kMaxDW], mu[kMaxKW], lists[kMaxKW] = {};                // memory now; next micro-batch; devices whose list the type heads
+    uint64_t may = 0, heads = 0;                                    // types that may run; that head all their devices
+    uint8_t home[kMaxKW] = {}, symbol[kMaxKW] = {};                 // lowest device and symbol there
+    auto look = [&](int g) {
+        bool ok = mu[g] < c.leads[g] + NR;
+        for (uint64_t a = producers[g]; ok && a; a &= a - 1) ok = mu[__builtin_ctzll(a)] > mu[g];
+        may = (may & ~(1ull << g)) | (uint64_t)ok << g;
+    };
+    auto new_head = [&](int d) {
+        if (!alive[d]) return;
+        const int g = type[d][order[d][__builtin_ctz(alive[d])]];
+        if (++lists[g] == __builtin_popcount(p->mask[g])) heads |= 1ull << g;
+    };
+    for (int g = 0; g < K; g++) mu[g] = c.leads[g];
+    for (int g = 0; g < K; g++) look(g);
+    for (int d = D - 1; d >= 0; d--) {
+        const int n = kp.ntd[d] * NR;
+        alive[d] = n >= 32 ? 0xFFFFFFFFu : (1u << n) - 1u;
+        mem[d] = 0;
+        c.peak[d] = INT_MIN;
+        for (int pos = 0; pos < n; pos++) at[d][order[d][pos]] |= 1u << pos;
+        for (int y = 0; y < kp.ntd[d]; y++) {
+            const int g = type[d][y];
+            here[d] |= 1ull << g; home[g] = (uint8_t)d; symbol[g] = (uint8_t)y;
+            mem[d] += kp.m_of[d][y] * c.leads[g];
+        }
+        new_head(d);
+    }
+    // takes the earliest entry of type g out of device d's list
+    auto take = [&](int g, int d, int y) {
+        const uint32_t first = alive[d] & (0u - alive[d]), bit = at[d][y] & (0u - at[d][y]);
+        at[d][y] ^= bit;
+        alive[d] ^= bit;
+        if (bit == first) { lists[g]--; heads &= ~(1ull << g); new_head(d); }
+        mem[d] += kp.m_of[d][y];
+        c.peak[d] = std::max(c.peak[d], mem[d]);
+        c.orders[d][c.order_len[d]++] = (uint8_t)g;
+    };
+    auto place = [&](int g) {
+        take(g, home[g], symbol[g]);
+        for (uint32_t on = p->mask[g] & (p->mask[g] - 1); on; on &= on - 1) {
+            const int d = __builtin_ctz(on);
+            int y = 0;
+            while (type[d][y] != g) y++;
+            take(g, d, y);
+        }
+        mu[g]++;
+        look(g);
+        for (uint64_t s = consumers[g]; s; s &= s - 1) look(__builtin_ctzll(s));
+    };
+    c.status = kOk;
+    for (int placed = 0; placed < kp.total; placed++) {
+        if (const uint64_t now = may & heads) { place(__builtin_ctzll(now)); continue; }
+        int d = 0;
+        if (kp.space == kSampledRepair) while (d < D && !(here[d] & may)) d++;
+        if (kp.space != kSampledRepair || d == D) { c.status = kDeadlock; break; }
+        uint32_t can = 0;
+        for (int y = 0; y < kp.ntd[d]; y++) can |= may >> type[d][y] & 1 ? at[d][y] : 0u;
+        place(type[d][order[d][__builtin_ctz(can)]]);
+    }
+    for (int d = 0; d < D; d++) {
+        if (c.peak[d] == INT_MIN) c.peak[d] = 0;                    // a device without blocks
+        if (c.status == kOk && c.peak[d] > kp.M) c.status = kMem;
+    }
 }
 
 // p->starts and p->period_right of the running best just read
@@ -1327,34 +1478,27 @@ private:
 }  // namespace
 
 // The running best as it is on the device, into p->result and p->detail.  The record is read on every call: scoring
-// launches that the caller captured in a graph change it when they are replayed, without a call of this library.
-// One launch: the candidate is decoded on the device from the record there, unless the workspace has it already; record and
-// candidate come back by mail, the record alone where it names the candidate this handle has.
+// launches that the caller captured in a graph change it when they are replayed, without a call of this library.  It names its
+// candidate by the index, from which the host decodes it unless it did before.
 static int read_back(tessel_problem *p)
 {
+    DevResult now;
     Mailbox mail(p->mail);
-    int le = launch_detail(p->kp, p->ws, mail.box, mail.told, p->result.period, p->result.index, p->stream);
-    if (mail.box) le = mail.wait(le, p->stream);
-    if (le) return hip_fail(p, le);
     if (mail.box) {
-        memcpy(&p->result, mail.box->words, sizeof p->result);
-        if (!mail.box->whole) return TESSEL_OK;
-        memcpy(&p->detail, mail.box->words + kMailDetail, sizeof p->detail);
+        const int le = mail.wait(launch_tell(p->ws, kWsResultOff, sizeof now, mail.box, mail.told, p->stream), p->stream);
+        if (le) return hip_fail(p, le);
+        memcpy(&now, mail.box->words, sizeof now);
     } else {
-        struct { unsigned char bytes[kWsDetailOff]; DevDetail detail; } both;
-        static_assert(offsetof(decltype(both), detail) == kWsDetailOff && kWsResultOff == 0, "result and detail are copied in one piece");
-        hipError_t e = hipMemcpyAsync(&both, p->ws, sizeof both, hipMemcpyDeviceToHost, p->stream);
+        hipError_t e = hipMemcpyAsync(&now, (char *)p->ws + kWsResultOff, sizeof now, hipMemcpyDeviceToHost, p->stream);
         if (e != hipSuccess) return hip_fail(p, (int)e);
         e = hipStreamSynchronize(p->stream);
         if (e != hipSuccess) return hip_fail(p, (int)e);
-        DevResult now;
-        memcpy(&now, both.bytes, sizeof now);
-        const bool known = now.period != INT_MAX && now.period == p->result.period && now.index == p->result.index;
-        p->result = now;
-        if (known) return TESSEL_OK;
-        p->detail = both.detail;
     }
-    if (p->result.period != INT_MAX) check_period(p);
+    const bool known = now.period == p->result.period && now.index == p->result.index;
+    p->result = now;
+    if (now.period == INT_MAX || known) return TESSEL_OK;
+    decode_candidate(p, now.index, p->detail);
+    check_period(p);
     return TESSEL_OK;
 }
 
@@ -1410,7 +1554,7 @@ extern "C" int tessel_best_candidate(tessel_problem *p, int32_t *leads, int32_t 
     int rc = fetch_best(p);
     if (rc) return rc;
     if (p->result.period == INT_MAX) return TESSEL_E_NO_FEASIBLE;
-    const DevDetail &c = p->detail;
+    const Detail &c = p->detail;
     if (leads) for (int i = 0; i < p->kp.K; i++) leads[i] = c.leads[i];
     if (order_len) for (int d = 0; d < p->kp.D; d++) order_len[d] = c.order_len[d];
     if (orders) for (int d = 0; d < p->kp.D; d++) for (int k = 0; k < kMaxPos; k++) orders[d * kMaxPos + k] = k < c.order_len[d] ? c.orders[d][k] : -1;
@@ -1431,7 +1575,7 @@ extern "C" int tessel_best_candidate(tessel_problem *p, int32_t *leads, int32_t 
 // J = 0: the plain greedy schedule.  Per phase every type offers its lowest unscheduled micro-batch.
 static int complete_with(tessel_problem *p, tessel_schedule *out, uint64_t ordinal, int J)
 {
-    const DevDetail &c = p->detail;
+    const Detail &c = p->detail;
     const int N = out->num_microbatches, K = p->kp.K, D = p->kp.D, NR = p->kp.NR, M = p->kp.M;
     int maxlead = 0;
     for (int i = 0; i < K; i++) maxlead = std::max(maxlead, c.leads[i]);
@@ -1594,7 +1738,7 @@ static int bind_completion(tessel_problem *p, int N, int J)
     if (rc) return rc;
     if (p->result.period == INT_MAX) return TESSEL_E_NO_FEASIBLE;
     if (p->comp_ready && p->comp_index == p->result.index && p->comp.N == N && p->comp.J == J) return TESSEL_OK;
-    const DevDetail &c = p->detail;
+    const Detail &c = p->detail;
     const int K = p->kp.K, D = p->kp.D, NR = p->kp.NR;
     if (N < 1 || J < 0 || J > 65535) return TESSEL_E_INVALID_ARG;
     int maxlead = 0;

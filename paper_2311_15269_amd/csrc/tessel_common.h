@@ -19,9 +19,6 @@ struct BlockRec {
     uint32_t n_high;             // (sums of records) bits of n_sweeps above 32 << 16 | those of n_blocks
 };
 
-constexpr uint32_t kDrawLeadBase = 0u;
-constexpr uint32_t kDrawOrdBase = 128u;
-
 __device__ __forceinline__ uint32_t byte_of(uint32_t packed, uint32_t y) { return (packed >> (8u * y)) & 0xFFu; }
 
 __device__ __forceinline__ bool key_less(int pa, uint64_t ia, int pb, uint64_t ib)

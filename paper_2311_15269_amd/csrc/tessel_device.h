@@ -43,6 +43,7 @@ TESSEL_HD uint32_t stream_draw16(uint32_t ka, uint32_t kb, uint32_t j)
 {
     return (stream_word(ka, kb, j >> 1) >> (16u * (j & 1u))) & 0xFFFFu;
 }
+constexpr uint32_t kDrawLeadBase = 0u, kDrawOrdBase = 128u;    // first draw of the lead steps, of device 0's order (32 a device)
 constexpr uint64_t kCompletionKey = 0x632BE59BD9B4E019ULL;      // separates the completion stream from the candidates'
 
 constexpr int kMaxD = 8;         // simulated devices of the problems the fast kernel and the chain path of the general one take
@@ -154,8 +155,6 @@ struct KParams {
     int32_t  graph_codes;        // GraphTab::codes
     uint32_t graph_lds;          // GraphTab::lds_bytes
     uint32_t graph_slot_words;   // words of one candidate's slot: GraphTab::meta + nwords
-    int32_t  detail_lanes;       // log2 of the lanes a device takes in the wave that decodes the best candidate (one per type on it),
-                                 // -1: its devices, types or producers do not fit one wave so
     int32_t  many;               // some device holds more than kMaxLT block types (3-bit symbols; sampled spaces only)
     const int8_t   *leadtab;     // CANONICAL: [nlead][K] in device memory
     const uint64_t *wtab;        // CANONICAL: arrangements by remaining counts, base NR+1 digits
@@ -194,9 +193,9 @@ struct DevResult {
     uint64_t n_blocks;               // blocks placed by the builds of the fast kernel
 };
 
-// Decoded best candidate, written by the detail kernel.
-struct DevDetail {
-    int32_t status, pad;         // status -1: nothing decoded since the search began
+// Decoded best candidate, on the host.
+struct Detail {
+    int32_t status;
     uint64_t index;
     int32_t peak[kMaxDW];
     int32_t leads[kMaxKW];
@@ -205,16 +204,13 @@ struct DevDetail {
 };
 
 // What a result call is told, written by the GPU into pinned host memory: words from the device, then `told` as the last one.
-constexpr int kMailWords = 512;
+constexpr int kMailWords = 48;
 struct DevMail {
     uint32_t told;                   // the number the host gave with the launch, once everything else is there
-    uint32_t whole;                  // the decoded candidate is there too (else only the record: the host has that candidate)
-    uint32_t pad[14];
-    uint32_t words[kMailWords];      // DevResult, at kMailDetail DevDetail; or a completion's record
+    uint32_t pad[15];
+    uint32_t words[kMailWords];      // DevResult, or a completion's record
 };
-constexpr int kMailDetail = 64;
-static_assert(sizeof(DevResult) <= kMailDetail * 4 && kMailDetail * 4 + sizeof(DevDetail) <= kMailWords * 4, "mail holds record and candidate");
-static_assert(sizeof(DevResult) % 4 == 0 && sizeof(DevDetail) % 4 == 0, "mail is sent by words");
+static_assert(sizeof(DevResult) <= kMailWords * 4 && sizeof(DevResult) % 4 == 0, "mail holds a record, by words");
 
 // Searched completion (warm-up / cool-down orders as perturbed greedy schedules around the best window):
 // what the kernel needs of the problem and of the best candidate, by block type, and the running best.
@@ -257,7 +253,6 @@ struct CompRec { int32_t makespan; int32_t pad; uint64_t ordinal; };
 
 constexpr size_t kWsResultOff = 0;
 constexpr size_t kWsCompletionOff = 192;       // DevCompletion
-constexpr size_t kWsDetailOff = 256;
 constexpr size_t kWsLeftOff = 7936;            // by program word, how many of the candidates one wave in 16 built first were alive after it
 constexpr size_t kWsParamsOff = 8192;          // KParams of the bound problem
 constexpr size_t kWsTablesOff = 16384;         // lead table, arrangement table
@@ -283,10 +278,10 @@ constexpr int kStageMetaWords = 12;                             // ring 1: R, HM
                                                                 // the device records (4 words each) and the program so far
 
 static_assert(sizeof(CompParams) <= 1024, "completion parameters must fit their workspace slot");
-static_assert(sizeof(DevResult) <= kWsCompletionOff && kWsCompletionOff + sizeof(DevCompletion) <= kWsDetailOff, "result records overlap");
+static_assert(sizeof(DevResult) <= kWsCompletionOff && kWsCompletionOff + sizeof(DevCompletion) <= kWsLeftOff, "result records overlap");
 static_assert(sizeof(CompParams) <= 1024 && sizeof(CompMatrix) <= 3072, "completion parameters must fit their workspace slots");
 static_assert(sizeof(KParams) <= kWsTablesOff - kWsParamsOff, "parameter block must fit its workspace slot");
-static_assert(sizeof(DevDetail) <= kWsLeftOff - kWsDetailOff && kWsLeftOff + kWave * 4 <= kWsParamsOff, "detail record must fit its workspace slot");
+static_assert(kWsLeftOff + kWave * 4 <= kWsParamsOff, "histogram must fit its workspace slot");
 
 // ------------------------------------------------------------------ the graph kernel (tessel_graph.hip)
 // Problems the fast kernel does not take (graphs with fan-in or fan-out, more than 8 devices, 32 types, 4 types on a
@@ -356,13 +351,8 @@ struct LaunchShape { int blocks, list_blocks, threads; size_t lds_bytes; };   //
 const void *graph_kernel(const KParams &kp);
 int launch_graph(const KParams &kp, uint64_t first, uint64_t count, int blocks, void *recs, int32_t *code, int32_t *peak, void *ws,
                  uint32_t *slots, void *stream);
-// tessel_detail.hip: decodes the candidate of the running best (if there is one) into the workspace's DevDetail
-// `mail` (may be null): record and candidate go there too, the candidate only if the record names another than `known_index`
-// at `known_period` (INT32_MAX: none)
-int launch_detail(const KParams &kp, void *ws, DevMail *mail, uint32_t told, int32_t known_period, uint64_t known_index, void *stream);
-// `bytes` of the workspace from `offset` on (multiples of four) to `mail`
+// tessel_mail.hip: `bytes` of the workspace from `offset` on (multiples of four) to `mail`
 int launch_tell(void *ws, size_t offset, size_t bytes, DevMail *mail, uint32_t told, void *stream);
-int detail_lanes(int devices, int most_types, int most_producers);    // KParams::detail_lanes
 // kernels.hip
 // max_blocks: 0, or the most workgroups the workspace has queues for
 LaunchShape eval_launch_shape(const KParams &kp, int num_cus, int max_blocks);

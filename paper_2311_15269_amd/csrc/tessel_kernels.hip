@@ -2344,10 +2344,9 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const BlockRec *__
     for (int s = 0; s < kNumStatus; s++) res->n_status[s] += a.cnt[s];
 }
 
-__global__ void reset_kernel(DevResult *res, DevDetail *detail, uint32_t *left_after)
+__global__ void reset_kernel(DevResult *res, uint32_t *left_after)
 {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
-        detail->status = -1;                     // no candidate decoded yet
         for (int w = 0; w < kWave; w++) left_after[w] = 0;
         res->period = INT_MAX; res->pad = 0; res->index = ~0ull; res->n_evaluated = 0; res->n_sweeps = 0; res->n_blocks = 0;
         res->n_retried = 0; res->n_deferred = 0; res->overflow = 0; res->defer_count = 0; res->arrived = 0;
@@ -2713,7 +2712,7 @@ int launch_score(const KParams &kp, uint64_t first, uint64_t count, int32_t *cod
 int launch_reset(void *ws, void *stream)
 {
     hipLaunchKernelGGL(reset_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, (DevResult *)((char *)ws + kWsResultOff),
-                       (DevDetail *)((char *)ws + kWsDetailOff), (uint32_t *)((char *)ws + kWsLeftOff));
+                       (uint32_t *)((char *)ws + kWsLeftOff));
     return (int)hipGetLastError();
 }
 
