@@ -188,6 +188,7 @@ static bool code_tables(const tessel_problem &p, GraphTab &gt, const std::vector
     gt.lds_bytes = std::max(build_end, at);
     memset(gt.tab, 0, sizeof gt.tab);
     gt.codes = ts == 256 ? 2 : 1;
+    gt.apart = 1;                                            // (a chain's types share its ring: KParams::ring_kept)
     gt.np = packed ? 0 : nb;
     gt.code_rows = (uint32_t)rows;
     std::vector<int> code(K, 0);
@@ -261,12 +262,19 @@ static bool graph_code_tables(const tessel_problem &p, GraphTab &gt, const std::
     const uint32_t build_end = at + (uint32_t)(D * rows) * row;
     gt.state = at; at += (uint32_t)kp.nslots * half;
     gt.prev = at; at += (uint32_t)D * half;
-    gt.strash = at; at += (uint32_t)(2 * NR) * half;             // (a ring that nobody reads)
+    const uint32_t apart = at;
+    for (int r = 0; r < kp.ntok; r++) if (kp.ring_kept[r] == kp.ring_base[r]) at += (uint32_t)NR * half;
+    gt.apart_rows = (int)((at - apart) / half);
+    // (a ring that nobody reads: a type without consumers is N_R micro-batches from its lead on, which is 0 unless it is fixed)
+    gt.strash = at; at += (uint32_t)(kp.has_fixed ? 2 * NR : NR) * half;
     at = (at + row - 1) / row * row;
     gt.leads = at; at += (uint32_t)((kp.ntok + 3) / 4) * row;
-    if (std::max(build_end, at) > 64 * 1024 - row) return false;
+    if (std::max(build_end, at) > 64 * 1024 - row) { gt.apart_rows = 0; return false; }
     gt.lds_bytes = std::max(build_end, at);
     memset(gt.tab, 0, sizeof gt.tab);
+    gt.apart = 1;
+    for (uint32_t r = 0, row_at = (apart - gt.state) / half; r < (uint32_t)kp.ntok; r++)
+        if (kp.ring_kept[r] == kp.ring_base[r]) { gt.ring[r] = (uint32_t)kp.ring_base[r] | row_at << 16; row_at += (uint32_t)NR; }
     gt.codes = 3;
     gt.np = 0;
     gt.code_rows = rows;

@@ -326,6 +326,8 @@ struct GraphTab {
     // 3: such graphs, with up to two producers and two consumers a type
     int32_t  codes;
     uint32_t code_rows;          // rows of a device record
+    int32_t  apart;              // the rows that keep the last boundary's values are no rings' own; how many of them
+    int32_t  apart_rows;         // lie behind the device times at the last boundary
     uint32_t free0, free1;       // graphs: codes without a first, a second producer
     uint32_t waits[kMaxDW];      // graphs: by device its word of waiting micro-batches where all producers have none ahead
     uint32_t links[kMaxKW][4];   // block types, every chain from its last to its first: address of the word with the type's waiting

@@ -79,9 +79,9 @@ def test_random_graphs(gpu, seed):
     _compare(gpu, random_graph(random.Random(1000 + seed), seed % 6 == 5), seed * 7919, 2000)
 
 
-@pytest.mark.parametrize("prob", [W.kshape_problem(4, 4), W.diamond_problem(3, 3)], ids=["kshape", "diamond"])
+@pytest.mark.parametrize("prob", [W.kshape_problem(4, 4), W.diamond_problem(3, 3), W.diamond_problem(4, 5)], ids=["kshape", "diamond-3", "diamond-4"])
 def test_many_rounds(gpu, monkeypatch, prob):
-    """several rounds a wave: slots are used again, stragglers wait for the longer search"""
+    """several rounds a wave: slots are used again, stragglers wait for the longer search; periods of cycles through two windows"""
     n = 700001
     got = []
     for words in (None, "1"):
