@@ -1681,32 +1681,37 @@ extern "C" int tessel_complete_schedule(tessel_problem *p, tessel_schedule *out)
 
 // ---- searched completion: many perturbed greedy completions scored on the GPU -----------------------
 // uploads what the kernel needs of the problem and of the best candidate (once per best candidate, N, J)
-// The R replayed windows as a (max, +) matrix (CompMatrix), for problems whose types sit on one device each and that
-// the kernel's per-type path takes.  A dry run of the replay finds the state slots read before they are written (the
+// The R replayed windows as a (max, +) matrix (CompMatrix).  A dry run of the replay finds the state slots read before they are written (the
 // inputs) and the slots written (the outputs); one run per input with that input at 0 and the others at "no path"
 // gives the longest paths.
 static void window_matrix(const CompParams &cp, CompMatrix &cm)
 {
     memset(&cm, 0, sizeof cm);
-    bool single = cp.npaths <= 8 && !cp.dag;
-    for (int i = 0; i < cp.K; i++) single = single && cp.mask[i] != 0 && (cp.mask[i] & (cp.mask[i] - 1)) == 0;
-    if (!single) return;
     const int TR = cp.tok_ring, tmask = TR - 1, oFree = cp.npaths * TR, nslot = oFree + cp.D;      // rings first, then the devices
-    struct Blk { int fr, tk, t; bool has_a; };
-    std::vector<Blk> blocks;
+    // what a block waits for and what it leaves its end time in: its devices, the entries of its producers and its own
+    std::vector<int> slots, wrote, times;
+    struct Span { int reads, writes; };                     // block b's in `slots` and `wrote`: from spans[b] on
+    std::vector<Span> spans(1, Span{0, 0});
     for (int k = 0; k < cp.R; k++)
         for (int s = 0; s < cp.nseq; s++) {
             const int i = cp.seq[s], mu = (int)cp.lead[i] + (int)cp.occ[s] + cp.NR * k;
-            blocks.push_back({oFree + __builtin_ctz((unsigned)cp.mask[i]), (int)cp.path[i] * TR + (mu & tmask), cp.t[i], cp.pred[i] >= 0});
+            auto entry = [&](int g) -> int { return (int)cp.path[g] * TR + (mu & tmask); };
+            for (unsigned on = cp.mask[i]; on; on &= on - 1) { slots.push_back(oFree + __builtin_ctz(on)); wrote.push_back(slots.back()); }
+            if (cp.dag) for (uint32_t rest = cp.predmask[i]; rest; rest &= rest - 1) slots.push_back(entry(__builtin_ctz(rest)));
+            else if (cp.pred[i] >= 0) slots.push_back(entry(i));
+            if (cp.path[i] != 0xFF) wrote.push_back(entry(i));
+            spans.push_back({(int)slots.size(), (int)wrote.size()});
+            times.push_back(cp.t[i]);
         }
+    const size_t n = times.size();
     std::vector<int> state(nslot, 0);                       // 0 untouched, 1 read first, 2 written first; then: written at all
     std::vector<char> written(nslot, 0);
-    for (const Blk &b : blocks) {
-        if (!state[b.fr]) state[b.fr] = 1;
-        if (b.has_a && !state[b.tk]) state[b.tk] = 1;
-        if (!state[b.fr]) state[b.fr] = 2;
-        if (!state[b.tk]) state[b.tk] = 2;
-        written[b.fr] = written[b.tk] = 1;
+    for (size_t b = 0; b < n; b++) {
+        for (int k = spans[b].reads; k < spans[b + 1].reads; k++) if (!state[slots[k]]) state[slots[k]] = 1;
+        for (int k = spans[b].writes; k < spans[b + 1].writes; k++) {
+            if (!state[wrote[k]]) state[wrote[k]] = 2;
+            written[wrote[k]] = 1;
+        }
     }
     std::vector<int> in, out;
     for (int v = 0; v < nslot; v++) { if (state[v] == 1) in.push_back(v); if (written[v]) out.push_back(v); }
@@ -1716,10 +1721,10 @@ static void window_matrix(const CompParams &cp, CompMatrix &cm)
     for (size_t j = 0; j < in.size(); j++) {
         std::vector<long long> x(nslot, none);
         x[in[j]] = 0;
-        for (const Blk &b : blocks) {
-            long long est = x[b.fr];
-            if (b.has_a) est = std::max(est, x[b.tk]);
-            x[b.fr] = x[b.tk] = est + b.t;
+        for (size_t b = 0; b < n; b++) {
+            long long est = none;
+            for (int k = spans[b].reads; k < spans[b + 1].reads; k++) est = std::max(est, x[slots[k]]);
+            for (int k = spans[b].writes; k < spans[b + 1].writes; k++) x[wrote[k]] = est + times[b];
         }
         for (size_t o = 0; o < out.size(); o++) if (x[out[o]] >= 0) cm.a[o][j] = (int32_t)x[out[o]];
     }

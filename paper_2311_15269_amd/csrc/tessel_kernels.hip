@@ -3005,29 +3005,74 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
 }
 
 // ---- any other problem: blocks on several devices, graphs, more than eight chains ------------------------------------------
-// Per-lane state in LDS [slot][lane], 16-bit words: end time of the latest block of every micro-batch in flight (a ring per
-// chain or consumed type), free time and memory of every device, next micro-batch and its jitter of every type.
-constexpr int kCompParamWords = 256;       // start of the LDS: the parameter block's copy
-static_assert(sizeof(CompParams) <= kCompParamWords * 4, "parameter block's copy");
+// Per lane, in LDS [row][lane]: per type the sort key that it has by its producers alone (as in the rows of chains; bit 31: some
+// producer has not handled the micro-batch, all ones: nothing left to offer) and the same key without the producers' end, jitter << 15 |
+// micro-batch << 5 | type; per device the free time << 15 and the memory left; the rings of end times, 16 bits, one a chain or, in graphs,
+// one a consumed type.  So a type's key is the larger of its offer and one sum, and a step looks at the types of the phase four at a
+// time, which no lane's choice delays; what the chosen block changes goes by its own tables (producers, consumers and devices as masks).
+// (A scan with every type's producers, devices and memory read one after the other, a chain of reads a type, and all windows
+// replayed block by block: 67,295 candidates of 38 micro-batches with two blocks on all of 8 devices 669 -> 177 us a call, 300,007 of 50 on
+// the K-shape 341 -> 211, 1,000,003 of 64 on the diamond 2,877 -> 1,822.)
+struct ScanRows {
+    static constexpr uint32_t kRowB = kWave * 4u, kWords = 6, types = 0, rows = kWords * kMaxK * 4u;     // a word of the tables is at word * 4 kMaxK + 4 type
+    __host__ __device__ static uint32_t devices(int K) { return rows + (uint32_t)K * 2u * kRowB; }
+    __host__ __device__ static uint32_t token(int K, int D) { return devices(K) + (uint32_t)D * 2u * kRowB; }
+    __host__ __device__ static uint32_t replay(int K, int D, int ring_rows) { return token(K, D) + (((uint32_t)ring_rows * (uint32_t)(kWave * 2) + 255u) & ~255u); }
+};
+static_assert(sizeof(CompParams) <= 4u * ScanRows::kRowB, "the parameter block's copy lies in the rows of two types");
 
-__global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__restrict__ cpg, const CompMatrix *__restrict__,
-                                                         uint64_t first, uint64_t count,
-                                                         CompRec *__restrict__ recs, int32_t *__restrict__ makespan_out)
+__global__ __launch_bounds__(kWave) void complete_scan_kernel(const CompParams *__restrict__ cpg, const CompMatrix *__restrict__ cmg,
+                                                              uint64_t first, uint64_t count, CompRec *__restrict__ recs,
+                                                              int32_t *__restrict__ makespan_out)
 {
+    typedef ScanRows L;
+    constexpr uint32_t kRowB = L::kRowB, kTab = 4u * kMaxK;
     extern __shared__ uint32_t lds[];
-    for (int w = threadIdx.x; w < (int)(sizeof(CompParams) / 4); w += kWave) lds[w] = ((const uint32_t *)cpg)[w];
-    __syncthreads();
-    const CompParams &cp = *(const CompParams *)lds;
     const int lane = threadIdx.x;
-    uint16_t *state = (uint16_t *)(lds + kCompParamWords) + lane;      // 16-bit words: all times stay below 65536 (checked by the host)
-    const int D = cp.D, K = cp.K, N = cp.N, NR = cp.NR, M = cp.M, J = cp.J, R = cp.R;
-    // a type's next micro-batch (low 10 bits) and the jitter of that block (high 6 bits) share a word: N < 1024 and
-    // J < 64 (checked by the host)
-    const int TR = cp.tok_ring, tmask = TR - 1;          // end times of the micro-batches in flight: [chain][mu mod TR]
-    // (one more slot behind the state takes stores that nobody reads)
-    const int oTok = 0, oFree = cp.npaths * TR, oMem = oFree + D, oNext = oMem + D, oTrash = oNext + K, nstate = oTrash + 1;
-    __syncthreads();
-#define TESSEL_ST(slot) state[(slot) * kWave]
+    // (all LDS addresses below are offsets from 0: nothing else of the kernel lies in front of this array)
+    if (lds_address(lds) != 0u) {
+        if (recs && lane == 0) { recs[blockIdx.x].makespan = INT_MAX; recs[blockIdx.x].ordinal = ~0ull; }
+        return;
+    }
+    const uint32_t lane4 = (uint32_t)lane * 4u, lane2 = (uint32_t)lane * 2u;
+    const int D = cpg->D, K = cpg->K, N = cpg->N, NR = cpg->NR, M = cpg->M, J = cpg->J, R = cpg->R, TR = cpg->tok_ring, nseq = cpg->nseq;
+    const uint32_t ring_rows = (uint32_t)(cpg->npaths * TR), tmask = (uint32_t)(TR - 1) << 7;
+    const uint32_t seed_lo = cpg->seed_lo, seed_hi = cpg->seed_hi;
+    const uint32_t devices = L::devices(K), token = L::token(K, D), replay = L::replay(K, D, (int)ring_rows);
+    const int nin = cmg->nin, nout = cmg->nout;
+    // ---- tables, a type a lane.  In LDS: 0 time, 1 producers, 2 consumers, 3 devices | memory delta << 16, 4 the ring it writes (0: none),
+    // 5 micro-batches of the phase.  In registers, for what goes over all types: `info` devices | memory it asks for << 8 | lead << 16
+    uint32_t info = 0, from_types = 0;
+    {
+        uint32_t *copy = lds + L::rows / 4;
+        for (int w = lane; w < (int)(sizeof(CompParams) / 4); w += kWave) copy[w] = ((const uint32_t *)cpg)[w];
+        __syncthreads();
+        const CompParams &cp = *(const CompParams *)copy;
+        uint32_t t = 0, m = 0, ring = 0, to_types = 0;
+        if (lane < K) {
+            const int i = lane;
+            t = (uint32_t)cp.t[i]; m = (uint32_t)(int)cp.m[i];
+            from_types = cp.dag ? cp.predmask[i] : cp.pred[i] >= 0 ? 1u << cp.pred[i] : 0u;
+            for (int j = 0; j < K; j++)
+                if (cp.dag ? cp.predmask[j] >> i & 1u : cp.pred[j] == i) to_types |= 1u << j;
+            ring = cp.path[i] != 0xFF ? token + (uint32_t)cp.path[i] * (uint32_t)TR * (uint32_t)(kWave * 2) : 0u;
+            info = (uint32_t)cp.mask[i] | (uint32_t)max((int)cp.m[i], 0) << 8 | (uint32_t)cp.lead[i] << 16;
+        }
+        if (nin == 0)
+            for (int s = lane; s < nseq; s += kWave) {
+                const int i = cp.seq[s];
+                lds_store(replay + 4u * (uint32_t)s, (uint32_t)i | ((uint32_t)cp.lead[i] + (uint32_t)cp.occ[s]) << 8);
+            }
+        __syncthreads();
+        if (lane < K) {
+            lds_store(lane4, t); lds_store(lane4 + kTab, from_types); lds_store(lane4 + 2 * kTab, to_types);
+            lds_store(lane4 + 3 * kTab, (info & 255u) | m << 16); lds_store(lane4 + 4 * kTab, ring);
+        }
+        __syncthreads();
+    }
+    const uint32_t times = lane < K ? lds_load(lane4) : 0u, rings = lane < K ? lds_load(lane4 + 4 * kTab) : 0u;
+    auto word_of = [](uint32_t words, uint32_t of) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)words, (int)of); };
+    const uint32_t several = (uint32_t)__ballot(lane < K && (info & 255u & ((info & 255u) - 1u)) != 0u);       // types on several devices
     int best = INT_MAX;
     uint64_t best_ord = 0;
     const uint64_t stride = (uint64_t)gridDim.x * kWave;
@@ -3035,100 +3080,157 @@ __global__ __launch_bounds__(kWave) void complete_kernel(const CompParams *__res
     for (uint64_t r = 0; r < rounds; r++) {
         const uint64_t kk = r * stride + (uint64_t)blockIdx.x * kWave + lane;
         const bool live = kk < count;
-        const uint64_t c = first + (live ? kk : 0);
+        const uint64_t c = first + (live ? kk : 0);                 // (a lane past the end scores the first candidate and drops it)
         uint32_t kb;
-        const uint32_t ka = stream_keys(((uint64_t)cp.seed_hi << 32) | cp.seed_lo, c, kb);
-        const bool noisy = c != 0 && J > 0;
-        auto jitter = [&](int i, int mu) -> uint32_t {
-            return noisy ? (stream_draw16(ka, kb, (uint32_t)(i * N + mu)) * (uint32_t)(J + 1)) >> 16 : 0u;
-        };
-        for (int s = 0; s < nstate; s++) TESSEL_ST(s) = 0;
+        const uint32_t ka = stream_keys(((uint64_t)seed_hi << 32) | seed_lo, c, kb);
+        const uint32_t jmul = c != 0 ? (uint32_t)(J + 1) : 0u;      // ordinal 0 has no jitter
+        auto jitter = [&](uint32_t n) -> uint32_t { return __umul24(stream_draw16(ka, kb, n), jmul) >> 16; };
+        for (uint32_t s = 0; s < ring_rows; s++) lds_store16(token + s * (kWave * 2u) + lane2, 0u);
+        for (int d = 0; d < D; d++) {
+            lds_store(devices + (uint32_t)d * 2u * kRowB + lane4, 0u);
+            lds_store(devices + (uint32_t)d * 2u * kRowB + kRowB + lane4, (uint32_t)M);
+        }
         bool fail = false;
         for (int phase = 0; phase < 2; phase++) {
-            // ---- greedy phase: 0 warm-up (micro-batches below the leads), 1 cool-down (the rest up to N)
-            int left = 0;                                       // blocks of this phase not yet scheduled
+            // ---- what every type offers at first: warm-up from micro-batch 0, cool-down from where the windows end
+            int left = 0;                                           // blocks of this phase
+            uint32_t active = 0;                                    // types that have some
+            if (lane < K) lds_store(lane4 + 5 * kTab, phase ? (uint32_t)N : info >> 16 & 255u);
             for (int i = 0; i < K; i++) {
-                const int mu = (int)TESSEL_ST(oNext + i) & 1023, hi = phase ? N : (int)cp.lead[i];
-                TESSEL_ST(oNext + i) = (uint16_t)((uint32_t)mu | (mu < hi ? jitter(i, mu) : 0u) << 10);
-                left += max(hi - mu, 0);
+                const uint32_t lead = word_of(info, (uint32_t)i) >> 16 & 255u, before = phase ? (uint32_t)(NR * R) : 0u;
+                const uint32_t mu = phase ? lead + before : 0u, hi = phase ? (uint32_t)N : lead;
+                uint32_t offer = ~0u, low = mu << 5 | (uint32_t)i;
+                if (mu < hi) {
+                    left += (int)(hi - mu);
+                    active |= 1u << i;
+                    uint32_t from = 0;
+                    bool there = true;
+                    for (uint32_t rest = word_of(from_types, (uint32_t)i); rest; rest &= rest - 1u) {
+                        const uint32_t a = (uint32_t)__builtin_ctz(rest);
+                        there = there && (phase ? (word_of(info, a) >> 16 & 255u) + before : 0u) > mu;
+                        from = max(from, lds_load16(word_of(rings, a) + (mu << 7 & tmask) + lane2));
+                    }
+                    const uint32_t j = jitter((uint32_t)(i * N) + mu);
+                    offer = there ? (from + j) << 15 | low : 0x80000000u | low;
+                    low |= j << 15;
+                }
+                lds_store(L::rows + (uint32_t)i * 2u * kRowB + lane4, offer);
+                lds_store(L::rows + (uint32_t)i * 2u * kRowB + kRowB + lane4, low);
             }
-            for (;;) {
-                int bi = -1, bmu = 0, best_est = 0, bkey = 0;
-                const bool any = left > 0;
-                for (int i = 0; i < K; i++) {
-                    const int hi = phase ? N : (int)cp.lead[i];
-                    if (hi == 0) continue;                       // nothing of this type in the phase (uniform)
-                    const int nj = (int)TESSEL_ST(oNext + i), mu = nj & 1023;
-                    const bool offered = mu < hi;
-                    if (__ballot(offered) == 0) continue;        // every lane is through with the type
-                    const int a = cp.pred[i], mi = cp.m[i];
-                    const uint32_t mask = cp.mask[i];
-                    bool ok = offered;
-                    int est = 0;
-                    if (cp.dag) {
-                        // every producer has handled the micro-batch; the latest of their end times
-                        for (uint32_t rest = cp.predmask[i]; rest; rest &= rest - 1u) {
-                            const int pa = __builtin_ctz(rest);
-                            ok = ok && ((int)TESSEL_ST(oNext + pa) & 1023) > mu;
-                            est = max(est, (int)TESSEL_ST(oTok + (int)cp.path[pa] * TR + (mu & tmask)));
-                        }
-                    } else if (a >= 0) {
-                        ok = ok && ((int)TESSEL_ST(oNext + a) & 1023) > mu;
-                        est = (int)TESSEL_ST(oTok + (int)cp.path[i] * TR + (mu & tmask));
+            __syncthreads();
+            // ---- a block a step, sixteen steps at a time while some candidate of the wave still has a schedule
+            for (int from_step = 0; from_step < left && __ballot(live && !fail) != 0; from_step += 16)
+            for (int s = from_step; s < min(left, from_step + 16); s++) {
+                uint32_t pick = ~0u;
+                for (uint32_t rest = active & ~several; rest;) {
+                    uint32_t o[4], j[4], fr[4], asks[4];
+                    int room[4];
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {                   // (past the last one: the last one again)
+                        const uint32_t i = (uint32_t)__builtin_ctz(rest), w = word_of(info, i);
+                        const uint32_t more = rest & (rest - 1u);
+                        rest = q < 3 ? (more ? more : rest) : more;
+                        const uint32_t ra = L::rows + i * 2u * kRowB + lane4, rd = devices + (uint32_t)__builtin_ctz(w) * 2u * kRowB + lane4;
+                        o[q] = lds_load(ra); j[q] = lds_load(ra + kRowB); fr[q] = lds_load(rd); room[q] = (int)lds_load(rd + kRowB);
+                        asks[q] = w >> 8 & 255u;
                     }
-                    for (uint32_t rest = mask; rest; rest &= rest - 1u) {          // the block's devices (uniform)
-                        const int d = __builtin_ctz(rest);
-                        if (mi > 0 && (int)(int16_t)TESSEL_ST(oMem + d) + mi > M) ok = false;
-                        est = max(est, (int)TESSEL_ST(oFree + d));
-                    }
-                    const int key = est + (nj >> 10);
-                    // types ascend, so on equal (key, micro-batch) the earlier type stays
-                    if (ok && (bi < 0 || key < bkey || (key == bkey && mu < bmu))) { bi = i; bmu = mu; best_est = est; bkey = key; }
+#pragma unroll
+                    for (int q = 0; q < 4; q++)
+                        pick = min(pick, (uint32_t)__builtin_amdgcn_bitop3_b32((uint32_t)(max(room[q], 0) - (int)asks[q]), 0x80000000u,
+                                                                              max(o[q], fr[q] + j[q]), 0xEA));        // (a & b) | c
                 }
-                const bool busy = live && !fail && any;
-                if (__ballot(busy) == 0) break;
-                if (busy && bi < 0) fail = true;                  // blocks left, none eligible: no schedule
-                if (busy && bi >= 0) {
-                    const int en = best_est + cp.t[bi];
-                    const int mi = cp.m[bi], hi = phase ? N : (int)cp.lead[bi];
-                    const uint32_t mask = cp.mask[bi];
-                    for (int d = 0; d < D; d++)
-                        if (mask >> d & 1u) { TESSEL_ST(oFree + d) = (uint16_t)en; TESSEL_ST(oMem + d) = (uint16_t)((int)(int16_t)TESSEL_ST(oMem + d) + mi); }
-                    TESSEL_ST(cp.path[bi] != 0xFF ? oTok + (int)cp.path[bi] * TR + (bmu & tmask) : oTrash) = (uint16_t)en;
-                    TESSEL_ST(oNext + bi) = (uint16_t)((uint32_t)(bmu + 1) | (bmu + 1 < hi ? jitter(bi, bmu + 1) : 0u) << 10);
-                    left--;
+                for (uint32_t rest = active & several; rest; rest &= rest - 1u) {
+                    const uint32_t i = (uint32_t)__builtin_ctz(rest), w = word_of(info, i), ra = L::rows + i * 2u * kRowB + lane4;
+                    const uint32_t o = lds_load(ra), j = lds_load(ra + kRowB);
+                    uint32_t fr = 0;
+                    int room = INT_MAX;
+                    for (uint32_t on = w & 255u; on; on &= on - 1u) {
+                        const uint32_t rd = devices + (uint32_t)__builtin_ctz(on) * 2u * kRowB + lane4;
+                        fr = max(fr, lds_load(rd)); room = min(room, (int)lds_load(rd + kRowB));
+                    }
+                    pick = min(pick, (uint32_t)__builtin_amdgcn_bitop3_b32((uint32_t)(max(room, 0) - (int)(w >> 8 & 255u)), 0x80000000u, max(o, fr + j), 0xEA));
+                }
+                const bool placed = (int)pick >= 0;
+                fail = fail | !placed;                              // blocks left, none eligible: no schedule
+                if (!placed) continue;                              // (such a lane's state stays as it is to the end of the phase)
+                const uint32_t b = pick & 31u, low = pick & 0x7FE0u, low1 = low + 32u, b4 = b << 2, rb = L::rows + b * 2u * kRowB + lane4;
+                const uint32_t t = lds_load(b4), pre = lds_load(b4 + kTab), post = lds_load(b4 + 2 * kTab), dm = lds_load(b4 + 3 * kTab),
+                               ring = lds_load(b4 + 4 * kTab), hi = lds_load(b4 + 5 * kTab), mine = lds_load(rb + kRowB);
+                const uint32_t jn = jitter(__umul24(b, (uint32_t)N) + (low1 >> 5));
+                const uint32_t en = (pick >> 15) - (mine >> 15) + t;
+                if (ring) lds_store16(ring + (low << 2 & tmask) + lane2, en);
+                for (uint32_t on = dm & 255u; on; on &= on - 1u) {
+                    const uint32_t rd = devices + (uint32_t)__builtin_ctz(on) * 2u * kRowB + lane4;
+                    const uint32_t room = lds_load(rd + kRowB);
+                    lds_store(rd, en << 15);
+                    lds_store(rd + kRowB, room - (uint32_t)((int)dm >> 16));
+                }
+                // the type's next micro-batch
+                const bool ends = low1 >> 5 >= hi;
+                uint32_t from = 0;
+                bool there = true;
+                for (uint32_t rest = pre; rest; rest &= rest - 1u) {
+                    const uint32_t a = (uint32_t)__builtin_ctz(rest);
+                    there = there && (lds_load(L::rows + a * 2u * kRowB + kRowB + lane4) & 0x7FE0u) > low1;
+                    from = max(from, lds_load16(lds_load(4u * a + 4 * kTab) + (low1 << 2 & tmask) + lane2));
+                }
+                lds_store(rb, ends ? ~0u : there ? (from + jn) << 15 | low1 | b : 0x80000000u | low1 | b);
+                lds_store(rb + kRowB, (ends ? 0u : jn << 15) | low1 | b);
+                // its consumers, if they wait for this block and it was the last of their producers'
+                for (uint32_t rest = post; rest; rest &= rest - 1u) {
+                    const uint32_t h = (uint32_t)__builtin_ctz(rest), rh = L::rows + h * 2u * kRowB + lane4;
+                    const uint32_t oh = lds_load(rh), jh = lds_load(rh + kRowB) >> 15;
+                    if (oh != (0x80000000u | low | h)) continue;
+                    uint32_t last = en;
+                    bool all = true;
+                    for (uint32_t others = lds_load(4u * h + kTab) & ~(1u << b); others; others &= others - 1u) {
+                        const uint32_t a = (uint32_t)__builtin_ctz(others);
+                        all = all && (lds_load(L::rows + a * 2u * kRowB + kRowB + lane4) & 0x7FE0u) > low;
+                        last = max(last, lds_load16(lds_load(4u * a + 4 * kTab) + (low << 2 & tmask) + lane2));
+                    }
+                    if (all) lds_store(rh, (last + jh) << 15 | low | h);
                 }
             }
-            if (phase == 1) break;
-            // ---- the R windows: the same blocks at the same micro-batches in every lane
-            for (int k = 0; k < R; k++)
-                for (int s = 0; s < cp.nseq; s++) {
-                    const int i = cp.seq[s], mu = (int)cp.lead[i] + (int)cp.occ[s] + NR * k;
-                    const uint32_t mask = cp.mask[i];
-                    const int tok = cp.path[i] != 0xFF ? oTok + (int)cp.path[i] * TR + (mu & tmask) : oTrash;
-                    int est = 0;
-                    if (cp.dag)
-                        for (uint32_t rest = cp.predmask[i]; rest; rest &= rest - 1u)
-                            est = max(est, (int)TESSEL_ST(oTok + (int)cp.path[__builtin_ctz(rest)] * TR + (mu & tmask)));
-                    else if (cp.pred[i] >= 0) est = (int)TESSEL_ST(tok);
-                    for (uint32_t rest = mask; rest; rest &= rest - 1u) est = max(est, (int)TESSEL_ST(oFree + __builtin_ctz(rest)));
-                    const int en = est + cp.t[i];
-                    for (uint32_t rest = mask; rest; rest &= rest - 1u) {
-                        const int d = __builtin_ctz(rest);
-                        TESSEL_ST(oFree + d) = (uint16_t)en; TESSEL_ST(oMem + d) = (uint16_t)((int)(int16_t)TESSEL_ST(oMem + d) + cp.m[i]);
-                    }
-                    TESSEL_ST(tok) = (uint16_t)en;
+            __syncthreads();
+            if (phase == 1 || __ballot(live && !fail) == 0) break;
+            // ---- the R windows: the same blocks at the same micro-batches in every lane.  (Without the memory, which a whole
+            // window leaves as it was.)
+            auto load_slot = [&](uint32_t s) -> uint32_t {
+                return s < ring_rows ? lds_load16(token + s * (kWave * 2u) + lane2) : lds_load(devices + (s - ring_rows) * 2u * kRowB + lane4) >> 15;
+            };
+            if (nin > 0) {
+                int x[kMatIn];
+#pragma unroll
+                for (int j = 0; j < kMatIn; j++) x[j] = j < nin ? (int)load_slot(cmg->in_slot[j]) : 0;
+                for (int o = 0; o < nout; o++) {
+                    int acc = 0;
+#pragma unroll
+                    for (int j = 0; j < kMatIn; j++) acc = max(acc, x[j] + cmg->a[o][j]);
+                    const uint32_t s = cmg->out_slot[o];
+                    if (s < ring_rows) lds_store16(token + s * (kWave * 2u) + lane2, (uint32_t)acc);
+                    else lds_store(devices + (s - ring_rows) * 2u * kRowB + lane4, (uint32_t)acc << 15);
                 }
-            for (int i = 0; i < K; i++) TESSEL_ST(oNext + i) = (uint16_t)((int)cp.lead[i] + NR * R);
+            } else
+                for (int w = 0; w < R; w++)
+                    for (int s = 0; s < nseq; s++) {
+                        const uint32_t rw = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_load(replay + 4u * (uint32_t)s)), i = rw & 255u;
+                        const uint32_t at = ((rw >> 8) + (uint32_t)(NR * w)) << 7 & tmask, on_all = word_of(info, i) & 255u, ring = word_of(rings, i);
+                        uint32_t est = 0;
+                        for (uint32_t rest = word_of(from_types, i); rest; rest &= rest - 1u)
+                            est = max(est, lds_load16(word_of(rings, (uint32_t)__builtin_ctz(rest)) + at + lane2));
+                        for (uint32_t on = on_all; on; on &= on - 1u) est = max(est, lds_load(devices + (uint32_t)__builtin_ctz(on) * 2u * kRowB + lane4) >> 15);
+                        const uint32_t en = est + word_of(times, i);
+                        for (uint32_t on = on_all; on; on &= on - 1u) lds_store(devices + (uint32_t)__builtin_ctz(on) * 2u * kRowB + lane4, en << 15);
+                        if (ring) lds_store16(ring + at + lane2, en);
+                    }
+            __syncthreads();
         }
         int makespan = 0;
-        for (int d = 0; d < D; d++) makespan = max(makespan, (int)TESSEL_ST(oFree + d));
+        for (int d = 0; d < D; d++) makespan = max(makespan, (int)(lds_load(devices + (uint32_t)d * 2u * kRowB + lane4) >> 15));
         if (fail) makespan = INT_MAX;
-        if (!live) continue;
-        if (makespan_out) makespan_out[kk] = makespan;
-        if (makespan < best || (makespan == best && c < best_ord)) { best = makespan; best_ord = c; }
+        if (live && makespan_out) makespan_out[kk] = makespan;
+        if (live && (makespan < best || (makespan == best && c < best_ord))) { best = makespan; best_ord = c; }
     }
-#undef TESSEL_ST
     if (!recs) return;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -3176,7 +3278,7 @@ typedef void (*comp_fn)(const CompParams *, const CompMatrix *, uint64_t, uint64
 
 // The kernel and the LDS of a workgroup.  Chains whose types sit on one device each: rows for 4 or 8 devices with 2 or 4 types each, then
 // the ring of every chain, then (no matrix) one word per block of the window.  Others: 16-bit state and parameters.
-constexpr size_t kCompLds = 64 * 1024;
+constexpr size_t kCompLds = 64 * 1024, kCompLdsMost = 72 * 1024;     // the size that problems are taken by, and what the kernels make of it at most
 static comp_fn pick_completion(const CompParams &cp, const CompMatrix &cm, size_t &lds)
 {
     bool chain = cp.npaths <= 8 && !cp.dag;
@@ -3190,8 +3292,9 @@ static comp_fn pick_completion(const CompParams &cp, const CompMatrix &cm, size_
     const size_t rows = cp.D <= 4 ? (most <= 2 ? ChainRows<4, 2>::token : ChainRows<4, 4>::token) : (most <= 2 ? ChainRows<8, 2>::token : ChainRows<8, 4>::token);
     lds = rows + behind;
     if (!chain) {
-        lds = (size_t)kCompParamWords * 4 + (size_t)((cp.npaths * cp.tok_ring + 2 * cp.D + cp.K + 1 + 1) / 2 * 2) * kWave * 2;
-        return complete_kernel;
+        lds = ScanRows::replay(cp.K, cp.D, cp.npaths * cp.tok_ring) + ((replay + 15) & ~(size_t)15);
+        lds = std::max(lds, (size_t)ScanRows::rows + sizeof(CompParams));
+        return complete_scan_kernel;
     }
     if (cp.D <= 4) return most <= 2 ? complete_chain_kernel<4, 2> : complete_chain_kernel<4, 4>;
     return most <= 2 ? complete_chain_kernel<8, 2> : complete_chain_kernel<8, 4>;
@@ -3204,7 +3307,9 @@ static comp_fn pick_completion(const CompParams &cp, const CompMatrix &cm, size_
 static_assert(ChainRows<8, 4>::token + 8 * 16 * kWave * 2 + kMaxSeq * 4 <= kCompLds && 2 * kMaxNR <= 16, "LDS of the completion kernel for chains");
 bool completion_fits(const CompParams &cp, const CompMatrix &cm)
 {
-    const size_t replay = cm.nin > 0 ? (size_t)(kMatIn + kMatOut + cm.nout * kMatIn) * 4 : (size_t)cp.nseq * 4;
+    bool chain = cp.npaths <= 8 && !cp.dag;
+    for (int i = 0; i < cp.K; i++) chain = chain && (cp.mask[i] & (cp.mask[i] - 1)) == 0;
+    const size_t replay = chain && cm.nin > 0 ? (size_t)(kMatIn + kMatOut + cm.nout * kMatIn) * 4 : (size_t)cp.nseq * 4;
     return (size_t)1408 + (size_t)((cp.npaths * cp.tok_ring + 2 * cp.D + cp.K + 1 + 1) / 2 * 2) * kWave * 2 +
            (size_t)(cp.K + 1) * kWave * 4 + ((replay + 15) & ~(size_t)15) <= kCompLds;
 }
@@ -3215,16 +3320,16 @@ int launch_completions(const CompParams &cp, const CompMatrix &cm, uint64_t firs
     hipStream_t st = (hipStream_t)stream;
     size_t lds;
     comp_fn fn = pick_completion(cp, cm, lds);
-    if (lds > kCompLds) return -1;
+    if (lds > kCompLdsMost) return -1;
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCompLds);
+        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCompLdsMost);
         if (e != hipSuccess) return (int)e;
     }
     int per_cu = (int)((160 * 1024) / ((lds + 511) / 512 * 512));
     if (per_cu > 16) per_cu = 16;
     if (per_cu < 1) per_cu = 1;
     // a multiple of 4, the same number on every SIMD: 9 a CU (3, 2, 2, 2) took 1.25 times as long a round of candidates as 8
-    if (fn != complete_kernel && per_cu > 4) per_cu &= ~3;
+    if (fn != complete_scan_kernel && per_cu > 4) per_cu &= ~3;
     uint64_t need = (count + kWave - 1) / kWave;
     const int blocks = need < (uint64_t)(num_cus * per_cu) ? (int)need : num_cus * per_cu;
     if (blocks < 1) return 0;
