@@ -814,9 +814,8 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
             for (int d = 0; d < D; d++) if (code_on[i][d] >= 0) grp |= 1u << code_on[i][d];
             for (int d = 0; d < D; d++) if (code_on[i][d] >= 0) { kp.grp_code[code_on[i][d]] = grp; kp.home_code[code_on[i][d]] = (uint8_t)home[i]; }
             const bool multi = (desc->dev_mask[i] & (desc->dev_mask[i] - 1)) != 0;
-            const bool multi_next = kp.succ[i] >= 0 && (desc->dev_mask[kp.succ[i]] & (desc->dev_mask[kp.succ[i]] - 1)) != 0;
             if (multi) { if (kp.ntp < kMaxD) kp.tp_group[kp.ntp++] = grp; else ok = false; }
-            if (multi || multi_next) kp.slow_mask |= grp;
+            if (multi) kp.several |= grp;
         }
         kp.fast_tp = kp.tp;
         kp.tp_all = kp.tp;

@@ -129,7 +129,7 @@ struct KParams {
     int32_t  ntp;                // number of such types
     int32_t  tp_all;             // each of them sits on every device
     uint32_t tp_group[kMaxD];    // their codes, one mask per type
-    uint32_t slow_mask;          // codes of types that sit on several devices or whose consumer does
+    uint32_t several;            // codes of types that sit on several devices
     uint32_t grp_code[kMaxK];    // by code: all codes of the same type
     uint8_t  home_code[kMaxK];   // by code: the type's code on its lowest device (63: no such code)
     // Dependency graphs that are not disjoint chains (a block type with several producers or consumers): scored by the

@@ -844,8 +844,9 @@ struct FastProgram {
 constexpr int kFastTableWords = 16 * kMaxK;      // uniform tables at the start of the fast kernel's LDS
 constexpr int kSweepTabWord = 12 * kMaxK;        // ... of which the sweeps' three tables by code; a multiple of 64 words, so
                                                  // that one two-address LDS read fetches a code's first and third word
-constexpr int kTpListWord = 5 * kMaxK + kMaxD;
-constexpr int kTpTableWords = kTpListWord + 2 * kWave;       // the TP variants' own tables behind them, and their list of candidates
+constexpr int kTpListWord = 6 * kMaxK + kMaxD;
+// the TP variants' own tables behind them, and their list of candidates (up to a multiple of 64 words: rows of 256 bytes)
+constexpr int kTpTableWords = (kTpListWord + 2 * kWave + kWave - 1) / kWave * kWave;
 // Everything a lane reads by a run-time index lies word by word: word w of entry i at w * 64 + i words, so that
 // lanes with different entries hit different banks, a lane's words of one entry come with two-address reads
 // (stride 64 words), and an LDS atomic on one word of the records meets no bank twice.
@@ -860,16 +861,16 @@ struct FastLds {
     uint32_t *type_tab;   // [4][64], code in the low half of every 64: what placing one block of the type does:
                           //   word 0: added to the last word of its device record: memory delta << 16, one waiting
                           //      micro-batch of the type less, one more for its consumer if that sits on the same device
-                          //   word 1: one-hot mask of the consumer's code (0: none)
-                          //   word 2: consumer on another device: LDS address of the last word of that device's record
-                          //      (lane 0); otherwise, TP variants: 0xFFFFFFFF, else that of the type's own device
-                          //      (word 3 is 0 then).  Not TP: plus 4 * symbol of the type (rows are 256 bytes)
+                          //   word 1: the consumer's codes (0: none)
+                          //   word 2: LDS address of the last word (lane 0) of the record of the consumer's lowest device, if that is another one,
+                          //      else of the type's own device (word 3 is 0 then); plus 4 * symbol of the type (rows are 256 bytes)
                           //   word 3: the increment of that word (one waiting micro-batch of the consumer)
                           // the upper halves hold chain_tab, vtab, cum_tab, predbit_tab
     uint32_t *chain_tab;  // [32]  KParams::chain_tab
     uint32_t *vtab;       // [32]  KParams::vtab
     uint32_t *cum_tab, *predbit_tab;   // [32] each: KParams::cum_code, pred_bit
     uint32_t *grp_tab;    // [32]  TP variants: KParams::grp_code
+    uint32_t *mem_tab;    // [32]  TP variants: by code, memory delta << 16
     uint32_t *tpg_tab;    // [8]   TP variants: KParams::tp_group (read in every build step with a uniform index; an array in
                           //       registers indexed at run time went to scratch memory)
     uint32_t rec;         // build: LDS address of the records [DM][4][64]: word 0: low plane, 1: high plane,
@@ -891,7 +892,7 @@ struct FastConst {
     uint32_t mpack[DM];
     // blocks on several devices (TP variants of the kernel only)
     int ntp, tp_all;
-    uint32_t slow;
+    uint32_t several;                // codes of types on several devices
 };
 
 // One block of the window: s = max(device free, previous block of the micro-batch); both become s + t.  The
@@ -1508,9 +1509,10 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
             // entries of it remain; its consumer gets one more and becomes runnable
             // remaining entries of the same type: alive & ~(lo ^ ly) & ~(hi ^ hy)
             const uint32_t rest = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(alive, a.x, ly, 0x90), a.y, hy, 0x90);
-            // two or more were waiting (the shift, 4 * symbol, is in the low bits of the table entry where no type sits on several devices)
-            const uint32_t more = (a.w >> (TP ? 4u * (c & 3u) : e.z & 31u)) & 14u;
-            const uint32_t onec = 1u << c;
+            // two or more were waiting (the shift, 4 * symbol, is in the low bits of the table entry)
+            const uint32_t more = (a.w >> (e.z & 31u)) & 14u;
+            // (a type on several devices: its codes on all of them)
+            const uint32_t onec = TP ? L.grp_tab[c] : 1u << c;
             // exhausted: no entry of the type is left; it stays runnable only if entries are left and another
             // micro-batch waits.  (Masks, all ones: entries are left; another one waits.)
             const uint32_t some = (uint32_t)((int)(rest | (0u - rest)) >> 31), waits = (uint32_t)((int)(0u - more) >> 31);
@@ -1522,56 +1524,42 @@ __device__ __forceinline__ void build_words(const KParams &P, const FastConst<DM
             // signed); one sum updates both
             const uint32_t w_new = a.w + e.x;
             const bool active = repair || building;
-            uint32_t r_fin = r_new, x_fin = x_new, hm_fin = hm_new;
+            uint32_t hm_fin = hm_new;
             if (active) {
                 lds_store(ra + 2u * kRecWordStep, alive);
                 lds_store(ra + 3u * kRecWordStep, w_new);
-                // (without blocks on several devices every table entry names a word: a type without a consumer on
-                // another device adds 0 to its own record)
-                if (!TP) lds_fetch_add(__builtin_amdgcn_bitop3_b32(e.z, ~31u, lane4, 0xEA), e.w);       // (a & b) | c: rows of 256 bytes
-                else if (e.z != 0xFFFFFFFFu) lds_fetch_add(e.z + lane4, e.w);
+                // (a type without a consumer on another device adds 0 to its own record)
+                lds_fetch_add(__builtin_amdgcn_bitop3_b32(e.z, ~31u, lane4, 0xEA), e.w);       // (a & b) | c: rows of 256 bytes
                 worst = max(worst, (int)w_new >> 16);
-                // the program names a type by its code on its lowest device
-                acc |= (TP ? (uint32_t)__builtin_ctz(L.grp_tab[c]) : c) << (5 * j);
+                acc |= c << (5 * j);
             }
             if (TP) {
-                const bool slow = active && ((C.slow >> c) & 1u);
-                if (__ballot(slow) != 0 && slow) {
-                    // the type sits on several devices, or its consumer does: all codes of the type in R and X, its
-                    // earliest entry out of every other device it occupies, one more waiting micro-batch on every
-                    // device of the consumer (the table entry of such a type leaves all that to this path)
-                    const uint32_t G = L.grp_tab[c], Gs = e.y;
-                    const int mtype = (int)e.w;
-                    x_fin = X | (rest == 0 ? G : 0u);
-                    r_fin = (R & ~G) | (min(rest, more) != 0 ? G : 0u) | (Gs & ~x_fin);
+                const bool several = active && ((C.several >> c) & 1u);
+                if (__ballot(several) != 0 && several) {
+                    // The block's earliest entry out of the lists of its other devices.  (It was picked on its lowest device: whichever of its codes
+                    // is the lowest bit of all, that one is.  So the micro-batches that wait for it are counted there alone, and what is left to
+                    // do on the others is their list, head and memory.)
+                    const uint32_t mem = L.mem_tab[c];
 #pragma unroll
                     for (int dd = 0; dd < DM; dd++) {
-                        const uint32_t nib = (G >> (4 * dd)) & 15u;
-                        if (dd >= C.D || nib == 0 || 4u * dd == d4) continue;
-                        const uint32_t sym = (uint32_t)__builtin_ctz(nib);
+                        if (dd >= C.D) continue;
+                        if (C.tp_all ? dd == 0 : ((onec >> (4 * dd)) & 15u) == 0 || 4u * dd == d4) continue;
                         const uint32_t rq = (uint32_t)dd * kRecDevStep + rec_lane;
                         const uint4 q = rec_load(rq);
-                        const uint32_t ls = 0u - (sym & 1u), hs = 0u - (sym >> 1);
-                        const uint32_t same = q.z & ~(q.x ^ ls) & ~(q.y ^ hs);
-                        const uint32_t pos = (uint32_t)__builtin_ctz(same | 0x80000000u);
-                        const uint32_t left = q.z & ~(1u << pos);
-                        const uint32_t wq = q.w + ((uint32_t)mtype << 16) - (1u << (4u * sym));
+                        const uint32_t y3 = (uint32_t)__builtin_amdgcn_sbfe((int)onec, 4 * dd + 3, 1);
+                        const uint32_t ls = (uint32_t)__builtin_amdgcn_sbfe((int)onec, 4 * dd + 1, 1) | y3, hs = (uint32_t)__builtin_amdgcn_sbfe((int)onec, 4 * dd + 2, 1) | y3;
+                        const uint32_t same = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(q.z, q.x, ls, 0x90), q.y, hs, 0x90);
+                        const uint32_t left = __builtin_amdgcn_bitop3_b32(q.z, same, 0u - same, 0x70), wq = q.w + mem;
                         lds_store(rq + 2u * kRecWordStep, left);
                         lds_store(rq + 3u * kRecWordStep, wq);
                         worst = max(worst, (int)wq >> 16);
-                        const uint32_t ph = (uint32_t)__builtin_ctz(left | 0x80000000u);
-                        const uint32_t yh = __builtin_amdgcn_ubfe(q.x, ph, 1) | (__builtin_amdgcn_ubfe(q.y, ph, 1) << 1);
-                        hm_fin = (hm_fin & ~(15u << (4 * dd))) | (1u << (4 * dd + yh));
-                    }
-#pragma unroll
-                    for (int dd = 0; dd < DM; dd++) {
-                        const uint32_t nib = (Gs >> (4 * dd)) & 15u;
-                        if (dd >= C.D || nib == 0) continue;
-                        lds_fetch_add((uint32_t)dd * kRecDevStep + 3u * kRecWordStep + rec_lane, 1u << (4u * (uint32_t)__builtin_ctz(nib)));
+                        const uint32_t ph = low_bit(left), h2 = q.y >> (ph & 31u);
+                        const uint32_t ch = __builtin_amdgcn_bitop3_b32(__builtin_amdgcn_bitop3_b32(q.x >> (ph & 31u), h2 + h2, 1u, 0xE4), 3u, 4u * dd, 0xEA);
+                        hm_fin = (hm_fin & ~(15u << (4 * dd))) | 1u << ch;
                     }
                 }
             }
-            if (active) { R = r_fin; X = x_fin; HM = hm_fin; }
+            if (active) { R = r_new; X = x_new; HM = hm_fin; }
         }
         return acc;
     };
@@ -1625,16 +1613,10 @@ __device__ __forceinline__ void fill_type_tab(const KParams &P, uint32_t *type_t
     const bool has_su = su != 63u, same = has_su && (su >> 2) == dev;
     const uint32_t inc = has_su ? 1u << (4u * (su & 3u)) : 0u;
     const uint32_t last = rec + 3u * kRecWordStep;            // last word of device 0's record, lane 0
-    uint4 e;
-    if (TP && ((P.slow_mask >> lane) & 1u))
-        // a type on several devices, or with such a consumer: the step's slow path does the consumer's part
-        e = make_uint4(((uint32_t)m << 16) - (1u << (4u * y)), has_su ? P.grp_code[su & 31u] : 0u, 0xFFFFFFFFu, (uint32_t)m);
-    else
-        e = make_uint4(((uint32_t)m << 16) - (1u << (4u * y)) + (same ? inc : 0u),
-                       has_su ? 1u << (su & 31u) : 0u,
-                       has_su && !same ? last + (su >> 2) * kRecDevStep + (TP ? 0u : 4u * y)
-                                       : TP ? 0xFFFFFFFFu : last + (dev < (uint32_t)DM ? dev : 0u) * kRecDevStep + 4u * y,
-                       has_su && !same ? inc : 0u);
+    const uint4 e = make_uint4(((uint32_t)m << 16) - (1u << (4u * y)) + (same ? inc : 0u),
+                               !has_su ? 0u : TP && P.grp_code[su & 31u] ? P.grp_code[su & 31u] : 1u << (su & 31u),
+                               last + (has_su && !same ? su >> 2 : dev < (uint32_t)DM ? dev : 0u) * kRecDevStep + 4u * y,
+                               has_su && !same ? inc : 0u);
     type_tab[lane] = e.x; type_tab[2 * kMaxK + lane] = e.y; type_tab[4 * kMaxK + lane] = e.z; type_tab[6 * kMaxK + lane] = e.w;
 }
 
@@ -1719,7 +1701,8 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     L.predbit_tab = lds + 7 * kMaxK;
     L.tt_tab = (uint4 *)(lds + kFastTableWords);              // 128 words, TP variants only
     L.grp_tab = lds + kFastTableWords + 4 * kMaxK;            // TP variants only
-    L.tpg_tab = lds + kFastTableWords + 5 * kMaxK;            // TP variants only
+    L.mem_tab = lds + kFastTableWords + 5 * kMaxK;            // TP variants only
+    L.tpg_tab = lds + kFastTableWords + 6 * kMaxK;            // TP variants only
     L.sw_tab = lds + kSweepTabWord;
     L.ch_tab = lds + kSweepTabWord + kMaxK;
     L.in_tab = lds + kSweepTabWord + 2 * kMaxK;
@@ -1750,6 +1733,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
         L.vtab[lane] = lane < 24 ? P.vtab[lane] : 0u;
         if (TP && lane < kMaxD) L.tpg_tab[lane] = P.tp_group[lane];
         if (TP) L.grp_tab[lane] = P.grp_code[lane] ? P.grp_code[lane] : 1u << lane;
+        if (TP) L.mem_tab[lane] = (uint32_t)((int32_t)(inf << 6) >> 24) << 16;
         L.cum_tab[lane] = P.cum_code[lane]; L.predbit_tab[lane] = P.pred_bit[lane];
     }
     __syncthreads();
@@ -1759,7 +1743,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     C.step_q16 = P.step_q16; C.seed = P.seed;
 #pragma unroll
     for (int d = 0; d < DM; d++) { C.ntd[d] = P.ntd[d]; C.mpack[d] = P.mpack[d]; }
-    C.ntp = TP ? P.ntp : 0; C.slow = TP ? P.slow_mask : 0u; C.tp_all = TP ? P.tp_all : 0;
+    C.ntp = TP ? P.ntp : 0; C.several = TP ? P.several : 0u; C.tp_all = TP ? P.tp_all : 0;
 
     int best = INT_MAX;
     uint64_t best_idx = 0;
