@@ -32,8 +32,9 @@ struct tessel_problem {
     std::vector<int32_t> dep_src, dep_dst;
     std::vector<int8_t> leadtab;        // CANONICAL
     std::vector<uint64_t> wtab;         // CANONICAL
-    std::vector<char> tables;           // CANONICAL: the two, and where they are small KParams::orders and leadrows, in a row, each from a
-                                        // multiple of 256 bytes on, as the workspace gets them
+    // What a workspace starts with, copied in one piece: an empty record, the parameters, and from kWsTablesOff on (CANONICAL) the two
+    // tables, where they are small KParams::orders and leadrows, and the graph kernel's tables, each from a multiple of 256 bytes on
+    std::vector<char> image;
     size_t table_at[4] = {0, 0, 0, 0};
     uint64_t nlead = 0;
     uint64_t count = 0;
@@ -942,13 +943,24 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
         const size_t bytes[4] = {p->leadtab.size(), p->wtab.size() * 8, orders * 8, leadrows * 4};
         size_t total = 0;
         for (int k = 0; k < 4; k++) { p->table_at[k] = total; total = (total + bytes[k] + 255) & ~(size_t)255; }
-        p->tables.resize(total);
-        memcpy(p->tables.data(), p->leadtab.data(), bytes[0]);
-        memcpy(p->tables.data() + p->table_at[1], p->wtab.data(), bytes[1]);
+        p->image.resize(kWsTablesOff + total);
+        char *tables = p->image.data() + kWsTablesOff;
+        memcpy(tables, p->leadtab.data(), bytes[0]);
+        memcpy(tables + p->table_at[1], p->wtab.data(), bytes[1]);
         if (kp.ranked) {
-            fill_ranked(*p, (uint64_t *)(p->tables.data() + p->table_at[2]), (uint32_t *)(p->tables.data() + p->table_at[3]));
+            fill_ranked(*p, (uint64_t *)(tables + p->table_at[2]), (uint32_t *)(tables + p->table_at[3]));
             for (int d = 0; d < kp.D; d++) kp.recip[d] = kp.cdev[d] > 1 ? (uint32_t)(((uint64_t)1 << 32) / kp.cdev[d]) : 0u;
             if (!kp.fast_tp) list_pairs(*p, kWsTablesMax - total);
+        }
+    }
+    if (p->image.empty()) p->image.resize(kWsTablesOff);
+    kp.graph_at = (uint32_t)kWsGraphOff;                             // (where the tables leave it no room: a copy of its own)
+    if (kp.graph_ok) {
+        const size_t at = (p->image.size() + 255) & ~(size_t)255, bytes = offsetof(GraphTab, tab) + (size_t)p->graph.ntab * 4;
+        if (at + bytes <= kWsTablesOff + kWsTablesMax) {
+            p->image.resize(at + bytes);
+            memcpy(p->image.data() + at, &p->graph, bytes);
+            kp.graph_at = (uint32_t)at;
         }
     }
     *out = p;
@@ -1012,8 +1024,9 @@ static int range_ok(const tessel_problem *p, uint64_t first, uint64_t count)
     return TESSEL_OK;
 }
 
-// binds the workspace: uploads the tables of the exhaustive spaces and clears the running best
-static int bind_workspace(tessel_problem *p, void *ws, size_t bytes, hipStream_t st, int max_blocks = 0)
+// Binds the workspace: parameters, tables and the running best `start` (null: none yet) in one copy.  (Two or three copies and a kernel
+// for the record took 15 to 25 us more, most of the way to a new handle's first answer in small spaces.)
+static int bind_workspace(tessel_problem *p, void *ws, size_t bytes, hipStream_t st, int max_blocks = 0, const DevResult *start = nullptr)
 {
     if (!ws || ((uintptr_t)ws & 255u)) return TESSEL_E_WORKSPACE;
     int rc = ensure_device(p);
@@ -1021,24 +1034,27 @@ static int bind_workspace(tessel_problem *p, void *ws, size_t bytes, hipStream_t
     if (bytes < eval_workspace_bytes(p->kp, p->num_cus, max_blocks)) return TESSEL_E_WORKSPACE;
     if (p->ws == ws && owns_workspace(p)) return TESSEL_OK;
     char *base = (char *)ws + kWsTablesOff;
-    if (!p->tables.empty()) {
-        if (p->tables.size() > kWsTablesMax) return TESSEL_E_TOOBIG;
-        hipError_t e = hipMemcpyAsync(base, p->tables.data(), p->tables.size(), hipMemcpyHostToDevice, st);
-        if (e != hipSuccess) return hip_fail(p, (int)e);
+    if (p->image.size() > kWsTablesOff + kWsTablesMax) return TESSEL_E_TOOBIG;
+    if (p->kp.space == kCanonical) {
         p->kp.leadtab = (const int8_t *)(base + p->table_at[0]);
         p->kp.wtab = (const uint64_t *)(base + p->table_at[1]);
         p->kp.orders = (const uint64_t *)(base + p->table_at[2]);
         p->kp.leadrows = (const uint32_t *)(base + p->table_at[3]);
-        p->kp.pair_tab = (uint32_t *)(base + ((p->tables.size() + 255) & ~(size_t)255));
+        p->kp.pair_tab = (uint32_t *)((char *)ws + ((p->image.size() + 255) & ~(size_t)255));
     }
-    hipError_t pe = hipMemcpyAsync((char *)ws + kWsParamsOff, &p->kp, sizeof(KParams), hipMemcpyHostToDevice, st);
+    DevResult none;
+    memset(&none, 0, sizeof none);
+    none.period = INT_MAX; none.index = ~0ull;
+    memcpy(p->image.data() + kWsResultOff, start ? start : &none, sizeof none);
+    memcpy(p->image.data() + kWsParamsOff, &p->kp, sizeof(KParams));
+    // (without tables up to the end of the parameters)
+    const size_t upto = p->image.size() > kWsTablesOff ? p->image.size() : kWsParamsOff + sizeof(KParams);
+    hipError_t pe = hipMemcpyAsync(ws, p->image.data(), upto, hipMemcpyHostToDevice, st);
     if (pe != hipSuccess) return hip_fail(p, (int)pe);
-    if (p->kp.graph_ok) {
+    if (p->kp.graph_ok && p->kp.graph_at == kWsGraphOff) {
         pe = hipMemcpyAsync((char *)ws + kWsGraphOff, &p->graph, sizeof(GraphTab), hipMemcpyHostToDevice, st);
         if (pe != hipSuccess) return hip_fail(p, (int)pe);
     }
-    int e = launch_reset(ws, st);
-    if (e) return hip_fail(p, e);
     p->ws = ws; p->ws_ready = true; p->max_blocks = max_blocks;
     p->comp_ready = false;              // the completion parameters lived in the workspace bound before
     p->ranges.clear();
@@ -2029,11 +2045,18 @@ extern "C" int tessel_search_run(const tessel_problem_desc *desc, tessel_search 
         tessel_problem *p = nullptr;
         int rc = tessel_problem_create(&d, &p);
         if (rc) return rc;
-        rc = tessel_eval_candidates(p, io->best_index, 1, workspace_dev, workspace_bytes, hip_stream);
-        tessel_result r;
-        if (!rc) rc = tessel_best(p, &r);
-        if (!rc && (r.period != io->best_period || r.index != io->best_index)) rc = TESSEL_E_HIP;   // never expected
+        // (the incumbent as the only candidate scored; its period is checked like that of every record read back)
+        DevResult best;
+        memset(&best, 0, sizeof best);
+        best.period = io->best_period; best.index = io->best_index; best.n_evaluated = 1; best.n_status[kOk] = 1;
+        rc = bind_workspace(p, workspace_dev, workspace_bytes, (hipStream_t)hip_stream, 0, &best);
         if (rc) { tessel_problem_destroy(p); return rc; }
+        p->stream = (hipStream_t)hip_stream;
+        p->ranges.push_back({io->best_index, 1});
+        p->result = best;
+        decode_candidate(p, best.index, p->detail);
+        check_period(p);
+        if (!p->period_right) { tessel_problem_destroy(p); return TESSEL_E_HIP; }        // never expected
         *best_out = p;
     }
     return TESSEL_OK;

@@ -154,6 +154,7 @@ struct KParams {
     int32_t  graph_np, graph_chain;      // GraphTab::np, chain
     int32_t  graph_codes;        // GraphTab::codes
     uint32_t graph_lds;          // GraphTab::lds_bytes
+    uint32_t graph_at;           // where in the workspace its tables are
     uint32_t graph_slot_words;   // words of one candidate's slot: GraphTab::meta + nwords
     int32_t  many;               // some device holds more than kMaxLT block types (3-bit symbols; sampled spaces only)
     const int8_t   *leadtab;     // CANONICAL: [nlead][K] in device memory

@@ -1064,7 +1064,7 @@ int launch_graph(const KParams &kp, uint64_t first, uint64_t count, int blocks, 
 {
     DevResult *res = (DevResult *)((char *)ws + kWsResultOff);
     hipLaunchKernelGGL(pick_graph(kp), dim3(blocks), dim3(kWave), kp.graph_lds, (hipStream_t)stream, (const KParams *)((char *)ws + kWsParamsOff),
-                       (const GraphTab *)((char *)ws + kWsGraphOff), first, count, (BlockRec *)recs, code, peak,
+                       (const GraphTab *)((char *)ws + kp.graph_at), first, count, (BlockRec *)recs, code, peak,
                        (uint64_t *)((char *)ws + kWsListOff), &res->defer_count, kWsListCap, &res->overflow, slots);
     return (int)hipGetLastError();
 }
