@@ -848,13 +848,16 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
         {
             // chain_tab lists every chain from its last block to its first, one chain after the other
             std::vector<int> pos(K, 0);
+            for (int d = 0; d < kMaxD; d++) kp.no_pred[d] = 0xFFFFu;
             for (int k = 0; k < K; k++) pos[kp.rtopo[k]] = k;
             for (int i = 0; i < K && ok; i++) {
                 uint32_t cum = 0;
                 for (int g = i; kp.succ[g] >= 0; g = kp.succ[g]) cum |= 1u << pos[g];
                 for (int d = 0; d < D; d++) if (code_on[i][d] >= 0) {
                     kp.cum_code[code_on[i][d]] = cum;
-                    kp.pred_bit[code_on[i][d]] = kp.pred[i] < 0 ? 0u : 1u << pos[kp.pred[i]];
+                    if (kp.pred[i] < 0) { kp.first_codes |= 1u << code_on[i][d]; continue; }
+                    kp.pred_pos[d] |= (uint32_t)pos[kp.pred[i]] << (8 * (code_on[i][d] & 3));
+                    kp.no_pred[d] &= ~(15u << (4 * (code_on[i][d] & 3)));
                 }
                 if (kp.succ[i] >= 0 && kp.edge_out[i] < kMaxK) kp.dep_bit[kp.edge_out[i]] = kp.cross_out[i] ? 1u << pos[i] : 0u;
             }
@@ -862,7 +865,6 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
         }
         for (int d = 0; d < D; d++) {
             kp.vtab[d] = (uint32_t)d | (1u << 6) | ((uint32_t)(kp.ntd[d] > 0) << 17);
-            kp.code_mask |= ((1u << kp.ntd[d]) - 1u) << (4 * d);
             for (int y = 0; y < kp.ntd[d]; y++) kp.mpack[d] |= ((uint32_t)kp.m_of[d][y] & 0xFFu) << (8 * y);
         }
         int v = D, path = 0;

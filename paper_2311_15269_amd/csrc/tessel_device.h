@@ -118,9 +118,11 @@ struct KParams {
     // sampled leads as sums of per-dependency steps (bit k of the step mask = dependency out of the k-th
     // entry of chain_tab)
     uint32_t cum_code[kMaxK];    // by code: step bits whose sum (capped at N_R-1) is the type's lead
-    uint32_t pred_bit[kMaxK];    // by code: step bit of the dependency from its producer (0 = first of its chain)
+    uint32_t pred_pos[kMaxD];    // by device, eight bits a type: the position of the step bit of the dependency from its producer (0, which is no
+                                 // dependency's: first of its chain, or no type)
+    uint32_t no_pred[kMaxD];     // by device: 15 in the four bits of such types
+    uint32_t first_codes;        // codes of types that are the first of their chain
     uint32_t dep_bit[kMaxK];     // by dependency number: its step bit, 0 if both ends sit on the same device set
-    uint32_t code_mask;          // codes that block types have
     uint32_t mpack[kMaxD];       // memory deltas of the device's 4 types, 8 bits each (signed)
     int32_t  eigen_tries;        // window sweeps a candidate gets at first, and
     int32_t  retry_tries;        // ... from the start again when those found no eigenvector (both: test knobs)

@@ -865,10 +865,8 @@ struct FastLds {
                           //   word 2: LDS address of the last word (lane 0) of the record of the consumer's lowest device, if that is another one,
                           //      else of the type's own device (word 3 is 0 then); plus 4 * symbol of the type (rows are 256 bytes)
                           //   word 3: the increment of that word (one waiting micro-batch of the consumer)
-                          // the upper halves hold chain_tab, vtab, cum_tab, predbit_tab
+                          // the upper half of the first holds chain_tab
     uint32_t *chain_tab;  // [32]  KParams::chain_tab
-    uint32_t *vtab;       // [32]  KParams::vtab
-    uint32_t *cum_tab, *predbit_tab;   // [32] each: KParams::cum_code, pred_bit
     uint32_t *grp_tab;    // [32]  TP variants: KParams::grp_code
     uint32_t *mem_tab;    // [32]  TP variants: by code, memory delta << 16
     uint32_t *tpg_tab;    // [8]   TP variants: KParams::tp_group (read in every build step with a uniform index; an array in
@@ -1102,7 +1100,7 @@ __device__ __forceinline__ void reset_sweep_state(const FastConst<DM> &C, const 
 // five devices left so many to the general kernel that its pass took 563 of 1,690 us; a call 1,590 -> 1,090 us.  Not in the
 // variants for 24 values, which have no registers left for it: 2 to 5 % slower over 48 to 112 blocks.)
 template <int DM, int VM, bool TP>
-__device__ __forceinline__ int period_fast(const FastConst<DM> &C, const FastLds &L, const FastProgram &prog, int lane,
+__device__ __forceinline__ int period_fast(const KParams &P, const FastConst<DM> &C, const FastLds &L, const FastProgram &prog, int lane,
                                            const Mu &lead_code, bool want, int tries, bool settle,
                                            uint32_t &nsweeps_used)
 {
@@ -1117,8 +1115,10 @@ __device__ __forceinline__ int period_fast(const FastConst<DM> &C, const FastLds
 #pragma unroll
     for (int v = 0; v < VM; v++) {
         if (v < V) {
-            const uint32_t e = L.vtab[v];
-            const bool on = (e >> 6 & 1u) ? (e >> 17 & 1u) != 0 : lead_code.get((e >> 7) & 31u) > ((e >> 13) & 15u);
+            // (the value's entry through scalar loads: its code is a constant of the wave)
+            const uint32_t e = P.vtab[v], c = (e >> 7) & 31u;
+            const uint32_t half = c & 16u ? (c & 8u ? (uint32_t)(lead_code.hi >> 32) : (uint32_t)lead_code.hi) : c & 8u ? (uint32_t)(lead_code.lo >> 32) : (uint32_t)lead_code.lo;
+            const bool on = (e >> 6 & 1u) ? (e >> 17 & 1u) != 0 : (half >> (4u * (c & 7u)) & 15u) > ((e >> 13) & 15u);
             live |= (on ? 1u : 0u) << v;
         }
     }
@@ -1138,7 +1138,7 @@ __device__ __forceinline__ int period_fast(const FastConst<DM> &C, const FastLds
 #pragma unroll
             for (int v = 0; v < VM; v++) {
                 if (v < V) {
-                    const uint32_t x = *(const uint32_t *)((const char *)L.dfree + value_offset(L.vtab[v]));
+                    const uint32_t x = *(const uint32_t *)((const char *)L.dfree + value_offset(P.vtab[v]));
                     const uint32_t dv = live >> v & 1u ? x - prev[v] : 0u;
                     prev[v] = x;
                     now = dv > top ? 0u : now;
@@ -1157,7 +1157,7 @@ __device__ __forceinline__ int period_fast(const FastConst<DM> &C, const FastLds
 #pragma unroll
         for (int v = 0; v < VM; v++) {
             if (v < V) {
-                const uint32_t x = *(const uint32_t *)((const char *)L.dfree + value_offset(L.vtab[v]));
+                const uint32_t x = *(const uint32_t *)((const char *)L.dfree + value_offset(P.vtab[v]));
                 const uint32_t dv = x - prev[v];
                 prev[v] = x;
                 if (live >> v & 1u) {
@@ -1238,7 +1238,7 @@ __device__ __forceinline__ int entry_memory(uint32_t leads, uint32_t mpack)
 // candidates of 40 blocks with two on all of four devices leave here, 5.69 -> 1.68 ms.  In the others next to no lead vector
 // exceeds a cap that any candidate meets.
 template <int DM>
-__device__ __forceinline__ bool entry_over(const KParams &P, const FastConst<DM> &C, const FastLds &L, uint64_t idx)
+__device__ __forceinline__ bool entry_over(const KParams &P, const FastConst<DM> &C, uint64_t idx)
 {
     uint32_t kb;
     const uint32_t ka = stream_keys(C.seed, idx, kb), S = lead_steps<DM>(P, C, ka, kb);
@@ -1248,7 +1248,7 @@ __device__ __forceinline__ bool entry_over(const KParams &P, const FastConst<DM>
         if (d >= C.D || C.ntd[d] == 0) continue;
         uint32_t leads = 0;
 #pragma unroll
-        for (int y = 0; y < kMaxLT; y++) leads |= min((uint32_t)C.NR - 1u, (uint32_t)__builtin_popcount(S & L.cum_tab[4 * d + y])) << (4 * y);
+        for (int y = 0; y < kMaxLT; y++) leads |= min((uint32_t)C.NR - 1u, (uint32_t)__builtin_popcount(S & P.cum_code[4 * d + y])) << (4 * y);
         most = max(most, entry_memory(leads, C.mpack[d]));
     }
     return most > C.M;
@@ -1372,23 +1372,23 @@ __device__ __forceinline__ void build_begin(const KParams &P, const FastConst<DM
 #pragma unroll
         for (int d = 0; d < DM; d++) {
             if (d >= C.D) continue;
-            uint32_t mud = 0, qd = 0;
+            // (The tables through scalar loads: what a code has of its own is the operand of one instruction.  By words from LDS, with a
+            // compare and a select for a type without a producer, 16 instructions a code instead of nine.)
+            const uint32_t pos = P.pred_pos[d];
+            uint32_t mud = 0, qd = P.no_pred[d];             // 15: no producer, never waits
 #pragma unroll
             for (int y = 0; y < kMaxLT; y++) {               // (a code without a type has no bits in the tables: lead 0, never read)
-                const int c = 4 * d + y;
-                const uint32_t pb = L.predbit_tab[c];
-                const uint32_t cnt = (uint32_t)__builtin_popcount(S & L.cum_tab[c]);
-                const uint32_t lead = min(NR - 1u, cnt);
-                // micro-batches its producer handled in the previous window already; 15: no producer, never waits
-                const uint32_t wait = pb ? min(NR - 1u, cnt + ((S & pb) ? 1u : 0u)) - lead : 15u;
+                const uint32_t lead = min(NR - 1u, (uint32_t)__builtin_popcount(S & P.cum_code[4 * d + y]));
+                // its producer handled one micro-batch more in the previous window if their dependency steps and the cap is not reached
+                const uint32_t wait = min((S >> (pos >> (8 * y) & 31u)) & 1u, NR - 1u - lead);
                 mud |= lead << (4 * y);
                 qd |= wait << (4 * y);
-                R |= (wait ? 1u : 0u) << c;
+                R |= wait << (4 * d + y);
             }
             if (d < 4) { mu.lo |= (uint64_t)mud << (16 * d); Q.lo = (Q.lo & ~(0xFFFFull << (16 * d))) | ((uint64_t)qd << (16 * d)); }
             else { mu.hi |= (uint64_t)mud << (16 * (d - 4)); Q.hi = (Q.hi & ~(0xFFFFull << (16 * (d - 4)))) | ((uint64_t)qd << (16 * (d - 4))); }
         }
-        R &= P.code_mask;
+        R |= P.first_codes;
     } else if (!sampled && P.ranked) {
         const uint4 a = ((const uint4 *)row)[0], b = ((const uint4 *)row)[1];
         mu.lo = (uint64_t)a.x | ((uint64_t)a.y << 32); mu.hi = (uint64_t)a.z | ((uint64_t)a.w << 32);
@@ -1694,11 +1694,8 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     const KParams &P = *Pp;
     const int lane = threadIdx.x;
     FastLds L;
-    L.type_tab = lds;                                         // 4 x 64 words, the upper half of every 64:
+    L.type_tab = lds;                                         // 4 x 64 words, the lower half of every 64
     L.chain_tab = lds + kMaxK;
-    L.vtab = lds + 3 * kMaxK;
-    L.cum_tab = lds + 5 * kMaxK;
-    L.predbit_tab = lds + 7 * kMaxK;
     L.tt_tab = (uint4 *)(lds + kFastTableWords);              // 128 words, TP variants only
     L.grp_tab = lds + kFastTableWords + 4 * kMaxK;            // TP variants only
     L.mem_tab = lds + kFastTableWords + 5 * kMaxK;            // TP variants only
@@ -1730,11 +1727,9 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
             L.in_tab[lane] = (1u << (16u + 4u * ((uint32_t)lane & 3u))) | (8u + 4u * ((uint32_t)lane & 3u));
         }
         L.chain_tab[lane] = P.chain_tab[lane];
-        L.vtab[lane] = lane < 24 ? P.vtab[lane] : 0u;
         if (TP && lane < kMaxD) L.tpg_tab[lane] = P.tp_group[lane];
         if (TP) L.grp_tab[lane] = P.grp_code[lane] ? P.grp_code[lane] : 1u << lane;
         if (TP) L.mem_tab[lane] = (uint32_t)((int32_t)(inf << 6) >> 24) << 16;
-        L.cum_tab[lane] = P.cum_code[lane]; L.predbit_tab[lane] = P.pred_bit[lane];
     }
     __syncthreads();
     FastConst<DM> C;
@@ -1851,7 +1846,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
             }
         if (again) { head3 = (head3 + n) & (kRingSlots - 1u); count3 -= n; }
         else { head2 = (head2 + n) & (kRingSlots - 1u); count2 -= n; }
-        const int T = period_fast<DM, VM, TP>(C, L, prog, lane, lead_code, have, again ? retry_tries : tries, again, nsw);
+        const int T = period_fast<DM, VM, TP>(P, C, L, prog, lane, lead_code, have, again ? retry_tries : tries, again, nsw);
         const bool open = have && T < 0;                  // no eigenvector within the sweeps allowed
         if (!again) {
             const uint32_t k = push_program(open, idx, pk, prog, ring3, head3 + count3);
@@ -1992,7 +1987,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
                 kk = r++ * stride + (uint64_t)blockIdx.x * kWave + lane;
                 valid = kk < count;
                 const uint64_t idx = first + (valid ? kk : 0u);
-                const bool over = entry_over<DM>(P, C, L, idx);
+                const bool over = entry_over<DM>(P, C, idx);
                 reject(valid && over, idx, kMem, 0);
                 const uint64_t fits = __ballot(valid && !over);
                 if (valid && !over) tp_list[nleft + rank_in(fits)] = (uint32_t)kk;
