@@ -1097,8 +1097,8 @@ __device__ __forceinline__ void reset_sweep_state(const FastConst<DM> &C, const 
 // that grew by D then grew by D now.  No cycle ratio exceeds the largest growth; and a value that grew by D got its time from one that
 // grew by D the time before (that one's growth bounds its own from above), which is again one of these, so following them
 // closes a cycle of ratio D.  (Pipelines whose devices before the slowest one keep a smaller growth for ever: 8.7 M candidates of 70 blocks on
-// five devices left so many to the general kernel that its pass took 563 of 1,690 us; a call 1,590 -> 1,090 us.  Not in the
-// variants for 24 values, which have no registers left for it: 2 to 5 % slower over 48 to 112 blocks.)
+// five devices left so many to the general kernel that its pass took 563 of 1,690 us; a call 1,590 -> 1,090 us.  2^18 of 80 blocks on
+// eight: 719 -> 159.)
 template <int DM, int VM, bool TP>
 __device__ __forceinline__ int period_fast(const KParams &P, const FastConst<DM> &C, const FastLds &L, const FastProgram &prog, int lane,
                                            const Mu &lead_code, bool want, int tries, bool settle,
@@ -1133,7 +1133,7 @@ __device__ __forceinline__ int period_fast(const KParams &P, const FastConst<DM>
         if (__ballot(!done) == 0) break;
         sweep_fast<DM, TP>(C, L, prog, lane, lead_code, !done);
         nsweeps_used += done ? 0u : 1u;
-        if (VM <= 16 && settle) {
+        if (settle) {
             uint32_t top = 0, now = 0;                    // the largest growth, and the values that have it
 #pragma unroll
             for (int v = 0; v < VM; v++) {
@@ -2353,7 +2353,28 @@ static eval_fn pick_kernel(const KParams &kp)
     return eval_kernel<8, 24>;
 }
 
-static int fast_dm(const KParams &kp) { return kp.D <= 2 ? 2 : kp.D <= 4 ? 4 : 8; }
+// devices of the fast kernel's variant: 2, 4 or 8 (two devices with more than 16 boundary values go with four:
+// the X-shape on two devices at six micro-batches 431 us for 2^21 candidates, 482 with a variant for two and 24 values)
+static int fast_dm(const KParams &kp)
+{
+    const int V = kp.nsweeps - 1;
+    return kp.D <= 2 && (kp.fast_tp || V <= 16) ? 2 : kp.D <= 4 ? 4 : 8;
+}
+
+// Boundary values of the variant: the fewest that hold the problem's.  Most windows of five and more micro-batches on up to four devices have
+// 9 to 16.  With room for 24, which the registers do not hold without spills in the sweeps, 2^20 candidates of a pipeline at eight
+// micro-batches take 198 us on two devices and 485 on four, with room for 16 172 and 435.  (2^21 of the X-shape on three devices: 658 and 1,015 us at
+// three and four micro-batches, 367 and 639 now: there the general kernel had to find periods that the longer search settles.)
+template <int MODE>
+static fast_fn pick_fast_mode(const KParams &kp)
+{
+    const int V = kp.nsweeps - 1;
+    switch (fast_dm(kp)) {
+    case 2: return V <= 4 ? eval_fast_kernel<2, 4, MODE> : eval_fast_kernel<2, 16, MODE>;
+    case 4: return V <= 8 ? eval_fast_kernel<4, 8, MODE> : V <= 16 ? eval_fast_kernel<4, 16, MODE> : eval_fast_kernel<4, 24, MODE>;
+    default: return V <= 16 ? eval_fast_kernel<8, 16, MODE> : eval_fast_kernel<8, 24, MODE>;
+    }
+}
 
 static fast_fn pick_fast(const KParams &kp)
 {
@@ -2369,19 +2390,7 @@ static fast_fn pick_fast(const KParams &kp)
             return kp.D <= 2 ? eval_fast_kernel<2, 24, 1, true> : kp.D <= 4 ? eval_fast_kernel<4, 24, 1, true> : eval_fast_kernel<8, 24, 1, true>;
         return kp.D <= 2 ? eval_fast_kernel<2, 24, 0, true> : kp.D <= 4 ? eval_fast_kernel<4, 24, 0, true> : eval_fast_kernel<8, 24, 0, true>;
     }
-    if (kp.space == kSampledRepair) {
-        if (kp.D <= 2) return V <= 4 ? eval_fast_kernel<2, 4, 2> : eval_fast_kernel<2, 24, 2>;
-        if (kp.D <= 4) return V <= 8 ? eval_fast_kernel<4, 8, 2> : eval_fast_kernel<4, 24, 2>;
-        return V <= 16 ? eval_fast_kernel<8, 16, 2> : eval_fast_kernel<8, 24, 2>;
-    }
-    if (kp.space == kSampledStrict) {
-        if (kp.D <= 2) return V <= 4 ? eval_fast_kernel<2, 4, 1> : eval_fast_kernel<2, 24, 1>;
-        if (kp.D <= 4) return V <= 8 ? eval_fast_kernel<4, 8, 1> : eval_fast_kernel<4, 24, 1>;
-        return V <= 16 ? eval_fast_kernel<8, 16, 1> : eval_fast_kernel<8, 24, 1>;
-    }
-    if (kp.D <= 2) return V <= 4 ? eval_fast_kernel<2, 4, 0> : eval_fast_kernel<2, 24, 0>;
-    if (kp.D <= 4) return V <= 8 ? eval_fast_kernel<4, 8, 0> : eval_fast_kernel<4, 24, 0>;
-    return V <= 16 ? eval_fast_kernel<8, 16, 0> : eval_fast_kernel<8, 24, 0>;
+    return kp.space == kSampledRepair ? pick_fast_mode<2>(kp) : kp.space == kSampledStrict ? pick_fast_mode<1>(kp) : pick_fast_mode<0>(kp);
 }
 
 // Whether a launch looks its candidates up in tables of the orders that go together (order_pairs_kernel), and for how many lead vectors
@@ -2643,7 +2652,8 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
         const uint32_t leads = code ? 0u : pair_leads(kp, first, count, lead0);
         if (leads) {
             const uint32_t chunks = leads * (kp.pair_words / 2);
-            const pairs_fn pf = kp.D <= 2 ? order_pairs_kernel<2> : kp.D <= 4 ? order_pairs_kernel<4> : order_pairs_kernel<8>;
+            const int dm = fast_dm(kp);
+            const pairs_fn pf = dm == 2 ? order_pairs_kernel<2> : dm == 4 ? order_pairs_kernel<4> : order_pairs_kernel<8>;
             hipLaunchKernelGGL(pf, dim3(std::min<uint32_t>(chunks, (uint32_t)num_cus * 12u)), dim3(kWave),
                                (size_t)kFastTableWords * 4 + (size_t)fast_dm(kp) * kWave * 16, st, kp_dev, lead0, chunks, kp.pair_tab);
             rc = (int)hipGetLastError();
