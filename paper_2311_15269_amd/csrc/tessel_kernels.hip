@@ -2765,14 +2765,17 @@ int eval_blocks_that_fit(const KParams &kp, int num_cus, size_t bytes)
 // The key of an offer is max(offer, (free time + jitter) << 15 | the same low bits), with bit 31 where its memory does not fit.  A
 // step changes the keys of the block's own device, worked out anew (four at most), and the offer of its consumer, if that waits
 // for this very micro-batch: with the block's end and the jitter it has already.  So a pick is the smallest of eight words, not of the
-// keys of all types, which were kept in LDS before and of which a step changed up to five: 115 vector instructions a step now.
-// Bound by the steps' own chain at two waves a SIMD (LDS: 17.7 KB a wave for 8 devices and 32 types): five rounds of LDS reads with 115
-// vector instructions between them, which issue for half of the time.  2^20 candidates of 64 micro-batches on 8 devices, as a call:
-// 2.47 -> 1.38 ms; 41 000 of 40 on 7 devices: 326 -> 202 us.
+// keys of all types, which were kept in LDS before and of which a step changed up to five.  It is known when the step ends: the
+// smallest keys of the other devices and the offers of the block's own are read with the rest of the state, the block's own words all
+// ones by then, and its new ones and the consumer's key join them in registers.
+// Bound by vector issue at two waves a SIMD (LDS: 17.7 KB a wave for 8 devices and 32 types): 116 vector instructions and two rounds of LDS
+// reads a step (table words; state).  With five rounds (smallest keys, table words, state, offers, all in a row) the same time, until the waves
+// of a SIMD took turns, see below.  2^20 candidates of 64 micro-batches on 8 devices, as a call: 2.47 ms with a key a type, 1.38 with a key a device,
+// 1.32 with turns, 1.23 with two rounds as well.
 template <int DM, int SY>
 struct ChainRows {
     static constexpr uint32_t kRowB = kWave * 4u;
-    static constexpr uint32_t types = 0, more = 512, mpos = 640, init = 704, rows = 1024;      // tables: by type, by type, by device, by code
+    static constexpr uint32_t types = 0, more = 512, room = 640, init = 768, mpos = 896, rows = 1024;     // tables: by type (three), by code, by device
     static constexpr uint32_t least = rows, dev = least + DM * kRowB, jit = dev + DM * kRowB, offer = jit + DM * kRowB;
     static constexpr uint32_t ones = offer + DM * SY * kRowB, token = ones + kRowB;
 };
@@ -2792,7 +2795,7 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
     }
     const uint32_t lane4 = (uint32_t)lane * 4u, lane2 = (uint32_t)lane * 2u;
     const int D = cpg->D, K = cpg->K, N = cpg->N, NR = cpg->NR, M = cpg->M, J = cpg->J, R = cpg->R, TR = cpg->tok_ring, nseq = cpg->nseq;
-    const uint32_t ring_rows = (uint32_t)(cpg->npaths * TR), tmask = (uint32_t)(TR - 1) << 7, oFree = ring_rows;
+    const uint32_t ring_rows = (uint32_t)(cpg->npaths * TR), tmask = (uint32_t)(TR - 1) << 7, tring = (uint32_t)(TR - 1) << 5, oFree = ring_rows;
     const uint32_t seed_lo = cpg->seed_lo, seed_hi = cpg->seed_hi;
     const uint32_t replay = L::token + ((ring_rows * (uint32_t)(kWave * 2) + 255u) & ~255u);      // words of the windows' blocks (no matrix)
     const int nin = cmg->nin, nout = cmg->nout;
@@ -2833,6 +2836,8 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
             }
         }
         __syncthreads();
+        if (lane < K) lds[L::room / 4 + lane] = lds[L::mpos / 4 + device_of(lane)];      // what the types of its device ask for
+        __syncthreads();
     }
     auto uniform_word = [&](uint32_t a) -> uint32_t { return (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_load(a)); };
     // What the start of a phase goes by, a word a lane: by code, by type, by device.  (A phase visits the codes that block types have.  All of a
@@ -2847,6 +2852,7 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
     uint64_t best_ord = 0;
     const uint64_t stride = (uint64_t)gridDim.x * kWave;
     const uint64_t rounds = (count + stride - 1) / stride;          // the same trip count for every lane of the grid
+    const uint32_t slot = __builtin_amdgcn_s_getreg((3 << 11) | 4);     // the wave's place on its SIMD (bits 0 to 3 of HW_ID)
     for (uint64_t r = 0; r < rounds; r++) {
         const uint64_t kk = r * stride + (uint64_t)blockIdx.x * kWave + lane;
         const bool live = kk < count;
@@ -2858,15 +2864,15 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
         for (uint32_t s = 0; s < ring_rows; s++) lds_store16(L::token + s * (kWave * 2u) + lane2, 0u);
         for (int d = 0; d < DM; d++) { lds_store(L::dev + (uint32_t)d * L::kRowB + lane4, 0u); lds_store(L::least + (uint32_t)d * L::kRowB + lane4, ~0u); }
         bool fail = false;
-        // the smallest key of a device whose types' offers are at `at`: free time, jitters, memory left (not below 0)
-        auto least_key = [&](uint32_t at, uint32_t fr, uint32_t jits, int room, uint32_t mp) -> uint32_t {
+        // an offer's key: not before its device is free (jitter included); bit 31 where the memory left is below 0
+        auto key_of = [](uint32_t o, uint32_t from, int room) -> uint32_t {
+            return __builtin_amdgcn_bitop3_b32((uint32_t)room, 0x80000000u, max(o, from << 15 | (o & 0x7FFFu)), 0xEA);
+        };
+        // the smallest key of a device's offers: free time, jitters, memory left (not below 0)
+        auto least_key = [&](const uint32_t *o, uint32_t fr, uint32_t jits, int room, uint32_t mp) -> uint32_t {
             uint32_t low = ~0u;
 #pragma unroll
-            for (int y = 0; y < SY; y++) {
-                const uint32_t o = lds_load(at + (uint32_t)y * L::kRowB);
-                const uint32_t key = max(o, ((fr + (jits >> (8 * y) & 255u)) << 15) | (o & 0x7FFFu));
-                low = min(low, (uint32_t)__builtin_amdgcn_bitop3_b32((uint32_t)(room - (int)(mp >> (8 * y) & 255u)), 0x80000000u, key, 0xEA));
-            }
+            for (int y = 0; y < SY; y++) low = min(low, key_of(o[y], fr + (jits >> (8 * y) & 255u), room - (int)(mp >> (8 * y) & 255u)));
             return low;
         };
         for (int phase = 0; phase < 2; phase++) {
@@ -2893,56 +2899,82 @@ __global__ __launch_bounds__(kWave) void complete_chain_kernel(const CompParams 
                 }
                 lds_store(L::jit + dd, jits);
                 const uint32_t fm = lds_load(L::dev + dd);
-                lds_store(L::least + dd, least_key(L::offer + d * SY * L::kRowB + lane4, fm & 0xFFFFu, jits, max(M - ((int)fm >> 16), 0),
-                                                   word_of(by_dev, d)));
+                uint32_t o[SY];
+#pragma unroll
+                for (int y = 0; y < SY; y++) o[y] = lds_load(L::offer + (d * SY + y) * L::kRowB + lane4);
+                lds_store(L::least + dd, least_key(o, fm & 0xFFFFu, jits, max(M - ((int)fm >> 16), 0), word_of(by_dev, d)));
             }
             __syncthreads();
             // ---- a block a step
+            auto least_of_all = [&]() -> uint32_t {
+                uint32_t low = ~0u;
+#pragma unroll
+                for (int d = 0; d < DM; d++) low = min(low, lds_load(L::least + (uint32_t)d * L::kRowB + lane4));
+                return low;
+            };
+            uint32_t pick = least_of_all();
             // (Sixteen steps at a time while some candidate of the wave still has a schedule: under a tight cap whole waves are stuck after a
             // few.  2^20 candidates of 250 blocks, all stuck: a call of 256 us without, 190 with it.  Looked at in every step it cost the others 8 %.)
-            for (int from = 0; from < left && __ballot(live && !fail) != 0; from += 16)
-            for (int s = from; s < min(left, from + 16); s++) {
-                uint32_t pick = ~0u;
+            for (int from = 0; from < left && __ballot(live && (int)pick >= 0) != 0; from += 16) {
+                // (the waves of a SIMD issue first in turns of 41 us.  All at the same priority, the older of two does: it was done after 1,010 us,
+                // the younger after 1,350, alone on the SIMD for the rest.)
+                if ((((uint32_t)__builtin_amdgcn_s_memrealtime() >> 12) + slot) & 1u) __builtin_amdgcn_s_setprio(1);
+                else __builtin_amdgcn_s_setprio(0);
+                for (int s = from; s < min(left, from + 16); s++) {
+                    if ((int)pick < 0) continue;                        // blocks left, none eligible: the lane's state stays as it is
+                    const uint32_t b = pick & 31u, low = pick & 0x7FE0u, low1 = low + 32u;
+                    const uint32_t T0 = lds_load(L::types + 16u * b), T1 = lds_load(L::types + 16u * b + 4u), T2 = lds_load(L::types + 16u * b + 8u),
+                                   T3 = lds_load(L::types + 16u * b + 12u), U = lds_load(L::more + 4u * b), mp = lds_load(L::room + 4u * b);
+                    uint32_t jn = jitter(__umul24(b, (uint32_t)N) + (low1 >> 5));
+                    TESSEL_PIN(jn);
+                    // (second round: everything these words name)
+                    const uint32_t dd = (T0 & 0xF00u) + lane4, cd = (T3 & 0xF00u) + lane4, ring = (T0 >> 16) + lane2, oc = (T2 >> 16) + lane4;
+                    const uint32_t ob = (T2 & 0xFFFFu) + lane4, at = (T0 & 0xF00u) * SY + L::offer + lane4;
+                    lds_store(L::least + dd, ~0u);
+                    lds_store(ob, ~0u);
+                    uint32_t fm = lds_load(L::dev + dd), jits = lds_load(L::jit + dd);
+                    uint32_t off_c = lds_load(oc), fm_c = lds_load(L::dev + cd), jits_c = lds_load(L::jit + cd);
+                    uint32_t off_p = lds_load((U & 0xFF00u) + lane4), tk = lds_load16(ring + ((low1 & tring) << 2));
+                    uint32_t o[SY], others[DM];
 #pragma unroll
-                for (int d = 0; d < DM; d++) pick = min(pick, lds_load(L::least + (uint32_t)d * L::kRowB + lane4));
-                const bool placed = (int)pick >= 0;
-                fail = fail | !placed;                              // blocks left, none eligible: no schedule
-                if (!placed) continue;                              // (such a lane's state stays as it is to the end of the phase)
-                const uint32_t b = pick & 31u, low = pick & 0x7FE0u, low1 = low + 32u;
-                const uint32_t T0 = lds_load(L::types + 16u * b), T1 = lds_load(L::types + 16u * b + 4u), T2 = lds_load(L::types + 16u * b + 8u),
-                               T3 = lds_load(L::types + 16u * b + 12u), U = lds_load(L::more + 4u * b);
-                const uint32_t jn = jitter(__umul24(b, (uint32_t)N) + (low1 >> 5));
-                // (second round: everything these words name)
-                const uint32_t dd = (T0 & 0xF00u) + lane4, cd = (T3 & 0xF00u) + lane4, ring = (T0 >> 16) + lane2, oc = (T2 >> 16) + lane4;
-                uint32_t fm = lds_load(L::dev + dd), jits = lds_load(L::jit + dd), mp = lds_load(L::mpos + ((T0 & 0xF00u) >> 6));
-                uint32_t off_c = lds_load(oc), fm_c = lds_load(L::dev + cd), jits_c = lds_load(L::jit + cd);
-                uint32_t off_p = lds_load((U & 0xFF00u) + lane4), tk = lds_load16(ring + (low1 << 2 & tmask));
-                TESSEL_PIN(fm); TESSEL_PIN(jits); TESSEL_PIN(mp); TESSEL_PIN(off_c); TESSEL_PIN(fm_c); TESSEL_PIN(jits_c); TESSEL_PIN(off_p); TESSEL_PIN(tk);
-                const uint32_t yb = T3 >> 24 & 31u;
-                const uint32_t en = (pick >> 15) - (jits >> yb & 255u) + (T1 & 0xFFFFu);
-                const uint32_t fm_new = ((fm + (T1 & 0xFFFF0000u)) & 0xFFFF0000u) | en;
-                const uint32_t jits_new = (jits & ~(255u << yb)) | jn << yb;
-                // the type's next micro-batch: there if its producer's offer is beyond it (nothing left to offer: all ones)
-                const uint32_t from = T3 >> 30 & 1u ? tk : 0u, low_b = low1 | b;
-                uint32_t off_b = (off_p & 0x7FE0u) > low1 ? (from + jn) << 15 | low_b : 0x80000000u | low_b;
-                off_b = low1 >= U >> 16 ? ~0u : off_b;
-                lds_store(L::dev + dd, fm_new);
-                lds_store(L::jit + dd, jits_new);
-                lds_store16(ring + (low << 2 & tmask), en);
-                lds_store((T2 & 0xFFFFu) + lane4, off_b);
-                // its consumer, if that waits for this block.  (No consumer: a row of all ones, which no block matches.)
-                {
-                    const uint32_t jc = jits_c >> (T3 >> 16 & 31u) & 255u, low_c = off_c & 0x7FFFu;
-                    const bool waits = off_c == (0x80000000u | low | (T3 & 31u));
-                    const uint32_t now = (en + jc) << 15 | low_c;
-                    lds_store(oc, waits ? now : off_c);
-                    const int room = max(M - ((int)fm_c >> 16), 0) - (int)(U & 127u);
-                    const uint32_t key = __builtin_amdgcn_bitop3_b32((uint32_t)room, 0x80000000u, max(now, ((fm_c & 0xFFFFu) + jc) << 15 | low_c), 0xEA);
-                    // (on the block's own device the store below follows)
-                    __hip_atomic_fetch_min((lds_word *)(uintptr_t)(L::least + cd), waits ? key : ~0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    for (int y = 0; y < SY; y++) o[y] = lds_load(at + (uint32_t)y * L::kRowB);
+#pragma unroll
+                    for (int d = 0; d < DM; d++) others[d] = lds_load(L::least + (uint32_t)d * L::kRowB + lane4);
+                    TESSEL_PIN(fm); TESSEL_PIN(jits); TESSEL_PIN(off_c); TESSEL_PIN(fm_c); TESSEL_PIN(jits_c); TESSEL_PIN(off_p); TESSEL_PIN(tk);
+                    const uint32_t yb = T3 >> 24 & 31u;
+                    const uint32_t en = (pick >> 15) - (jits >> yb & 255u) + (T1 & 0xFFFFu);
+                    const uint32_t fm_new = ((fm + (T1 & 0xFFFF0000u)) & 0xFFFF0000u) | en;
+                    const uint32_t jits_new = (jits & ~(255u << yb)) | jn << yb;
+                    // the type's next micro-batch: there if its producer's offer is beyond it (nothing left to offer: all ones)
+                    const uint32_t from = T3 >> 30 & 1u ? tk : 0u, low_b = low1 | b;
+                    const uint32_t there = (from + jn) << 15;
+                    uint32_t off_b = ((off_p & 0x7FE0u) > low1 ? there : 0x80000000u) | low_b;
+                    off_b = low1 >= U >> 16 ? ~0u : off_b;
+                    lds_store(L::dev + dd, fm_new);
+                    lds_store(L::jit + dd, jits_new);
+                    lds_store16(ring + ((low & tring) << 2), en);
+                    lds_store(ob, off_b);
+                    const int room = max(M - ((int)fm_new >> 16), 0);
+                    const uint32_t mine = min(least_key(o, en, jits_new, room, mp), key_of(off_b, en + jn, room - (int)(mp >> yb & 255u)));
+                    lds_store(L::least + dd, mine);
+                    // its consumer, if that waits for this block.  (No consumer: a row of all ones, which no block matches.)
+                    {
+                        const uint32_t jc = jits_c >> (T3 >> 16 & 31u) & 255u, low_c = off_c & 0x7FFFu;
+                        const bool waits = off_c == (0x80000000u | low | (T3 & 31u));
+                        const uint32_t now = (en + jc) << 15 | low_c;
+                        lds_store(oc, waits ? now : off_c);
+                        const uint32_t fm_now = cd == dd ? fm_new : fm_c;
+                        uint32_t key = key_of(now, (fm_now & 0xFFFFu) + jc, max(M - ((int)fm_now >> 16), 0) - (int)(U & 127u));
+                        TESSEL_PIN(key);
+                        key = waits ? key : ~0u;
+                        __hip_atomic_fetch_min((lds_word *)(uintptr_t)(L::least + cd), key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        pick = min(mine, key);
+#pragma unroll
+                        for (int d = 0; d < DM; d++) pick = min(pick, others[d]);
+                    }
                 }
-                lds_store(L::least + dd, least_key((T0 & 0xF00u) * SY + L::offer + lane4, en, jits_new, max(M - ((int)fm_new >> 16), 0), mp));
             }
+            fail = fail | (pick != ~0u);                            // (what is left has a key, with bit 31; nothing left: all ones)
             __syncthreads();
             if (phase == 1 || __ballot(live && !fail) == 0) break;
             // ---- the R windows: the same blocks at the same micro-batches in every lane.  (Without the memory, which a whole
