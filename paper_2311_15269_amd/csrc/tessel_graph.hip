@@ -277,6 +277,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
             const uint32_t e0 = step(), e1 = step();
             prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
             if (!REPAIR || (wi & 7) == 7) {
+                if ((wi & 7) == 7) take_turn();
                 const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
                 if (__ballot(going) == 0) { whole = false; break; }
             }
@@ -372,6 +373,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
             const uint32_t e0 = step(), e1 = step();
             prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
             if (!REPAIR || (wi & 7) == 7) {
+                if ((wi & 7) == 7) take_turn();
                 const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
                 if (__ballot(going) == 0) { whole = false; break; }
             }
@@ -695,6 +697,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
             const uint32_t e0 = step(), e1 = step();
             prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
             if (!REPAIR || (wi & 7) == 7) {
+                if ((wi & 7) == 7) take_turn();
                 const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
                 if (__ballot(going) == 0) { whole = false; break; }
             }
@@ -843,6 +846,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
 #pragma unroll
             for (int q = 0; q < 4; q++) cur[q] = prog[(size_t)q * kProgRow];
             for (int wi = 0; wi < nwords; wi += 4) {
+                if ((wi & 12) == 0) take_turn();
                 const int ahead = wi + 4 < nwords ? wi + 4 : wi;
 #pragma unroll
                 for (int q = 0; q < 4; q++) nxt[q] = prog[(size_t)(ahead + q) * kProgRow];
