@@ -193,8 +193,8 @@ def main():
                             "frac": ops * rate / 1e12 / PEAK_INT32_OPS, "traffic": None, "kernel": "complete_chain_kernel<8, 4>",
                             "peak_is": "nominal rate of the slower class (maxima, compares, shifts left), to which most of the operations belong",
                             "algorithmic_ops_per_candidate": ops,
-                            "limited_by": "latency: every scheduled block of the greedy phases is a chain of dependent per-lane "
-                                          "decisions through LDS, at two waves per SIMD "
+                            "limited_by": "vector issue at two waves per SIMD: every scheduled block of the greedy phases is a chain "
+                                          "of dependent per-lane decisions, two rounds of LDS reads each "
                                           "(profiles/complete_kernel_cfg5_kernel_trace_counters.md)"}}
         if not args.no_cpu_baseline:
             from oracle import Oracle

@@ -205,8 +205,8 @@ int  tessel_score_candidates(tessel_problem *p, uint64_t first, uint64_t count,
                              void *workspace_dev, size_t workspace_bytes, void *hip_stream);
 
 /* Returns the running best as it is when everything queued on the stream of the last call is done, which the call
- * waits for.  (One kernel on that stream decodes the best candidate and stores it with the counters into pinned host memory, where
- * this thread looks for it.  All work queued before is complete and visible by then; the kernel itself may take some microseconds more
+ * waits for.  (One kernel on that stream stores the best key and the counters into pinned host memory, where
+ * this thread looks for them; the best candidate is decoded from its index on the host.  All work queued before is complete and visible by then; the kernel itself may take some microseconds more
  * to end, so that a query of the stream right after the call may still say busy.  The first result call of a process
  * allocates that memory, 34 KB by hipHostMalloc, held until the process ends; where that is refused, or all of its sixteen
  * boxes are in use by other threads, the results are copied instead.)  NO_FEASIBLE when
@@ -219,7 +219,7 @@ int  tessel_score_candidates(tessel_problem *p, uint64_t first, uint64_t count,
  * orders (never expected; worked out on the host, apart from the kernels). */
 int  tessel_best(tessel_problem *p, tessel_result *out);
 
-/* Decoded form of the best candidate as the GPU decoded it: leads[K], order_len[D] and
+/* Decoded form of the best candidate, worked out on the host from its index: leads[K], order_len[D] and
  * orders[D][32] (block type ids in device order, after repair in the REPAIR space), and
  * its least start times at T*: starts[K*N_R] at type*N_R + occurrence. Any pointer may be NULL. */
 int  tessel_best_candidate(tessel_problem *p, int32_t *leads, int32_t *order_len, int32_t *orders,

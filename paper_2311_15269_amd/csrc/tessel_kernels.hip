@@ -3321,8 +3321,8 @@ static comp_fn pick_completion(const CompParams &cp, const CompMatrix &cm, size_
     return most <= 2 ? complete_chain_kernel<8, 2> : complete_chain_kernel<8, 4>;
 }
 
-// Problems are taken up to 64 KB of parameters, 16-bit state, a key a type and the windows' words.  (The kernels need less: the last two are
-// those of an earlier one, and what it refused is still refused.  Only graphs and blocks on several devices come near, with a ring of 16
+// Problems are taken up to 64 KB of parameters, 16-bit state, a key a type and the windows' words.  (The last two are those of
+// an earlier kernel, and what it refused is still refused; the kernel for chains needs less, the other up to 5 KB more, hence kCompLdsMost.  Only graphs and blocks on several devices come near, with a ring of 16
 // rows for every consumed type; rings of chains have at most 16 rows too, the next power of two from twice the micro-batches of a window on,
 // and there are at most eight.)
 static_assert(ChainRows<8, 4>::token + 8 * 16 * kWave * 2 + kMaxSeq * 4 <= kCompLds && 2 * kMaxNR <= 16, "LDS of the completion kernel for chains");
