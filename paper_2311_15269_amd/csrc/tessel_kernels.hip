@@ -1679,14 +1679,14 @@ __global__ __launch_bounds__(kWave) void order_pairs_kernel(const KParams *__res
 
 // (Waves per SIMD: what the registers of the variant allow without spills in the loops; the TP variants with four waves
 // and 24 boundary values, or 8 devices, spilled up to 600 registers.)
-template <int DM, int VM, int MODE, bool TP = false>
+template <int DM, int VM, int MODE, bool TP = false, bool PAIRS = false>
 __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3) void eval_fast_kernel(const KParams *__restrict__ Pp, uint64_t first, uint64_t count,
                                                           BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
                                                           int32_t *__restrict__ peak_out, int tries, int retry_tries,
                                                           uint64_t *__restrict__ out_list, uint32_t *__restrict__ out_count,
                                                           uint32_t out_cap, uint32_t *__restrict__ overflow, uint32_t *ring_base,
                                                           uint32_t ring_words, int stage_words, int adapt, uint32_t *left_after,
-                                                          const uint32_t *__restrict__ pairs, uint32_t lead0)
+                                                          const uint32_t *__restrict__ pairs, uint32_t lead0, uint32_t scatter)
 {
     extern __shared__ uint32_t lds[];
     // the sweeps address their tables by LDS byte address from 0: the kernel has no other LDS in front of this array
@@ -1905,26 +1905,28 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
 
     const uint64_t stride = (uint64_t)gridDim.x * kWave;
     uint64_t rounds = (count + stride - 1) / stride;                // the same trip count for every lane of the grid
-    // With tables of the orders that go together (`pairs`): candidates come from there.  A unit is 32 neighbours in the order of the
+    // With tables of the orders that go together (PAIRS): candidates come from there.  A unit is 32 neighbours in the order of the
     // first device, their other orders and leads alike: a bit each by the pairs that device is in, all or none by the others.
     // Those that are left go to a list of the wave, as offsets (in ring 1, which a window built in one go leaves free), until there are
-    // 64.  The units of a wave's lanes lie far apart, so that every wave gets its share: the ones with anything left lie together.
-    constexpr bool kPairs = MODE == 0 && !TP;
+    // 64.  The units of a wave's lanes lie far apart, so that every wave gets its share: the ones with anything left lie together.  (A
+    // variant of its own: as a branch in the others it cost launches without tables 2 to 4 %.)
     static_assert(63 + 32 * kWave <= (4 + kStageMetaWords + 4 * 2) * (int)kRingSlots, "the list of a wave fits its ring");
     uint32_t *const left_list = ring1;
     uint32_t nleft = 0, out = 0;                                     // candidates on it; per lane: candidates that the tables reject
-    uint32_t n0 = 0, wpr = 0, group0 = 0, units = 0, unit_lanes = 0, unit_rounds = 0, unit_round = blockIdx.x;
-    if (kPairs && pairs) {
+    uint32_t n0 = 0, wpr = 0, group0 = 0, units = 0, unit_lanes = 0, unit_rounds = 0, unit_round = blockIdx.x, unit_shift = 0;
+    if (PAIRS) {
         n0 = (uint32_t)P.cdev[0];
         wpr = (n0 + 31u) / 32u;
         group0 = (uint32_t)(first / n0);
         units = ((uint32_t)((first + count - 1) / n0) - group0 + 1u) * wpr;
         unit_lanes = min((units + gridDim.x - 1u) / gridDim.x, (uint32_t)kWave);
         unit_rounds = (units + unit_lanes - 1u) / unit_lanes;
+        if (scatter) unit_shift = (uint32_t)lane * 0x9E3779B1u % unit_rounds;
         rounds = 0;
     }
     auto look_up = [&]() {
-        const uint32_t unit = (uint32_t)lane * unit_rounds + unit_round;
+        uint32_t unit = unit_round + unit_shift;
+        unit = (unit < unit_rounds ? unit : unit - unit_rounds) + (uint32_t)lane * unit_rounds;
         unit_round += gridDim.x;
         uint32_t left = 0, at0 = 0;
         if ((uint32_t)lane < unit_lanes && unit < units) {
@@ -2004,7 +2006,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
                 kk = valid ? tp_list[nleft + (uint32_t)lane] : 0u;
             } else r++;
         } else r++;
-        if (kPairs && pairs) {
+        if (PAIRS) {
             while (nleft < (uint32_t)kWave && unit_round < unit_rounds) look_up();
             const uint32_t n = min(nleft, (uint32_t)kWave);
             if (n == 0) return;
@@ -2075,7 +2077,7 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
     // Later phases first: a ring is served as soon as it holds 64 candidates, so that it never holds more than 127;
     // when the wave's share is used up the rings are drained on partial waves.  Every condition is wave-uniform.
     for (;;) {
-        const bool fresh = r < rounds || nleft > 0 || (kPairs && unit_round < unit_rounds);
+        const bool fresh = r < rounds || nleft > 0 || (PAIRS && unit_round < unit_rounds);
         // (one call for both rings of programs, so that the sweeps exist once in the code)
         const bool again = count3 >= (uint32_t)kWave || (!fresh && count1 == 0 && count2 == 0 && count3 > 0);
         const bool sweep = again || count2 >= (uint32_t)kWave || (!fresh && count1 == 0 && count2 > 0);
@@ -2092,9 +2094,9 @@ __global__ __launch_bounds__(kWave, MODE && !(TP && (DM > 4 || VM > 10)) ? 4 : 3
         uint64_t oi = ((uint64_t)ihi << 32) | ilo;
         if (key_less(op, oi, best, best_idx)) { best = op; best_idx = oi; }
         nsw += __shfl_xor(nsw, off);
-        if (kPairs) out += __shfl_xor(out, off);
+        if (PAIRS) out += __shfl_xor(out, off);
     }
-    if (kPairs) { nev += out; cnt[kDeadlock] += out; }
+    if (PAIRS) { nev += out; cnt[kDeadlock] += out; }
     if (lane == 0) {
         BlockRec rr;
         rr.period = best; rr.n_retried = nretry; rr.index = best_idx; rr.n_evaluated = nev; rr.n_sweeps = nsw; rr.n_blocks = nblocks; rr.n_high = 0;
@@ -2336,7 +2338,7 @@ __global__ void reset_kernel(DevResult *res, uint32_t *left_after)
 // ------------------------------------------------------------------ launchers
 typedef void (*eval_fn)(TESSEL_EVAL_KERNEL_ARGS);
 typedef void (*fast_fn)(const KParams *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, int, int, uint64_t *, uint32_t *,
-                        uint32_t, uint32_t *, uint32_t *, uint32_t, int, int, uint32_t *, const uint32_t *, uint32_t);
+                        uint32_t, uint32_t *, uint32_t *, uint32_t, int, int, uint32_t *, const uint32_t *, uint32_t, uint32_t);
 typedef void (*pairs_fn)(const KParams *, uint32_t, uint32_t, uint32_t *);
 
 // problems too wide for the fast kernel and the chain path (their state stays in LDS where 64 KB hold it)
@@ -2365,14 +2367,14 @@ static int fast_dm(const KParams &kp)
 // 9 to 16.  With room for 24, which the registers do not hold without spills in the sweeps, 2^20 candidates of a pipeline at eight
 // micro-batches take 198 us on two devices and 485 on four, with room for 16 172 and 435.  (2^21 of the X-shape on three devices: 658 and 1,015 us at
 // three and four micro-batches, 367 and 639 now: there the general kernel had to find periods that the longer search settles.)
-template <int MODE>
+template <int MODE, bool PAIRS = false>
 static fast_fn pick_fast_mode(const KParams &kp)
 {
     const int V = kp.nsweeps - 1;
     switch (fast_dm(kp)) {
-    case 2: return V <= 4 ? eval_fast_kernel<2, 4, MODE> : eval_fast_kernel<2, 16, MODE>;
-    case 4: return V <= 8 ? eval_fast_kernel<4, 8, MODE> : V <= 16 ? eval_fast_kernel<4, 16, MODE> : eval_fast_kernel<4, 24, MODE>;
-    default: return V <= 16 ? eval_fast_kernel<8, 16, MODE> : eval_fast_kernel<8, 24, MODE>;
+    case 2: return V <= 4 ? eval_fast_kernel<2, 4, MODE, false, PAIRS> : eval_fast_kernel<2, 16, MODE, false, PAIRS>;
+    case 4: return V <= 8 ? eval_fast_kernel<4, 8, MODE, false, PAIRS> : V <= 16 ? eval_fast_kernel<4, 16, MODE, false, PAIRS> : eval_fast_kernel<4, 24, MODE, false, PAIRS>;
+    default: return V <= 16 ? eval_fast_kernel<8, 16, MODE, false, PAIRS> : eval_fast_kernel<8, 24, MODE, false, PAIRS>;
     }
 }
 
@@ -2415,6 +2417,24 @@ static uint32_t pair_leads(const KParams &kp, uint64_t first, uint64_t count, ui
     if (!always && (count < kPairCandidates || n * kp.pair_bits * 4 > count)) return 0;
     lead0 = (uint32_t)l0;
     return (uint32_t)n;
+}
+
+// How eval_fast_kernel shares the units of such a launch out: a lane's lie one behind the other, those of a wave's lanes at equal distances.
+// Where that distance comes back to nearly the same order of the second device with every lane, every second or third, the lanes start at
+// places without an order instead (2,000,003 candidates of 252 orders a device, 378 of them between lanes: 194 -> 117 us and 246 -> 143 on three
+// and four devices, 171 and 223 without tables).  Equal distances are better by up to 15 % otherwise, and with few orders there is no
+// telling (0.89 to 1.12).
+static uint32_t scatter_units(const KParams &kp, uint64_t first, uint64_t count, uint32_t blocks)
+{
+    const uint64_t n0 = kp.cdev[0], words = (n0 + 31) / 32, units = ((first + count - 1) / n0 - first / n0 + 1) * words;
+    const uint64_t lanes = std::min<uint64_t>((units + blocks - 1) / blocks, kWave), apart = (units + lanes - 1) / lanes;
+    const uint64_t turn = kp.cdev[1] * words;
+    if (turn <= 512) return 0;
+    for (uint64_t k = 1; k <= 3; k++) {
+        const uint64_t off = apart * k % turn;
+        if (std::min(off, turn - off) < turn / 16) return 1;
+    }
+    return 0;
 }
 
 // state and program of the general kernel's lanes: in LDS, except for wide problems that 64 KB do not hold
@@ -2660,9 +2680,10 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
             if (rc) return rc;
             stage = (kp.total + 5) / 6;                             // (what is left mostly runs to the end)
         }
+        if (leads) ff = pick_fast_mode<0, true>(kp);
         hipLaunchKernelGGL(ff, dim3(blocks), dim3(kWave), fast_lds_bytes(kp), st, kp_dev, first, count, recs, code, peak, kp.eigen_tries,
                            kp.retry_tries, list, &res->defer_count, kWsListCap, &res->overflow, behind, ring_words(kp), stage, adapt, left_after,
-                           leads ? kp.pair_tab : nullptr, lead0);
+                           leads ? kp.pair_tab : nullptr, lead0, leads ? scatter_units(kp, first, count, (uint32_t)blocks) : 0u);
         rc = (int)hipGetLastError();
     }
     if (rc) return rc;

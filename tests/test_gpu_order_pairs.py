@@ -1,6 +1,6 @@
 """CANONICAL ranges by tables of the orders that go together (TESSEL_PAIRS=1: wherever they fit, 0: nowhere), against the oracle:
 one to several words of 32 orders of the first device, ranges that begin and end inside a word, of one candidate and of several lead
-vectors, indices from 2^32 on, devices of one, two and four types or none, dependencies that come back to a device, fixed leads."""
+vectors, units shared out without equal distances (scattered), indices from 2^32 on, devices of one, two and four types or none, dependencies that come back to a device, fixed leads."""
 import pytest
 
 from paper_2311_15269_amd import workloads as W
@@ -29,6 +29,7 @@ CASES = [("6-orders-whole", linear(2, 2, 2), 0, 288), ("6-orders-three-devices",
          ("70-orders-one", linear(4, 4, 4), 1063399420, 1), ("70-orders-in-a-word", linear(4, 4, 4), 1063399423, 7),
          ("70-orders-across-words", linear(4, 4, 4), 1063399400, 130), ("70-orders", linear(4, 4, 4), 1063390001, 40001),
          ("70-orders-leads", linear(2, 4, 5), 5000, 60001), ("252-orders", linear(3, 5, 5), 900000001, 30007),
+         ("252-orders-scattered", linear(3, 5, 5), 900000001, 63501),
          ("6-orders-8-devices", linear(8, 2, 2), 9000001, 30001), ("above-2^32", linear(5, 4, 6), 284464890000, 9001),
          ("across-2^32", dict(forward(4, 2, 6), fixed_leads=LEADS), (1 << 32) - 2000, 4001),
          ("four-types", placed([0, 1, 1, 0], 2, 2, 3), 777, 20011), ("back-and-forth", placed([0, 1, 0, 2], 3, 2, 3), 30000, 20011),
