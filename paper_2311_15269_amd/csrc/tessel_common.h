@@ -54,11 +54,15 @@ __device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c)
 #define TESSEL_PIN(x) asm volatile("" : "+v"(x))
 
 // The waves of a SIMD issue first in turns of 10 us, by their place on it (bits 0 to 3 of HW_ID) and the clock.  At one priority the oldest
-// does: waves with the same work end one after the other, and the last runs alone.  2^22 of the K-shape, four waves a SIMD: 538 -> 480 us a
-// call; 100,003 windows of 288 blocks on 12 devices, one round of candidates at three waves: 260 -> 235.
-__device__ __forceinline__ void take_turn()
+// does: waves with the same work end one after the other, and the last runs alone.  `turns`, a wave's word: among how many it takes turns
+// less one (a mask), the highest step of these that it gets << 2, what is added to the step << 4; 0, looked at by the callers: no turns.  (The clock takes a
+// wave that is alone on its SIMD some 300 cycles a look, 300 candidates of 72 to 96 blocks 2 to 4 us a call; the callers put the call out of the way,
+// which is worth another 0.5.)
+__host__ __device__ constexpr uint32_t turns_of(uint32_t mask, uint32_t highest, uint32_t add) { return mask | highest << 2 | add << 4; }
+__device__ __forceinline__ void take_turn(uint32_t turns)
 {
-    const uint32_t turn = (((uint32_t)__builtin_amdgcn_s_memrealtime() >> 10) + __builtin_amdgcn_s_getreg((3 << 11) | 4)) & 3u;
+    const uint32_t clock = ((uint32_t)__builtin_amdgcn_s_memrealtime() >> 10) + __builtin_amdgcn_s_getreg((3 << 11) | 4);
+    const uint32_t turn = min(clock & turns & 3u, turns >> 2 & 3u) + (turns >> 4);
     if (turn == 0u) __builtin_amdgcn_s_setprio(0);
     else if (turn == 1u) __builtin_amdgcn_s_setprio(1);
     else if (turn == 2u) __builtin_amdgcn_s_setprio(2);

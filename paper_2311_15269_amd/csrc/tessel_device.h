@@ -354,8 +354,11 @@ struct LaunchShape { int blocks, list_blocks, threads; size_t lds_bytes; };   //
 
 // tessel_graph.hip
 const void *graph_kernel(const KParams &kp);
+// take_turn's words, of the first `more` workgroups, which have candidates in the last round, and of the others: for waves that seven eighths of their
+// first 64 candidates and more survive the build of, from there on; for all others, and up to there
+struct GraphTurns { uint32_t more, last, others, few_last, few_others; };
 int launch_graph(const KParams &kp, uint64_t first, uint64_t count, int blocks, void *recs, int32_t *code, int32_t *peak, void *ws,
-                 uint32_t *slots, void *stream);
+                 uint32_t *slots, GraphTurns turns, void *stream);
 // tessel_mail.hip: `bytes` of the workspace from `offset` on (multiples of four) to `mail`
 int launch_tell(void *ws, size_t offset, size_t bytes, DevMail *mail, uint32_t told, void *stream);
 // kernels.hip

@@ -80,13 +80,15 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
                                                            uint64_t count, BlockRec *__restrict__ recs, int32_t *__restrict__ code_out,
                                                            int32_t *__restrict__ peak_out, uint64_t *__restrict__ out_list,
                                                            uint32_t *__restrict__ out_count, uint32_t out_cap,
-                                                           uint32_t *__restrict__ overflow, uint32_t *slots_all)
+                                                           uint32_t *__restrict__ overflow, uint32_t *slots_all, GraphTurns waves)
 {
     extern __shared__ uint32_t lds[];
     // all LDS addresses below are offsets from 0: nothing else of the kernel lies in front of this array
     if (lds_address(lds) != 0u) { if (threadIdx.x == 0) *overflow = 0x100u; return; }
     const KParams &P = *Pp;
     const GraphTab &G = *Gp;
+    const bool in_last = blockIdx.x < waves.more;
+    uint32_t turns = in_last ? waves.few_last : waves.few_others;
     const int lane = threadIdx.x;
     const uint32_t lane4 = (uint32_t)lane * 4u;
     for (int w = lane; w < G.ntab; w += kWave) lds[w] = G.tab[w];
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
             const uint32_t e0 = step(), e1 = step();
             prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
             if (!REPAIR || (wi & 7) == 7) {
-                if ((wi & 7) == 7) take_turn();
+                if (__builtin_expect((wi & 7) == 7 && turns != 0, 0)) take_turn(turns);
                 const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
                 if (__ballot(going) == 0) { whole = false; break; }
             }
@@ -373,7 +375,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
             const uint32_t e0 = step(), e1 = step();
             prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
             if (!REPAIR || (wi & 7) == 7) {
-                if ((wi & 7) == 7) take_turn();
+                if (__builtin_expect((wi & 7) == 7 && turns != 0, 0)) take_turn(turns);
                 const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
                 if (__ballot(going) == 0) { whole = false; break; }
             }
@@ -697,7 +699,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
             const uint32_t e0 = step(), e1 = step();
             prog[(size_t)wi * kProgRow] = e0 | e1 << 16;
             if (!REPAIR || (wi & 7) == 7) {
-                if ((wi & 7) == 7) take_turn();
+                if (__builtin_expect((wi & 7) == 7 && turns != 0, 0)) take_turn(turns);
                 const bool going = valid && (REPAIR ? !(drop_mem && worst > M) : building);
                 if (__ballot(going) == 0) { whole = false; break; }
             }
@@ -846,7 +848,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
 #pragma unroll
             for (int q = 0; q < 4; q++) cur[q] = prog[(size_t)q * kProgRow];
             for (int wi = 0; wi < nwords; wi += 4) {
-                if ((wi & 12) == 0) take_turn();
+                if (__builtin_expect((wi & 12) == 0 && turns != 0, 0)) take_turn(turns);
                 const int ahead = wi + 4 < nwords ? wi + 4 : wi;
 #pragma unroll
                 for (int q = 0; q < 4; q++) nxt[q] = prog[(size_t)(ahead + q) * kProgRow];
@@ -1019,6 +1021,10 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
             const bool valid = kk < count;
             build(valid ? first + kk : first, valid);
             __syncthreads();
+            if (r == 1 && slots_in(1u, false, unused) >= 7u * (uint32_t)kWave / 8u) {
+                turns = in_last ? waves.last : waves.others;
+                __builtin_amdgcn_s_setprio(0);
+            }
         } else break;
     }
     if (!recs) return;
@@ -1041,7 +1047,7 @@ __global__ __launch_bounds__(kWave, KIND >= 3 ? 4 : 1) void eval_graph_kernel(co
 
 // ------------------------------------------------------------------ launcher
 typedef void (*graph_fn)(const KParams *, const GraphTab *, uint64_t, uint64_t, BlockRec *, int32_t *, int32_t *, uint64_t *, uint32_t *,
-                         uint32_t, uint32_t *, uint32_t *);
+                         uint32_t, uint32_t *, uint32_t *, GraphTurns);
 
 template <bool REPAIR, int KIND>
 static graph_fn pick_np(int np)
@@ -1064,12 +1070,12 @@ static graph_fn pick_graph(const KParams &kp) { return kp.space == kSampledRepai
 const void *graph_kernel(const KParams &kp) { return (const void *)pick_graph(kp); }
 
 int launch_graph(const KParams &kp, uint64_t first, uint64_t count, int blocks, void *recs, int32_t *code, int32_t *peak, void *ws,
-                 uint32_t *slots, void *stream)
+                 uint32_t *slots, GraphTurns turns, void *stream)
 {
     DevResult *res = (DevResult *)((char *)ws + kWsResultOff);
     hipLaunchKernelGGL(pick_graph(kp), dim3(blocks), dim3(kWave), kp.graph_lds, (hipStream_t)stream, (const KParams *)((char *)ws + kWsParamsOff),
                        (const GraphTab *)((char *)ws + kp.graph_at), first, count, (BlockRec *)recs, code, peak,
-                       (uint64_t *)((char *)ws + kWsListOff), &res->defer_count, kWsListCap, &res->overflow, slots);
+                       (uint64_t *)((char *)ws + kWsListOff), &res->defer_count, kWsListCap, &res->overflow, slots, turns);
     return (int)hipGetLastError();
 }
 

@@ -2635,6 +2635,33 @@ static int launch_general(const KParams &kp, void *ws, uint64_t first, uint64_t 
     return (int)hipGetLastError();
 }
 
+// How the waves of the graph kernel take turns on their SIMD (take_turn), by the rounds of candidates that a wave of the grid has.  Time with
+// turns by that without, geometric means over 55 chains and graphs, least and most in brackets (2^22 candidates of the K-shape 538 -> 480 us a
+// call; 100,003 windows of 288 blocks on 12 devices, one round of three waves a SIMD, 260 -> 235):
+//   12 or 16 waves a CU, all alike
+//       up to 0.3 of a round 1.01 (the clock), 0.4 0.98, 0.75 to one 0.96 (0.92, 1.01)
+//       the last round filled to five eighths and more 0.92 to 0.97 (0.89, 1.02)
+//       4.2 rounds and more 0.96 to 0.92 (0.87, 1.03)
+//   fewer than that in the last round, of 1.06 to 3.5: the waves with candidates in it are the oldest and ended sooner at one priority, but where few
+//   candidates survive the build a round more is a build more, and the sweeps are for the end
+//       seven eighths of the candidates and more survive: all alike 1.00 to 1.08 (0.92, 1.15), so not so, but
+//           up to 1.25 rounds none (the waves of the last round first 1.02)
+//           from 2 on, to a quarter, these first, the others in turns on the three steps below: 0.98 (0.93, 1.02) in 2.1 rounds, 0.94 in 3.2
+//           more of it, these first, both by twos: 0.98 (0.96, 1.02) in 1.3 to 2.6 rounds, 0.99 in 3.5
+//       fewer: all alike 0.97 (0.91, 1.02); up to 1.25 rounds 0.99 (0.95, 1.12), there these first and the others below, 0.99 (0.95, 1.02)
+//   other numbers of waves, unlike on the SIMDs, or fewer: 0.99 to 1.01 (0.91, 1.11), no order to it
+static GraphTurns graph_turns(uint64_t count, int blocks, int num_cus)
+{
+    const uint64_t round = (uint64_t)blocks * kWave, last = (count - 1) % round + 1;
+    constexpr uint32_t alike = turns_of(3, 3, 0);
+    constexpr uint32_t first = turns_of(0, 0, 3), below = turns_of(3, 2, 0);
+    if (blocks < 12 * num_cus || blocks % (4 * num_cus) != 0 || 3 * count < round) return {0, 0, 0, 0, 0};
+    if (count <= round || count > 4 * round || 8 * last >= 5 * round) return {0, alike, alike, alike, alike};
+    const uint32_t more = (uint32_t)((last + kWave - 1) / kWave);
+    if (4 * last > round) return {more, turns_of(1, 1, 2), turns_of(1, 1, 0), alike, alike};
+    return count > 2 * round ? GraphTurns{more, first, below, alike, alike} : GraphTurns{more, 0, 0, first, below};
+}
+
 // Scores [first, first+count).  Where the problem allows it: the fast kernel (a short eigenvector search, a longer one
 // for the candidates that did not converge) or the graph kernel, then the general kernel over what these could not finish (next
 // to nothing in most problems).  Otherwise the general kernel alone.  `recs` may be null: per-candidate outputs only.
@@ -2661,11 +2688,11 @@ static int launch_pass(const KParams &kp, uint64_t first, uint64_t count, void *
         return (int)hipGetLastError();
     }
     int rc;
-    if (graph)
+    if (graph) {
         // (every problem its tables hold: on 24 blocks of three devices 4.5 times the general kernel's rate, on 96 to 288
         // blocks 34 to 78 times; one to 4,096 scores of 6 to 12 blocks 33 to 54 us against 39 to 82)
-        rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, behind, st);
-    else {
+        rc = launch_graph(kp, first, count, blocks, recs, code, peak, ws, behind, graph_turns(count, s.blocks, num_cus), st);
+    } else {
         int adapt = 0;
         int stage = stage_words(kp, peak != nullptr, count, s.blocks, adapt);
         uint32_t lead0 = 0;
