@@ -128,7 +128,9 @@ typedef struct {
     uint64_t n_reject[TESSEL_NUM_STATUS];     /* indexed by TESSEL_STATUS_*; [0] unused        */
     uint64_t n_window_sweeps;                 /* sweeps of the window spent on period computations
                                                  (0 when the graph or the general kernel did the
-                                                 scoring)                                        */
+                                                 scoring; this and the next of a handle of
+                                                 tessel_search_run: what scoring the incumbent
+                                                 alone takes)                                    */
     uint64_t n_blocks_placed;                 /* blocks the builds placed in executable order: a candidate that
                                                  is over the cap early is not built to the end by
                                                  tessel_eval_candidates (exact in the REPAIR space, an upper
@@ -325,8 +327,9 @@ int  tessel_search_workspace_bytes(const tessel_problem_desc *desc, const tessel
  * serial time, which would leave a problem that cannot beat serial execution without any
  * schedule).  desc->nr and desc->fixed_leads are ignored.  Synchronises `hip_stream` between
  * launches.  On success *best_out (if not NULL) is a new problem handle of window size
- * best_nr, bound to `workspace_dev`, whose running best is the incumbent: tessel_best,
- * tessel_best_candidate and tessel_complete_schedule apply; the caller destroys it.
+ * best_nr, bound to `workspace_dev`, whose running best is the incumbent, as if that
+ * alone had been scored: tessel_best, tessel_best_candidate and tessel_complete_schedule apply; the caller destroys it.  Nothing
+ * that the call queued is left on `hip_stream`.
  * Errors: those of tessel_problem_create for any window size, WORKSPACE, HIP, and NO_FEASIBLE
  * (the fields of *io are still filled in; no handle is returned). */
 int  tessel_search_run(const tessel_problem_desc *desc, tessel_search *io, void *workspace_dev,

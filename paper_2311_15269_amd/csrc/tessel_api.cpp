@@ -1407,15 +1407,79 @@ void decode_candidate(const tessel_problem *p, uint64_t idx, Detail &c)
     }
 }
 
-// p->starts and p->period_right of the running best just read
+// p->starts and p->period_right of the running best just read, and of its window if it has one
+void check_period(tessel_problem *p, bool executable, const Window &w, const std::vector<int> &rank)
+{
+    std::vector<int> s;
+    p->starts.assign((size_t)p->kp.K * p->kp.NR, 0);
+    p->period_right = executable && is_least_period(w, p->result.period, s);
+    if (p->period_right)
+        for (size_t k = 0; k < p->starts.size(); k++) p->starts[k] = s[rank[k]];
+}
+
 void check_period(tessel_problem *p)
 {
     Window w;
-    std::vector<int> rank, s;
-    p->starts.assign((size_t)p->kp.K * p->kp.NR, 0);
-    p->period_right = p->detail.status == kOk && make_window(p, p->detail, w, rank) && is_least_period(w, p->result.period, s);
-    if (p->period_right)
-        for (size_t k = 0; k < p->starts.size(); k++) p->starts[k] = s[rank[k]];
+    std::vector<int> rank;
+    const bool executable = p->detail.status == kOk && make_window(p, p->detail, w, rank);
+    check_period(p, executable, w, rank);
+}
+
+// The two counters of a record that scoring this candidate alone leaves behind: blocks placed, and the window sweeps of the fast kernel
+// (period_fast).  One sweep: the end times of all blocks of one window after those of the window before, 0 before the first.
+// The values whose growths tell the period: every device's last end, and for every chain and micro-batch on its way through
+// it at the window's end the last end on that micro-batch.
+void count_alone(const tessel_problem *p, const Window &w, const std::vector<int> &rank, DevResult &record)
+{
+    const KParams &kp = p->kp;
+    const int NR = kp.NR;
+    if (!kp.fast_ok || p->force_general) return;             // (the other kernels count neither)
+    record.n_blocks = (uint64_t)kp.total;
+    std::vector<int> values;
+    for (int d = 0; d < kp.D; d++)
+        if (const int n = p->detail.order_len[d]) values.push_back(rank[(int)p->detail.orders[d][n - 1] * NR + NR - 1]);
+    for (int head = 0; head < kp.K; head++) {
+        if (kp.pred[head] >= 0) continue;
+        for (int m = 0; m < p->detail.leads[head]; m++) {
+            int g = head;                                    // the last type of the chain that has handled micro-batch m + N_R
+            while (kp.succ[g] >= 0 && p->detail.leads[kp.succ[g]] > m) g = kp.succ[g];
+            values.push_back(rank[g * NR + m + NR - p->detail.leads[g]]);
+        }
+    }
+    std::vector<int> end, before, grown(values.size()), was;
+    // sweeps until the period shows, at most `tries`; `shown`: whether it did
+    auto sweeps = [&](int tries, bool settle, bool &shown) -> int {
+        end.assign(w.blocks, 0);
+        int top_before = 0;
+        for (int j = 0; j < tries; j++) {
+            before = end;
+            std::fill(end.begin(), end.end(), 0);
+            for (const Edge &e : w.edges) if (e.lag) end[e.v] = std::max(end[e.v], before[e.u]);       // (start times so far)
+            for (int u = 0; u < w.blocks; u++) {
+                end[u] += w.edges[w.from[u]].w;
+                for (int e = w.from[u]; e < w.from[u + 1]; e++)
+                    if (!w.edges[e].lag) end[w.edges[e].v] = std::max(end[w.edges[e].v], end[u]);
+            }
+            for (size_t v = 0; v < values.size(); v++) grown[v] = end[values[v]] - before[values[v]];
+            const int top = *std::max_element(grown.begin(), grown.end());
+            shown = *std::min_element(grown.begin(), grown.end()) == top;
+            if (settle && j > 0 && top == top_before) {
+                bool held = true;
+                for (size_t v = 0; v < values.size(); v++) held = held && (was[v] != top || grown[v] == top);
+                shown = shown || held;
+            }
+            if (shown) return j + 1;
+            top_before = top; was = grown;
+        }
+        return tries;
+    };
+    bool shown = false;
+    record.n_sweeps = (uint64_t)sweeps(kp.eigen_tries, false, shown);
+    if (!shown) {
+        record.n_sweeps += (uint64_t)sweeps(kp.retry_tries, true, shown);
+        record.n_retried = 1;
+        record.n_deferred = shown ? 0 : 1;
+    }
 }
 
 }  // namespace
@@ -2054,18 +2118,27 @@ extern "C" int tessel_search_run(const tessel_problem_desc *desc, tessel_search 
         tessel_problem *p = nullptr;
         int rc = tessel_problem_create(&d, &p);
         if (rc) return rc;
-        // (the incumbent as the only candidate scored; its period is checked like that of every record read back)
+        // (The incumbent as the only candidate scored.  Its period is checked like that of every record read back, while the copy is on its way.
+        // Once this returns nothing is to come that would write the workspace, on whatever stream the caller uses it then.)
         DevResult best;
         memset(&best, 0, sizeof best);
         best.period = io->best_period; best.index = io->best_index; best.n_evaluated = 1; best.n_status[kOk] = 1;
+        decode_candidate(p, best.index, p->detail);
+        Window w;
+        std::vector<int> rank;
+        const bool executable = p->detail.status == kOk && make_window(p, p->detail, w, rank);
+        if (executable) count_alone(p, w, rank, best);
         rc = bind_workspace(p, workspace_dev, workspace_bytes, (hipStream_t)hip_stream, 0, &best);
         if (rc) { tessel_problem_destroy(p); return rc; }
         p->stream = (hipStream_t)hip_stream;
         p->ranges.push_back({io->best_index, 1});
         p->result = best;
-        decode_candidate(p, best.index, p->detail);
-        check_period(p);
-        if (!p->period_right) { tessel_problem_destroy(p); return TESSEL_E_HIP; }        // never expected
+        check_period(p, executable, w, rank);
+        // (asked again and again: hipStreamSynchronize took 5 us more)
+        hipError_t e;
+        while ((e = hipStreamQuery((hipStream_t)hip_stream)) == hipErrorNotReady) { }
+        if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();       // (no later launch of this thread fails by it)
+        if (e != hipSuccess || !p->period_right) { tessel_problem_destroy(p); return TESSEL_E_HIP; }      // (the latter never expected)
         *best_out = p;
     }
     return TESSEL_OK;

@@ -123,3 +123,50 @@ def test_xshape_window_of_two_reaches_the_bubble_of_the_direct_bidirectional_sch
     for nr in (1, 2):
         sc = O.Oracle(dict(prob, NR=nr)).eval_index(got["index_nr"][nr - 1])
         assert sc["status"] == 0 and sc["period"] == got["period_nr"][nr - 1] and sc["peak_max"] <= 4
+
+
+def chains(seed):
+    """a problem of disjoint chains with times that few sweeps settle or that never all grow alike: forward-only, there and back, two ways, shared blocks"""
+    import random
+    rng = random.Random(seed)
+    D, nr = rng.randint(2, 8), rng.randint(1, 6)
+    space = rng.choice(["sampled_repair", "sampled_repair", "sampled_strict"])
+    kind = seed % 4
+    if kind == 0:
+        prob = {"name": "forward", "D": D, "K": D, "NR": 1, "M": 1, "t": [rng.randint(1, 9) for _ in range(D)], "m": [0] * D,
+                "dev_mask": [1 << d for d in range(D)], "deps": [(d, d + 1) for d in range(D - 1)], "space": space, "seed": seed, "lead_step_q16": 30000,
+                "fixed_leads": None}
+    elif kind == 1:
+        prob = W.pipeline_problem(W.linear_placement(D), [rng.randint(1, 7) for _ in range(D)], [rng.randint(1, 9) for _ in range(D)], D, 1, 20, space,
+                                  seed=seed, lead_step_q16=20000)
+    elif kind == 2:
+        prob = W.xshape_problem(min(D, 4), rng.randint(1, 3), rng.randint(1, 7), 1, 20, space, seed=seed, lead_step_q16=20000)
+    else:
+        every = (1 << D) - 1
+        prob = {"name": "shared", "D": D, "K": 2 * D + 2, "NR": 1, "M": 40, "t": [rng.randint(1, 6) for _ in range(2 * D + 2)],
+                "m": [2] + [1] * D + [-1] * D + [-2], "dev_mask": [every] + [1 << d for d in range(D)] + [1 << d for d in reversed(range(D))] + [every],
+                "deps": [(i, i + 1) for i in range(2 * D + 1)], "space": space, "seed": seed, "lead_step_q16": 20000, "fixed_leads": None}
+    return prob, nr if kind != 2 else min(nr, 4)
+
+
+ALONE = [(c[1], c[2], min(c[3], 6000), c[5]) for c in CASES] + [chains(seed) + (40, False) for seed in range(48)]
+
+
+@pytest.mark.parametrize("problem,max_nr,budget,bound", ALONE, ids=range(len(ALONE)))
+def test_the_handle_is_that_of_the_incumbent_scored_alone(gpu, problem, max_nr, budget, bound):
+    """best, candidate and counters of the returned handle, before and after another range, are those of a handle that scored the incumbent alone;
+    nothing of the search is left on the stream, so that the workspace is free for any other"""
+    import torch
+    got, best = gpu.search(problem, max_nr, budget, use_inflight_bound=bound)
+    if best is None:
+        assert got["best_nr"] == 0
+        return
+    assert torch.cuda.current_stream().query()
+    alone = gpu.Problem(dict(problem, NR=got["best_nr"], fixed_leads=None))
+    alone.eval_candidates(got["best_index"], 1)
+    assert best.best() == alone.best()
+    mine, his = best.best_candidate(), alone.best_candidate()
+    assert mine["leads"] == his["leads"] and mine["orders"] == his["orders"] and mine["starts"].tolist() == his["starts"].tolist()
+    for handle in (best, alone):
+        handle.eval_candidates(0, min(500, handle.candidate_count()))
+    assert best.best() == alone.best()
