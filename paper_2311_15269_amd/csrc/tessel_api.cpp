@@ -191,7 +191,6 @@ static bool code_tables(const tessel_problem &p, GraphTab &gt, const std::vector
     gt.codes = ts == 256 ? 2 : 1;
     gt.apart = 1;                                            // (a chain's types share its ring: KParams::ring_kept)
     gt.np = packed ? 0 : nb;
-    gt.code_rows = (uint32_t)rows;
     std::vector<int> code(K, 0);
     for (int d = 0; d < D; d++)
         for (int y = 0; y < kp.ntd[d]; y++)
@@ -246,14 +245,19 @@ static bool graph_code_tables(const tessel_problem &p, GraphTab &gt, const std::
 {
     const KParams &kp = p.kp;
     const int D = kp.D, K = kp.K, NR = kp.NR;
-    if (gt.chain || kp.tp || gt.np != 1 || 2 * D > 32 || K > 16 || NR > 8 || gt.maxin > 2 || gt.maxout > 2) return false;
+    constexpr int most_types = 16, most_nr = 8, most_devices = 16;
+    if (gt.chain || kp.tp || gt.np != 1 || D > most_devices || K > most_types || NR > most_nr || gt.maxin > 2 || gt.maxout > 2) return false;
     if (kp.space != kSampledStrict && kp.space != kSampledRepair) return false;
     size_t distinct = 0;
     for (int i = 0; i < K; i++) distinct += in[i].size();
     if (distinct != p.dep_src.size() || span_max > 30000) return false;
     if ((int64_t)kp.UB * (std::max(9, gt.retry_tries) + 1) > 65535) return false;
     constexpr int rows = 3, words = 8, mem_at = 16;
-    const uint32_t row = kWave * 4, half = row / 2, ts = 128;
+    constexpr uint32_t row = kWave * 4, half = row / 2, ts = 128;
+    // (the layout below overwrites that of words by type, so nothing is refused from here on)
+    static_assert(words * ts + most_types * 16 + 3 * row + (2 * most_devices + most_types * 3 * most_nr + 2 * most_nr) * half + most_types / 4 * row <= 64 * 1024 - row &&
+                  words * ts + most_types * 16 + 2 * row + most_devices * rows * row <= 64 * 1024 - row,
+                  "tables and the rows of the build and of the sweeps fit");
     uint32_t at = (uint32_t)words * ts;
     gt.sw = at; at += (uint32_t)K * 16;
     gt.ntab = (int)(at / 4);
@@ -270,7 +274,6 @@ static bool graph_code_tables(const tessel_problem &p, GraphTab &gt, const std::
     gt.strash = at; at += (uint32_t)(kp.has_fixed ? 2 * NR : NR) * half;
     at = (at + row - 1) / row * row;
     gt.leads = at; at += (uint32_t)((kp.ntok + 3) / 4) * row;
-    if (std::max(build_end, at) > 64 * 1024 - row) { gt.apart_rows = 0; return false; }
     gt.lds_bytes = std::max(build_end, at);
     memset(gt.tab, 0, sizeof gt.tab);
     gt.apart = 1;
@@ -278,7 +281,6 @@ static bool graph_code_tables(const tessel_problem &p, GraphTab &gt, const std::
         if (kp.ring_kept[r] == kp.ring_base[r]) { gt.ring[r] = (uint32_t)kp.ring_base[r] | row_at << 16; row_at += (uint32_t)NR; }
     gt.codes = 3;
     gt.np = 0;
-    gt.code_rows = rows;
     std::vector<int> code(K, 0);
     for (int d = 0; d < D; d++)
         for (int y = 0; y < kp.ntd[d]; y++) code[kp.type_of[d] >> (8 * y) & 0xFFu] = 2 * d + y;
