@@ -790,7 +790,6 @@ extern "C" int tessel_problem_create(const tessel_problem_desc *desc, tessel_pro
                 kp.mask_of[d] |= (desc->dev_mask[i] & 0xFFu) << (8 * n);
                 kp.tok_of[d] |= (uint32_t)(D + path_of[i] * 2 * NR) << (8 * n);
                 kp.home_of[d] |= (uint32_t)home[i] << (8 * n);
-                kp.t_of[d][n] = desc->time[i];
             }
             kp.predmask_of[d][n] = kp.predmask[i];
             kp.m_of[d][n] = desc->mem[i];

@@ -93,7 +93,6 @@ struct KParams {
     uint32_t mask_of[kMaxD];     // 4 x 8 bit: device mask of that type
     uint32_t tok_of[kMaxD];      // 4 x 8 bit: first token slot of the type's chain
     uint32_t home_of[kMaxD];     // 4 x 8 bit: (lowest device)*4 + local symbol there
-    int32_t  t_of[kMaxD][kMaxLT];
     int32_t  m_of[kMaxDW][kMaxLTW];
     int8_t   succ[kMaxK];        // consumer type of type g or -1
     uint8_t  edge_out[kMaxK];    // position of the dependency g -> succ[g] in the caller's list
@@ -328,7 +327,6 @@ struct GraphTab {
     // `codes`: 0 not such, 1 up to 32 codes, 2 up to 64; np is 0 then where a device's order and its entries left share a word
     // 3: such graphs, with up to two producers and two consumers a type
     int32_t  codes;
-    uint32_t code_rows;          // rows of a device record
     int32_t  apart;              // the rows that keep the last boundary's values are no rings' own; how many of them
     int32_t  apart_rows;         // lie behind the device times at the last boundary
     uint32_t free0, free1;       // graphs: codes without a first, a second producer
