@@ -3346,8 +3346,8 @@ __global__ void completion_reset_kernel(DevCompletion *res)
 typedef void (*comp_fn)(const CompParams *, const CompMatrix *, uint64_t, uint64_t, CompRec *, int32_t *);
 
 // The kernel and the LDS of a workgroup.  Chains whose types sit on one device each: rows for 4 or 8 devices with 2 or 4 types each, then
-// the ring of every chain, then (no matrix) one word per block of the window.  Others: 16-bit state and parameters.
-constexpr size_t kCompLds = 64 * 1024, kCompLdsMost = 72 * 1024;     // the size that problems are taken by, and what the kernels make of it at most
+// the ring of every chain, then (no matrix) one word per block of the window.  Others: the rows of ScanRows.
+constexpr size_t kCompLds = 64 * 1024;      // the size that problems are taken by
 static comp_fn pick_completion(const CompParams &cp, const CompMatrix &cm, size_t &lds)
 {
     bool chain = cp.npaths <= 8 && !cp.dag;
@@ -3370,7 +3370,7 @@ static comp_fn pick_completion(const CompParams &cp, const CompMatrix &cm, size_
 }
 
 // Problems are taken up to 64 KB of parameters, 16-bit state, a key a type and the windows' words.  (The last two are those of
-// an earlier kernel, and what it refused is still refused; the kernel for chains needs less, the other up to 5 KB more, hence kCompLdsMost.  Only graphs and blocks on several devices come near, with a ring of 16
+// an earlier kernel, and what it refused is still refused; the kernel for chains needs less, the other up to 5 KB more.  Only graphs and blocks on several devices come near, with a ring of 16
 // rows for every consumed type; rings of chains have at most 16 rows too, the next power of two from twice the micro-batches of a window on,
 // and there are at most eight.)
 static_assert(ChainRows<8, 4>::token + 8 * 16 * kWave * 2 + kMaxSeq * 4 <= kCompLds && 2 * kMaxNR <= 16, "LDS of the completion kernel for chains");
@@ -3389,9 +3389,9 @@ int launch_completions(const CompParams &cp, const CompMatrix &cm, uint64_t firs
     hipStream_t st = (hipStream_t)stream;
     size_t lds;
     comp_fn fn = pick_completion(cp, cm, lds);
-    if (lds > kCompLdsMost) return -1;
+    if (lds > lds_per_workgroup()) return -1;
     if (lds > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kCompLdsMost);
+        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
     int per_cu = (int)((160 * 1024) / ((lds + 511) / 512 * 512));
