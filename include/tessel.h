@@ -210,7 +210,7 @@ int  tessel_score_candidates(tessel_problem *p, uint64_t first, uint64_t count,
  * waits for.  (One kernel on that stream stores the best key and the counters into pinned host memory, where
  * this thread looks for them; the best candidate is decoded from its index on the host.  All work queued before is complete and visible by then; the kernel itself may take some microseconds more
  * to end, so that a query of the stream right after the call may still say busy.  The first result call of a process
- * allocates that memory, 34 KB by hipHostMalloc, held until the process ends; where that is refused, or all of its sixteen
+ * allocates that memory, 4 KB by hipHostMalloc, held until the process ends; where that is refused, or all of its sixteen
  * boxes are in use by other threads, the results are copied instead.)  NO_FEASIBLE when
  * nothing feasible has been scored (counters in *out are still valid).  If a launch left more
  * candidates to the general kernel than its list holds (2^20 of a range of up to 2^26: possible only
