@@ -1,5 +1,5 @@
-"""The decoded best candidate where a lane keeps a block type: one to eight types a device, 32 and 64 lanes filled to the last and one device
-more (where one lane keeps a device), as many producers as a lane's word holds and one more, blocks on several devices on both halves of the wave."""
+"""The best candidate as the host decodes it from its index, against the oracle candidate by candidate: one to eight types a device, the most and
+nearly the most devices, micro-batches and producers, blocks on several devices, every space, fixed leads."""
 import numpy as np
 import pytest
 
@@ -16,7 +16,6 @@ def folded(D, nr, cap):
                               "sampled_repair", seed=78, lead_step_q16=6000, name="folded-%d" % D)
 
 
-# (more than 64 lanes at 4 a device)
 def three_on_one(D, nr, space="sampled_repair"):
     """a forward-only pipeline whose last two stages sit on device 0 as well"""
     prob = inference(D, nr, space)
