@@ -2355,24 +2355,21 @@ static eval_fn pick_kernel(const KParams &kp)
     return eval_kernel<8, 24>;
 }
 
-// devices of the fast kernel's variant: 2, 4 or 8 (two devices with more than 16 boundary values go with four:
-// the X-shape on two devices at six micro-batches 431 us for 2^21 candidates, 482 with a variant for two and 24 values)
-static int fast_dm(const KParams &kp)
-{
-    const int V = kp.nsweeps - 1;
-    return kp.D <= 2 && (kp.fast_tp || V <= 16) ? 2 : kp.D <= 4 ? 4 : 8;
-}
+// devices of the fast kernel's variant: 2, 4 or 8
+static int fast_dm(const KParams &kp) { return kp.D <= 2 ? 2 : kp.D <= 4 ? 4 : 8; }
 
 // Boundary values of the variant: the fewest that hold the problem's.  Most windows of five and more micro-batches on up to four devices have
 // 9 to 16.  With room for 24, which the registers do not hold without spills in the sweeps, 2^20 candidates of a pipeline at eight
-// micro-batches take 198 us on two devices and 485 on four, with room for 16 172 and 435.  (2^21 of the X-shape on three devices: 658 and 1,015 us at
+// micro-batches take 198 us on two devices and 485 on four, with room for 16 172 and 435.  Two devices have 17 values at most (three chains at
+// five micro-batches, five at three).  By the variant for four devices 2^21 candidates take 796 us with repair, 516 without and 616 in a canonical
+// range, with room for 24 on two 428, 273 and 411.  (2^21 of the X-shape on three devices: 658 and 1,015 us at
 // three and four micro-batches, 367 and 639 now: there the general kernel had to find periods that the longer search settles.)
 template <int MODE, bool PAIRS = false>
 static fast_fn pick_fast_mode(const KParams &kp)
 {
     const int V = kp.nsweeps - 1;
     switch (fast_dm(kp)) {
-    case 2: return V <= 4 ? eval_fast_kernel<2, 4, MODE, false, PAIRS> : eval_fast_kernel<2, 16, MODE, false, PAIRS>;
+    case 2: return V <= 4 ? eval_fast_kernel<2, 4, MODE, false, PAIRS> : V <= 16 ? eval_fast_kernel<2, 16, MODE, false, PAIRS> : eval_fast_kernel<2, 24, MODE, false, PAIRS>;
     case 4: return V <= 8 ? eval_fast_kernel<4, 8, MODE, false, PAIRS> : V <= 16 ? eval_fast_kernel<4, 16, MODE, false, PAIRS> : eval_fast_kernel<4, 24, MODE, false, PAIRS>;
     default: return V <= 16 ? eval_fast_kernel<8, 16, MODE, false, PAIRS> : eval_fast_kernel<8, 24, MODE, false, PAIRS>;
     }

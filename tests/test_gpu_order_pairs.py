@@ -23,6 +23,12 @@ def placed(where, D, nr, cap):
     return W.pipeline_problem(where, [1 + i % 3 for i in range(len(where))], [2 + i % 2 for i in range(len(where))], D, nr, cap, "canonical")
 
 
+def seventeen(nr):
+    """two devices, chains of one, one and two types: 17 boundary values at five micro-batches"""
+    return {"name": "seventeen", "D": 2, "K": 4, "NR": nr, "M": 0, "t": [2, 3, 1, 4], "m": [0] * 4, "dev_mask": [1, 2, 1, 2], "deps": [(2, 3)],
+            "space": "canonical", "seed": 0, "lead_step_q16": 0, "fixed_leads": None}
+
+
 # name, problem, first index (None: the last `count` candidates), count
 CASES = [("6-orders-whole", linear(2, 2, 2), 0, 288), ("6-orders-three-devices", linear(3, 2, 2), 17, 1001),
          ("20-orders", linear(4, 3, 3), 1000003, 40000), ("20-orders-end", linear(4, 3, 3), None, 5003),
@@ -34,7 +40,8 @@ CASES = [("6-orders-whole", linear(2, 2, 2), 0, 288), ("6-orders-three-devices",
          ("across-2^32", dict(forward(4, 2, 6), fixed_leads=LEADS), (1 << 32) - 2000, 4001),
          ("four-types", placed([0, 1, 1, 0], 2, 2, 3), 777, 20011), ("back-and-forth", placed([0, 1, 0, 2], 3, 2, 3), 30000, 20011),
          ("no-blocks-on-1", placed([0, 2, 3], 4, 3, 2), 4001, 30001), ("nothing-on-the-first", placed([1, 2], 3, 3, 3), 5, 2001),
-         ("one-type-on-the-first", forward(3, 1, 3), 0, 10), ("three-types", rounds(2, 3, 2), 100, 8001)]
+         ("one-type-on-the-first", forward(3, 1, 3), 0, 10), ("three-types", rounds(2, 3, 2), 100, 8001),
+         ("17-values", seventeen(5), 30011, 20011)]
 
 
 @pytest.mark.parametrize("name,prob,first,count", CASES, ids=[c[0] for c in CASES])
