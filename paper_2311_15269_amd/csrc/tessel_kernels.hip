@@ -2488,15 +2488,20 @@ static size_t fast_lds_bytes(const KParams &kp)
            (share ? 0 : (size_t)(fast_dm(kp) * 2 + ntok) * kWave * 4);
 }
 
-// resident workgroups per CU as the runtime computes them from LDS and registers, 16 at most
+// Workgroups whose LDS a CU holds: it is given out in pieces of 1,280 bytes.  (The runtime's occupancy call counts finer.  With 13 workgroups of 12,288
+// bytes for each CU, where 12 fit, the last 256 began when the others had ended: 2^21 candidates of 30 blocks, ten of them on two of three
+// devices, 926 us, with 12 592.)
+static int lds_blocks(size_t lds_bytes) { return (int)(160 * 1024 / 1280 / ((std::max<size_t>(lds_bytes, 1) + 1279) / 1280)); }
+
+// resident workgroups per CU by LDS and, as the runtime computes them, by registers, 16 at most
 static int blocks_per_cu(const void *fn, size_t lds_bytes)
 {
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kWave, lds_bytes) != hipSuccess || per_cu < 1) {
         (void)hipGetLastError();
-        per_cu = (int)((160 * 1024) / ((lds_bytes + 511) / 512 * 512));
+        per_cu = 16;
     }
-    if (per_cu > 16) per_cu = 16;
+    per_cu = std::min({per_cu, lds_blocks(lds_bytes), 16});
     if (const char *env = getenv("TESSEL_BLOCKS_PER_CU")) {        // tuning knob: fewer resident workgroups per CU
         int want = atoi(env);
         if (want >= 1 && want < per_cu) per_cu = want;
@@ -3391,9 +3396,7 @@ int launch_completions(const CompParams &cp, const CompMatrix &cm, uint64_t firs
         hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return (int)e;
     }
-    int per_cu = (int)((160 * 1024) / ((lds + 511) / 512 * 512));
-    if (per_cu > 16) per_cu = 16;
-    if (per_cu < 1) per_cu = 1;
+    int per_cu = std::max(1, std::min(lds_blocks(lds), 16));
     // a multiple of 4, the same number on every SIMD: 9 a CU (3, 2, 2, 2) took 1.25 times as long a round of candidates as 8
     if (fn != complete_scan_kernel && per_cu > 4) per_cu &= ~3;
     uint64_t need = (count + kWave - 1) / kWave;
