@@ -2647,10 +2647,11 @@ static int launch_general(const KParams &kp, void *ws, uint64_t first, uint64_t 
 //   fewer than that in the last round, of 1.06 to 3.5: the waves with candidates in it are the oldest and ended sooner at one priority, but where few
 //   candidates survive the build a round more is a build more, and the sweeps are for the end
 //       seven eighths of the candidates and more survive: all alike 1.00 to 1.08 (0.92, 1.15), so not so, but
-//           up to 1.25 rounds none (the waves of the last round first 1.02)
 //           from 2 on, to a quarter, these first, the others in turns on the three steps below: 0.98 (0.93, 1.02) in 2.1 rounds, 0.94 in 3.2
 //           more of it, these first, both by twos: 0.98 (0.96, 1.02) in 1.3 to 2.6 rounds, 0.99 in 3.5
-//       fewer: all alike 0.97 (0.91, 1.02); up to 1.25 rounds 0.99 (0.95, 1.12), there these first and the others below, 0.99 (0.95, 1.02)
+//       fewer: all alike 0.97 (0.91, 1.02)
+//       up to 1.25 rounds, whoever survives: all alike 1.06 (0.97, 1.15), these first and the others below during the first build alone 1.02 (0.95, 1.05),
+//           which is known by its end only, so none
 //   other numbers of waves, unlike on the SIMDs, or fewer: 0.99 to 1.01 (0.91, 1.11), no order to it
 static GraphTurns graph_turns(uint64_t count, int blocks, int num_cus)
 {
@@ -2661,7 +2662,8 @@ static GraphTurns graph_turns(uint64_t count, int blocks, int num_cus)
     if (count <= round || count > 4 * round || 8 * last >= 5 * round) return {0, alike, alike, alike, alike};
     const uint32_t more = (uint32_t)((last + kWave - 1) / kWave);
     if (4 * last > round) return {more, turns_of(1, 1, 2), turns_of(1, 1, 0), alike, alike};
-    return count > 2 * round ? GraphTurns{more, first, below, alike, alike} : GraphTurns{more, 0, 0, first, below};
+    if (count < 2 * round) return {0, 0, 0, 0, 0};
+    return {more, first, below, alike, alike};
 }
 
 // Scores [first, first+count).  Where the problem allows it: the fast kernel (a short eigenvector search, a longer one
