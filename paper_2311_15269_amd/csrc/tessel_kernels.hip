@@ -2652,14 +2652,16 @@ static int launch_general(const KParams &kp, void *ws, uint64_t first, uint64_t 
 //       fewer: all alike 0.97 (0.91, 1.02)
 //       up to 1.25 rounds, whoever survives: all alike 1.06 (0.97, 1.15), these first and the others below during the first build alone 1.02 (0.95, 1.05),
 //           which is known by its end only, so none
-//   other numbers of waves, unlike on the SIMDs, or fewer: 0.99 to 1.01 (0.91, 1.11), no order to it
+//   other numbers of waves, unlike on the SIMDs, or fewer: 0.99 to 1.01 (0.91, 1.11) up to four rounds, no order to it; all alike in more, 5 to 14 waves a
+//       CU, 9 to 26 rounds: 0.97 (0.91, 1.02; 613 us with and 674 without, 568 and 603, 939 and 974)
 static GraphTurns graph_turns(uint64_t count, int blocks, int num_cus)
 {
     const uint64_t round = (uint64_t)blocks * kWave, last = (count - 1) % round + 1;
     constexpr uint32_t alike = turns_of(3, 3, 0);
     constexpr uint32_t first = turns_of(0, 0, 3), below = turns_of(3, 2, 0);
+    if (count > 4 * round && blocks > 4 * num_cus) return {0, alike, alike, alike, alike};
     if (blocks < 12 * num_cus || blocks % (4 * num_cus) != 0 || 3 * count < round) return {0, 0, 0, 0, 0};
-    if (count <= round || count > 4 * round || 8 * last >= 5 * round) return {0, alike, alike, alike, alike};
+    if (count <= round || 8 * last >= 5 * round) return {0, alike, alike, alike, alike};
     const uint32_t more = (uint32_t)((last + kWave - 1) / kWave);
     if (4 * last > round) return {more, turns_of(1, 1, 2), turns_of(1, 1, 0), alike, alike};
     if (count < 2 * round) return {0, 0, 0, 0, 0};
